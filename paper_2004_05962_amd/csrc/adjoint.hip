@@ -1,21 +1,20 @@
 // Adjoint BSI kernels for one volume: pass 1 (bricks -> partials) and pass 2
 // (fixed-order gather per control point).  See adjoint_device.h.
+#include <cmath>
+
 #include "adjoint_device.h"
 #include "bsi_internal.h"
 
 namespace bsi {
 
-template <int DX>
+template <bool Staged>
 __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI_ADJ_WPE))) void adj_pass1_kernel(
     const float* __restrict__ dfield, float* __restrict__ part, AdjGeom a, const float* __restrict__ lut) {
-  __shared__ AdjSmem<DX> sm;
+  extern __shared__ float adj_slabs[];
   const int nbricks = a.x.nb * a.y.nb * a.z.nb;
   const int brick = xcd_remap(blockIdx.x, gridDim.x);
   if (brick >= nbricks) return;  // uniform over the workgroup
-  if (adj_stage_all(a))  // uniform: a function of the geometry
-    adj_brick<DX, true, true>(dfield, part, a, lut, brick, sm, threadIdx.x);
-  else
-    adj_brick<DX, true, false>(dfield, part, a, lut, brick, sm, threadIdx.x);
+  adj_brick<true, Staged>(dfield, part, a, lut, brick, adj_slabs, threadIdx.x);
 }
 
 __global__ __launch_bounds__(kGatherThreads) void adj_pass2_kernel(const float* __restrict__ part,
@@ -32,32 +31,60 @@ AdjAxis make_axis(int n, int d, int u, int k) {
   a.k = k < a.U ? k : a.U;
   a.nb = (a.U + a.k - 1) / a.k;
   a.w = a.k * u;
-  // a brick of k whole tiles meets k + 3 control points; a brick of rows that
-  // may start inside a tile meets at most (w - 1)/d + 2 tiles, plus 3
-  a.cm = u == d ? a.k + 3 : (a.w - 1) / d + 5;
+  a.md = adj_magic(d);
+  a.cm = a.nb == 1 ? (n - 1) / d + 4 : adj_window(a.w, d);
   return a;
 }
 }  // namespace
 
-#ifndef BSI_ADJ_FIT
-#define BSI_ADJ_FIT 1
-#endif
-
-// Bricks of pass 1: kAdjBX voxels (one per lane) by kAdjBY rows by whole
-// z-tiles, about kAdjTargetZ planes deep (at least one tile).  Where fewer
-// tiles, but at least half as many, let a brick's whole window of partials fit
-// the LDS stage, the brick takes that depth: its partials are then stored
-// after its last load instead of one plane at a time between its loads.
+// Bricks of pass 1: 2 x 2 cells in x and y by whole z-tiles; the depth by the
+// rule stated with its constants (adjoint_device.h).  A pure function of the
+// geometry.
 AdjGeom make_adj_geom(const VolGeom& g) {
   AdjGeom a;
   a.g = g;
-  a.x = make_axis(g.nx, g.dx, 1, kAdjBX);
-  a.y = make_axis(g.ny, g.dy, 1, kAdjBY);
-  int kz = kAdjTargetZ / g.dz > 0 ? kAdjTargetZ / g.dz : 1;
-  const int kfit = kAdjStageFloats / (a.y.cm * a.x.cm * 3) - 3;  // deepest brick whose window fits
-  if (BSI_ADJ_FIT == 1 && kfit < kz && 2 * kfit >= kz) kz = kfit;
-  if (BSI_ADJ_FIT == 2 && kfit < kz && kfit >= 1) kz = kfit;
-  a.z = make_axis(g.nz, g.dz, g.dz, kz);
+  a.cell = adj_cell(g.dx);
+  if (g.dx <= 2) {  // narrow cells: evenly wide, so that the last brick's window is not kept for a few voxels
+    const int nb = (g.nx + kAdjCellsX * a.cell - 1) / (kAdjCellsX * a.cell);
+    a.cell = ((g.nx + nb * kAdjCellsX - 1) / (nb * kAdjCellsX) + g.dx - 1) / g.dx * g.dx;
+  }
+  a.cw = (imin(adj_window(a.cell, g.dx), (g.nx - 1) / g.dx + 4) + 3) / 4 * 4;
+  a.ch = imin(adj_window(kAdjCellY, g.dy), (g.ny - 1) / g.dy + 4);
+  a.x = make_axis(g.nx, g.dx, 1, kAdjCellsX * a.cell);
+  a.y = make_axis(g.ny, g.dy, 1, kAdjCellsY * kAdjCellY);
+  const int tiles = (g.nz + g.dz - 1) / g.dz;
+  const int plane = kAdjWaves * adj_slab(a);  // slab floats of one control plane
+  const int fit3 = kAdjSlabFloats3 / plane - 3, fit2 = kAdjSlabFloats2 / plane - 3;
+  const int fit = fit3 >= kAdjMinStaged ? fit3 : fit2;  // deepest brick whose slabs hold all of its planes
+  const bool staged = fit >= kAdjMinStaged;
+  int kmax = imin(tiles, imax(1, (staged ? kAdjDepthStaged : kAdjDepthTwo) / g.dz));
+  if (staged) kmax = imin(kmax, fit);
+  // z-bricks: the fewest of those with the least modelled time (kAdjCuCost)
+  const long base = (long)a.x.nb * a.y.nb;
+  const int most = (tiles + kmax - 1) / kmax;
+  int nbz = most;
+  double best = 0.;
+  for (int n = most; n <= tiles && n <= 64 * most; ++n) {
+    const int k = (tiles + n - 1) / n;
+    const double per_cu = (double)(base * ((tiles + k - 1) / k)) / kAdjCus;
+    const double cost = (k * g.dz + kAdjBrickCost) * fmax(ceil(per_cu) * kAdjCuCost, per_cu);
+    if (n == most || cost < best) {
+      best = cost;
+      nbz = n;
+    }
+    if (per_cu >= 4) break;
+  }
+  auto set_depth = [&](int k) {
+    a.z = make_axis(g.nz, g.dz, g.dz, k);
+    a.slots = a.z.cm <= fit + 3 ? a.z.cm : 2;
+  };
+  set_depth((int)((tiles + nbz - 1) / nbz));
+  if (a.z.k < kmax && adj_workspace_bytes(a) > kAdjShallowBytes) set_depth(kmax);
+  if (adj_limit_bytes(g) <= BSI_ADJOINT_NOALLOC_MAX_BYTES)
+    for (int deeper : {kAdjDepthMost, g.nz}) {
+      if (adj_workspace_bytes(a) <= kAdjScratchBytes) break;
+      set_depth(imin(tiles, imax(1, deeper / g.dz)));
+    }
   return a;
 }
 
@@ -65,26 +92,37 @@ size_t adj_workspace_bytes(const AdjGeom& a) {
   return (size_t)a.x.nb * a.y.nb * a.z.nb * a.x.cm * a.y.cm * a.z.cm * 3 * sizeof(float);
 }
 
+// The size that bsi_adjoint_noalloc's limit is stated for: the partials of bricks
+// of 64 x 16 voxel columns, about 48 planes deep (fewer, down to half, where a
+// brick's window then holds at most 6144 floats), with the window strides
+// (w - 1) / d + 5.  The limit is a property of the geometry alone and does not
+// move with the bricks that the kernels use.
+size_t adj_limit_bytes(const VolGeom& g) {
+  auto axis = [](int n, int d, int k, size_t* bricks, size_t* window) {
+    const int w = n < k ? n : k;
+    *bricks = (size_t)(n + w - 1) / w;
+    *window = (size_t)(d == 1 ? w + 3 : (w - 1) / d + 5);
+  };
+  size_t bx, by, wx, wy;
+  axis(g.nx, g.dx, 64, &bx, &wx);
+  axis(g.ny, g.dy, 16, &by, &wy);
+  int kz = imax(1, 48 / g.dz);
+  const int kfit = 6144 / (int)(wy * wx * 3) - 3;
+  if (kfit < kz && 2 * kfit >= kz) kz = kfit;
+  const int tiles = (g.nz + g.dz - 1) / g.dz;
+  kz = imin(kz, tiles);
+  const size_t bz = (size_t)(tiles + kz - 1) / kz;
+  return bx * by * bz * wx * wy * (size_t)(kz + 3) * 3 * sizeof(float);
+}
+
 hipError_t launch_adjoint_partials(const float* dfield, const AdjGeom& a, const float* lut, float* part,
                                   hipStream_t s) {
   const long nbricks = (long)a.x.nb * a.y.nb * a.z.nb;
   const dim3 grid((unsigned)nbricks), block(kAdjThreads);
-  static_assert(kAdjMaxDX == 12, "one case per specialised spacing");
-  switch (a.g.dx) {
-    case 1: hipLaunchKernelGGL(adj_pass1_kernel<1>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 2: hipLaunchKernelGGL(adj_pass1_kernel<2>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 3: hipLaunchKernelGGL(adj_pass1_kernel<3>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 4: hipLaunchKernelGGL(adj_pass1_kernel<4>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 5: hipLaunchKernelGGL(adj_pass1_kernel<5>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 6: hipLaunchKernelGGL(adj_pass1_kernel<6>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 7: hipLaunchKernelGGL(adj_pass1_kernel<7>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 8: hipLaunchKernelGGL(adj_pass1_kernel<8>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 9: hipLaunchKernelGGL(adj_pass1_kernel<9>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 10: hipLaunchKernelGGL(adj_pass1_kernel<10>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 11: hipLaunchKernelGGL(adj_pass1_kernel<11>, grid, block, 0, s, dfield, part, a, lut); break;
-    case 12: hipLaunchKernelGGL(adj_pass1_kernel<12>, grid, block, 0, s, dfield, part, a, lut); break;
-    default: hipLaunchKernelGGL(adj_pass1_kernel<0>, grid, block, 0, s, dfield, part, a, lut); break;
-  }
+  if (adj_staged(a))
+    hipLaunchKernelGGL(adj_pass1_kernel<true>, grid, block, adj_lds_bytes(a), s, dfield, part, a, lut);
+  else
+    hipLaunchKernelGGL(adj_pass1_kernel<false>, grid, block, adj_lds_bytes(a), s, dfield, part, a, lut);
   return hipGetLastError();
 }
 

@@ -1,121 +1,104 @@
 // Adjoint of Eq. 1 (its transpose), as a deterministic two-pass gather.
 //
-// Pass 1 (one workgroup per brick), z-first.  A brick is kAdjBX = 64
-// consecutive x-voxels (one per lane) by kAdjBY rows by a run of whole
-// z-tiles.  Wave w of the workgroup owns rows y0 + w R .. y0 + w R + R - 1
-// (R = kAdjRows), so each lane owns one voxel column per row and marches z.
-// Per voxel plane it loads its R voxels (a wave reads 768 contiguous bytes per
-// row) and accumulates the z-contraction in registers,
-//   A_r[n] += Bz_n(w) * dfield[z][y_r][x]        (n = cz - tz, 4 planes),
-// the only per-voxel work.  When a z-tile ends, plane A[0] is finished for the
-// brick's voxel rows and is contracted in LDS:
-//   over x, per wave (its own rows), on tile lanes: lane (row, t) forms the
-//     x-moments of tile t, M_l = sum_o Bx_l(o) A0[row][t dx + o], and the 16
-//     lanes of a row combine them with row shifts (DPP):
-//     H[row][cx] = sum_l M_l(tile cx - l);
-//   then, after one workgroup barrier, over y, the same way on y-tile lanes:
-//     G[cy][cx] = sum_m N_m(tile cy - m),  N_m = sum_oy By_m(oy) H[t dy + oy][cx].
-// G is the brick's partial gradient of that control plane.  H is double-
-// buffered, so the barrier of plane k also orders the y-contraction of plane
-// k - 1 before the x-contraction of plane k + 1.  A brick's partials are staged
-// in LDS and stored after its last load (see kAdjStageFloats).
+// Pass 1, z-first.  A brick is 2 x 2 cells in x and y by a run of whole
+// z-tiles; a cell is 32 x 8 voxel columns (narrower in x at spacings 1 and 2,
+// adj_cell) and belongs to one wave.  Lane (h, v) = (lane / 32, lane % 32) of
+// the wave owns voxel v of the cell's rows h, 2 + h, 4 + h, 6 + h and marches z:
+// per voxel plane it loads its 4 voxels (a load instruction reads 2 row segments
+// of 384 bytes, three whole 128-byte lines each when rows are aligned; 16 x 16
+// columns, whose segments of 192 bytes split lines between waves, read 20%
+// slower) and accumulates the z-contraction in registers,
+//   A[n] += Bz_n(w) * dfield[z][y][x]        (n = cz - tz, 4 planes),
+// the only per-voxel work.  When a z-tile ends, control plane A[0] is finished
+// for the cell's columns and is contracted over y, then x, as two chained
+// matrix products on the matrix cores, straight from the accumulators, for each
+// half of 16 voxels:
+//   D[x][cy]  = sum_row  A[x][row] By[row][cy]      (2 steps of 4 rows)
+//   E[cx][cy] += sum_x   Bx[cx][x] D[x][cy]         (4 steps of 4 voxels)
+// (v_mfma_f32_16x16x4_f32, FP32 in and out: two row swaps between lanes turn
+// the accumulator registers into the first product's A operand, its result
+// registers are the second one's B operand, and the weight matrices of the
+// brick are 2 + 8 registers per lane).  A cell's window is at most 16 x 16
+// control points.  E goes to the wave's own slab in LDS; no wave waits for
+// another while it marches.  After the brick's last plane one barrier, and the
+// slabs of the brick's cells are summed in wave order into the brick's partials.
+// Where a brick's slabs would take more than kAdjSlabFloats, the slabs hold two
+// planes, and each plane is summed and stored when it is finished, after one
+// barrier per z-tile.
+//
+// What bounds it: reading dfield once (12 bytes per voxel).  The z-accumulation
+// is 12 FMAs per voxel (about 20 us of every SIMD at 512 x 512 x 256), the
+// contractions are 36 matrix instructions of 32 cycles per 256 columns and
+// z-tile (about 25 us at spacing 5), both under the 120 us that the read takes.
 //
 // Pass 2 (one thread per control point) sums, in fixed brick order, the
 // partials of the bricks whose voxels meet the point's support.  No atomics
 // anywhere: the bits depend on the inputs only.
 #pragma once
 
-#include <type_traits>
-
 #include "bsi_device.h"
 
 namespace bsi {
 
-#ifndef BSI_ADJ_ROWS
-#define BSI_ADJ_ROWS 2
-#endif
-#ifndef BSI_ADJ_WAVES
-#define BSI_ADJ_WAVES 8
-#endif
-#ifndef BSI_ADJ_TARGET_Z
-#define BSI_ADJ_TARGET_Z 48
-#endif
-// Waves per SIMD the pass-1 kernels are compiled for (a register bound of
-// 512 / this): 6 keeps three 512-thread workgroups per CU.
+// Waves per SIMD the pass-1 kernels are compiled for (a register bound of 512 /
+// this): 3, because at 4 the march and the contraction together spill, which cost
+// 12% at 512 x 512 x 256, spacing 5 (168 against 150 us).
 #ifndef BSI_ADJ_WPE
-#define BSI_ADJ_WPE 6
+#define BSI_ADJ_WPE 3
 #endif
-constexpr int kAdjRows = BSI_ADJ_ROWS;             // rows per lane (R)
-constexpr int kAdjWaves = BSI_ADJ_WAVES;           // waves per workgroup
+constexpr int kAdjCellsX = 2, kAdjCellsY = 2;      // cells of a brick, one per wave
+constexpr int kAdjWaves = kAdjCellsX * kAdjCellsY;
 constexpr int kAdjThreads = kAdjWaves * kWave;
-constexpr int kAdjBX = kWave;                      // brick width (voxels): one lane per voxel
-constexpr int kAdjBY = kAdjWaves * kAdjRows;       // brick height (rows)
-constexpr int kAdjTargetZ = BSI_ADJ_TARGET_Z;      // brick depth bound (voxels, at least one tile)
-constexpr int kAdjMaxDX = 12;                      // largest x spacing with its own kernel
-constexpr int kAdjTiles = 16;                      // tile lanes per row of lanes (DPP rows)
-// A brick of at most 16 rows meets at most 16 y-tiles (16 at spacing 1, at
-// most (kAdjBY - 1)/dy + 2 otherwise): one row of 16 y-tile lanes per column.
-static_assert(kAdjBY <= kAdjTiles, "a brick's y-tiles fit one row of tile lanes");
+constexpr int kAdjTile = 16;                       // points per axis of a matrix tile
+constexpr int kAdjCellX = 32, kAdjCellY = 8;       // voxel columns of a cell
+constexpr int kAdjSteps = 4;                       // a lane's voxels: rows 2 s + h
+// The brick depth rule (make_adj_geom), measured on pass 1 alone:
+// - the number of z-bricks: a CU reads at most about 28 bytes per ns, whatever
+//   it holds (a plane of a brick in 0.44 us), and all CUs together 22 each (0.54), so
+//   a launch takes (planes per brick + kAdjBrickCost) x the larger of kAdjCuCost x
+//   the bricks of the fullest CU and the bricks per CU on average, where
+//   kAdjBrickCost is what a brick's start and last four planes cost.  256 x 256 x 160,
+//   spacing 5: 29.4 us with 256 or 512 bricks, 32.6 with 384; 294 x 130 x 208,
+//   spacing 6: 27.5 with 405, 31.3 with 540, 33.6 with 270.
+// - depth bound where a brick's slabs hold all of its planes: 96 voxels
+//   (spacing 8 at 511 x 509 x 250: 140 us against 148 at 48).
+// - LDS of those slabs: three workgroups per CU, or, for the wide windows of
+//   spacings 2 and 3, two (512 x 228 x 385, spacing 3: 129 us; with two-plane
+//   slabs 138 to 147, as before them 145 to 152).
+// - depth with two-plane slabs (spacing 1, or 1 along z): 30 voxels (200^3,
+//   spacing 1: 144 us against 218 at 48; 174 before).
+constexpr int kAdjCus = 256;
+constexpr double kAdjCuCost = 0.9, kAdjBrickCost = 4;
+constexpr int kAdjDepthStaged = 96, kAdjDepthTwo = 30, kAdjDepthMost = 48;
+constexpr int kAdjMinStaged = 8;                                     // tiles a brick with whole slabs holds at least
+constexpr int kAdjSlabFloats3 = 13312, kAdjSlabFloats2 = 20000;      // slabs of 3 and of 2 workgroups per CU
+// Shallower bricks than the depth bounds are used up to this workspace size,
+// and deeper ones, of kAdjDepthMost planes or all of them, where only those fit
+// the fixed scratch of bsi_adjoint_noalloc and its limit takes the geometry.
+constexpr size_t kAdjShallowBytes = (size_t)32 << 20;
 
-// The kernels are specialised per x spacing DX = 1..kAdjMaxDX; DX = 0 is the
-// generic kernel for spacings above kAdjMaxDX, and DX = kAdjAnyTile a kernel
-// for any spacing 4..kAdjMaxDX taken at run time (the same operations, in the
-// same order, as the specialisation of that spacing).
-constexpr int kAdjAnyTile = -1;
+// Voxels of a cell along x at spacing d: the most, up to 32, whose window is at
+// most 16 control points ((31 + 2) / 3 + 4 = 15 at spacing 3; 24 / 2 + 3 = 15 at
+// spacing 2, where cells start on even voxels; w + 3 at spacing 1).  Along y a
+// cell of 8 rows meets at most 11.
+__host__ __device__ constexpr int adj_cell(int d) { return d == 1 ? 13 : d == 2 ? 24 : kAdjCellX; }
 
-// Window columns of a brick of kAdjBX voxels at x spacing dx (0: any spacing
-// above kAdjMaxDX; kAdjAnyTile: any of 4..kAdjMaxDX): a run of w voxels meets
-// at most (w - 1)/dx + 2 tiles, and exactly w / dx when the run is whole tiles
-// (spacing 1).
-__host__ __device__ constexpr int adj_cx_max(int dx) {
-  return dx == 1 ? kAdjBX + 3
-                 : (kAdjBX - 1) / (dx == kAdjAnyTile ? 4 : dx > 0 ? dx : kAdjMaxDX + 1) + 5;
+__host__ __device__ constexpr int adj_gcd(int a, int b) { return b == 0 ? a : adj_gcd(b, a % b); }
+// Largest control window of runs of w voxels that start at multiples of w, at
+// spacing d: the start's offset in its tile is at most d - gcd(w, d).
+__host__ __device__ constexpr int adj_window(int w, int d) { return (d - adj_gcd(w, d) + w - 1) / d + 4; }
+
+// v / d for 0 <= v <= 2^20 and 1 <= d <= 64, by m = adj_magic(d): the product is
+// above v / d by less than v / 2^32 < 1 / 64.
+__host__ __device__ inline uint32_t adj_magic(int d) { return (uint32_t)(((uint64_t)1 << 32) / (uint32_t)d + (d > 1)); }
+__host__ __device__ inline int adj_div(int v, int d, uint32_t m) {
+  return d == 1 ? v : (int)(((uint64_t)(uint32_t)v * m) >> 32);
 }
-// The x-contraction runs on tile lanes (16 x-tiles per row of 16 lanes) when a
-// brick row holds at most 16 tiles: x spacing 4 (bricks start on multiples of
-// 64, so exactly 16 tiles), 5..12, and the generic kernel (spacing 13 or more,
-// at most 6 tiles).  Spacings 1..3 sum each column directly (adj_xsum).
-__host__ __device__ constexpr bool adj_tile_lanes(int dx) { return dx == 0 || dx == kAdjAnyTile || dx >= 4; }
-
-// Finished partial planes are staged in LDS and stored once per brick.  On
-// this chip loads and stores share one counter of outstanding memory
-// operations, and a store issued while loads are in flight makes the next wait
-// for a load wait for everything: a store per finished plane would drain the
-// planes of loads in flight at every z-tile.  With the partials of a whole
-// brick staged (spacings of 5 and more at the default brick size), they are
-// stored after the brick's last load.
-#ifndef BSI_ADJ_STAGE_FLOATS
-#define BSI_ADJ_STAGE_FLOATS 6144
-#endif
-constexpr int kAdjStageFloats = BSI_ADJ_STAGE_FLOATS;  // 24 KB
-
-// Rows of H the y-contraction loads at once (one LDS round trip per group).
-#ifndef BSI_ADJ_YGROUP
-#define BSI_ADJ_YGROUP 1
-#endif
-constexpr int kAdjYGroup = BSI_ADJ_YGROUP;
-
-// Rows of the finished-plane buffer F carry dx - 1 voxels of zeros on each
-// side at x spacings 4..12, so a tile that reaches past the brick is
-// contracted without a test per voxel: its voxels outside the brick read zero
-// (the voxels of a ragged brick's row past its end are written as zeros too).
-__host__ __device__ constexpr int adj_fpad(int dx) {
-  return dx == kAdjAnyTile ? kAdjMaxDX - 1 : dx >= 4 && dx <= kAdjMaxDX ? dx - 1 : 0;
-}
-__host__ __device__ constexpr int adj_frow(int dx) { return kWave + 2 * adj_fpad(dx); }  // row stride (voxels)
-
-template <int DX>
-struct AdjSmem {
-  float F[kAdjBY * adj_frow(DX) * 3];        // finished plane, row by row (each wave writes its own rows)
-  float H[2][kAdjBY * adj_cx_max(DX) * 3];   // x-contracted rows, double-buffered
-  float P[kAdjStageFloats];                  // the brick's partial planes awaiting their store
-};
 
 struct AdjBrick {
   int x0, y0, z0, xe, ye, ze;  // voxel range [x0, xe) etc.
   int cx0, cy0, cz0;           // first control index of the window
   int Cx, Cy;                  // window extent in x, y
-  int ntx;                     // x-tiles of the brick inside the volume
 };
 
 __host__ __device__ inline AdjBrick adj_brick_geom(const AdjGeom& a, int brick) {
@@ -131,18 +114,17 @@ __host__ __device__ inline AdjBrick adj_brick_geom(const AdjGeom& a, int brick) 
   b.xe = adj_brick_begin(a.x, g.nx, bx + 1);
   b.ye = adj_brick_begin(a.y, g.ny, by + 1);
   b.ze = adj_brick_begin(a.z, g.nz, bz + 1);
-  b.cx0 = b.x0 / g.dx;
-  b.cy0 = b.y0 / g.dy;
-  b.cz0 = b.z0 / g.dz;
-  b.Cx = (b.xe - 1) / g.dx - b.cx0 + 4;
-  b.Cy = (b.ye - 1) / g.dy - b.cy0 + 4;
-  b.ntx = (b.xe - 1) / g.dx - b.cx0 + 1;
+  b.cx0 = adj_div(b.x0, g.dx, a.x.md);
+  b.cy0 = adj_div(b.y0, g.dy, a.y.md);
+  b.cz0 = bz * a.z.k;  // whole tiles
+  b.Cx = adj_div(b.xe - 1, g.dx, a.x.md) - b.cx0 + 4;
+  b.Cy = adj_div(b.ye - 1, g.dy, a.y.md) - b.cy0 + 4;
   return b;
 }
 
 // Control planes of a brick's window: the z-tiles of its voxels plus 3.
 __host__ __device__ inline int adj_brick_cz(const AdjGeom& a, const AdjBrick& b) {
-  return (b.ze - 1) / a.g.dz - b.cz0 + 4;
+  return adj_div(b.ze - 1, a.g.dz, a.z.md) - b.cz0 + 4;
 }
 
 // Floats per brick in the workspace, and the offset of window point
@@ -154,415 +136,418 @@ __host__ __device__ inline size_t adj_part_offset(const AdjGeom& a, int czl, int
   return ((size_t)(czl * a.y.cm + cyl) * a.x.cm + cxl) * 3;
 }
 
-// Whether a brick's whole window of partials (cm_z planes of cm_y * cm_x
-// points) fits the LDS stage; otherwise each plane is stored as it is finished.
-__host__ __device__ inline bool adj_stage_all(const AdjGeom& a) {
-  return (long)a.z.cm * a.y.cm * a.x.cm * 3 <= kAdjStageFloats;
+// Cell w of a brick, (w mod 2, w / 2) in x and y: its voxels [x0, x0 + nx) x
+// [y0, y0 + ny) and its window of Cx x Cy control points from (cx0, cy0).  A
+// cell past the volume has no voxels and no window.
+struct AdjCell {
+  int x0, nx, cx0, Cx;
+  int y0, ny, cy0, Cy;
+};
+__host__ __device__ inline AdjCell adj_cell_geom(const AdjGeom& a, const AdjBrick& b, int w) {
+  AdjCell c;
+  c.x0 = b.x0 + w % kAdjCellsX * a.cell;
+  c.y0 = b.y0 + w / kAdjCellsX * kAdjCellY;
+  c.nx = imax(0, imin(a.cell, b.xe - c.x0));
+  c.ny = imax(0, imin(kAdjCellY, b.ye - c.y0));
+  c.cx0 = adj_div(c.x0, a.g.dx, a.x.md);
+  c.cy0 = adj_div(c.y0, a.g.dy, a.y.md);
+  const bool any = c.nx > 0 && c.ny > 0;
+  c.Cx = any ? adj_div(c.x0 + c.nx - 1, a.g.dx, a.x.md) - c.cx0 + 4 : 0;
+  c.Cy = any ? adj_div(c.y0 + c.ny - 1, a.g.dy, a.y.md) - c.cy0 + 4 : 0;
+  return c;
 }
 
-// Voxel 0 of brick row `row` in F (voxels -fpad .. 63 + fpad are addressable).
-template <int DX>
-__device__ __forceinline__ float* adj_frow_ptr(AdjSmem<DX>& sm, int row) {
-  return sm.F + (row * adj_frow(DX) + adj_fpad(DX)) * 3;
+// LDS slabs: wave w's plane in slot s begins at float (s * kAdjWaves + w) *
+// slab; component c of point (cyl, cxl) of the cell's window is at
+// adj_slab_point.  Rows hold a multiple of 4 points: a lane's 4 columns of E are
+// one 16-byte store.
+__host__ __device__ inline int adj_slab(const AdjGeom& a) { return 3 * a.ch * a.cw; }
+__host__ __device__ inline int adj_slab_at(const AdjGeom& a, int slot, int w) { return (slot * kAdjWaves + w) * adj_slab(a); }
+__host__ __device__ inline int adj_slab_point(const AdjGeom& a, int c, int cyl, int cxl) {
+  return (c * a.ch + cyl) * a.cw + cxl;
+}
+// Slots: every plane of the brick, or two in turn.
+__host__ __device__ inline bool adj_staged(const AdjGeom& a) { return a.slots >= a.z.cm; }
+__host__ __device__ inline size_t adj_lds_bytes(const AdjGeom& a) {
+  return (size_t)a.slots * kAdjWaves * adj_slab(a) * sizeof(float);
 }
 
-// This wave's R rows of F get voxel `lane` of the finished plane (zero past
-// the brick's end).
-template <int DX, int R>
-__device__ __forceinline__ void adj_put_f(AdjSmem<DX>& sm, const AdjBrick& b, int wave, int lane, int r, F3 v) {
-  if (lane >= b.xe - b.x0) v = F3{0.f, 0.f, 0.f};
-  stf3(adj_frow_ptr<DX>(sm, wave * R + r) + lane * 3, v);
-}
-
-// Zero the pads of this wave's R rows of F (wave-local: the wave's next
-// wave_lds_sync orders it before the x-contraction reads them).
-template <int DX, int R>
-__device__ __forceinline__ void adj_zero_fpad(AdjSmem<DX>& sm, int wave, int lane) {
-  constexpr int P = adj_fpad(DX);
-  if constexpr (P > 0) {
-    for (int i = lane; i < R * 2 * P * 3; i += kWave) {
-      const int r = i / (2 * P * 3), j = i - r * (2 * P * 3);  // j: float within the row's two pads
-      const int v = j / 3, c = j - v * 3;                       // pad voxel, component
-      const int xl = v < P ? v - P : kWave + (v - P);
-      adj_frow_ptr<DX>(sm, wave * R + r)[xl * 3 + c] = 0.f;
-    }
-  }
-}
-
-// Value of lane i - N of this lane's row of 16 lanes, 0 for i < N (DPP
-// row_shr); row_shl: lane i + N, 0 for i + N >= 16.  Lanes past the row's
-// edge read the zero `old` operand.
-template <int N>
-__device__ __forceinline__ float row_shr(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x110 + N, 0xF, 0xF, true));
-}
-template <int N>
-__device__ __forceinline__ float row_shl(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x100 + N, 0xF, 0xF, true));
-}
-
-// Window column of tile lanes: lane t of a row of 16 holds the moments M_l of
-// tile t; this forms
-//   cm = S[t]      = sum_{l <= t} M_l(tile t - l)
-//   cw = S[16 + t] = sum_{l > t}  M_l(tile 16 + t - l)   (t < 3)
-// l ascending.  The shifts bring in zero for the terms a lane does not take
-// (row_shr by l for l > t, row_shl by 16 - l for l <= t), and adding zero is
-// exact, so no per-lane selects are needed.  Idle lanes hold M = 0, so columns
-// past the last tile come out right.  Every lane of the wave takes part (no
-// lane may be inactive).
-__device__ __forceinline__ void adj_combine(const F3 (&M)[4], F3& cm, F3& cw) {
-  cm = M[0];
-  cm.x += row_shr<1>(M[1].x);
-  cm.y += row_shr<1>(M[1].y);
-  cm.z += row_shr<1>(M[1].z);
-  cm.x += row_shr<2>(M[2].x);
-  cm.y += row_shr<2>(M[2].y);
-  cm.z += row_shr<2>(M[2].z);
-  cm.x += row_shr<3>(M[3].x);
-  cm.y += row_shr<3>(M[3].y);
-  cm.z += row_shr<3>(M[3].z);
-  cw.x = row_shl<15>(M[1].x);
-  cw.y = row_shl<15>(M[1].y);
-  cw.z = row_shl<15>(M[1].z);
-  cw.x += row_shl<14>(M[2].x);
-  cw.y += row_shl<14>(M[2].y);
-  cw.z += row_shl<14>(M[2].z);
-  cw.x += row_shl<13>(M[3].x);
-  cw.y += row_shl<13>(M[3].y);
-  cw.z += row_shl<13>(M[3].z);
-  // cm is formed here, not sunk into the callers' conditional stores (which
-  // keeps all nine shifted values live at once and spills)
-  asm volatile("" : "+v"(cm.x), "+v"(cm.y), "+v"(cm.z));
-}
-
-// Moments += w_l * v for l = 0..3.
-__device__ __forceinline__ void adj_moment_step(const float* __restrict__ w, const F3& v, F3 (&M)[4]) {
+// This lane's voxels within the plane: byte offset, from the cell's first voxel,
+// of voxel v of row 2 s + h, clamped into the cell so that every lane loads from
+// a valid address without a branch (a clamped voxel's weights are zero).  8 rows
+// of at most 2^20 voxels: below 2^32 bytes.
+__host__ __device__ inline int adj_lane_row(int lane, int s) { return 2 * s + lane / kAdjCellX; }
+__host__ __device__ inline void adj_cell_offsets(int nx, int cnx, int cny, int lane, uint32_t (&off)[kAdjSteps]) {
+  const int v = imin(lane % kAdjCellX, cnx - 1);
 #pragma unroll
-  for (int l = 0; l < 4; ++l) {
-    M[l].x = fmaf(w[l], v.x, M[l].x);
-    M[l].y = fmaf(w[l], v.y, M[l].y);
-    M[l].z = fmaf(w[l], v.z, M[l].z);
-  }
+  for (int s = 0; s < kAdjSteps; ++s)
+    off[s] = ((uint32_t)imin(adj_lane_row(lane, s), cny - 1) * (uint32_t)nx + (uint32_t)v) * 12u;
 }
 
-// Streaming load of one voxel of dfield: non-temporal, since every voxel is
-// read once; the read stream then does not leave the caches full of dfield
-// lines that the next kernel's writes have to displace.
+// Load of one voxel of dfield through a buffer resource over the cell's part
+// of a plane (uniform base, 32-bit lane offset: no address arithmetic per load).
+// Stream: non-temporal, since every voxel is read once; the read stream then
+// does not leave the caches full of dfield lines that the next kernel's writes
+// have to displace.
 template <bool Stream>
-__device__ __forceinline__ F3 ldf3_dfield(const float* p) {
-  if constexpr (Stream)
-    return F3{__builtin_nontemporal_load(p), __builtin_nontemporal_load(p + 1), __builtin_nontemporal_load(p + 2)};
+__device__ __forceinline__ F3 adj_load_voxel(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  // the whole vector is converted: a bit cast of single elements reads element 0 for all three
+  const fwd_f3 v = __builtin_bit_cast(fwd_f3, __builtin_amdgcn_raw_buffer_load_b96(rs, (int)off, 0, Stream ? kCpolNT : 0));
+  return F3{v.x, v.y, v.z};
+}
+// Bytes of that part: the cell's rows, up to its last voxel.
+__host__ __device__ inline uint32_t adj_cell_bytes(int nx, int cnx, int cny) {
+  return ((uint32_t)(cny - 1) * (uint32_t)nx + (uint32_t)cnx) * 12u;
+}
+
+// Weight matrices of a cell, the entries of lane (q, m) = (lane / 16, lane % 16).
+// y[t] = By of row adj_step_row(t, q) at control row cy0 + m (the first
+// product's B operand); x[g][i] = Bx of voxel 16 g + 4 q + i at control column
+// cx0 + m (the second product's A operand).  Zero outside a voxel's window and
+// for voxels outside the cell.  A weight inside its window that is zero (B3 at
+// offset 0) is kept as -0: the same in every sum, but its bits tell the two kinds
+// apart (adj_cell_sparse).
+struct AdjWeights {
+  float x[2][4], y[2];
+};
+// The row that lanes 16 k .. 16 k + 15 hold in step t of the first product,
+// after the row swaps of adj_cell_emit.
+__host__ __device__ constexpr int adj_step_row(int t, int k) { return 4 * t + 2 * (k & 1) + (k >> 1); }
+// Weight of voxel o0 + v (o0: the offset in its tile of the cell's first voxel, `in`: v lies in the cell)
+// at the cell's control index c; rows: the weight rows of this spacing.  Every
+// lane loads, from a row and entry within the table.
+__device__ __forceinline__ float adj_weight(const float* __restrict__ rows, int d, uint32_t magic, int o0, int v, int c,
+                                            bool in) {
+  const int t = adj_div(o0 + v, d, magic), l = c - t;
+  const float w = rows[4 * (o0 + v - t * d) + (l & 3)];
+  return in && (uint32_t)l < 4u ? (w == 0.f ? -0.f : w) : 0.f;
+}
+__device__ __forceinline__ AdjWeights adj_cell_weights(const AdjGeom& a, const AdjCell& c, const float* __restrict__ lut,
+                                                       int lane) {
+  const int m = lane % kAdjTile, q = lane / kAdjTile;
+  const float *rx = lut_row(lut, a.g.dx, 0), *ry = lut_row(lut, a.g.dy, 0);
+  const int ox = c.x0 - c.cx0 * a.g.dx, oy = c.y0 - c.cy0 * a.g.dy;
+  AdjWeights w;
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int v = kAdjTile * g + 4 * q + i;
+      w.x[g][i] = adj_weight(rx, a.g.dx, a.x.md, ox, v, m, v < c.nx);
+    }
+    const int row = adj_step_row(g, q);
+    w.y[g] = adj_weight(ry, a.g.dy, a.y.md, oy, row, m, row < c.ny);
+  }
+  return w;
+}
+
+typedef float adj_f4 __attribute__((ext_vector_type(4)));
+
+// Swap the odd rows of 16 lanes of a with the even rows of b: from a = row pair
+// (2 s, 2 s + 1) and b = row pair (2 s + 2, 2 s + 3) of 32 voxels each, a becomes
+// the first 16 voxels of the rows 2 s, 2 s + 2, 2 s + 1, 2 s + 3 and b the last 16.
+__device__ __forceinline__ void adj_swap_rows(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b),
+                                                  false, false);
+  const uint32_t ra = r[0], rb = r[1];
+  a = __builtin_bit_cast(float, ra);
+  b = __builtin_bit_cast(float, rb);
+}
+
+// The value of lane (q, (m - N) mod 16) of this lane's row of 16 (DPP row_ror).
+template <int N>
+__device__ __forceinline__ float adj_row_ror(float v) {
+  if constexpr (N == 0) return v;
   else
-    return ldf3(p);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xF, 0xF, true));
 }
 
-// Offsets (floats, within a voxel plane) of this lane's R voxels: row
-// y0 + wave R + r, column x0 + lane, both clamped into the brick so that every
-// lane loads from a valid address without a branch.  A clamped lane's values
-// are never read: the x-contraction reads only columns inside the brick and
-// the y-contraction only rows inside it.  A plane holds < 2^32 floats.
-template <int R>
-__host__ __device__ inline void adj_offsets(const AdjBrick& b, int nx, int wave, int lane, uint32_t (&off)[R]) {
-  const int x = imin(b.x0 + lane, b.xe - 1);
+// E of a plane that holds an infinity or a NaN, whose product with a zero
+// weight would reach the whole window: the same sums over each point's own
+// support only.  f[g][t]: the first product's operands of half g.
+// Lane (q, m) forms columns 4 q + j, row m.
+__device__ __forceinline__ adj_f4 adj_cell_sparse(const float (&f)[2][2], const AdjWeights& w, int lane) {
+  const int m = lane % kAdjTile, q = lane / kAdjTile;
+  adj_f4 e{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int y = imin(b.y0 + wave * R + r, b.ye - 1);
-    off[r] = ((uint32_t)y * (uint32_t)nx + (uint32_t)x) * 3u;
+  for (int t = 0; t < 2; ++t)
+#pragma unroll 1
+    for (int k = 0; k < 4; ++k) {  // the row that lanes 16 k .. hold in step t
+      const float wy = __shfl(w.y[t], kAdjTile * k + m);
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll 1
+          for (int v4 = 0; v4 < 4; ++v4) {  // voxel 16 g + 4 v4 + i
+            const float val = __shfl(f[g][t], kAdjTile * k + 4 * v4 + i);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float wx = __shfl(w.x[g][i], kAdjTile * v4 + 4 * q + j);
+              if (__builtin_bit_cast(uint32_t, wx) != 0 && __builtin_bit_cast(uint32_t, wy) != 0)
+                e[j] = fmaf(wx, wy * val, e[j]);
+            }
+          }
+    }
+  return e;
+}
+
+// Components [C0, C0 + N) of a finished plane, together in one set of products:
+// component C0 + c takes rows c S .. of the first product's result, so that the
+// second product's 16 columns hold N windows of at most S rows.
+template <int C0, int N, int S>
+__device__ __forceinline__ void adj_contract(const float (&f)[3][2][2], const AdjWeights& w, adj_f4& E) {
+  static_assert(N * S <= kAdjTile || N == 1, "the windows fit a tile");
+  adj_f4 D[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) D[g] = adj_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      D[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[C0][g][t], w.y[t], D[g], 0, 0, 0);
+      if constexpr (N > 1)
+        D[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[C0 + 1][g][t], adj_row_ror<S % 16>(w.y[t]), D[g], 0, 0, 0);
+      if constexpr (N > 2)
+        D[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[C0 + 2][g][t], adj_row_ror<2 * S % 16>(w.y[t]), D[g], 0, 0, 0);
+    }
+  E = adj_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) E = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x[g][i], D[g][i], E, 0, 0, 0);
+}
+
+// Contract a finished plane of a cell (f3[s]: this lane's voxel of row
+// 2 s + h) and store its window to `dst`, the wave's slab slot: all of a slab's
+// rows and columns (those past the cell's window are zeros).  cw, ch: of the
+// geometry; ch decides how many components share the products (a uniform
+// branch, the same bits: the other components only add zeros).  28 matrix
+// instructions for windows of up to 8 rows, 20 for up to 5 (spacings 4 and 6 and
+// up) and 36 for more (spacing 1).  Every lane of the wave takes part.
+__device__ __forceinline__ void adj_cell_emit(const F3 (&f3)[kAdjSteps], const AdjWeights& w, float* __restrict__ dst,
+                                              int cw, int ch, int lane) {
+  const int m = lane % kAdjTile, q = lane / kAdjTile;
+  float f[3][2][2];  // [component][half][step]
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    f[0][0][t] = f3[2 * t].x, f[1][0][t] = f3[2 * t].y, f[2][0][t] = f3[2 * t].z;
+    f[0][1][t] = f3[2 * t + 1].x, f[1][1][t] = f3[2 * t + 1].y, f[2][1][t] = f3[2 * t + 1].z;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) adj_swap_rows(f[c][0][t], f[c][1][t]);
   }
-}
-
-// x-contraction of one window column cx for one brick row (spacings 1..3):
-//   sum over voxels x of the brick in cx's support [(cx-3)dx, (cx+1)dx),
-//   ascending, of Bx_{cx - floor(x/dx)}(x - floor(x/dx) dx) * F[x - x0].
-template <int DX>
-__device__ __forceinline__ F3 adj_xsum(const float* __restrict__ Fr, const AdjBrick& b, int cx,
-                                       const float* __restrict__ lut) {
-  F3 s{0.f, 0.f, 0.f};
-#pragma unroll 1
-  for (int j = 0; j < 4; ++j) {  // tile cx - 3 + j, weight index l = 3 - j
-    const int xt = (cx - 3 + j) * DX - b.x0;  // the tile's first voxel, brick-relative
-#pragma unroll
-    for (int o = 0; o < DX; ++o) {
-      const int xl = xt + o;
-      if (xl >= 0 && xl < b.xe - b.x0) {
-        const float w = lut_row(lut, DX, o)[3 - j];  // uniform: a scalar load
-        const float* q = Fr + xl * 3;
-        s.x = fmaf(w, q[0], s.x);
-        s.y = fmaf(w, q[1], s.y);
-        s.z = fmaf(w, q[2], s.z);
-      }
-    }
-  }
-  return s;
-}
-
-// First half of a finished plane's emission (collective over the workgroup,
-// wave-local work) for workgroups of W waves of R rows each (W R = kAdjBY):
-// this wave's rows of the plane (lane = voxel; get(r) gives row r) go through
-// its rows of the LDS buffer F and are contracted over x into H[czl & 1].  The caller then places one
-// workgroup barrier and calls adj_emit_y.
-template <int DX, int R>
-__device__ __forceinline__ void adj_emit_xf(const AdjBrick& b, AdjSmem<DX>& sm, const float* __restrict__ lut,
-                                            int dx, int tid, int czl);
-
-template <int DX, int R, class Get>
-__device__ __forceinline__ void adj_emit_x(const AdjBrick& b, AdjSmem<DX>& sm, const float* __restrict__ lut,
-                                           int dx, int tid, int czl, Get get) {
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
-  wave_lds_sync();  // this wave's x-contraction of the previous plane is done with its rows of F
-#pragma unroll
-  for (int r = 0; r < R; ++r) adj_put_f<DX, R>(sm, b, wave, lane, r, get(r));
-  wave_lds_sync();
-  adj_emit_xf<DX, R>(b, sm, lut, dx, tid, czl);
-}
-
-// The x-contraction of this wave's rows, already in F.
-template <int DX, int R>
-__device__ __forceinline__ void adj_emit_xf(const AdjBrick& b, AdjSmem<DX>& sm, const float* __restrict__ lut,
-                                            int dx, int tid, int czl) {
-  static_assert(kWave / kAdjTiles >= R, "a wave's rows fit its rows of 16 tile lanes");
-  constexpr int CXM = adj_cx_max(DX);
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
-  float* H = sm.H[czl & 1];  // czl counts the brick's finished planes
-  const int nrow = b.ye - b.y0 - wave * R;  // this wave's rows inside the brick
-  if constexpr (adj_tile_lanes(DX)) {
-    // lane (rr, t) = (lane / 16, lane % 16): tile cx0 + t of row rr,
-    //   M_l = sum_o Bx_l(o) F[rr][t dx + o - x0]   (o ascending, voxels in the brick)
-    const int rr = lane / kAdjTiles, t = lane % kAdjTiles;
-    const bool act = rr < R && rr < nrow && t < b.ntx;
-    F3 M[4];
-#pragma unroll
-    for (int l = 0; l < 4; ++l) M[l] = F3{0.f, 0.f, 0.f};
-    if (act) {
-      const int xt = (b.cx0 + t) * dx - b.x0;  // the tile's first voxel, brick-relative (may be < 0)
-      const float* Fr = adj_frow_ptr<DX>(sm, wave * R + rr);
-      if constexpr (adj_fpad(DX) > 0) {
-        // voxels xt .. xt + dx - 1 lie in -(dx - 1) .. 63 + dx - 1: no tests
-        if constexpr (DX > 0) {
-#pragma unroll
-          for (int o = 0; o < DX; ++o) adj_moment_step(lut_row(lut, DX, o), ldf3(Fr + (xt + o) * 3), M);
-        } else {  // kAdjAnyTile: dx from the geometry, the same operations in the same order
-#pragma unroll 1
-          for (int o = 0; o < dx; ++o) adj_moment_step(lut_row(lut, dx, o), ldf3(Fr + (xt + o) * 3), M);
-        }
-      } else {
-        const int nxb = b.xe - b.x0;
-        auto voxel = [&](int o) {
-          const int xl = xt + o;
-          if (xl >= 0 && xl < nxb) adj_moment_step(lut_row(lut, dx, o), ldf3(Fr + xl * 3), M);
-        };
-        // pairs of voxels in flight: few registers while the z-accumulators
-        // and the next planes' loads are live
-#pragma unroll 1
-        for (int o = 0; o < dx; o += 2) {
-          voxel(o);
-          if (o + 1 < dx) voxel(o + 1);
-        }
-      }
-    }
-    F3 cm, cw;
-    adj_combine(M, cm, cw);  // every lane of the wave takes part
-    if (rr < R && rr < nrow) {
-      float* hrow = H + (wave * R + rr) * CXM * 3;
-      if (t < b.Cx) stf3(hrow + t * 3, cm);
-      if (t < 3 && kAdjTiles + t < b.Cx) stf3(hrow + (kAdjTiles + t) * 3, cw);
-    }
+  // an infinity or NaN anywhere in the plane makes every entry of its E
+  // non-finite (0 * inf = NaN), so any one entry per set of products tells
+  float probe;
+  // E's columns 4 q .. of row `row` of component `comp`
+  auto store = [&](const adj_f4& E, int row, int comp) {
+    if (row < ch && comp < 3 && 4 * q < cw)
+      *reinterpret_cast<adj_f4*>(dst + (comp * ch + row) * cw + 4 * q) = E;
+  };
+  if (ch <= 5) {
+    adj_f4 E;
+    adj_contract<0, 3, 5>(f, w, E);
+    const int c = (m >= 5) + (m >= 10) + (m >= 15);
+    store(E, m - 5 * c, c);
+    probe = E[0];
+  } else if (ch <= 8) {
+    adj_f4 E, E2;
+    adj_contract<0, 2, 8>(f, w, E);
+    adj_contract<2, 1, 16>(f, w, E2);
+    store(E, m & 7, m >> 3);
+    store(E2, m, 2);
+    probe = E[0] + E2[0];
   } else {
-    const int items = imin(nrow, R) * b.Cx;
-    for (int it = lane; it < items; it += kWave) {
-      const int r = it / b.Cx, cxl = it - r * b.Cx;
-      stf3(H + ((wave * R + r) * CXM + cxl) * 3, adj_xsum<DX>(adj_frow_ptr<DX>(sm, wave * R + r), b, b.cx0 + cxl, lut));
-    }
+    adj_f4 E, E1, E2;
+    adj_contract<0, 1, 16>(f, w, E);
+    store(E, m, 0);
+    adj_contract<1, 1, 16>(f, w, E1);
+    store(E1, m, 1);
+    adj_contract<2, 1, 16>(f, w, E2);
+    store(E2, m, 2);
+    probe = E[0] + E1[0] + E2[0];
+  }
+  if (__builtin_expect(__any(!(fabsf(probe) < __builtin_inff())), 0)) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) store(adj_cell_sparse(f[c], w, lane), m, c);
   }
 }
 
-// Second half (after the workgroup barrier), for workgroups of W waves: the
-// y-contraction of H[czl & 1] into window plane czl of the brick's partials,
-// on y-tile lanes: lane (c4, ty) = (lane / 16, lane % 16) of wave w takes
-// column cxl = 4 w + c4 (then + 4 W ...) and y-tile cy0 + ty; it forms
-//   N_m = sum over the tile's rows y in the brick (ascending) of By_m(v(y)) H[y][cxl]
-// and the 16 lanes of a row finish window rows ty and, for ty < 3, 16 + ty.
-// StageAll: the partials go to the LDS stage, and after the brick's last
-// plane (last) the whole staged window is stored as one contiguous run of
-// padded planes; otherwise straight to the workspace.
-template <int DX, int W, bool StageAll>
-__device__ __forceinline__ void adj_emit_y(const AdjGeom& a, const AdjBrick& b, float* __restrict__ pbase,
-                                           AdjSmem<DX>& sm, const float* __restrict__ lut, int tid, int czl,
-                                           bool last) {
-  constexpr int CXM = adj_cx_max(DX);
-  const VolGeom& g = a.g;
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
-  const float* H = sm.H[czl & 1];
-  const int nty = b.Cy - 3;  // y-tiles meeting the brick (<= 16)
-  const int c4 = lane / kAdjTiles, ty = lane % kAdjTiles;
-  for (int c0 = wave * 4; c0 < b.Cx; c0 += W * 4) {  // uniform over the wave
-    const int cxl = c0 + c4;
-    const bool act = cxl < b.Cx && ty < nty;
-    F3 N[4];
+// Sum the slabs of planes czl0 .. czl0 + np - 1 (slots slot0 ..) over the
+// brick's cells, in wave order, into the brick's partials.  Collective over
+// `threads` threads, after a barrier.
+__device__ __forceinline__ void adj_combine_slabs(const AdjGeom& a, const AdjBrick& b, const float* __restrict__ slabs,
+                                                  float* __restrict__ pbase, int czl0, int np, int slot0, int tid,
+                                                  int threads) {
+  // items: (plane, point), a wave's lanes consecutive; plane and row of an item
+  // by reciprocal (at most 2^11 points, and 2^16 items: exact)
+  const int slab = adj_slab(a), comp = a.ch * a.cw;
+  const int points = b.Cy * b.Cx, n = np * points;
+  const uint32_t mp = adj_magic(points), mc = adj_magic(b.Cx);
+  int fx[kAdjWaves], fy[kAdjWaves], nx[kAdjWaves], ny[kAdjWaves];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) N[m] = F3{0.f, 0.f, 0.f};
-    const int y1 = (b.cy0 + ty) * g.dy;  // the tile's first row
-    const float* hc = H + (act ? cxl : 0) * 3;
-    // rows in groups of kAdjYGroup, loaded together (a row outside the brick, or of
-    // an idle lane, reads a valid row and counts as zero); the trip counts are
-    // uniform, so the weights are scalar loads
-#pragma unroll 1
-    for (int oy0 = 0; oy0 < g.dy; oy0 += kAdjYGroup) {
-      F3 v[kAdjYGroup];
+  for (int w = 0; w < kAdjWaves; ++w) {
+    const AdjCell c = adj_cell_geom(a, b, w);
+    fx[w] = c.cx0 - b.cx0;
+    fy[w] = c.cy0 - b.cy0;
+    nx[w] = c.Cx;
+    ny[w] = c.Cy;
+  }
+  for (int i = tid; i < n; i += threads) {
+    const int p = adj_div(i, points, mp), j = i - p * points;
+    const int cyl = adj_div(j, b.Cx, mc), cxl = j - cyl * b.Cx;
+    const float* slot = slabs + (slot0 + p) * kAdjWaves * slab;
+    F3 s{0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < kAdjYGroup; ++j) {
-        const int y = y1 + oy0 + j;
-        const bool ok = act && oy0 + j < g.dy && y >= b.y0 && y < b.ye;
-        v[j] = ldf3(hc + (ok ? y - b.y0 : 0) * CXM * 3);
-        if (!ok) v[j] = F3{0.f, 0.f, 0.f};
+    for (int w = 0; w < kAdjWaves; ++w) {
+      const int y = cyl - fy[w], x = cxl - fx[w];
+      if ((uint32_t)y < (uint32_t)ny[w] && (uint32_t)x < (uint32_t)nx[w]) {
+        const float* v = slot + w * slab + y * a.cw + x;
+        s.x += v[0];
+        s.y += v[comp];
+        s.z += v[2 * comp];
       }
-#pragma unroll
-      for (int j = 0; j < kAdjYGroup; ++j)
-        if (oy0 + j < g.dy) adj_moment_step(lut_row(lut, g.dy, oy0 + j), v[j], N);
     }
-    F3 gm, gw;
-    adj_combine(N, gm, gw);  // every lane of the wave takes part
-    if (cxl < b.Cx) {
-      float* dst = StageAll ? sm.P : pbase;
-      if (ty < b.Cy) stf3(dst + adj_part_offset(a, czl, ty, cxl), gm);
-      if (ty < 3 && kAdjTiles + ty < b.Cy) stf3(dst + adj_part_offset(a, czl, kAdjTiles + ty, cxl), gw);
-    }
-  }
-  if constexpr (StageAll) {
-    if (last) {
-      // a following brick of this workgroup writes the stage only after the
-      // barrier at its start
-      __syncthreads();
-      const int n = (czl + 1) * a.y.cm * a.x.cm;
-      for (int i = tid; i < n; i += W * kWave) stf3(pbase + i * 3, ldf3(sm.P + i * 3));
-    }
+    stf3(pbase + adj_part_offset(a, czl0 + p, cyl, cxl), s);
   }
 }
 
-template <bool Stream>
-__device__ __forceinline__ void adj_load(const float* __restrict__ plane, const uint32_t (&off)[kAdjRows],
-                                         F3 (&d)[kAdjRows]) {
+// Where a wave is along z while it marches a brick of the aligned grid: the
+// plane's offset in its z-tile, for its weights.  Bricks start on a tile.
+struct AdjZ {
+  const float* row;  // weight rows of this z spacing
+  int dz, oz;
+  __device__ __forceinline__ AdjZ(const float* lut, int dz_) : row(lut_row(lut, dz_, 0)), dz(dz_), oz(0) {}
+  __device__ __forceinline__ const float* weights() const { return row + 4 * oz; }
+  // step to the next plane; true when this one was its tile's last
+  __device__ __forceinline__ bool step() {
+    oz = oz + 1 == dz ? 0 : oz + 1;
+    return oz == 0;
+  }
+};
+
+// a0 .. a3 <- a1, a2, a3, 0, in place.  Written as instructions on four fixed
+// registers: as assignments, the compiler gives the shifted values registers of
+// their own and copies all 48 accumulators at every plane (96 moves per plane).
+__device__ __forceinline__ void adj_shift(float& a0, float& a1, float& a2, float& a3) {
+  asm volatile("v_mov_b32 %0, %1\n\tv_mov_b32 %1, %2\n\tv_mov_b32 %2, %3\n\tv_mov_b32 %3, 0"
+               : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3));
+}
+
+// March np voxel planes of a cell: the lane's voxel s of plane z is at
+// base + z * zs + off[s] (bytes; `bytes`: adj_cell_bytes).  emit(f, czl) is called for each finished
+// control plane, czl = 0, 1, ... in order, the last three of them after the
+// last plane; setup() once, after the first loads are issued.  acc[n] is the z-accumulation of control plane tile + n; the
+// accumulators move down when a tile ends (48 moves, against 48 FMAs per plane).
+//
+// Two register sets, each holding one plane's loads.  The loop is unrolled over
+// them and its loads are unconditional (past the end, from the last plane
+// again), so each set keeps fixed registers, and waiting for one set's loads
+// leaves the other set's in flight.
+template <bool Stream, class Z, class Setup, class Emit>
+__device__ __forceinline__ void adj_march(const char* base, size_t zs, uint32_t bytes, const uint32_t (&off)[kAdjSteps],
+                                          int np, Z zp, Setup&& setup, Emit&& emit) {
+  F3 acc[4][kAdjSteps];
 #pragma unroll
-  for (int r = 0; r < kAdjRows; ++r) d[r] = ldf3_dfield<Stream>(plane + off[r]);
+  for (int n = 0; n < 4; ++n)
+#pragma unroll
+    for (int s = 0; s < kAdjSteps; ++s) acc[n][s] = F3{0.f, 0.f, 0.f};
+  const char* ahead = base;  // the plane to be loaded next, at most the last
+  int left = np - 1;         // planes after it
+  int czl = 0;
+  auto load = [&](F3(&d)[kAdjSteps]) {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(ahead), 0, (int)bytes, kBufferFlags);
+#pragma unroll
+    for (int s = 0; s < kAdjSteps; ++s) d[s] = adj_load_voxel<Stream>(rs, off[s]);
+    ahead += left > 0 ? zs : 0;
+    --left;
+  };
+  auto add = [&](const F3(&d)[kAdjSteps]) {
+    const float* ws = zp.weights();  // uniform: one scalar load
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const float w = ws[n];
+#pragma unroll
+      for (int s = 0; s < kAdjSteps; ++s) {
+        acc[n][s].x = fmaf(w, d[s].x, acc[n][s].x);
+        acc[n][s].y = fmaf(w, d[s].y, acc[n][s].y);
+        acc[n][s].z = fmaf(w, d[s].z, acc[n][s].z);
+      }
+    }
+  };
+  auto finish = [&]() {
+    emit(acc[0], czl++);
+#pragma unroll
+    for (int s = 0; s < kAdjSteps; ++s) {
+      adj_shift(acc[0][s].x, acc[1][s].x, acc[2][s].x, acc[3][s].x);
+      adj_shift(acc[0][s].y, acc[1][s].y, acc[2][s].y, acc[3][s].y);
+      adj_shift(acc[0][s].z, acc[1][s].z, acc[2][s].z, acc[3][s].z);
+    }
+    asm volatile("s_nop 4");  // the moves above are done before a lane swap may read their results
+  };
+  F3 d0[kAdjSteps], d1[kAdjSteps];
+  load(d0);
+  __builtin_amdgcn_sched_barrier(0);  // d0's loads are issued first: waiting for them leaves d1's in flight
+  load(d1);
+  __builtin_amdgcn_sched_barrier(0);
+  setup();  // what the emission needs, while the first loads are on their way
+  // pairs of planes, with one way in and one way back, so that both sets'
+  // loads are in flight on either
+#pragma unroll 1
+  for (int pairs = np >> 1; pairs > 0; --pairs) {
+    add(d0);
+    load(d0);
+    if (zp.step()) finish();
+    add(d1);
+    load(d1);
+    if (zp.step() && (pairs > 1 || (np & 1))) finish();
+  }
+  if (np & 1) add(d0);
+  // after the last plane, the four control planes in hand, in order
+#pragma unroll 1
+  for (int k = 0; k < 4; ++k) finish();
 }
 
 // Pass 1 for one brick.  Collective over the workgroup (kAdjThreads threads).
-// Stream: dfield is read with non-temporal loads.  StageAll: adj_stage_all(a).
-template <int DX, bool Stream, bool StageAll>
+// Stream: dfield is read with non-temporal loads.  Staged: adj_staged(a).
+template <bool Stream, bool Staged>
 __device__ __forceinline__ void adj_brick(const float* __restrict__ dfield, float* __restrict__ part,
                                           const AdjGeom& a, const float* __restrict__ lut, int brick,
-                                          AdjSmem<DX>& sm, int tid) {
-  constexpr int R = kAdjRows;
+                                          float* __restrict__ slabs, int tid) {
   const VolGeom& g = a.g;
-  const int dx = DX > 0 ? DX : g.dx;
   const AdjBrick b = adj_brick_geom(a, brick);
   float* pbase = part + (size_t)brick * adj_brick_stride(a);
-  __syncthreads();  // a previous brick of this workgroup may still read the LDS buffers
-
   const int lane = tid & (kWave - 1), wave = uniform(tid / kWave);
-  uint32_t off[R];
-  adj_offsets<R>(b, g.nx, wave, lane, off);
-  const size_t zs = (size_t)g.ny * g.nx * 3;
-  const float* plane0 = dfield + (size_t)b.z0 * zs;
-
-  // acc[k][r]: the z-accumulation of control plane c for row r, in slot
-  // k = (c - cz0) & 3, so the accumulators never move: in tile t (phase
-  // ph = t & 3) slot k takes weight Bz_((k - ph) & 3), and slot ph holds the
-  // plane that finishes with the tile.  (The slot code below is written out
-  // in this function, not in lambdas: every access to acc must be visible
-  // with a constant index when it is promoted to registers.)
-  F3 acc[4][R];
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-#pragma unroll
-    for (int r = 0; r < R; ++r) acc[k][r] = F3{0.f, 0.f, 0.f};
-  adj_zero_fpad<DX, R>(sm, wave, lane);
-  int t = 0;   // tile index within the brick (z-bricks are whole tiles: b.z0 = cz0 dz)
-  int oz = 0;  // offset within the tile
-  const float* ahead = plane0 + 2 * zs;  // the plane two ahead of the next one
-
-// Control plane CZL, in slot PH (uniform), goes to this wave's rows of F and
-// the slot is cleared, then the shared emission.
-// A scalar branch to the slot's own code: constant register indices, no selects.
-#define BSI_ADJ_PUT_SLOT(K)                                                                \
-  _Pragma("unroll") for (int r = 0; r < R; ++r) {                                        \
-    adj_put_f<DX, R>(sm, b, wave, lane, r, acc[K][r]);                                   \
-    acc[K][r] = F3{0.f, 0.f, 0.f};                                                       \
+  const AdjCell c = adj_cell_geom(a, b, wave);
+  const bool any = c.nx > 0 && c.ny > 0;
+  __syncthreads();  // a previous brick of this workgroup may still read the slabs
+  // A cell past the volume has nothing to add; with two slots it marches all
+  // the same (the brick's first voxels, nothing stored), for the barriers.
+  if (!Staged || any) {
+    AdjWeights w;
+    const int cnx = any ? c.nx : 1, cny = any ? c.ny : 1;
+    uint32_t off[kAdjSteps];
+    adj_cell_offsets(g.nx, cnx, cny, lane, off);
+    const uint32_t bytes = adj_cell_bytes(g.nx, cnx, cny);
+    const size_t zs = (size_t)g.ny * g.nx * 12;
+    const char* base = reinterpret_cast<const char*>(dfield) + (size_t)b.z0 * zs +
+                       ((size_t)(any ? c.y0 : b.y0) * g.nx + (any ? c.x0 : b.x0)) * 12;
+    const auto setup = [&] { w = adj_cell_weights(a, c, lut, lane); };
+    adj_march<Stream>(base, zs, bytes, off, b.ze - b.z0, AdjZ(lut, g.dz), setup, [&](const F3(&f)[kAdjSteps], int czl) {
+      const int slot = Staged ? czl : czl & 1;
+      adj_cell_emit(f, w, slabs + adj_slab_at(a, slot, wave), a.cw, a.ch, lane);
+      if constexpr (!Staged) {
+        // the barrier of plane czl + 1 orders this sum before the slot's next store
+        __syncthreads();
+        adj_combine_slabs(a, b, slabs, pbase, czl, 1, slot, tid, kAdjThreads);
+      }
+    });
   }
-#define BSI_ADJ_PUT(PH)                                                                    \
-  switch (PH) {                                                                          \
-    case 0: BSI_ADJ_PUT_SLOT(0) break;                                                   \
-    case 1: BSI_ADJ_PUT_SLOT(1) break;                                                   \
-    case 2: BSI_ADJ_PUT_SLOT(2) break;                                                   \
-    default: BSI_ADJ_PUT_SLOT(3) break;                                                  \
+  if constexpr (Staged) {
+    __syncthreads();
+    adj_combine_slabs(a, b, slabs, pbase, 0, adj_brick_cz(a, b), 0, tid, kAdjThreads);
   }
-// The emission runs at raised wave priority: the work before and after the
-// tile's barrier then takes issue slots ahead of waves that are only streaming
-// planes (they wait on memory anyway), so the workgroup's waves reach the
-// barrier sooner.
-#define BSI_ADJ_EMIT(CZL, PH, LAST)                                                        \
-  {                                                                                      \
-    __builtin_amdgcn_s_setprio(2);                                                       \
-    wave_lds_sync(); /* this wave's x-contraction of the previous plane is done with F */ \
-    BSI_ADJ_PUT(PH)                                                                      \
-    wave_lds_sync();                                                                     \
-    adj_emit_xf<DX, R>(b, sm, lut, dx, tid, (CZL));                                      \
-    __syncthreads();                                                                     \
-    adj_emit_y<DX, kAdjWaves, StageAll>(a, b, pbase, sm, lut, tid, (CZL), (LAST));       \
-    __builtin_amdgcn_s_setprio(0);                                                       \
-  }
-
-// One voxel plane Z from register set D: z-accumulation, the loads of the
-// plane two ahead into the same registers (when LOAD), then the emission when
-// a z-tile ends.
-#define BSI_ADJ_PLANE(D, Z, LOAD)                                                          \
-  {                                                                                      \
-    const int ph = t & 3;                                                                \
-    const float* ws_ = lut_rot_row(lut, g.dz, oz, ph); /* Bz_((k - ph) & 3): one scalar load */ \
-    _Pragma("unroll") for (int k = 0; k < 4; ++k) {                                      \
-      const float w = ws_[k];                                                            \
-      _Pragma("unroll") for (int r = 0; r < R; ++r) {                                    \
-        acc[k][r].x = fmaf(w, D[r].x, acc[k][r].x);                                      \
-        acc[k][r].y = fmaf(w, D[r].y, acc[k][r].y);                                      \
-        acc[k][r].z = fmaf(w, D[r].z, acc[k][r].z);                                      \
-      }                                                                                  \
-    }                                                                                    \
-    if (LOAD) adj_load<Stream>(ahead, off, D);                                           \
-    ahead += zs;                                                                         \
-    if (++oz == g.dz && (Z) + 1 < b.ze) {                                                \
-      BSI_ADJ_EMIT(t, ph, false)                                                         \
-      oz = 0;                                                                            \
-      ++t;                                                                               \
-    }                                                                                    \
-  }
-
-  // Two register sets, each holding one plane's loads.  The loop is unrolled
-  // over them, and its main part runs only while every plane of the pair and
-  // every plane two ahead exists, so its loads are unconditional: each set
-  // keeps fixed registers, and waiting for one set's loads leaves the other
-  // set's in flight.  (Both sets are first loaded unconditionally, from the
-  // brick's last plane when it is one plane deep, so the loop is entered with
-  // the same loads in flight on every path.)
-  F3 d0[R], d1[R];
-  adj_load<Stream>(plane0, off, d0);
-  adj_load<Stream>(plane0 + (b.ze - b.z0 > 1 ? zs : 0), off, d1);
-  int z = b.z0;
-  for (; z + 4 <= b.ze; z += 2) {
-    BSI_ADJ_PLANE(d0, z, true)
-    BSI_ADJ_PLANE(d1, z + 1, true)
-  }
-  for (; z < b.ze; z += 2) {
-    BSI_ADJ_PLANE(d0, z, z + 2 < b.ze)
-    if (z + 1 < b.ze) BSI_ADJ_PLANE(d1, z + 1, z + 3 < b.ze)
-  }
-  // The brick's last four control planes, t .. t + 3 (the last three are
-  // shared with the next brick), in slots (t + n) & 3, in ascending order.
-#pragma unroll 1
-  for (int n = 0; n < 4; ++n) BSI_ADJ_EMIT(t + n, (t + n) & 3, n == 3)
-#undef BSI_ADJ_PLANE
-#undef BSI_ADJ_EMIT
-#undef BSI_ADJ_PUT
-#undef BSI_ADJ_PUT_SLOT
 }
 
 // Pass 2 for one control point (cx, cy, cz): fixed-order sum of brick partials.

@@ -45,9 +45,10 @@ struct VolDesc {
 };
 
 enum Pass { kFwd = 0, kAdj1 = 1, kAdj2 = 2, kAdj1Tiles = 3 };
-constexpr int kNumClasses = kAdjMaxDX + 1;  // class dx for dx <= kAdjMaxDX, class 0 otherwise
-constexpr int kTilesLo = 4;                  // classes kTilesLo..kAdjMaxDX: the tile-lane spacings
-inline int dx_class(int dx) { return dx <= kAdjMaxDX ? dx : 0; }
+constexpr int kMaxClassDX = 12;              // x spacings with a class of their own
+constexpr int kNumClasses = kMaxClassDX + 1;  // class dx for dx <= kMaxClassDX, class 0 otherwise
+constexpr int kTilesLo = 4;                  // classes kTilesLo..kMaxClassDX may share one launch
+inline int dx_class(int dx) { return dx <= kMaxClassDX ? dx : 0; }
 constexpr int kPtThreads = kGatherThreads;  // pass 2's workgroup
 constexpr int kClassStreams = 3;  // pass-1 class launches run on the caller's stream and these
 
@@ -138,9 +139,9 @@ __device__ __forceinline__ int find_volume(const VolDesc* __restrict__ v, int co
 // live across the body (pass 1's body needs every scalar register it can get:
 // with a loop around it, its scalar registers spill to vector registers and
 // those to scratch).
-template <bool Persistent, class Body>
+template <bool Persistent, bool Runs, class Body>
 __device__ __forceinline__ void batch_for_items(int64_t total, Body&& body) {
-  const ItemRange r = batch_items(blockIdx.x, gridDim.x, total, Persistent);
+  const ItemRange r = batch_items(blockIdx.x, gridDim.x, total, Persistent, Runs);
   if constexpr (Persistent) {
     for (int64_t item = r.first; item < total; item += r.step) body(item);
   } else {
@@ -152,7 +153,7 @@ template <class T, bool NT, bool Persistent>
 __global__ __launch_bounds__(T::threads) void batch_fwd_kernel(const VolDesc* __restrict__ vols, int count,
                                                                int64_t total, const float* __restrict__ lut) {
   __shared__ FwdSmem<3, T> sm;
-  batch_for_items<Persistent>(total, [&](const int64_t item) {
+  batch_for_items<Persistent, false>(total, [&](const int64_t item) {
     const int vi = uniform(find_volume(vols, count, item, kFwd));
     const VolDesc& d = vols[vi];
     const VolGeom g = d.a.g;
@@ -169,34 +170,32 @@ __global__ __launch_bounds__(T::threads) void batch_fwd_kernel(const VolDesc* __
   });
 }
 
-// Pass 1 over the volumes of one x-spacing class (DX = 1..kAdjMaxDX, or 0 for
-// the generic path), each class with its own descriptor sub-table, so every
-// launch keeps the register footprint of its own specialisation.
-// (DX = kAdjAnyTile: the volumes of every spacing 4..12, item numbering
-// first[kAdj1Tiles]; the same bits as each spacing's own kernel.)
-template <int DX, bool Persistent>
+// Pass 1 over the volumes of one x-spacing class, or (AllTiles, item numbering
+// first[kAdj1Tiles]) of every spacing 4..12: one kernel for every spacing, the
+// launches differ in the descriptor sub-table and the LDS they ask for.
+template <bool AllTiles, bool Persistent>
 __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI_ADJ_WPE))) void batch_adj1_kernel(
     const VolDesc* __restrict__ vols, int count, int64_t total, const float* __restrict__ lut) {
-  __shared__ AdjSmem<DX> sm;
-  constexpr int kPass = DX == kAdjAnyTile ? kAdj1Tiles : kAdj1;
-  batch_for_items<Persistent>(total, [&](const int64_t item) {
+  extern __shared__ float batch_slabs[];
+  constexpr int kPass = AllTiles ? kAdj1Tiles : kAdj1;
+  batch_for_items<Persistent, true>(total, [&](const int64_t item) {
     const int vi = uniform(find_volume(vols, count, item, kPass));
     const VolDesc& d = vols[vi];
     const AdjGeom a = d.a;
     // ordinary loads: with the forward running beside pass 1 in the graph,
     // streaming loads measured 2-5% slower here
     const int brick = (int)(item - d.first[kPass]);
-    if (adj_stage_all(a))
-      adj_brick<DX, false, true>(as_global(d.dfield), as_global(d.part), a, lut, brick, sm, threadIdx.x);
+    if (adj_staged(a))  // uniform: a function of the geometry
+      adj_brick<false, true>(as_global(d.dfield), as_global(d.part), a, lut, brick, batch_slabs, threadIdx.x);
     else
-      adj_brick<DX, false, false>(as_global(d.dfield), as_global(d.part), a, lut, brick, sm, threadIdx.x);
+      adj_brick<false, false>(as_global(d.dfield), as_global(d.part), a, lut, brick, batch_slabs, threadIdx.x);
   });
 }
 
 template <bool Persistent>
 __global__ __launch_bounds__(kPtThreads) void batch_adj2_kernel(const VolDesc* __restrict__ vols, int count,
                                                                  int64_t total) {
-  batch_for_items<Persistent>(total, [&](const int64_t item) {
+  batch_for_items<Persistent, true>(total, [&](const int64_t item) {
     const int vi = uniform(find_volume(vols, count, item, kAdj2));
     const VolDesc& d = vols[vi];
     const AdjGeom a = d.a;
@@ -316,13 +315,18 @@ hipError_t launch_pass(bsi_batch* p, int pass, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int DX>
-void launch_adj1_dx(const bsi_batch* p, const VolDesc* v, int n, int64_t ct, int per_cu, hipStream_t s) {
+// Pass 1 over the descriptors v[0 .. n), ct items, with the LDS of the largest.
+template <bool AllTiles>
+void launch_adj1(const bsi_batch* p, int first, int n, int64_t ct, hipStream_t s) {
+  const int per_cu = kAdjPerCu[p->cfg.k[kKAdjPerCu]];
+  size_t lds = 0;
+  for (int i = first; i < first + n; ++i) lds = std::max(lds, adj_lds_bytes(p->cls_host[(size_t)i].a));
+  const VolDesc* v = p->d_cls + first;
   const dim3 gd((unsigned)pass_grid(p, ct, per_cu)), bd(kAdjThreads);
   if (!pass_persistent(ct, per_cu))
-    hipLaunchKernelGGL((batch_adj1_kernel<DX, false>), gd, bd, 0, s, v, n, ct, p->lut);
+    hipLaunchKernelGGL((batch_adj1_kernel<AllTiles, false>), gd, bd, lds, s, v, n, ct, p->lut);
   else
-    hipLaunchKernelGGL((batch_adj1_kernel<DX, true>), gd, bd, 0, s, v, n, ct, p->lut);
+    hipLaunchKernelGGL((batch_adj1_kernel<AllTiles, true>), gd, bd, lds, s, v, n, ct, p->lut);
 }
 
 // Adjoint pass 1 over the volumes of x-spacing class c, on stream s.
@@ -330,24 +334,7 @@ hipError_t launch_adj1_class(bsi_batch* p, int c, hipStream_t s) {
   const int n = p->cls_first[c + 1] - p->cls_first[c];
   const int64_t ct = p->cls_total[c];
   if (n == 0 || ct == 0) return hipSuccess;
-  const int per_cu = kAdjPerCu[p->cfg.k[kKAdjPerCu]];
-  const VolDesc* v = p->d_cls + p->cls_first[c];
-  static_assert(kAdjMaxDX == 12, "one case per specialised spacing");
-  switch (c) {
-    case 1: launch_adj1_dx<1>(p, v, n, ct, per_cu, s); break;
-    case 2: launch_adj1_dx<2>(p, v, n, ct, per_cu, s); break;
-    case 3: launch_adj1_dx<3>(p, v, n, ct, per_cu, s); break;
-    case 4: launch_adj1_dx<4>(p, v, n, ct, per_cu, s); break;
-    case 5: launch_adj1_dx<5>(p, v, n, ct, per_cu, s); break;
-    case 6: launch_adj1_dx<6>(p, v, n, ct, per_cu, s); break;
-    case 7: launch_adj1_dx<7>(p, v, n, ct, per_cu, s); break;
-    case 8: launch_adj1_dx<8>(p, v, n, ct, per_cu, s); break;
-    case 9: launch_adj1_dx<9>(p, v, n, ct, per_cu, s); break;
-    case 10: launch_adj1_dx<10>(p, v, n, ct, per_cu, s); break;
-    case 11: launch_adj1_dx<11>(p, v, n, ct, per_cu, s); break;
-    case 12: launch_adj1_dx<12>(p, v, n, ct, per_cu, s); break;
-    default: launch_adj1_dx<0>(p, v, n, ct, per_cu, s); break;
-  }
+  launch_adj1<false>(p, p->cls_first[c], n, ct, s);
   return hipGetLastError();
 }
 
@@ -381,8 +368,7 @@ int32_t enqueue_adjoint(bsi_batch* p, hipStream_t s) {
     hipStream_t st = b == 0 ? s : p->cls_side[b - 1];
     if (order[k] == kNumClasses) {
       const int n = p->cls_first[kNumClasses] - p->cls_first[kTilesLo];
-      launch_adj1_dx<kAdjAnyTile>(p, p->d_cls + p->cls_first[kTilesLo], n, p->tiles_total,
-                                  kAdjPerCu[p->cfg.k[kKAdjPerCu]], st);
+      launch_adj1<true>(p, p->cls_first[kTilesLo], n, p->tiles_total, st);
       e = hipGetLastError();
     } else {
       e = launch_adj1_class(p, order[k], st);

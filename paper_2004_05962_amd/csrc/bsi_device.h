@@ -15,8 +15,6 @@ constexpr int kMaxSpacing = 64;
 // Basis table for every spacing d in [1, kMaxSpacing]: row (d, o) holds
 // B0..B3(o/d), the weights of Eq. 1 at in-tile offset o.
 constexpr int kLutFloats = 4 * kMaxSpacing * (kMaxSpacing + 1) / 2;
-// Rotated rows (lut_rot_row), stored after the basis table in the same array.
-constexpr int kLutRotFloats = 4 * kLutFloats;
 constexpr int kNumXcd = 8;  // MI355X: 8 accelerator complex dies, 32 CUs each
 
 // 12-byte vector of the three displacement components.  Packed with 4-byte
@@ -35,12 +33,12 @@ struct VolGeom {
 // units of u voxels (a tile, or a single voxel when a tile is taller than a
 // brick may be), and brick b of nb holds the k units [b*k, (b+1)*k), the last
 // brick the rest.  A brick is w = k*u voxels wide, so brick boundaries sit at
-// multiples of w: with k = 16 x-tiles of d voxels a brick row is 192 d bytes,
-// a multiple of 64, and rows that start on a 64-byte boundary are cut only at
-// 64-byte boundaries.  cm bounds the number of control points whose support
+// multiples of w: a brick row of 64 voxels is 768 bytes, and rows that start on
+// a 64-byte boundary are cut only at 64-byte boundaries.  cm bounds the number of control points whose support
 // meets one brick (the partial-window stride).
 struct AdjAxis {
   int32_t u, U, k, nb, w, cm;
+  uint32_t md;  // reciprocal of the spacing (adj_magic)
 };
 
 // The adjoint's bricks (see adjoint_device.h).  A pure function of the
@@ -48,6 +46,9 @@ struct AdjAxis {
 struct AdjGeom {
   VolGeom g;
   AdjAxis x, y, z;
+  int32_t cell;      // voxels in x of one wave's cell
+  int32_t cw, ch;    // the largest control window of a cell (cw rounded up to a multiple of 4)
+  int32_t slots;     // control planes of slabs held in LDS
 };
 
 // First voxel of brick b (b <= nb; brick nb begins at the axis end n).  For
@@ -66,11 +67,6 @@ __host__ __device__ constexpr int imax(int a, int b) { return a > b ? a : b; }
 
 __device__ __forceinline__ const float* lut_row(const float* lut, int d, int o) {
   return lut + 4 * ((d * (d - 1)) / 2 + o);
-}
-// Row (d, o) rotated by ph: element k is B_((k - ph) & 3)(o/d).  `lut` is the
-// basis table's device pointer; the rotated rows follow it.
-__device__ __forceinline__ const float* lut_rot_row(const float* lut, int d, int o, int ph) {
-  return lut + kLutFloats + 16 * ((d * (d - 1)) / 2 + o) + 4 * ph;
 }
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -94,15 +90,30 @@ __host__ __device__ __forceinline__ int xcd_remap(int id, int n) {
   return xcd * q + (xcd < r ? xcd : r) + k;
 }
 
+// An order for items that differ in size: runs of kXcdRun consecutive items per XCD in turn.
+// Items of one volume are alike, but not those of different volumes (brick
+// depth, rows, z-chunks), so one contiguous range per XCD leaves XCDs idle at the
+// end (pass 1 of the 32-volume workload: 22% of the time); runs keep most
+// neighbours on one XCD.  The ids past the last whole round keep their place.
+constexpr int kXcdRun = 16;
+__host__ __device__ __forceinline__ int xcd_runs(int id, int n) {
+  const int round = kNumXcd * kXcdRun;
+  if (id >= n / round * round) return id;
+  const int xcd = id % kNumXcd, k = id / kNumXcd;
+  return (k / kXcdRun * kNumXcd + xcd) * kXcdRun + k % kXcdRun;
+}
+
 // Work items of workgroup `block` of `grid` over [0, total) in a batched
 // launch: first, first + step, ... while below total.  A persistent grid
 // steps by its size; a grid of one workgroup per item (grid = total) takes
-// its one item and steps past the end.
+// its one item and steps past the end.  runs: in runs per XCD (xcd_runs; the
+// adjoint's passes), otherwise one contiguous range per XCD (the forward, whose
+// items are alike enough: 628 against 633 us).
 struct ItemRange {
   int64_t first, step;
 };
-__host__ __device__ inline ItemRange batch_items(int block, int grid, int64_t total, bool persistent) {
-  return ItemRange{xcd_remap(block, grid), persistent ? (int64_t)grid : total};
+__host__ __device__ inline ItemRange batch_items(int block, int grid, int64_t total, bool persistent, bool runs) {
+  return ItemRange{runs ? xcd_runs(block, grid) : xcd_remap(block, grid), persistent ? (int64_t)grid : total};
 }
 
 // Order this wave's LDS writes before its following LDS reads (and vice versa):

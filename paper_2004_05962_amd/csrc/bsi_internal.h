@@ -29,6 +29,11 @@ int32_t make_geom(const int32_t dims[3], const int32_t spacing[3], VolGeom* g);
 int32_t check_control_plane(int32_t gx, int32_t gy);  // UNSUPPORTED at 2^31 floats or more
 AdjGeom make_adj_geom(const VolGeom& g);
 size_t adj_workspace_bytes(const AdjGeom& a);
+// bsi_adjoint_noalloc: what its limit is compared with, and its scratch.  The
+// partials of a geometry within the limit take at most 1.11 times as much
+// (spacing 1, a width a little above a multiple of 26 voxels).
+size_t adj_limit_bytes(const VolGeom& g);
+constexpr size_t kAdjScratchBytes = BSI_ADJOINT_NOALLOC_MAX_BYTES / 8 * 9;
 
 // Forward launch shape (workgroups of kFwdRows waves; z split into chunks).
 struct FwdLaunch {

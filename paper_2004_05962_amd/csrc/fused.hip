@@ -20,7 +20,7 @@
 // gradient; only the loss is summed in another order.
 //
 // Each workgroup sums its voxels' squared residuals in a fixed order into one
-// loss partial per brick; pass 2 is the adjoint's fixed-order gather, and the
+// loss partial; pass 2 is the adjoint's fixed-order gather, and the
 // loss is the fixed-order sum of the partials.  No atomics.
 #include "adjoint_device.h"
 #include "bsi_internal.h"
@@ -30,77 +30,102 @@ namespace bsi {
 
 namespace {
 
-// The fused pass uses the adjoint's bricks with one row per lane: kAdjBY
-// waves of 64 lanes, so each lane keeps the forward's 4 contracted planes and
-// the adjoint's 4 accumulators for a single voxel column.
-constexpr int kFusedWaves = kAdjBY;
+// The fused pass uses the adjoint's bricks with one voxel column per lane: 16
+// waves of one row each, lane = x, so each lane keeps the forward's 4 contracted
+// planes and the adjoint's 4 accumulators of a single column.  When a z-tile
+// ends, the rows of the finished control plane meet in LDS (F, two in turn, one
+// barrier per tile), and the first kAdjWaves waves contract one cell each with
+// the adjoint's matrix products (adj_cell_emit: the same operations on the same
+// values, so the same bits) while the others go on with the next tile.
+constexpr int kFusedWaves = kAdjCellsY * kAdjCellY;
 constexpr int kFusedThreads = kFusedWaves * kWave;
+// Floats per row of F: 64 voxels, padded so that the 2 rows a cell's lanes read
+// at once start 32 banks apart.
+constexpr int kFusedFRow = kWave * 3 + 32;
 
-// A staged control plane: the brick's window of at most kAdjBY + 3 rows by
-// adj_cx_max(DX) columns (pitch adj_cx_max(DX) points).
-template <int DX>
-__host__ __device__ constexpr int fused_slot_floats() {
-  return (kAdjBY + 3) * adj_cx_max(DX) * 3;
-}
-template <int DX>
-__host__ __device__ constexpr int fused_loads() {  // staged floats per thread
-  return (fused_slot_floats<DX>() + kFusedThreads - 1) / kFusedThreads;
-}
-
-template <int DX>
-struct FusedSmem {
-  AdjSmem<DX> adj;
-  float ring[2][fused_slot_floats<DX>()];
-  float red[kFusedThreads];
+// LDS (floats): F[2], the two-slot ring of staged control planes (the brick's
+// window, pitch x.cm points), the reduction, the slabs.
+struct FusedLds {
+  int F, ring, slot, red, slabs, total;
 };
+__host__ __device__ inline FusedLds fused_lds(const AdjGeom& a) {
+  FusedLds l;
+  l.F = 0;
+  l.ring = 2 * kFusedWaves * kFusedFRow;
+  l.slot = a.y.cm * a.x.cm * 3;
+  l.red = l.ring + 2 * l.slot;
+  l.slabs = (l.red + kFusedThreads + 3) / 4 * 4;  // 16-byte aligned
+  l.total = l.slabs + a.slots * kAdjWaves * adj_slab(a);
+  return l;
+}
+// Staged floats per thread: one plane's window is at most 825 floats at
+// spacings dx >= 3, dy >= 2, and at most 2640 at spacing 1.
+__host__ __device__ constexpr int fused_loads(int slot) { return (slot + kFusedThreads - 1) / kFusedThreads; }
+constexpr int kFusedMaxLoads = 3;
+
+// A workgroup takes `deep` consecutive z-bricks of one (x, y) brick column: it
+// marches on through their borders with the planes it has contracted, and
+// only the adjoint's partials are cut there.  So the depth of a workgroup is
+// chosen for this kernel, which runs one workgroup per CU and pays for the
+// first 4 control planes, and not by the adjoint's bricks: as deep as leaves
+// kFusedTargetWg workgroups.
+constexpr int kFusedTargetWg = 256;
+struct FusedSplit {
+  int deep, nz;  // z-bricks per workgroup, workgroups along z
+};
+__host__ __device__ inline FusedSplit fused_split(const AdjGeom& a) {
+  const long base = (long)a.x.nb * a.y.nb;
+  long nz = (kFusedTargetWg + base - 1) / base;
+  nz = nz < a.z.nb ? nz : a.z.nb;
+  FusedSplit f;
+  f.deep = (int)((a.z.nb + nz - 1) / nz);
+  f.nz = (a.z.nb + f.deep - 1) / f.deep;
+  return f;
+}
 
 // Loads of control plane cz's window into registers (thread tid takes floats
 // e = tid + k kFusedThreads of the Cy x Cx x 3 window), and their store into a
-// slot with row pitch adj_cx_max(DX) points.
-template <int DX>
+// slot with row pitch x.cm points.
+template <int L>
 struct FusedStage {
-  int src[fused_loads<DX>()];  // float offset within a control plane, -1 outside the window
-  int dst[fused_loads<DX>()];
+  int src[L];  // float offset within a control plane, -1 outside the window
+  int dst[L];
 };
 
-template <int DX>
-__device__ __forceinline__ FusedStage<DX> fused_stage_map(const VolGeom& g, const AdjBrick& b, int tid) {
-  constexpr int CXM = adj_cx_max(DX);
-  FusedStage<DX> m;
+template <int L>
+__device__ __forceinline__ FusedStage<L> fused_stage_map(const AdjGeom& a, const AdjBrick& b, int tid) {
+  FusedStage<L> m;
   const int wrow = b.Cx * 3;
 #pragma unroll
-  for (int k = 0; k < fused_loads<DX>(); ++k) {
+  for (int k = 0; k < L; ++k) {
     const int e = tid + k * kFusedThreads;
     const int cyl = e / wrow, i = e - cyl * wrow;
     const bool in = cyl < b.Cy;
-    m.src[k] = in ? ((b.cy0 + cyl) * g.gx + b.cx0) * 3 + i : -1;
-    m.dst[k] = cyl * CXM * 3 + i;
+    m.src[k] = in ? ((b.cy0 + cyl) * a.g.gx + b.cx0) * 3 + i : -1;
+    m.dst[k] = cyl * a.x.cm * 3 + i;
   }
   return m;
 }
 
-template <int DX>
-__device__ __forceinline__ void fused_fetch(const float* __restrict__ grid, const VolGeom& g, const FusedStage<DX>& m,
-                                            int cz, float (&r)[fused_loads<DX>()]) {
+template <int L>
+__device__ __forceinline__ void fused_fetch(const float* __restrict__ grid, const VolGeom& g, const FusedStage<L>& m,
+                                            int cz, float (&r)[L]) {
   const float* plane = grid + (size_t)cz * g.gy * g.gx * 3;
 #pragma unroll
-  for (int k = 0; k < fused_loads<DX>(); ++k) r[k] = m.src[k] >= 0 ? plane[m.src[k]] : 0.f;
+  for (int k = 0; k < L; ++k) r[k] = m.src[k] >= 0 ? plane[m.src[k]] : 0.f;
 }
 
-template <int DX>
-__device__ __forceinline__ void fused_stage(float* __restrict__ slot, const FusedStage<DX>& m,
-                                            const float (&r)[fused_loads<DX>()]) {
+template <int L>
+__device__ __forceinline__ void fused_stage(float* __restrict__ slot, const FusedStage<L>& m, const float (&r)[L]) {
 #pragma unroll
-  for (int k = 0; k < fused_loads<DX>(); ++k)
+  for (int k = 0; k < L; ++k)
     if (m.src[k] >= 0) slot[m.dst[k]] = r[k];
 }
 
 // Q = sum_m By_m (sum_l Bx_l phi[row + m][col + l]) from a staged plane: the
 // operations of the forward kernel's contraction (fwd_contract), in its order.
-template <int DX>
-__device__ __forceinline__ F3 fused_contract(const float* __restrict__ slot, int base, const float (&bx)[4],
+__device__ __forceinline__ F3 fused_contract(const float* __restrict__ slot, int base, int pitch, const float (&bx)[4],
                                              const float (&by)[4]) {
-  constexpr int P = adj_cx_max(DX) * 3;  // floats per staged row
   float q[3];
   {
     const float* p = slot + base;
@@ -110,7 +135,7 @@ __device__ __forceinline__ F3 fused_contract(const float* __restrict__ slot, int
   }
 #pragma unroll 1
   for (int m = 1; m < 4; ++m) {
-    const float* p = slot + base + m * P;
+    const float* p = slot + base + m * pitch;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       const float r = fmaf(bx[3], p[9 + c], fmaf(bx[2], p[6 + c], fmaf(bx[1], p[3 + c], bx[0] * p[c])));
@@ -121,88 +146,99 @@ __device__ __forceinline__ F3 fused_contract(const float* __restrict__ slot, int
 }
 
 // Pairs: the sampler's x-neighbour loads (trilinear_load): 1 for nx >= 2, 0 for nx == 1.
-template <int DX, bool StageAll, int Pairs>
-__device__ __forceinline__ void fused_brick(const float* __restrict__ grid, const float* __restrict__ moving,
-                                            const float* __restrict__ fixed, float* __restrict__ part,
-                                            float* __restrict__ lpart, const AdjGeom& a,
-                                            const float* __restrict__ lut, int brick, FusedSmem<DX>& sm, int tid) {
-  constexpr int R = 1;
-  constexpr int CXM = adj_cx_max(DX);
+// L: staged floats per thread.
+template <int L, bool Staged, int Pairs>
+__global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float* __restrict__ grid,
+                                                                  const float* __restrict__ moving,
+                                                                  const float* __restrict__ fixed,
+                                                                  float* __restrict__ part,
+                                                                  float* __restrict__ lpart, AdjGeom a, FusedSplit fs,
+                                                                  const float* __restrict__ lut) {
+  extern __shared__ float fused_smem[];
+  const FusedLds lds = fused_lds(a);
+  float* ring = fused_smem + lds.ring;
+  float* red = fused_smem + lds.red;
+  float* slabs = fused_smem + lds.slabs;
   const VolGeom& g = a.g;
-  const int dx = DX > 0 ? DX : g.dx;
-  const AdjBrick b = adj_brick_geom(a, brick);
-  float* pbase = part + (size_t)brick * adj_brick_stride(a);
+  const int tid = threadIdx.x;
+  const int item = xcd_remap(blockIdx.x, gridDim.x);
+  const int nxy = a.x.nb * a.y.nb;
+  const int bz0 = item / nxy * fs.deep, bz1 = imin(bz0 + fs.deep, a.z.nb);
+  const int bxy = item % nxy;
+  AdjBrick b = adj_brick_geom(a, bz0 * nxy + bxy);
+  int bz = bz0;
+  const int zend = adj_brick_begin(a.z, g.nz, bz1);  // the workgroup's last plane + 1
   const int lane = tid & (kWave - 1), wave = uniform(tid / kWave);
 
-  // this lane's voxels: column x, rows y[r]; forward weights and window bases
-  const int x = b.x0 + lane;
-  const int xc = imin(x, b.xe - 1);
-  const int tx = xc / dx;
-  float bx[4];
+  // this lane's voxel column (x, y): forward weights and window base
+  const int x = b.x0 + lane, y = b.y0 + wave;
+  const int xc = imin(x, b.xe - 1), yc = imin(y, b.ye - 1);
+  const bool act = x < b.xe && y < b.ye;
+  const int tx = xc / g.dx, ty = yc / g.dy;
+  float bx[4], by[4];
   {
-    const float* w = lut_row(lut, dx, xc - tx * dx);
+    const float* wx = lut_row(lut, g.dx, xc - tx * g.dx);
+    const float* wy = lut_row(lut, g.dy, yc - ty * g.dy);
 #pragma unroll
-    for (int l = 0; l < 4; ++l) bx[l] = w[l];
+    for (int l = 0; l < 4; ++l) bx[l] = wx[l], by[l] = wy[l];
   }
-  int yv[R], base[R];
-  bool act[R];
-  float by[R][4];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    yv[r] = b.y0 + wave * R + r;
-    act[r] = x < b.xe && yv[r] < b.ye;
-    const int yc = imin(yv[r], b.ye - 1);
-    const int ty = yc / g.dy;
-    const float* w = lut_row(lut, g.dy, yc - ty * g.dy);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) by[r][m] = w[m];
-    base[r] = ((ty - b.cy0) * CXM + (tx - b.cx0)) * 3;
-  }
-  const FusedStage<DX> map = fused_stage_map<DX>(g, b, tid);
-  adj_zero_fpad<DX, R>(sm.adj, wave, lane);
+  const int pitch = a.x.cm * 3;
+  const int base = (ty - b.cy0) * pitch + (tx - b.cx0) * 3;
+  const FusedStage<L> map = fused_stage_map<L>(a, b, tid);
+  // the cell whose planes this wave contracts (waves 0 .. kAdjWaves - 1)
+  const AdjCell cell = adj_cell_geom(a, b, imin(wave, kAdjWaves - 1));
+  const bool contracts = wave < kAdjWaves && cell.nx > 0 && cell.ny > 0;
+  const AdjWeights cw = adj_cell_weights(a, cell, lut, lane);
 
   // Q of the 4 control planes of the first z-tile, one plane staged at a time
   int tz = b.cz0;  // z-bricks are whole tiles: b.z0 = tz * dz
-  F3 Q[R][4];
-  float st[fused_loads<DX>()];
+  F3 Q[4];
+  float st[L];
 #pragma unroll 1
   for (int j = 0; j < 4; ++j) {
-    __syncthreads();  // the slot's previous plane has been contracted (or a previous brick is done)
-    fused_fetch<DX>(grid, g, map, tz + j, st);
-    fused_stage<DX>(sm.ring[(tz + j) & 1], map, st);
+    __syncthreads();  // the slot's previous plane has been contracted
+    fused_fetch<L>(grid, g, map, tz + j, st);
+    fused_stage<L>(ring + ((tz + j) & 1) * lds.slot, map, st);
     __syncthreads();
+    const F3 q = fused_contract(ring + ((tz + j) & 1) * lds.slot, base, pitch, bx, by);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const F3 q = fused_contract<DX>(sm.ring[(tz + j) & 1], base[r], bx, by[r]);
-#pragma unroll
-      for (int n = 0; n < 3; ++n) Q[r][n] = Q[r][n + 1];
-      Q[r][3] = q;
-    }
+    for (int n = 0; n < 3; ++n) Q[n] = Q[n + 1];
+    Q[3] = q;
   }
   // the next tile's new plane tz + 4 (when another tile follows inside the
-  // brick, it is at most ceil(nz/dz) + 2 = gz - 1)
-  bool more = (tz + 1) * g.dz < b.ze;
-  if (more) fused_fetch<DX>(grid, g, map, tz + 4, st);
+  // workgroup's range, it is at most ceil(nz/dz) + 2 = gz - 1)
+  if ((tz + 1) * g.dz < zend) fused_fetch<L>(grid, g, map, tz + 4, st);
 
-  F3 acc[R][4];
+  F3 acc[4];
 #pragma unroll
-  for (int r = 0; r < R; ++r)
-#pragma unroll
-    for (int n = 0; n < 4; ++n) acc[r][n] = F3{0.f, 0.f, 0.f};
+  for (int n = 0; n < 4; ++n) acc[n] = F3{0.f, 0.f, 0.f};
   float l2 = 0.f;
-  auto finish = [&](int czl, bool last) {
-    F3 f[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) f[r] = acc[r][0];
-    adj_emit_x<DX, R>(b, sm.adj, lut, dx, tid, czl, [&](int r) { return f[r]; });
+  int turn = 0;  // which F the next plane goes to
+  // The finished plane acc[0] to F, the barrier, its contraction into the
+  // slabs; the accumulators move up.  A wave's store to F[turn] two planes on
+  // follows a barrier that the contracting waves reach after their reads.
+  auto emit = [&](int czl) {
+    float* F = fused_smem + lds.F + turn * kFusedWaves * kFusedFRow;
+    stf3(F + wave * kFusedFRow + lane * 3, acc[0]);
     __syncthreads();
-    adj_emit_y<DX, kFusedWaves, StageAll>(a, b, pbase, sm.adj, lut, tid, czl, last);
+    const int slot = Staged ? czl : czl & 1;
+    if (contracts) {
+      F3 f[kAdjSteps];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-#pragma unroll
-      for (int n = 0; n < 3; ++n) acc[r][n] = acc[r][n + 1];
-      acc[r][3] = F3{0.f, 0.f, 0.f};
+      for (int s = 0; s < kAdjSteps; ++s)
+        f[s] = ldf3(F + (cell.y0 - b.y0 + adj_lane_row(lane, s)) * kFusedFRow +
+                    (cell.x0 - b.x0 + lane % kAdjCellX) * 3);
+      adj_cell_emit(f, cw, slabs + adj_slab_at(a, slot, wave), a.cw, a.ch, lane);
     }
+    if constexpr (!Staged) {
+      __syncthreads();
+      adj_combine_slabs(a, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, 1, slot, tid,
+                        kFusedThreads);
+    }
+    turn ^= 1;
+#pragma unroll
+    for (int n = 0; n < 3; ++n) acc[n] = acc[n + 1];
+    acc[3] = F3{0.f, 0.f, 0.f};
   };
 
   // Per voxel plane, in two stages: (a) T from the 4 contracted planes, the
@@ -214,15 +250,13 @@ __device__ __forceinline__ void fused_brick(const float* __restrict__ grid, cons
   // a clamped sample position), so that no load is conditional and waiting
   // for one plane's loads leaves the next plane's in flight; (b) ignores the
   // values of such lanes.
-  static_assert(R == 1, "one voxel row per lane");
   struct Pending {
     SampleIn s;
     float fx;
     float w[4];  // Bz_0..3 of the plane's offset in its tile
   };
   const size_t izs = (size_t)g.ny * g.nx;
-  const int y = yv[0];
-  const size_t fxy = (size_t)imin(y, b.ye - 1) * g.nx + xc;  // the lane's (clamped) voxel column
+  const size_t fxy = (size_t)yc * g.nx + xc;  // the lane's (clamped) voxel column
   auto stage_a = [&](int z, int oz) {
     Pending p;
     const float* wz = lut_row(lut, g.dz, oz);
@@ -230,15 +264,15 @@ __device__ __forceinline__ void fused_brick(const float* __restrict__ grid, cons
     for (int n = 0; n < 4; ++n) p.w[n] = wz[n];
     p.fx = fixed[(size_t)z * izs + fxy];
     // T as the forward kernel forms it
-    const F3 t{fmaf(p.w[3], Q[0][3].x, fmaf(p.w[2], Q[0][2].x, fmaf(p.w[1], Q[0][1].x, p.w[0] * Q[0][0].x))),
-               fmaf(p.w[3], Q[0][3].y, fmaf(p.w[2], Q[0][2].y, fmaf(p.w[1], Q[0][1].y, p.w[0] * Q[0][0].y))),
-               fmaf(p.w[3], Q[0][3].z, fmaf(p.w[2], Q[0][2].z, fmaf(p.w[1], Q[0][1].z, p.w[0] * Q[0][0].z)))};
+    const F3 t{fmaf(p.w[3], Q[3].x, fmaf(p.w[2], Q[2].x, fmaf(p.w[1], Q[1].x, p.w[0] * Q[0].x))),
+               fmaf(p.w[3], Q[3].y, fmaf(p.w[2], Q[2].y, fmaf(p.w[1], Q[1].y, p.w[0] * Q[0].y))),
+               fmaf(p.w[3], Q[3].z, fmaf(p.w[2], Q[2].z, fmaf(p.w[1], Q[1].z, p.w[0] * Q[0].z)))};
     p.s = trilinear_load<Pairs>(moving, g.nx, g.ny, g.nz, (float)x + t.x, (float)y + t.y, (float)z + t.z);
     return p;
   };
   auto stage_b = [&](const Pending& p) {
     F3 d{0.f, 0.f, 0.f};
-    if (act[0]) {
+    if (act) {
       // the SSD kernel's residual and gradient
       const Sample s = trilinear_finish(p.s);
       const float res = s.w - p.fx;
@@ -249,14 +283,14 @@ __device__ __forceinline__ void fused_brick(const float* __restrict__ grid, cons
     // the adjoint's z-accumulation
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      acc[0][n].x = fmaf(p.w[n], d.x, acc[0][n].x);
-      acc[0][n].y = fmaf(p.w[n], d.y, acc[0][n].y);
-      acc[0][n].z = fmaf(p.w[n], d.z, acc[0][n].z);
+      acc[n].x = fmaf(p.w[n], d.x, acc[n].x);
+      acc[n].y = fmaf(p.w[n], d.y, acc[n].y);
+      acc[n].z = fmaf(p.w[n], d.z, acc[n].z);
     }
   };
 
-  for (int z = b.z0; z < b.ze;) {  // one z-tile (the brick's last may be partial)
-    const int np = imin(g.dz, b.ze - z);
+  for (int z = b.z0; z < zend;) {  // one z-tile (the volume's last may be partial)
+    const int np = imin(g.dz, zend - z);
     // two register sets, used in turn (a copy from one to the other would
     // wait for the loads it copies)
     Pending p0 = stage_a(z, 0);
@@ -275,60 +309,42 @@ __device__ __forceinline__ void fused_brick(const float* __restrict__ grid, cons
       stage_b(p0);
     }
     z += np;
-    if (np == g.dz && z < b.ze) {
-      // plane tz + 4 goes to the slot of plane tz + 2, contracted before the
-      // previous tile's barrier; the emission's barrier orders the store
-      // before the contraction below
-      fused_stage<DX>(sm.ring[(tz + 4) & 1], map, st);
-      F3 f[R];
+    // plane tz + 4 goes to the slot of plane tz + 2, contracted before the
+    // previous tile's barrier; the emission's barrier orders the store
+    // before the contraction below
+    const bool more = z < zend;
+    if (more) fused_stage<L>(ring + ((tz + 4) & 1) * lds.slot, map, st);
+    emit(tz - b.cz0);
+    if (more) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) f[r] = acc[r][0];
-      adj_emit_x<DX, R>(b, sm.adj, lut, dx, tid, tz - b.cz0, [&](int r) { return f[r]; });
-      __syncthreads();
-      adj_emit_y<DX, kFusedWaves, StageAll>(a, b, pbase, sm.adj, lut, tid, tz - b.cz0, false);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-#pragma unroll
-        for (int n = 0; n < 3; ++n) {
-          acc[r][n] = acc[r][n + 1];
-          Q[r][n] = Q[r][n + 1];
-        }
-        acc[r][3] = F3{0.f, 0.f, 0.f};
-        Q[r][3] = fused_contract<DX>(sm.ring[(tz + 4) & 1], base[r], bx, by[r]);
+      for (int n = 0; n < 3; ++n) Q[n] = Q[n + 1];
+      Q[3] = fused_contract(ring + ((tz + 4) & 1) * lds.slot, base, pitch, bx, by);
+    }
+    if (z == b.ze) {  // the brick's last three control planes, then the next brick
+#pragma unroll 1
+      for (int n = 1; n < 4; ++n) emit(tz - b.cz0 + n);
+      if constexpr (Staged) {
+        // the next plane's barrier orders this sum before its store to the slabs
+        __syncthreads();
+        adj_combine_slabs(a, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), 0, adj_brick_cz(a, b), 0,
+                          tid, kFusedThreads);
       }
+      if (more) b = adj_brick_geom(a, ++bz * nxy + bxy);
+    }
+    if (more) {
       ++tz;
-      more = (tz + 1) * g.dz < b.ze;
-      if (more) fused_fetch<DX>(grid, g, map, tz + 4, st);
+      if ((tz + 1) * g.dz < zend) fused_fetch<L>(grid, g, map, tz + 4, st);
     }
   }
-#pragma unroll 1
-  for (int n = 0; n < 4; ++n) finish(tz - b.cz0 + n, n == 3);
 
-  // loss partial of the brick: fixed-order tree over the workgroup
-  sm.red[tid] = l2;
+  // the workgroup's loss partial: fixed-order tree
+  red[tid] = l2;
   __syncthreads();
   for (int h = kFusedThreads / 2; h > 0; h >>= 1) {
-    if (tid < h) sm.red[tid] += sm.red[tid + h];
+    if (tid < h) red[tid] += red[tid + h];
     __syncthreads();
   }
-  if (tid == 0) lpart[brick] = sm.red[0];
-}
-
-template <int DX, int Pairs = 1>
-__global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float* __restrict__ grid,
-                                                                  const float* __restrict__ moving,
-                                                                  const float* __restrict__ fixed,
-                                                                  float* __restrict__ part,
-                                                                  float* __restrict__ lpart, AdjGeom a,
-                                                                  const float* __restrict__ lut) {
-  __shared__ FusedSmem<DX> sm;
-  const int nbricks = a.x.nb * a.y.nb * a.z.nb;
-  const int brick = xcd_remap(blockIdx.x, gridDim.x);
-  if (brick >= nbricks) return;  // uniform over the workgroup
-  if (adj_stage_all(a))
-    fused_brick<DX, true, Pairs>(grid, moving, fixed, part, lpart, a, lut, brick, sm, threadIdx.x);
-  else
-    fused_brick<DX, false, Pairs>(grid, moving, fixed, part, lpart, a, lut, brick, sm, threadIdx.x);
+  if (tid == 0) lpart[item] = red[0];
 }
 
 }  // namespace
@@ -342,7 +358,7 @@ size_t fused_workspace_bytes(const AdjGeom& a) {
 // fixed-order gather of each control point's partials), and with `descend`
 // also the descent update grid -= eta grad of the points they gather (pass 1
 // has finished reading the grid: it ran before, on the same stream); workgroup
-// nblk sums the bricks' loss partials in a fixed order.
+// nblk sums the loss partials in a fixed order.
 constexpr int kTailThreads = kGatherThreads;
 
 __global__ __launch_bounds__(kTailThreads) void fused_tail_kernel(const float* __restrict__ part,
@@ -381,40 +397,34 @@ hipError_t launch_ssd_fused(const float* grid, const float* moving, const float*
   float* part = static_cast<float*>(workspace);
   float* lpart = reinterpret_cast<float*>(static_cast<char*>(workspace) +
                                           (adj_workspace_bytes(a) + 255) / 256 * 256);
-  const long nbricks = (long)a.x.nb * a.y.nb * a.z.nb;
-  const dim3 gridd((unsigned)nbricks), block(kFusedThreads);
-#define BSI_FUSED_CASE(D)                                                                               \
-  case D:                                                                                               \
-    hipLaunchKernelGGL(fused_pass1_kernel<D>, gridd, block, 0, s, grid, moving, fixed, part, lpart, a, lut); \
-    break;
-  static_assert(kAdjMaxDX == 12, "one case per specialised spacing");
-  // a volume one voxel wide samples its x-neighbours one by one (generic kernel)
-  switch (a.g.nx >= 2 ? a.g.dx : -1) {
-    case -1:
-      hipLaunchKernelGGL((fused_pass1_kernel<0, 0>), gridd, block, 0, s, grid, moving, fixed, part, lpart, a, lut);
-      break;
-    BSI_FUSED_CASE(1)
-    BSI_FUSED_CASE(2)
-    BSI_FUSED_CASE(3)
-    BSI_FUSED_CASE(4)
-    BSI_FUSED_CASE(5)
-    BSI_FUSED_CASE(6)
-    BSI_FUSED_CASE(7)
-    BSI_FUSED_CASE(8)
-    BSI_FUSED_CASE(9)
-    BSI_FUSED_CASE(10)
-    BSI_FUSED_CASE(11)
-    BSI_FUSED_CASE(12)
-    default: BSI_FUSED_CASE(0)
+  const FusedSplit fs = fused_split(a);
+  const long items = (long)a.x.nb * a.y.nb * fs.nz;
+  const FusedLds lds = fused_lds(a);
+  const dim3 gridd((unsigned)items), block(kFusedThreads);
+  const size_t bytes = (size_t)lds.total * sizeof(float);
+#define BSI_FUSED_LAUNCH(L, STAGED, PAIRS)                                                                        \
+    hipLaunchKernelGGL((fused_pass1_kernel<L, STAGED, PAIRS>), gridd, block, bytes, s, grid, moving, fixed, part, \
+                       lpart, a, fs, lut)
+  // a volume one voxel wide samples its x-neighbours one by one
+  const bool staged = adj_staged(a), one = fused_loads(lds.slot) <= 1;
+  if (a.g.nx < 2) {
+    if (staged) BSI_FUSED_LAUNCH(kFusedMaxLoads, true, 0);
+    else BSI_FUSED_LAUNCH(kFusedMaxLoads, false, 0);
+  } else if (one) {
+    if (staged) BSI_FUSED_LAUNCH(1, true, 1);
+    else BSI_FUSED_LAUNCH(1, false, 1);
+  } else {
+    if (staged) BSI_FUSED_LAUNCH(kFusedMaxLoads, true, 1);
+    else BSI_FUSED_LAUNCH(kFusedMaxLoads, false, 1);
   }
-#undef BSI_FUSED_CASE
+#undef BSI_FUSED_LAUNCH
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t nblk = adj_gather_blocks(a.g);
-  if (nblk + 1 >= ((int64_t)1 << 31) || nbricks >= ((int64_t)1 << 31))
+  if (nblk + 1 >= ((int64_t)1 << 31))
     return hipErrorInvalidConfiguration;  // a field far beyond device memory
   hipLaunchKernelGGL(fused_tail_kernel, dim3((unsigned)(nblk + 1)), dim3(kTailThreads), 0, s, part, grad, descend_grid,
-                     eta, descend_grid != nullptr ? 1 : 0, lpart, (int)nbricks, loss, a, (int)nblk);
+                     eta, descend_grid != nullptr ? 1 : 0, lpart, (int)items, loss, a, (int)nblk);
   return hipGetLastError();
 }
 

@@ -47,6 +47,10 @@ __device__ __forceinline__ int gen_weights(const GenAxis& a, int v, float (&w)[4
   return i;
 }
 
+__device__ __forceinline__ F3 ldf3_nt(const float* p) {
+  return F3{__builtin_nontemporal_load(p), __builtin_nontemporal_load(p + 1), __builtin_nontemporal_load(p + 2)};
+}
+
 constexpr int kGenMaxZ = 256;  // voxel planes per workgroup (z table in LDS)
 
 struct GenFwdSmem {
@@ -379,7 +383,7 @@ __global__ __launch_bounds__(kGzThreads) __attribute__((amdgpu_waves_per_eu(BSI_
         acc[k][r].z = fmaf(ws[k], D[r].z, acc[k][r].z);                                       \
       }                                                                                       \
     if (LOAD) {                                                                               \
-      _Pragma("unroll") for (int r = 0; r < kGzRows; ++r) D[r] = ldf3_dfield<true>(ahead + off[r]); \
+      _Pragma("unroll") for (int r = 0; r < kGzRows; ++r) D[r] = ldf3_nt(ahead + off[r]); \
     }                                                                                         \
     ahead += plane;                                                                           \
     if ((Z) + 1 == tend && (Z) + 1 < b.ze) {                                                  \
@@ -395,9 +399,9 @@ __global__ __launch_bounds__(kGzThreads) __attribute__((amdgpu_waves_per_eu(BSI_
   const float* base0 = dfield + (size_t)b.z0 * plane;
   F3 d0[kGzRows], d1[kGzRows];
 #pragma unroll
-  for (int r = 0; r < kGzRows; ++r) d0[r] = ldf3_dfield<true>(base0 + off[r]);
+  for (int r = 0; r < kGzRows; ++r) d0[r] = ldf3_nt(base0 + off[r]);
 #pragma unroll
-  for (int r = 0; r < kGzRows; ++r) d1[r] = ldf3_dfield<true>(base0 + (b.ze - b.z0 > 1 ? plane : 0) + off[r]);
+  for (int r = 0; r < kGzRows; ++r) d1[r] = ldf3_nt(base0 + (b.ze - b.z0 > 1 ? plane : 0) + off[r]);
   const float* ahead = base0 + 2 * plane;
   int t = b.cz0;                    // the z-tile of the plane at hand (the brick starts on a tile)
   int tend = T.first[2][t + 1];     // its end

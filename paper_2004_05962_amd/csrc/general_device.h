@@ -66,6 +66,64 @@ __host__ __device__ inline int gen_tile(const GenAxis& a, int v) {
 }
 
 
+constexpr int kAdjTiles = 16;  // tile lanes per row of lanes (DPP rows)
+
+// Value of lane i - N of this lane's row of 16 lanes, 0 for i < N (DPP
+// row_shr); row_shl: lane i + N, 0 for i + N >= 16.  Lanes past the row's
+// edge read the zero `old` operand.
+template <int N>
+__device__ __forceinline__ float row_shr(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x110 + N, 0xF, 0xF, true));
+}
+template <int N>
+__device__ __forceinline__ float row_shl(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x100 + N, 0xF, 0xF, true));
+}
+
+// Window column of tile lanes: lane t of a row of 16 holds the moments M_l of
+// tile t; this forms
+//   cm = S[t]      = sum_{l <= t} M_l(tile t - l)
+//   cw = S[16 + t] = sum_{l > t}  M_l(tile 16 + t - l)   (t < 3)
+// l ascending.  The shifts bring in zero for the terms a lane does not take
+// (row_shr by l for l > t, row_shl by 16 - l for l <= t), and adding zero is
+// exact, so no per-lane selects are needed.  Idle lanes hold M = 0, so columns
+// past the last tile come out right.  Every lane of the wave takes part (no
+// lane may be inactive).
+__device__ __forceinline__ void adj_combine(const F3 (&M)[4], F3& cm, F3& cw) {
+  cm = M[0];
+  cm.x += row_shr<1>(M[1].x);
+  cm.y += row_shr<1>(M[1].y);
+  cm.z += row_shr<1>(M[1].z);
+  cm.x += row_shr<2>(M[2].x);
+  cm.y += row_shr<2>(M[2].y);
+  cm.z += row_shr<2>(M[2].z);
+  cm.x += row_shr<3>(M[3].x);
+  cm.y += row_shr<3>(M[3].y);
+  cm.z += row_shr<3>(M[3].z);
+  cw.x = row_shl<15>(M[1].x);
+  cw.y = row_shl<15>(M[1].y);
+  cw.z = row_shl<15>(M[1].z);
+  cw.x += row_shl<14>(M[2].x);
+  cw.y += row_shl<14>(M[2].y);
+  cw.z += row_shl<14>(M[2].z);
+  cw.x += row_shl<13>(M[3].x);
+  cw.y += row_shl<13>(M[3].y);
+  cw.z += row_shl<13>(M[3].z);
+  // cm is formed here, not sunk into the callers' conditional stores (which
+  // keeps all nine shifted values live at once and spills)
+  asm volatile("" : "+v"(cm.x), "+v"(cm.y), "+v"(cm.z));
+}
+
+// Moments += w_l * v for l = 0..3.
+__device__ __forceinline__ void adj_moment_step(const float* __restrict__ w, const F3& v, F3 (&M)[4]) {
+#pragma unroll
+  for (int l = 0; l < 4; ++l) {
+    M[l].x = fmaf(w[l], v.x, M[l].x);
+    M[l].y = fmaf(w[l], v.y, M[l].y);
+    M[l].z = fmaf(w[l], v.z, M[l].z);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Bricks of the z-first adjoint (general.hip): 64 x-voxels by 16 rows by the
 // voxels of kz whole z-tiles.

@@ -34,40 +34,60 @@ struct Check {
 
 // Loads and LDS indices of pass 1 (adj_brick) for one brick.
 bool check_adj_brick(const AdjGeom& a, const AdjBrick& b, Check& ck) {
-  const size_t plane = (size_t)a.g.nx * a.g.ny * 3;
-  REQUIRE(b.z0 == b.cz0 * a.g.dz, "z-bricks start on tile boundaries (the march starts at offset 0)");
-  REQUIRE(b.xe - b.x0 <= kAdjBX && b.ye - b.y0 <= kAdjBY, "brick within one lane per voxel and row");
-  const int dxc = a.g.dx <= kAdjMaxDX ? a.g.dx : 0;
-  REQUIRE(b.Cx <= adj_cx_max(dxc), "x window within the H buffer's row");
-  REQUIRE(b.Cy - 3 <= kAdjTiles, "y-tiles within one row of tile lanes");
-  if (adj_tile_lanes(dxc)) REQUIRE(b.ntx <= kAdjTiles, "x-tiles within one row of tile lanes");
-  if (a.g.dx >= 4 && a.g.dx <= kAdjMaxDX) {  // the run-time-spacing kernel (batched pass 1) reads the same bricks
-    REQUIRE(b.Cx <= adj_cx_max(kAdjAnyTile), "x window within the run-time-spacing kernel's H row");
-    for (int t = 0; t < b.ntx; ++t) {
-      const int xt = (b.cx0 + t) * a.g.dx - b.x0;
-      REQUIRE(xt >= -adj_fpad(kAdjAnyTile) && xt + a.g.dx <= kWave + adj_fpad(kAdjAnyTile),
-              "x-tile within the run-time-spacing kernel's padded F row");
+  const VolGeom& g = a.g;
+  const size_t plane = (size_t)g.nx * g.ny * 12;
+  const size_t lds = adj_lds_bytes(a) / sizeof(float);
+  const int cz = adj_brick_cz(a, b);
+  REQUIRE(b.z0 == b.cz0 * g.dz, "z-bricks start on tile boundaries (the march starts at offset 0)");
+  REQUIRE(b.ye - b.y0 <= kAdjCellsY * kAdjCellY && b.xe - b.x0 <= kAdjCellsX * a.cell, "brick within its cells");
+  REQUIRE(a.slots >= 2 && (!adj_staged(a) || cz <= a.slots), "slots for the brick's planes");
+  REQUIRE(adj_lds_bytes(a) <= 80000, "LDS request of two workgroups per CU");
+  std::vector<int> voxels((size_t)(b.xe - b.x0) * (b.ye - b.y0), 0), points((size_t)b.Cx * b.Cy, 0);
+  for (int w = 0; w < kAdjWaves; ++w) {
+    const AdjCell c = adj_cell_geom(a, b, w);
+    const bool any = c.nx > 0 && c.ny > 0;
+    if (adj_staged(a) && !any) continue;  // the wave only meets the barrier
+    REQUIRE(c.Cx <= kAdjTile && c.Cx <= a.cw && c.Cy <= kAdjTile && c.Cy <= a.ch,
+            "window within a matrix tile and the slab");
+    if (any) {
+      REQUIRE(c.cx0 >= b.cx0 && c.cx0 + c.Cx <= b.cx0 + b.Cx && c.cy0 >= b.cy0 && c.cy0 + c.Cy <= b.cy0 + b.Cy,
+              "cell window within the brick's");
+      for (int j = 0; j < c.Cy; ++j)
+        for (int i = 0; i < c.Cx; ++i) points[(size_t)(c.cy0 - b.cy0 + j) * b.Cx + c.cx0 - b.cx0 + i] = 1;
+      // a slab entry of the last slot, row and column
+      REQUIRE((size_t)adj_slab_at(a, a.slots - 1, w) + adj_slab(a) <= lds, "slab store outside the LDS request");
+      REQUIRE(a.cw % 4 == 0 && adj_slab_point(a, 2, a.ch - 1, a.cw - 4) + 4 <= adj_slab(a), "slab store outside its slab");
+      REQUIRE(a.ch <= kAdjTile && a.cw <= kAdjTile && adj_slab_point(a, 2, c.Cy - 1, c.Cx - 1) < adj_slab(a),
+              "slab read outside its slab");
+      // the fused step reads the finished plane's voxels of the cell from F, 16 rows of 64
+      REQUIRE(c.x0 - b.x0 + kAdjCellX <= kWave && c.y0 - b.y0 + kAdjCellY <= kAdjCellsY * kAdjCellY,
+              "cell within the fused step's rows");
     }
-  }
-  if (adj_fpad(dxc) > 0)  // a tile's voxels, read without tests, lie within the row and its zero pads
-    for (int t = 0; t < b.ntx; ++t) {
-      const int xt = (b.cx0 + t) * a.g.dx - b.x0;
-      REQUIRE(xt >= -adj_fpad(dxc) && xt + a.g.dx <= kWave + adj_fpad(dxc), "x-tile within the padded F row");
-    }
-  if (adj_stage_all(a)) REQUIRE((size_t)adj_brick_cz(a, b) * a.y.cm * a.x.cm * 3 <= (size_t)kAdjStageFloats,
-                                "staged partials within the LDS stage");
-  for (int w = 0; w < kAdjWaves; ++w)
+    const int cnx = any ? c.nx : 1, cny = any ? c.ny : 1;
+    const size_t base = ((size_t)(any ? c.y0 : b.y0) * g.nx + (any ? c.x0 : b.x0)) * 12;
     for (int lane = 0; lane < kWave; ++lane) {
-      uint32_t off[kAdjRows];
-      adj_offsets<kAdjRows>(b, a.g.nx, w, lane, off);
-      for (int r = 0; r < kAdjRows; ++r) {
-        REQUIRE((size_t)off[r] + 3 <= plane, "pass-1 load outside its voxel plane");
-        const int x = (int)(off[r] / 3 % a.g.nx), y = (int)(off[r] / 3 / a.g.nx);
+      uint32_t off[kAdjSteps];
+      adj_cell_offsets(g.nx, cnx, cny, lane, off);
+      for (int s = 0; s < kAdjSteps; ++s) {
+        REQUIRE(base + off[s] + 12 <= plane, "pass-1 load outside its voxel plane");
+        REQUIRE(off[s] + 12 <= adj_cell_bytes(g.nx, cnx, cny), "pass-1 load outside its buffer");
+        const size_t v = (base + off[s]) / 12;
+        const int x = (int)(v % g.nx), y = (int)(v / g.nx);
         REQUIRE(x >= b.x0 && x < b.xe && y >= b.y0 && y < b.ye, "pass-1 load outside its brick");
+        if (any && lane % kAdjCellX < c.nx && adj_lane_row(lane, s) < c.ny) {
+          REQUIRE(x == c.x0 + lane % kAdjCellX && y == c.y0 + adj_lane_row(lane, s), "pass-1 lane's voxel");
+          ++voxels[(size_t)(y - b.y0) * (b.xe - b.x0) + x - b.x0];
+        }
       }
     }
-  // the fused step stages each control plane's window (Cy rows x Cx points)
-  REQUIRE(b.Cy <= kAdjBY + 3, "fused staging rows");
+  }
+  for (int n : voxels) REQUIRE(n == 1, "every voxel of the brick has one lane");
+  for (int n : points) REQUIRE(n == 1, "every window point of the brick lies in a cell's window");
+  // the rows that the first product's steps take: each of the cell's rows once
+  int rows = 0;
+  for (int t = 0; t < 2; ++t)
+    for (int k = 0; k < 4; ++k) rows |= 1 << adj_step_row(t, k);
+  REQUIRE(rows == (1 << kAdjCellY) - 1, "product steps cover the cell's rows");
   return true;
 }
 
@@ -351,12 +371,12 @@ int bsi_check_general_indices(const int32_t dims[3], const float spacing[3], con
 // once and every workgroup's loop ends within ceil(total / grid) passes.
 int bsi_check_batch_items(char* msg, int msglen) {
   Check ck;
-  auto run = [&](int64_t total, int grid, bool persistent) -> bool {
+  auto run_order = [&](int64_t total, int grid, bool persistent, bool runs) -> bool {
     std::vector<int> hit((size_t)total, 0);
     const int64_t max_pass = (total + grid - 1) / grid;
     for (int b = 0; b < grid; ++b) {
       int64_t passes = 0;
-      for (ItemRange r = batch_items(b, grid, total, persistent); r.first < total; r.first += r.step) {
+      for (ItemRange r = batch_items(b, grid, total, persistent, runs); r.first < total; r.first += r.step) {
         REQUIRE(r.first >= 0, "item below zero");
         REQUIRE(++passes <= max_pass, "a workgroup's item loop does not end");
         ++hit[(size_t)r.first];
@@ -364,6 +384,9 @@ int bsi_check_batch_items(char* msg, int msglen) {
     }
     for (int h : hit) REQUIRE(h == 1, "an item taken other than once");
     return true;
+  };
+  auto run = [&](int64_t total, int grid, bool persistent) -> bool {
+    return run_order(total, grid, persistent, false) && run_order(total, grid, persistent, true);
   };
   for (int64_t total : {1L, 2L, 7L, 8L, 9L, 100L, 1000L, 4097L, 20000L}) {
     if (!run(total, (int)total, false)) break;

@@ -3,8 +3,8 @@
 // tight serving loops, harnesses that forbid hipMalloc.
 //
 // The adjoint's partials (what bsi_adjoint keeps in the caller's workspace) go
-// to `scratch`, a static device array of BSI_ADJOINT_NOALLOC_MAX_BYTES, which
-// every GPU the library runs on holds until the process ends.  All calls on
+// to `scratch`, a static device array of a little over
+// BSI_ADJOINT_NOALLOC_MAX_BYTES, which every GPU the library runs on holds until the process ends.  All calls on
 // one GPU share that GPU's array: calls that may overlap on one GPU (several
 // streams or host threads) race on it, and the caller must order them.
 // Nothing needs clearing between calls: pass 1 writes every partial that
@@ -16,8 +16,7 @@
 
 namespace bsi {
 
-constexpr size_t kScratchBytes = BSI_ADJOINT_NOALLOC_MAX_BYTES;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kAdjScratchBytes];
 
 namespace {
 
@@ -66,10 +65,10 @@ int32_t bsi_adjoint_noalloc(const float* dfield, const int32_t dims[3], const in
     return BSI_ERR_INVALID_ARG;
   }
   const AdjGeom a = make_adj_geom(g);
-  const size_t need = adj_workspace_bytes(a);
-  if (need > kScratchBytes) {
+  const size_t need = adj_limit_bytes(g);
+  if (need > BSI_ADJOINT_NOALLOC_MAX_BYTES || adj_workspace_bytes(a) > kAdjScratchBytes) {
     set_error("bsi_adjoint_noalloc: this geometry needs " + std::to_string(need) +
-              " bytes of scratch, more than its fixed " + std::to_string(kScratchBytes) +
+              " bytes of scratch, more than its fixed " + std::to_string(BSI_ADJOINT_NOALLOC_MAX_BYTES) +
               "; use bsi_adjoint with a workspace");
     return BSI_ERR_UNSUPPORTED;
   }
