@@ -13,6 +13,7 @@
 #include "adjoint_device.h"
 #include "bsi_internal.h"
 #include "general_device.h"
+#include "warp_device.h"
 
 namespace bsi {
 namespace {
@@ -176,6 +177,18 @@ bool check_adjoint(const AdjGeom& a, BrickCheck brick_check, Check& ck) {
               REQUIRE(adj_part_addr(a, bx, by, bz, cx, cy, cz) + 3 <= ws, "pass-2 load outside the workspace");
             }
       }
+  return true;
+}
+
+// The sampling kernels' columns and z-chunks, and their loss partials.
+bool check_columns(const VolGeom& g, Check& ck) {
+  const ColLaunch c = make_col_launch(g);
+  const int64_t plane = (int64_t)g.nx * g.ny;
+  REQUIRE(c.npb >= 1 && (int64_t)c.npb * kColThreads >= plane && (int64_t)(c.npb - 1) * kColThreads < plane,
+          "column blocks cover the plane");
+  REQUIRE(c.nzb >= 1 && c.zchunk >= 1 && (int64_t)c.nzb * c.zchunk >= g.nz && (int64_t)(c.nzb - 1) * c.zchunk < g.nz,
+          "z-chunks cover the volume");
+  REQUIRE((size_t)c.npb * c.nzb <= ssd_partial_count(g), "loss partials within the SSD workspace");
   return true;
 }
 
@@ -346,7 +359,7 @@ int bsi_check_indices(const int32_t dims[3], const int32_t spacing[3], char* msg
     return -1;
   }
   Check ck;
-  check_adjoints(g, ck) && check_forward(g, ck);
+  check_adjoints(g, ck) && check_forward(g, ck) && check_columns(g, ck);
   std::snprintf(msg, msglen, "%s", ck.msg.c_str());
   return ck.ok ? 0 : 1;
 }

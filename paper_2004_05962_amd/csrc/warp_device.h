@@ -96,9 +96,59 @@ __device__ __forceinline__ Sample trilinear_finish(const SampleIn& c) {
   return s;
 }
 
-__device__ __forceinline__ Sample trilinear(const float* __restrict__ img, int nx, int ny, int nz, float px, float py,
-                                            float pz) {
-  return trilinear_finish(trilinear_load(img, nx, ny, nz, px, py, pz));
+// trilinear_load through a buffer resource over an image below 4 GiB: one 32-bit
+// lane offset, and the cell's other rows at the uniform distances sy and sz (bytes
+// to the next row and plane; 0 along an axis of one voxel, whose corners coincide).
+// The same operations on the same values as trilinear_load.  Pairs as there.
+template <int Pairs>
+__device__ __forceinline__ SampleIn trilinear_load_buffer(__amdgpu_buffer_rsrc_t img, int nx, int ny, int nz, int sy,
+                                                          int sz, float px, float py, float pz) {
+  const Axis ax = sample_axis(px, nx), ay = sample_axis(py, ny), az = sample_axis(pz, nz);
+  const int o = (int)((((uint32_t)az.i0 * (uint32_t)ny + (uint32_t)ay.i0) * (uint32_t)nx + (uint32_t)ax.i0) * 4u);
+  SampleIn s;
+  if constexpr (Pairs == 1) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 q00 = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(img, o, 0, 0));
+    const f2 q01 = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(img, o, sy, 0));
+    const f2 q10 = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(img, o, sz, 0));
+    const f2 q11 = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(img, o, sy + sz, 0));
+    s.c000 = q00.x, s.c001 = q00.y, s.c010 = q01.x, s.c011 = q01.y;
+    s.c100 = q10.x, s.c101 = q10.y, s.c110 = q11.x, s.c111 = q11.y;
+  } else {
+    s.c000 = s.c001 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(img, o, 0, 0));
+    s.c010 = s.c011 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(img, o, sy, 0));
+    s.c100 = s.c101 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(img, o, sz, 0));
+    s.c110 = s.c111 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(img, o, sy + sz, 0));
+  }
+  s.fx = ax.f, s.fy = ay.f, s.fz = az.f;
+  s.inx = ax.in, s.iny = ay.in, s.inz = az.in;
+  return s;
+}
+
+// A volume sampled voxel by voxel: thread t of workgroup item (pb, zb) owns the
+// voxel column p = pb kColThreads + t of the plane, p = y nx + x, and takes it
+// through the planes [zb zchunk, (zb + 1) zchunk).  Columns run on over the ends
+// of the rows, so that every lane is used at any width, the position in the row is
+// found once per column, and the two image planes of a voxel's cell are the next
+// voxel's too.
+constexpr int kColThreads = 256;
+struct ColLaunch {
+  int npb, nzb, zchunk;  // column blocks, z-chunks, planes per chunk
+};
+// About kColTarget workgroups (8 per CU), and at least kColPlanes planes per column where
+// the volume has them.
+constexpr long kColTarget = 2048;
+constexpr int kColPlanes = 4;
+inline ColLaunch make_col_launch(const VolGeom& g) {
+  ColLaunch c;
+  const int64_t columns = (int64_t)g.nx * g.ny;
+  c.npb = (int)((columns + kColThreads - 1) / kColThreads);
+  int64_t nzb = (kColTarget + c.npb - 1) / c.npb;
+  const int most = (g.nz + kColPlanes - 1) / kColPlanes;
+  if (nzb > most) nzb = most;
+  c.zchunk = (int)((g.nz + nzb - 1) / nzb);
+  c.nzb = (g.nz + c.zchunk - 1) / c.zchunk;
+  return c;
 }
 
 }  // namespace bsi
