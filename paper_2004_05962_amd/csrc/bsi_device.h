@@ -90,7 +90,8 @@ __host__ __device__ __forceinline__ int xcd_remap(int id, int n) {
   return xcd * q + (xcd < r ? xcd : r) + k;
 }
 
-// An order for items that differ in size: runs of kXcdRun consecutive items per XCD in turn.
+// Runs of kXcdRun consecutive items per XCD in turn, for items that differ in
+// size, or whose reads and writes at any moment should form one compact range.
 // Items of one volume are alike, but not those of different volumes (brick
 // depth, rows, z-chunks), so one contiguous range per XCD leaves XCDs idle at the
 // end (pass 1 of the 32-volume workload: 22% of the time); runs keep most

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kColThreads) void sample_kernel(const float* __rest
                                                               const float* __restrict__ fixed, VolGeom g,
                                                               ColLaunch L, float* __restrict__ out,
                                                               float* __restrict__ partials) {
-  const int item = xcd_remap(blockIdx.x, gridDim.x);
+  const int item = xcd_runs(blockIdx.x, gridDim.x);
   const int pb = item % L.npb, zb = item / L.npb;
   const size_t plane = (size_t)g.nx * g.ny;
   const size_t p0 = (size_t)pb * kColThreads;
@@ -99,8 +99,17 @@ constexpr int kReduceThreads = 1024;
 __global__ __launch_bounds__(kReduceThreads) void sum_kernel(const float* __restrict__ partials, long n,
                                                               float* __restrict__ out) {
   __shared__ float red[kReduceThreads];
+  // 8 loads in flight: one workgroup sums up to tens of thousands of partials
   float s = 0.f;
-  for (long i = threadIdx.x; i < n; i += kReduceThreads) s += partials[i];
+  long i = threadIdx.x;
+  for (; i + 7 * kReduceThreads < n; i += 8 * kReduceThreads) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = partials[i + k * kReduceThreads];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += v[k];
+  }
+  for (; i < n; i += kReduceThreads) s += partials[i];
   red[threadIdx.x] = s;
   __syncthreads();
   for (int h = kReduceThreads / 2; h > 0; h >>= 1) {

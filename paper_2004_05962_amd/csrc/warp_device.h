@@ -135,19 +135,16 @@ constexpr int kColThreads = 256;
 struct ColLaunch {
   int npb, nzb, zchunk;  // column blocks, z-chunks, planes per chunk
 };
-// About kColTarget workgroups (8 per CU), and at least kColPlanes planes per column where
-// the volume has them.
-constexpr long kColTarget = 2048;
+// kColPlanes planes per column: short workgroups in the order of the planes, so
+// that what is read and written at any moment is one compact range of addresses
+// (SSD at 512 x 400 x 220: 332 us, against 358 with planes for 2048 workgroups).
 constexpr int kColPlanes = 4;
 inline ColLaunch make_col_launch(const VolGeom& g) {
-  ColLaunch c;
   const int64_t columns = (int64_t)g.nx * g.ny;
+  ColLaunch c;
   c.npb = (int)((columns + kColThreads - 1) / kColThreads);
-  int64_t nzb = (kColTarget + c.npb - 1) / c.npb;
-  const int most = (g.nz + kColPlanes - 1) / kColPlanes;
-  if (nzb > most) nzb = most;
-  c.zchunk = (int)((g.nz + nzb - 1) / nzb);
-  c.nzb = (g.nz + c.zchunk - 1) / c.zchunk;
+  c.zchunk = kColPlanes;
+  c.nzb = (g.nz + kColPlanes - 1) / kColPlanes;
   return c;
 }
 
