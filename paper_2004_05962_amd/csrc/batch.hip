@@ -78,12 +78,13 @@ static_assert(kClassStreams + 1 >= 4, "the largest pass1_streams value");
 struct BatchConfig {
   int k[kNumKnobs];  // value index of each knob
 };
-// The starting point of the search: 8x1 forward, 512 items per volume, one
+// The starting point of the search: 8x1 forward, 2048 items per volume (short
+// workgroups in the order of the volumes: the forward 561 us against 672 with 512), one
 // workgroup per item in every pass, pass 1 in one launch for the spacings
 // 4..12 and per class for the rest over 4 streams, forward first with
 // ordinary stores (among the fastest graphs measured on the 32-volume
 // workload).
-static const BatchConfig kDefaultConfig = {{2, 0, 0, 0, 0, 2, 1, 0, 1}};
+static const BatchConfig kDefaultConfig = {{2, 1, 0, 0, 0, 2, 1, 0, 1}};
 
 int config_count() {
   int n = 1;
@@ -210,6 +211,7 @@ using namespace bsi;
 struct bsi_batch {
   int device = 0;
   int cus = 0;
+  int min_spacing = 0;  // the smallest x or y spacing of the volumes
   int count = 0;
   std::vector<VolDesc> host;  // descriptors (pointers filled by bind)
   std::vector<size_t> part_off;
@@ -277,7 +279,7 @@ int64_t pass_grid(const bsi_batch* p, int64_t total, int per_cu) {
 bool pass_persistent(int64_t total, int per_cu) { return per_cu > 0 || total > 0x7fffffff; }
 
 template <class T>
-void launch_fwd_shape(const bsi_batch* p, int64_t total, int per_cu, bool nt, hipStream_t s) {
+void launch_fwd_sized(const bsi_batch* p, int64_t total, int per_cu, bool nt, hipStream_t s) {
   const dim3 gd((unsigned)pass_grid(p, total, per_cu)), bd(T::threads);
   const bool pers = pass_persistent(total, per_cu);
   if (!pers && !nt)
@@ -290,6 +292,13 @@ void launch_fwd_shape(const bsi_batch* p, int64_t total, int per_cu, bool nt, hi
     hipLaunchKernelGGL((batch_fwd_kernel<T, true, true>), gd, bd, 0, s, p->d_desc, p->count, total, p->lut);
 }
 
+// Shape R x S: the instance for spacings of 3 and more when every volume has them.
+template <int R, int S>
+void launch_fwd_shape(const bsi_batch* p, int64_t total, int per_cu, bool nt, hipStream_t s) {
+  if (p->min_spacing >= 3) launch_fwd_sized<FwdTile<R, S, 1, 3>>(p, total, per_cu, nt, s);
+  else launch_fwd_sized<FwdTile<R, S, 1>>(p, total, per_cu, nt, s);
+}
+
 hipError_t launch_pass(bsi_batch* p, int pass, hipStream_t s) {
   const int64_t total = p->total[pass];
   if (total == 0) return hipSuccess;
@@ -298,9 +307,9 @@ hipError_t launch_pass(bsi_batch* p, int pass, hipStream_t s) {
     const bool nt = kFwdNT[p->cfg.k[kKFwdNT]] != 0;
     static_assert(kNumFwdShapes == 3, "one case per forward shape");
     switch (p->cfg.k[kKFwdShape]) {
-      case 0: launch_fwd_shape<FwdTile<4, 1, 1>>(p, total, per_cu, nt, s); break;
-      case 1: launch_fwd_shape<FwdTile<2, 2, 1>>(p, total, per_cu, nt, s); break;
-      default: launch_fwd_shape<FwdTile<8, 1, 1>>(p, total, per_cu, nt, s); break;
+      case 0: launch_fwd_shape<4, 1>(p, total, per_cu, nt, s); break;
+      case 1: launch_fwd_shape<2, 2>(p, total, per_cu, nt, s); break;
+      default: launch_fwd_shape<8, 1>(p, total, per_cu, nt, s); break;
     }
   } else if (pass == kAdj1) {
     return hipErrorInvalidValue;  // pass 1 is launched per class (launch_adj1_class)
@@ -594,6 +603,8 @@ int32_t bsi_batch_create(int32_t count, const int32_t* dims3xN, const int32_t* s
   p->part_off = std::move(off);
   for (int k = 0; k < 3; ++k) p->total[k] = tot[k];
   p->lut = lut;
+  p->min_spacing = BSI_MAX_SPACING;
+  for (const VolGeom& g : geoms) p->min_spacing = std::min({p->min_spacing, g.dx, g.dy});
   hipError_t e = hipDeviceGetAttribute(&p->cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) {
     delete p;

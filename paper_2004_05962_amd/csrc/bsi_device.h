@@ -159,13 +159,18 @@ constexpr int kFwdMaxCx = (kWave - 1) + 4;             // window width at spacin
 constexpr int kFwdMaxCy = (kFwdRows - 1) + 4;          // window height at spacing 1
 // Workgroup shape: R rows of S consecutive strips, one wave per (row, strip);
 // a lane owns V consecutive x-voxels, so a strip is 64 V voxels and a
-// workgroup row 64 S V.  The staged window is sized for spacing 1.
-template <int R, int S, int V>
+// workgroup row 64 S V.  M: the smallest spacing in x and y that the instance
+// takes; the staged window is sized for it.  At M = 3 a thread of the 4 x 1 shape
+// stages 2 floats per plane, at 5 one, at 1 six; the warm-up holds four planes'
+// loads in registers, and the 2 x 8 shape needs at most 64 of them for two
+// workgroups per CU (512 x 512 x 256, spacing 8: 270 us with one).
+template <int R, int S, int V, int M = 1>
 struct FwdTile {
-  static constexpr int rows = R, strips = S, lane_voxels = V;
+  static constexpr int rows = R, strips = S, lane_voxels = V, min_spacing = M;
   static constexpr int threads = kWave * R * S;
   static constexpr int width = kWave * S * V;  // voxels per workgroup row
-  static constexpr int max_cx = width - 1 + 4, max_cy = R - 1 + 4;
+  // a run of w voxels meets at most (w + M - 2) / M + 1 tiles
+  static constexpr int max_cx = (width + M - 2) / M + 4, max_cy = (R + M - 2) / M + 4;
 };
 using FwdTileDefault = FwdTile<kFwdRows, 1, 1>;
 // Staged window of one control plane for C components per point.
@@ -398,33 +403,35 @@ __device__ __forceinline__ void fwd_block(const float* __restrict__ grid, float*
 
   int tz = z0 / g.dz;
   int oz = z0 - tz * g.dz;
-  float r[fwd_loads<C, T>()];
-  // Warm-up: stage planes tz, tz+1, tz+2 one at a time (slots 0, 1, 0) and shift
-  // their contractions into q0..q2; then stage plane tz+3 into slot 1 (its
-  // contraction is the loop head).  One plane in flight keeps registers low.
+  // Warm-up: the loads of planes tz .. tz+3 are issued together (one wait for
+  // memory instead of four), then pass through the two slots in pairs:
+  // contracted into q0, q1, then q2; plane tz+3 stays in slot 1 (its contraction
+  // is the loop head).
   FwdVal<C> q0[V], q1[V], q2[V];
-#pragma unroll
-  for (int k = 0; k < V; ++k)
-#pragma unroll
-    for (int c = 0; c < C; ++c) q0[k].v[c] = q1[k].v[c] = q2[k].v[c] = 0.f;
-#pragma unroll 1
-  for (int j = 0; j < 3; ++j) {
-    __syncthreads();  // the slot may still be read (previous item or iteration)
-    fwd_fetch<C, T>(grid, g, map, tz + j, r);
-    fwd_stage<C, T>(sm.ring[j & 1], tid, r);
+  float r[fwd_loads<C, T>()];
+  {
+    float r1[fwd_loads<C, T>()], r2[fwd_loads<C, T>()], r3[fwd_loads<C, T>()];
+    fwd_fetch<C, T>(grid, g, map, tz, r);
+    fwd_fetch<C, T>(grid, g, map, tz + 1, r1);
+    fwd_fetch<C, T>(grid, g, map, tz + 2, r2);
+    fwd_fetch<C, T>(grid, g, map, tz + 3, r3);
+    __syncthreads();  // the slots may still be read (previous item)
+    fwd_stage<C, T>(sm.ring[0], tid, r);
+    fwd_stage<C, T>(sm.ring[1], tid, r1);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < V; ++k) {
-      const FwdVal<C> qn = contract(sm.ring[j & 1], k);
-      q0[k] = q1[k];
-      q1[k] = q2[k];
-      q2[k] = qn;
+      q0[k] = contract(sm.ring[0], k);
+      q1[k] = contract(sm.ring[1], k);
     }
+    __syncthreads();
+    fwd_stage<C, T>(sm.ring[0], tid, r2);
+    fwd_stage<C, T>(sm.ring[1], tid, r3);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < V; ++k) q2[k] = contract(sm.ring[0], k);
+    __syncthreads();  // slot 0 is free for plane tz + 4
   }
-  __syncthreads();
-  fwd_fetch<C, T>(grid, g, map, tz + 3, r);
-  fwd_stage<C, T>(sm.ring[1], tid, r);
-  __syncthreads();
   int slot3 = 1;  // slot holding plane tz + 3
 
   const size_t zstride = (size_t)g.ny * g.nx * C;

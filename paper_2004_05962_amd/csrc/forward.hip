@@ -7,15 +7,22 @@
 // 4 contracted control planes in registers, control points staged per plane in
 // LDS, and one coalesced 12-byte store per voxel (16 bytes per 4 scalar voxels).  The field write is the dominant HBM traffic (12 bytes per
 // voxel against 12 bytes per control point).
+#include <algorithm>
+#include <type_traits>
+
 #include "bsi_internal.h"
 
 namespace bsi {
 
+// Edge: rows off 64-byte boundaries.  Their workgroups share lines with their
+// neighbours, so runs of them stay on one XCD (xcd_runs); aligned ones share none
+// and go out in plane order (512 x 512 x 256, spacing 5: 141.6 us against 149.9; at
+// nx = 510 the runs take 164 us, the plane order 230).
 template <int C, class T, bool Edge>
-__global__ __launch_bounds__(T::threads) void fwd_kernel(const float* __restrict__ grid, float* __restrict__ field,
+__global__ __launch_bounds__(T::threads) __attribute__((amdgpu_waves_per_eu(C == 3 ? 8 : 6))) void fwd_kernel(const float* __restrict__ grid, float* __restrict__ field,
                                                           VolGeom g, const float* __restrict__ lut, FwdLaunch L) {
   __shared__ FwdSmem<C, T> sm;
-  int id = xcd_remap(blockIdx.x, gridDim.x);
+  int id = Edge ? xcd_runs(blockIdx.x, gridDim.x) : blockIdx.x;
   const int bx = id % L.nbx;
   id /= L.nbx;
   const int by = id % L.nby;
@@ -27,7 +34,7 @@ __global__ __launch_bounds__(T::threads) void fwd_kernel(const float* __restrict
 
 template <int C, class T, bool Edge>
 hipError_t launch_fwd(const float* grid, float* field, const VolGeom& g, const float* lut, hipStream_t s) {
-  const FwdLaunch L = make_fwd_launch(g, kFwdTargetBlocks, T::width, T::rows);
+  const FwdLaunch L = make_fwd_launch(g, kFwdTargetBlocks, T::width, T::rows, T::strips > 1 ? kFwdChunkWide : kFwdChunk);
   const long blocks = (long)L.nbx * L.nby * L.nbz;
   hipLaunchKernelGGL((fwd_kernel<C, T, Edge>), dim3((unsigned)blocks), dim3(T::threads), 0, s, grid, field, g, lut, L);
   return hipGetLastError();
@@ -73,17 +80,23 @@ hipError_t launch_span(const float* grid, float* field, const VolGeom& g, const 
   return hipGetLastError();
 }
 
-FwdLaunch make_fwd_launch(const VolGeom& g, long target, int width, int rows) {
+FwdLaunch make_fwd_launch(const VolGeom& g, long target, int width, int rows, int planes) {
   FwdLaunch L;
   L.nbx = (g.nx + width - 1) / width;
   L.nby = (g.ny + rows - 1) / rows;
   // Split z (at tile boundaries) until there are >= target workgroups: enough
-  // waves to keep the stores flowing, and no more (each chunk restages the 3
-  // control planes before its first tile).  The split does not change the
-  // arithmetic of any voxel.
+  // waves to keep the stores flowing; and until a chunk is about `planes` deep (at
+  // least 2 tiles), so that the workgroups at work write one compact range of the
+  // field at any moment.  Not more: each chunk contracts the 3 control planes
+  // before its first tile again.  The split does not change the arithmetic of any
+  // voxel.
   const int tiles_z = (g.nz + g.dz - 1) / g.dz;
   const long base = (long)L.nbx * L.nby;
   int chunks = (int)((target + base - 1) / base);
+  if (planes > 0) {
+    const int deep = std::max(2, (planes + g.dz - 1) / g.dz);
+    chunks = std::max(chunks, (tiles_z + deep - 1) / deep);
+  }
   if (chunks > tiles_z) chunks = tiles_z;
   if (chunks < 1) chunks = 1;
   const int tiles_per_chunk = (tiles_z + chunks - 1) / chunks;
@@ -92,13 +105,24 @@ FwdLaunch make_fwd_launch(const VolGeom& g, long target, int width, int rows) {
   return L;
 }
 
+// f(M) for the instance of the largest M in {1, A, B} that the spacings allow.
+template <int A, int B, class F>
+hipError_t fwd_for_spacing(const VolGeom& g, F&& f) {
+  const int d = g.dx < g.dy ? g.dx : g.dy;
+  if (d >= B) return f(std::integral_constant<int, B>{});
+  if (d >= A) return f(std::integral_constant<int, A>{});
+  return f(std::integral_constant<int, 1>{});
+}
+
 // Rows that start on 64-byte boundaries (every one, when nx * 12 bytes and the
 // field pointer are multiples of 64) are written whole segment by segment.
 // Wider than 256 voxels and with z-tiles of at least 5 planes, a workgroup of
 // 2 rows x 8 strips covers 512 voxels of each of its rows (at 512 x 512 x 256,
-// spacing 5: 167 against 172 us inside the forward + adjoint step).  Its 16
+// spacing 5: 141.6 us, against 172 as long z-chunks of one strip).  Its 16
 // waves meet at one barrier per z-tile, which cost more than it gained at
-// spacing 3 (0.224 against 0.189 ms).  Other rows take edge stores (fwd_block).
+// spacing 3 (0.224 against 0.189 ms), and its windows at spacings below 3 take
+// more registers than two workgroups per CU have.  Other rows take edge stores
+// (fwd_block).
 hipError_t launch_forward(const float* grid, float* field, const VolGeom& g, const float* lut,
                           hipStream_t s) {
 #if BSI_FWD_SPAN
@@ -108,10 +132,14 @@ hipError_t launch_forward(const float* grid, float* field, const VolGeom& g, con
   }
 #endif
   const bool aligned = (g.nx * 12) % 64 == 0 && reinterpret_cast<uintptr_t>(field) % 64 == 0;
-  if (aligned && g.nx > 256 && g.dz >= 5)
-    return launch_fwd<3, FwdTile<2, 8, 1>, false>(grid, field, g, lut, s);
-  if (aligned) return launch_fwd<3, FwdTileDefault, false>(grid, field, g, lut, s);
-  return launch_fwd<3, FwdTileDefault, true>(grid, field, g, lut, s);
+  return fwd_for_spacing<3, 5>(g, [&](auto m) {
+    constexpr int M = decltype(m)::value;
+    if constexpr (M >= 3)
+      if (aligned && g.nx > 256 && g.dz >= 5)
+        return launch_fwd<3, FwdTile<2, 8, 1, M>, false>(grid, field, g, lut, s);
+    if (aligned) return launch_fwd<3, FwdTile<kFwdRows, 1, 1, M>, false>(grid, field, g, lut, s);
+    return launch_fwd<3, FwdTile<kFwdRows, 1, 1, M>, true>(grid, field, g, lut, s);
+  });
 }
 
 hipError_t launch_forward_scalar(const float* grid, float* image, const VolGeom& g, const float* lut,
@@ -120,8 +148,12 @@ hipError_t launch_forward_scalar(const float* grid, float* image, const VolGeom&
   // each.  Otherwise one voxel per lane (4 stores per lane would each cover
   // only every fourth dword of the wave's span), with edge stores.
   if (g.nx % 4 == 0 && reinterpret_cast<uintptr_t>(image) % 16 == 0)
-    return launch_fwd<1, FwdTile<kFwdRows, 1, 4>, false>(grid, image, g, lut, s);
-  return launch_fwd<1, FwdTileDefault, true>(grid, image, g, lut, s);
+    return fwd_for_spacing<2, 4>(g, [&](auto m) {
+      return launch_fwd<1, FwdTile<kFwdRows, 1, 4, decltype(m)::value>, false>(grid, image, g, lut, s);
+    });
+  return fwd_for_spacing<2, 3>(g, [&](auto m) {
+    return launch_fwd<1, FwdTile<kFwdRows, 1, 1, decltype(m)::value>, true>(grid, image, g, lut, s);
+  });
 }
 
 }  // namespace bsi

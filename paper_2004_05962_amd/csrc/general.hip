@@ -53,19 +53,21 @@ __device__ __forceinline__ F3 ldf3_nt(const float* p) {
 
 constexpr int kGenMaxZ = 256;  // voxel planes per workgroup (z table in LDS)
 
+template <class T>
 struct GenFwdSmem {
-  FwdSmem<3> f;
+  FwdSmem<3, T> f;
   float zw[kGenMaxZ][4];  // z weights of the workgroup's planes
   int zt[kGenMaxZ];       // their window start floor(t_z)
 };
 
 // Edge: rows off 64-byte boundaries, written with edge stores (FwdEdgeStore).
-template <bool Edge>
+// T: the 4 x 1 shape for spacings of at least T::min_spacing in x and y.
+template <bool Edge, class T>
 __global__ __launch_bounds__(kFwdThreads) void gen_fwd_kernel(const float* __restrict__ grid,
                                                                float* __restrict__ field, VolGeom g, GenGeom q,
                                                                int nbx, int nby, int zchunk) {
-  __shared__ GenFwdSmem sm;
-  int id = xcd_remap(blockIdx.x, gridDim.x);
+  __shared__ GenFwdSmem<T> sm;
+  int id = xcd_runs(blockIdx.x, gridDim.x);
   const int bxi = id % nbx;
   id /= nbx;
   const int byi = id % nby;
@@ -76,19 +78,18 @@ __global__ __launch_bounds__(kFwdThreads) void gen_fwd_kernel(const float* __res
   const int lane = tid & (kWave - 1);
   const int wave = uniform(tid / kWave);
   // s >= 1: 64 voxels span at most 63 tile steps, so the window fits the
-  // staging layout (at most kFwdMaxCx x kFwdMaxCy points)
+  // staging layout (at most T::max_cx x T::max_cy points)
   const int cx0 = gen_tile(q.x, x0);
   const int ncx = gen_tile(q.x, min(x0 + kWave, g.nx) - 1) - cx0 + 4;
   const int cy0 = gen_tile(q.y, y0);
   const int ncy = gen_tile(q.y, min(y0 + kFwdRows, g.ny) - 1) - cy0 + 4;
-  const FwdStage<3> map = fwd_stage_map<3>(g, cx0, ncx, cy0, ncy, tid);
+  const FwdStage<3, T> map = fwd_stage_map<3, T>(g, cx0, ncx, cy0, ncy, tid);
   for (int i = tid; i < z1 - z0; i += kFwdThreads) {
     float w[4];
     sm.zt[i] = gen_weights(q.z, z0 + i, w);
 #pragma unroll
     for (int n = 0; n < 4; ++n) sm.zw[i][n] = w[n];
   }
-  // (the warm-up's first barrier orders the table before any read)
 
   const int x = x0 + lane, y = y0 + wave;
   const bool active = x < g.nx && y < g.ny;
@@ -96,30 +97,32 @@ __global__ __launch_bounds__(kFwdThreads) void gen_fwd_kernel(const float* __res
   float bx[4], wy[4];
   const int tx = gen_weights(q.x, xc, bx);
   const int ty = gen_weights(q.y, yc, wy);
-  const int base = (ty - cy0) * fwd_pitch<3>() + (tx - cx0) * 3;
+  const int base = (ty - cy0) * fwd_pitch<3, T>() + (tx - cx0) * 3;
 
   int tz = gen_tile(q.z, z0);
-  float r[fwd_loads<3>()];
-  // Warm-up as in the aligned forward: planes tz, tz+1, tz+2 through slots
-  // 0, 1, 0 into q0..q2, then plane tz+3 staged into slot 1.
+  // Warm-up as in the aligned forward: planes tz .. tz+3 loaded together, through
+  // the two slots in pairs into q0, q1, q2; plane tz+3 stays in slot 1.
+  float r[fwd_loads<3, T>()];
   FwdVal<3> q0, q1, q2;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) q0.v[c] = q1.v[c] = q2.v[c] = 0.f;
-#pragma unroll 1
-  for (int j = 0; j < 3; ++j) {
+  {
+    auto contract = [&](const float* slot) { return fwd_contract<3, T>(slot, base, bx[0], bx[1], bx[2], bx[3], wy); };
+    float r1[fwd_loads<3, T>()], r2[fwd_loads<3, T>()], r3[fwd_loads<3, T>()];
+    fwd_fetch<3, T>(grid, g, map, tz, r);
+    fwd_fetch<3, T>(grid, g, map, tz + 1, r1);
+    fwd_fetch<3, T>(grid, g, map, tz + 2, r2);
+    fwd_fetch<3, T>(grid, g, map, tz + 3, r3);
+    fwd_stage<3, T>(sm.f.ring[0], tid, r);
+    fwd_stage<3, T>(sm.f.ring[1], tid, r1);
+    __syncthreads();  // (also orders the z table before any read)
+    q0 = contract(sm.f.ring[0]);
+    q1 = contract(sm.f.ring[1]);
     __syncthreads();
-    fwd_fetch<3>(grid, g, map, tz + j, r);
-    fwd_stage<3>(sm.f.ring[j & 1], tid, r);
+    fwd_stage<3, T>(sm.f.ring[0], tid, r2);
+    fwd_stage<3, T>(sm.f.ring[1], tid, r3);
     __syncthreads();
-    const FwdVal<3> qn = fwd_contract<3>(sm.f.ring[j & 1], base, bx[0], bx[1], bx[2], bx[3], wy);
-    q0 = q1;
-    q1 = q2;
-    q2 = qn;
+    q2 = contract(sm.f.ring[0]);
+    __syncthreads();  // slot 0 is free for plane tz + 4
   }
-  __syncthreads();
-  fwd_fetch<3>(grid, g, map, tz + 3, r);
-  fwd_stage<3>(sm.f.ring[1], tid, r);
-  __syncthreads();
   int slot3 = 1;
 
   const size_t zstride = (size_t)g.ny * g.nx * 3;
@@ -127,12 +130,12 @@ __global__ __launch_bounds__(kFwdThreads) void gen_fwd_kernel(const float* __res
   FwdEdgeStore<3> edge(field, g, z0, yc, x0, xc);
   int z = z0;
   for (;;) {
-    const FwdVal<3> q3 = fwd_contract<3>(sm.f.ring[slot3], base, bx[0], bx[1], bx[2], bx[3], wy);
+    const FwdVal<3> q3 = fwd_contract<3, T>(sm.f.ring[slot3], base, bx[0], bx[1], bx[2], bx[3], wy);
     int zend = z;  // the planes of tile tz in this chunk (s >= 1: the next one is tz + 1)
     while (zend < z1 && sm.zt[zend - z0] == tz) ++zend;
     const bool more = zend < z1;
     // its new plane tz + 4 = t_z(zend) + 3 <= gz - 1: in bounds
-    if (more) fwd_fetch<3>(grid, g, map, tz + 4, r);
+    if (more) fwd_fetch<3, T>(grid, g, map, tz + 4, r);
     for (; z < zend; ++z, out += zstride) {
       const float* wz = sm.zw[z - z0];
       float t[3];
@@ -143,7 +146,7 @@ __global__ __launch_bounds__(kFwdThreads) void gen_fwd_kernel(const float* __res
       else if (active) fwd_store<3>(out, t);
     }
     if (!more) break;
-    fwd_stage<3>(sm.f.ring[slot3 ^ 1], tid, r);
+    fwd_stage<3, T>(sm.f.ring[slot3 ^ 1], tid, r);
     __syncthreads();
     slot3 ^= 1;
     ++tz;
@@ -541,12 +544,17 @@ hipError_t launch_forward_general(const float* grid, float* field, const VolGeom
   const int zchunk = (g.nz + chunks - 1) / chunks;
   const int nbz = (g.nz + zchunk - 1) / zchunk;
   // rows on 64-byte boundaries: non-temporal stores; otherwise edge stores
-  if ((g.nx * 12) % 64 == 0 && reinterpret_cast<uintptr_t>(field) % 64 == 0)
-    hipLaunchKernelGGL(gen_fwd_kernel<false>, dim3((unsigned)(base * nbz)), dim3(kFwdThreads), 0, s, grid, field,
-                       g, q, nbx, nby, zchunk);
-  else
-    hipLaunchKernelGGL(gen_fwd_kernel<true>, dim3((unsigned)(base * nbz)), dim3(kFwdThreads), 0, s, grid, field,
-                       g, q, nbx, nby, zchunk);
+  const bool aligned = (g.nx * 12) % 64 == 0 && reinterpret_cast<uintptr_t>(field) % 64 == 0;
+  const dim3 gd((unsigned)(base * nbz)), bd(kFwdThreads);
+  using T1 = FwdTile<kFwdRows, 1, 1>;
+  using T3 = FwdTile<kFwdRows, 1, 1, 3>;
+  if (q.x.s >= 3.f && q.y.s >= 3.f) {
+    if (aligned) hipLaunchKernelGGL((gen_fwd_kernel<false, T3>), gd, bd, 0, s, grid, field, g, q, nbx, nby, zchunk);
+    else hipLaunchKernelGGL((gen_fwd_kernel<true, T3>), gd, bd, 0, s, grid, field, g, q, nbx, nby, zchunk);
+  } else {
+    if (aligned) hipLaunchKernelGGL((gen_fwd_kernel<false, T1>), gd, bd, 0, s, grid, field, g, q, nbx, nby, zchunk);
+    else hipLaunchKernelGGL((gen_fwd_kernel<true, T1>), gd, bd, 0, s, grid, field, g, q, nbx, nby, zchunk);
+  }
   return hipGetLastError();
 }
 

@@ -196,8 +196,9 @@ bool check_adjoints(const VolGeom& g, Check& ck) { return check_adjoint(make_adj
 
 // The marching forward (fwd_block) with workgroup shape T and C components.
 template <int C, class T>
-bool check_forward_march(const VolGeom& g, Check& ck, long target = kFwdTargetBlocks) {
-  const FwdLaunch L = make_fwd_launch(g, target, T::width, T::rows);
+bool check_forward_march(const VolGeom& g, Check& ck, long target = kFwdTargetBlocks,
+                         int planes = T::strips > 1 ? kFwdChunkWide : kFwdChunk) {
+  const FwdLaunch L = make_fwd_launch(g, target, T::width, T::rows, planes);
   REQUIRE(L.zchunk % g.dz == 0 && L.zchunk > 0, "z chunks of whole tiles");
   REQUIRE((long)L.nbz * L.zchunk >= g.nz && (long)(L.nbz - 1) * L.zchunk < g.nz, "z chunks cover the volume");
   const size_t cplane = (size_t)g.gx * g.gy * C;
@@ -244,19 +245,29 @@ bool check_forward_span(const VolGeom& g, Check& ck) {
   return true;
 }
 
+// The shape's instances for every smallest spacing that the geometry allows.
+template <int C, int R, int S, int V>
+bool check_forward_shape(const VolGeom& g, Check& ck, long target = kFwdTargetBlocks) {
+  const int d = imin(g.dx, g.dy);
+  return check_forward_march<C, FwdTile<R, S, V>>(g, ck, target) &&
+         (d < 2 || check_forward_march<C, FwdTile<R, S, V, 2>>(g, ck, target)) &&
+         (d < 3 || check_forward_march<C, FwdTile<R, S, V, 3>>(g, ck, target)) &&
+         (d < 4 || check_forward_march<C, FwdTile<R, S, V, 4>>(g, ck, target)) &&
+         (d < 5 || check_forward_march<C, FwdTile<R, S, V, 5>>(g, ck, target));
+}
+
 // The batched forward's shapes and z-split targets (the schedule knobs).
 bool check_forward_batched(const VolGeom& g, Check& ck) {
   for (long target : {512L, 2048L, 8192L})
-    if (!(check_forward_march<3, FwdTile<4, 1, 1>>(g, ck, target) &&
-          check_forward_march<3, FwdTile<2, 2, 1>>(g, ck, target) &&
-          check_forward_march<3, FwdTile<8, 1, 1>>(g, ck, target)))
+    if (!(check_forward_shape<3, 4, 1, 1>(g, ck, target) && check_forward_shape<3, 2, 2, 1>(g, ck, target) &&
+          check_forward_shape<3, 8, 1, 1>(g, ck, target)))
       return false;
   return true;
 }
 
 bool check_forward(const VolGeom& g, Check& ck) {
-  return check_forward_march<3, FwdTileDefault>(g, ck) && check_forward_march<3, FwdTile<2, 8, 1>>(g, ck) &&
-         check_forward_march<1, FwdTile<kFwdRows, 1, 4>>(g, ck) && check_forward_march<1, FwdTileDefault>(g, ck) &&
+  return check_forward_shape<3, kFwdRows, 1, 1>(g, ck) && check_forward_shape<3, 2, 8, 1>(g, ck) &&
+         check_forward_shape<1, kFwdRows, 1, 4>(g, ck) && check_forward_shape<1, kFwdRows, 1, 1>(g, ck) &&
          check_forward_span<3>(g, ck) && check_forward_span<1>(g, ck) && check_forward_batched(g, ck);
 }
 
@@ -291,6 +302,20 @@ bool check_general_adjoint(const GenGeom& q, Check& ck) {
     T.tile[i] = tile[i].data();
     T.w[i] = nullptr;
     T.first[i] = first[i].data();
+  }
+  // the forward's window of 64 voxels x 4 rows within its staging capacity
+  {
+    using T1 = FwdTile<kFwdRows, 1, 1>;
+    using T3 = FwdTile<kFwdRows, 1, 1, 3>;
+    const bool three = q.x.s >= 3.f && q.y.s >= 3.f;
+    for (int x0 = 0; x0 < q.x.n; x0 += kWave) {
+      const int n = tile[0][(size_t)imin(x0 + kWave, q.x.n) - 1] - tile[0][(size_t)x0] + 4;
+      REQUIRE(n <= (three ? T3::max_cx : T1::max_cx), "forward window columns");
+    }
+    for (int y0 = 0; y0 < q.y.n; y0 += kFwdRows) {
+      const int n = tile[1][(size_t)imin(y0 + kFwdRows, q.y.n) - 1] - tile[1][(size_t)y0] + 4;
+      REQUIRE(n <= (three ? T3::max_cy : T1::max_cy), "forward window rows");
+    }
   }
   const GenAdj a = make_gen_adj(q);
   const GzLayout L = gz_layout(a);
