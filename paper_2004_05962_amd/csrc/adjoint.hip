@@ -17,9 +17,11 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI
   adj_brick<true, Staged>(dfield, part, a, lut, brick, adj_slabs, threadIdx.x);
 }
 
-__global__ __launch_bounds__(kGatherThreads) void adj_pass2_kernel(const float* __restrict__ part,
-                                                                    float* __restrict__ grad, AdjGeom a) {
-  adj_gather_block(part, grad, a, blockIdx.x, threadIdx.x);
+template <bool Small>
+__global__ __launch_bounds__(kGatherThreads) __attribute__((amdgpu_waves_per_eu(8))) void adj_pass2_kernel(
+    const float* __restrict__ part, float* __restrict__ grad, AdjGeom a) {
+  adj_gather_block<Small>(part, a, xcd_remap(blockIdx.x, gridDim.x), threadIdx.x,
+                          [&](size_t i, const F3& v) { stf3(grad + i * 3, v); });
 }
 
 namespace {
@@ -32,10 +34,32 @@ AdjAxis make_axis(int n, int d, int u, int k) {
   a.nb = (a.U + a.k - 1) / a.k;
   a.w = a.k * u;
   a.md = adj_magic(d);
+  a.mw = (int64_t)n * a.w < ((int64_t)1 << 32) ? adj_magic(a.w) : 0;
   a.cm = a.nb == 1 ? (n - 1) / d + 4 : adj_window(a.w, d);
   return a;
 }
 }  // namespace
+
+// The most bricks of an axis that meet the support of one control point.
+static int adj_most_bricks(const AdjAxis& x, int d) { return imin(x.nb, (4 * d + x.w - 2) / x.w + 1); }
+
+// Pass 2's workgroups.  One point per lane, in rows of 64, 32 or 16 points, whichever
+// leaves the fewest lanes idle (303 x 167 x 212, spacing 4, 79 points a row: 4.1 us
+// in rows of 16 against 5.2 of 64).  Where a point's bricks take many rounds of 8
+// loads and the points are few, a wave each: 512 x 512 x 256, spacing 64 (847
+// points, 54 rounds) 4.2 us against 14.8, 150 x 130 x 100, spacing 20 (880, 8) 3.8
+// against 6.9, but 512 x 512 x 256, spacing 24 (8750, 8) 6.8 against 5.8.
+static int adj_gather_lx(const AdjGeom& a) {
+  const VolGeom& g = a.g;
+  auto pairs = [](int n) { return (n + 1) / 2; };
+  const int rounds = pairs(adj_most_bricks(a.x, g.dx)) * pairs(adj_most_bricks(a.y, g.dy)) *
+                     pairs(adj_most_bricks(a.z, g.dz));
+  if (rounds > 1 && a.part_bytes != 0 && (int64_t)g.gx * g.gy * g.gz <= 512 * (int64_t)imin(rounds, 2048)) return -1;
+  int lx = 6;
+  for (int l = 5; l >= 4; --l)
+    if (((g.gx + (1 << l) - 1) >> l << l) < ((g.gx + (1 << lx) - 1) >> lx << lx)) lx = l;
+  return lx;
+}
 
 // Bricks of pass 1: 2 x 2 cells in x and y by whole z-tiles; the depth by the
 // rule stated with its constants (adjoint_device.h).  A pure function of the
@@ -85,6 +109,8 @@ AdjGeom make_adj_geom(const VolGeom& g) {
       if (adj_workspace_bytes(a) <= kAdjScratchBytes) break;
       set_depth(imin(tiles, imax(1, deeper / g.dz)));
     }
+  a.part_bytes = adj_workspace_bytes(a) <= kAdjGatherSmall ? (uint32_t)adj_workspace_bytes(a) : 0;
+  a.lx = adj_gather_lx(a);
   return a;
 }
 
@@ -127,9 +153,12 @@ hipError_t launch_adjoint_partials(const float* dfield, const AdjGeom& a, const 
 }
 
 hipError_t launch_adjoint_reduce(const float* part, float* grad, const AdjGeom& a, hipStream_t s) {
-  const int64_t nblk = adj_gather_blocks(a.g);
+  const int64_t nblk = adj_gather_blocks(a);
   if (nblk >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;  // a field far beyond device memory
-  hipLaunchKernelGGL(adj_pass2_kernel, dim3((unsigned)nblk), dim3(kGatherThreads), 0, s, part, grad, a);
+  if (a.part_bytes != 0)
+    hipLaunchKernelGGL(adj_pass2_kernel<true>, dim3((unsigned)nblk), dim3(kGatherThreads), 0, s, part, grad, a);
+  else
+    hipLaunchKernelGGL(adj_pass2_kernel<false>, dim3((unsigned)nblk), dim3(kGatherThreads), 0, s, part, grad, a);
   return hipGetLastError();
 }
 

@@ -88,11 +88,16 @@ __host__ __device__ constexpr int adj_gcd(int a, int b) { return b == 0 ? a : ad
 // spacing d: the start's offset in its tile is at most d - gcd(w, d).
 __host__ __device__ constexpr int adj_window(int w, int d) { return (d - adj_gcd(w, d) + w - 1) / d + 4; }
 
-// v / d for 0 <= v <= 2^20 and 1 <= d <= 64, by m = adj_magic(d): the product is
-// above v / d by less than v / 2^32 < 1 / 64.
+// v / d for 0 <= v and v d < 2^32, by m = adj_magic(d): the product is above v / d
+// by at most v / 2^32 < 1 / d.
 __host__ __device__ inline uint32_t adj_magic(int d) { return (uint32_t)(((uint64_t)1 << 32) / (uint32_t)d + (d > 1)); }
 __host__ __device__ inline int adj_div(int v, int d, uint32_t m) {
   return d == 1 ? v : (int)(((uint64_t)(uint32_t)v * m) >> 32);
+}
+
+// The brick of voxel v.
+__host__ __device__ inline int adj_brick_of_voxel(const AdjAxis& a, int v) {
+  return a.mw ? adj_div(v, a.w, a.mw) : v / a.w;
 }
 
 struct AdjBrick {
@@ -184,13 +189,13 @@ __host__ __device__ inline void adj_cell_offsets(int nx, int cnx, int cny, int l
     off[s] = ((uint32_t)imin(adj_lane_row(lane, s), cny - 1) * (uint32_t)nx + (uint32_t)v) * 12u;
 }
 
-// Load of one voxel of dfield through a buffer resource over the cell's part
-// of a plane (uniform base, 32-bit lane offset: no address arithmetic per load).
-// Stream: non-temporal, since every voxel is read once; the read stream then
+// Load of three floats through a buffer resource (uniform base, 32-bit lane offset:
+// no address arithmetic per load).  Stream: non-temporal, for the voxels of
+// dfield, since every one is read once; the read stream then
 // does not leave the caches full of dfield lines that the next kernel's writes
 // have to displace.
 template <bool Stream>
-__device__ __forceinline__ F3 adj_load_voxel(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+__device__ __forceinline__ F3 adj_load3(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
   // the whole vector is converted: a bit cast of single elements reads element 0 for all three
   const fwd_f3 v = __builtin_bit_cast(fwd_f3, __builtin_amdgcn_raw_buffer_load_b96(rs, (int)off, 0, Stream ? kCpolNT : 0));
   return F3{v.x, v.y, v.z};
@@ -465,7 +470,7 @@ __device__ __forceinline__ void adj_march(const char* base, size_t zs, uint32_t 
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(ahead), 0, (int)bytes, kBufferFlags);
 #pragma unroll
-    for (int s = 0; s < kAdjSteps; ++s) d[s] = adj_load_voxel<Stream>(rs, off[s]);
+    for (int s = 0; s < kAdjSteps; ++s) d[s] = adj_load3<Stream>(rs, off[s]);
     ahead += left > 0 ? zs : 0;
     --left;
   };
@@ -556,11 +561,8 @@ __device__ __forceinline__ void adj_brick(const float* __restrict__ dfield, floa
   }
 }
 
-// Pass 2 for one control point (cx, cy, cz): fixed-order sum of brick partials.
-// Bricks whose voxels meet the point's support [(c-3)d, (c+1)d) on each axis,
-// summed bz, then by, then bx ascending.  When no axis has more than two such
-// bricks all 8 loads are issued at once from clamped addresses and the valid
-// ones added in that order; otherwise a loop.
+// Pass 2: the fixed-order sum, per control point, of the partials of the bricks
+// whose voxels meet its support [(c-3)d, (c+1)d) on each axis.
 struct AdjSpan {
   int lo, hi;  // brick range
 };
@@ -568,95 +570,143 @@ struct AdjSpan {
 // First control index of brick b's window (b < nb): its first voxel's tile,
 // b * k when the units are whole tiles.
 __host__ __device__ inline int adj_brick_c0(const AdjAxis& ax, int b, int d) {
-  return ax.u == d ? b * ax.k : (b * ax.w) / d;
+  return ax.u == d ? b * ax.k : adj_div(b * ax.w, d, ax.md);
 }
 
 __host__ __device__ inline AdjSpan adj_span(const AdjAxis& ax, int c, int d, int n) {
   return AdjSpan{adj_brick_of_voxel(ax, imax(0, (c - 3) * d)), adj_brick_of_voxel(ax, imin(n, (c + 1) * d) - 1)};
 }
 
-// Workspace offset (floats) of control point (cx, cy, cz) in brick (bx, by, bz)'s partials.
+// Workspace offset (floats) of control point (cx, cy, cz) in brick (bx, by, bz)'s
+// partials: the sum of one term per axis.
+__host__ __device__ inline size_t adj_part_x(const AdjGeom& a, int bx, int cx) {
+  return bx * adj_brick_stride(a) + (cx - adj_brick_c0(a.x, bx, a.g.dx)) * 3;
+}
+__host__ __device__ inline size_t adj_part_y(const AdjGeom& a, int by, int cy) {
+  return by * (a.x.nb * adj_brick_stride(a)) + (cy - adj_brick_c0(a.y, by, a.g.dy)) * a.x.cm * 3;
+}
+__host__ __device__ inline size_t adj_part_z(const AdjGeom& a, int bz, int cz) {
+  return bz * ((size_t)a.y.nb * a.x.nb * adj_brick_stride(a)) + (cz - adj_brick_c0(a.z, bz, a.g.dz)) * (a.y.cm * a.x.cm * 3);
+}
 __host__ __device__ inline size_t adj_part_addr(const AdjGeom& a, int bx, int by, int bz, int cx, int cy, int cz) {
-  const int cxl = cx - adj_brick_c0(a.x, bx, a.g.dx);
-  const int cyl = cy - adj_brick_c0(a.y, by, a.g.dy);
-  const int czl = cz - adj_brick_c0(a.z, bz, a.g.dz);
-  return (size_t)((bz * a.y.nb + by) * a.x.nb + bx) * adj_brick_stride(a) + adj_part_offset(a, czl, cyl, cxl);
+  return adj_part_x(a, bx, cx) + adj_part_y(a, by, cy) + adj_part_z(a, bz, cz);
 }
 
-__device__ __forceinline__ F3 adj_gather_point(const float* __restrict__ part, const AdjGeom& a, int cx,
-                                               int cy, int cz) {
-  const VolGeom& g = a.g;
-  const AdjSpan sx = adj_span(a.x, cx, g.dx, g.nx), sy = adj_span(a.y, cy, g.dy, g.ny),
-                sz = adj_span(a.z, cz, g.dz, g.nz);
-  auto addr = [&](int bx, int by, int bz) { return part + adj_part_addr(a, bx, by, bz, cx, cy, cz); };
+// The partials of one point, of the bricks lo, lo + step, lo + 2 step .. of each span:
+// two by two by two, 8 loads in flight, summed pairwise.  Bound by the latency of
+// that one round, and at many points by the partials' bytes; so the instructions
+// before it are few and 8 waves per SIMD wait at once.  Small: at most kAdjGatherSmall
+// bytes of partials, read by buffer loads with 32-bit offsets; a brick past its span
+// adds kAdjGatherSmall to the offset, which is then past the buffer (three of them
+// and the largest offset stay below 2^32) and reads as zero without an access to
+// memory.  Otherwise 64-bit addresses, a branch per load, four of them in flight.
+constexpr uint32_t kAdjGatherSmall = 1u << 30;
+template <bool Small>
+__device__ __forceinline__ F3 adj_gather_point(const float* __restrict__ part, const AdjGeom& a, int cx, int cy, int cz,
+                                               AdjSpan sx, AdjSpan sy, AdjSpan sz, int step) {
   F3 s{0.f, 0.f, 0.f};
-  if (sx.hi - sx.lo <= 1 && sy.hi - sy.lo <= 1 && sz.hi - sz.lo <= 1) {
-    F3 v[2][2][2];
+  if constexpr (Small) {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(part), 0, (int)a.part_bytes, kBufferFlags);
+    for (int bz = sz.lo; bz <= sz.hi; bz += 2 * step)
+      for (int by = sy.lo; by <= sy.hi; by += 2 * step)
+        for (int bx = sx.lo; bx <= sx.hi; bx += 2 * step) {
+          uint32_t ox[2], oy[2], oz[2];
+          F3 v[2][2][2];
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-          v[k][j][i] = ldf3(addr(min(sx.lo + i, sx.hi), min(sy.lo + j, sy.hi), min(sz.lo + k, sz.hi)));
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-          if (sz.lo + k <= sz.hi && sy.lo + j <= sy.hi && sx.lo + i <= sx.hi) {
-            s.x += v[k][j][i].x;
-            s.y += v[k][j][i].y;
-            s.z += v[k][j][i].z;
+          for (int i = 0; i < 2; ++i) {
+            ox[i] = (uint32_t)adj_part_x(a, bx + i * step, cx) * 4;
+            oy[i] = (uint32_t)adj_part_y(a, by + i * step, cy) * 4;
+            oz[i] = (uint32_t)adj_part_z(a, bz + i * step, cz) * 4;
           }
-    return s;
+          if (bx + step > sx.hi) ox[1] = kAdjGatherSmall;
+          if (by + step > sy.hi) oy[1] = kAdjGatherSmall;
+          if (bz + step > sz.hi) oz[1] = kAdjGatherSmall;
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              const uint32_t oxy = ox[i] + oy[j];
+#pragma unroll
+              for (int k = 0; k < 2; ++k) v[k][j][i] = adj_load3<false>(rs, oxy + oz[k]);
+            }
+          s = s + (((v[0][0][0] + v[0][0][1]) + (v[0][1][0] + v[0][1][1])) +
+                   ((v[1][0][0] + v[1][0][1]) + (v[1][1][0] + v[1][1][1])));
+        }
+  } else {
+    for (int bz = sz.lo; bz <= sz.hi; bz += step)
+      for (int by = sy.lo; by <= sy.hi; by += 2 * step)
+        for (int bx = sx.lo; bx <= sx.hi; bx += 2 * step) {
+          F3 v[2][2];
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              const int x = bx + i * step, y = by + j * step;
+              v[j][i] = F3{0.f, 0.f, 0.f};
+              if (x <= sx.hi && y <= sy.hi) v[j][i] = ldf3(part + adj_part_addr(a, x, y, bz, cx, cy, cz));
+            }
+          s = s + ((v[0][0] + v[0][1]) + (v[1][0] + v[1][1]));
+        }
   }
-  for (int bz = sz.lo; bz <= sz.hi; ++bz)
-    for (int by = sy.lo; by <= sy.hi; ++by)
-      for (int bx = sx.lo; bx <= sx.hi; ++bx) {
-        const F3 v = ldf3(addr(bx, by, bz));
-        s.x += v.x;
-        s.y += v.y;
-        s.z += v.z;
-      }
   return s;
 }
 
-// Pass 2's workgroups: a wave takes up to 64 control points along x of one
-// control row (cy, cz), so the y- and z-brick spans, and their address terms,
-// are uniform over the wave (scalar).  A workgroup holds kGatherWaves rows.
-constexpr int kGatherWaves = 4;
-constexpr int kGatherThreads = kGatherWaves * kWave;
+// Pass 2's workgroups.  One lane per control point, 2^lx points along x by 256 >> lx
+// rows of one control plane; or one wave per point (lx < 0), whose lanes take every
+// 4th brick of each axis (make_adj_geom's rule).
+constexpr int kGatherThreads = 256;
+constexpr int kGatherLanes = 4;  // lanes per axis of a point's wave
 
-__host__ __device__ inline int adj_gather_xblocks(const VolGeom& g) { return (g.gx + kWave - 1) / kWave; }
-__host__ __device__ inline int adj_gather_yblocks(const VolGeom& g) {
-  return (g.gy + kGatherWaves - 1) / kGatherWaves;
-}
-__host__ __device__ inline int64_t adj_gather_blocks(const VolGeom& g) {
-  return (int64_t)adj_gather_xblocks(g) * adj_gather_yblocks(g) * g.gz;
+__host__ __device__ inline int64_t adj_gather_blocks(const AdjGeom& a) {
+  const VolGeom& g = a.g;
+  if (a.lx < 0) return ((int64_t)g.gx * g.gy * g.gz + kGatherThreads / kWave - 1) / (kGatherThreads / kWave);
+  const int nxb = (g.gx + (1 << a.lx) - 1) >> a.lx, rows = kGatherThreads >> a.lx;
+  return (int64_t)nxb * ((g.gy + rows - 1) / rows) * g.gz;
 }
 
-// Control point of lane `lane` of wave `wave` of pass-2 workgroup blk
-// (blk < adj_gather_blocks < 2^31); false for a lane past the grid.
-__host__ __device__ inline bool adj_gather_index(const VolGeom& g, int blk, int wave, int lane, int& cx, int& cy,
-                                                 int& cz) {
-  const int nxb = adj_gather_xblocks(g), nyb = adj_gather_yblocks(g);
+// Control point of thread tid of pass-2 workgroup blk (blk < adj_gather_blocks <
+// 2^31); false for a thread past the grid.
+__host__ __device__ inline bool adj_gather_index(const AdjGeom& a, int blk, int tid, int& cx, int& cy, int& cz) {
+  const VolGeom& g = a.g;
+  if (a.lx < 0) {
+    const int i = blk * (kGatherThreads / kWave) + tid / kWave, row = i / g.gx;  // below 2^20
+    cx = i - row * g.gx;
+    cz = row / g.gy;
+    cy = row - cz * g.gy;
+    return cz < g.gz;
+  }
+  const int nxb = (g.gx + (1 << a.lx) - 1) >> a.lx, rows = kGatherThreads >> a.lx, nyb = (g.gy + rows - 1) / rows;
   const int xb = blk % nxb;
   blk /= nxb;
-  cy = (blk % nyb) * kGatherWaves + wave;
+  cx = (xb << a.lx) + (tid & ((1 << a.lx) - 1));
+  cy = blk % nyb * rows + (tid >> a.lx);
   cz = blk / nyb;
-  cx = xb * kWave + lane;
   return cy < g.gy && cx < g.gx;
 }
 
-// Workgroup blk of pass 2, thread tid.
-__device__ __forceinline__ void adj_gather_block(const float* __restrict__ part, float* __restrict__ grad,
-                                                 const AdjGeom& a, int blk, int tid) {
+// Workgroup blk of pass 2, thread tid: put(i, v) for each control point i, by one thread.
+template <bool Small, class Put>
+__device__ __forceinline__ void adj_gather_block(const float* __restrict__ part, const AdjGeom& a, int blk, int tid,
+                                                 Put&& put) {
   int cx, cy, cz;
-  if (!adj_gather_index(a.g, blk, uniform(tid / kWave), tid & (kWave - 1), cx, cy, cz)) return;
-  const size_t i = ((size_t)cz * a.g.gy + cy) * a.g.gx + cx;
-  stf3(grad + i * 3, adj_gather_point(part, a, cx, cy, cz));
+  const VolGeom& g = a.g;
+  const bool wave = a.lx < 0;  // uniform: a function of the geometry
+  const int lane = tid % kWave;
+  if (!adj_gather_index(a, blk, wave ? uniform(tid / kWave) * kWave : tid, cx, cy, cz)) return;
+  AdjSpan sx = adj_span(a.x, cx, g.dx, g.nx), sy = adj_span(a.y, cy, g.dy, g.ny), sz = adj_span(a.z, cz, g.dz, g.nz);
+  if (wave) {
+    sx.lo += lane % kGatherLanes;
+    sy.lo += lane / kGatherLanes % kGatherLanes;
+    sz.lo += lane / (kGatherLanes * kGatherLanes);
+  }
+  F3 s = adj_gather_point<Small>(part, a, cx, cy, cz, sx, sy, sz, wave ? kGatherLanes : 1);
+  if (wave) {
+#pragma unroll
+    for (int h = 1; h < kWave; h *= 2) s = s + F3{__shfl_xor(s.x, h), __shfl_xor(s.y, h), __shfl_xor(s.z, h)};
+    if (lane != 0) return;
+  }
+  put(((size_t)cz * g.gy + cy) * g.gx + cx, s);
 }
 
 }  // namespace bsi

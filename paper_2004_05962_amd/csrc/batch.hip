@@ -194,13 +194,17 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI
 }
 
 template <bool Persistent>
-__global__ __launch_bounds__(kPtThreads) void batch_adj2_kernel(const VolDesc* __restrict__ vols, int count,
+__global__ __launch_bounds__(kPtThreads) __attribute__((amdgpu_waves_per_eu(8))) void batch_adj2_kernel(const VolDesc* __restrict__ vols, int count,
                                                                  int64_t total) {
   batch_for_items<Persistent, true>(total, [&](const int64_t item) {
     const int vi = uniform(find_volume(vols, count, item, kAdj2));
     const VolDesc& d = vols[vi];
     const AdjGeom a = d.a;
-    adj_gather_block(as_global(d.part), as_global(d.grad), a, (int)(item - d.first[kAdj2]), threadIdx.x);
+    float* grad = as_global(d.grad);
+    auto put = [&](size_t i, const F3& v) { stf3(grad + i * 3, v); };
+    const int blk = (int)(item - d.first[kAdj2]);
+    if (a.part_bytes != 0) adj_gather_block<true>(as_global(d.part), a, blk, threadIdx.x, put);
+    else adj_gather_block<false>(as_global(d.part), a, blk, threadIdx.x, put);
   });
 }
 
@@ -573,7 +577,7 @@ int32_t bsi_batch_create(int32_t count, const int32_t* dims3xN, const int32_t* s
       set_error("volume " + std::to_string(i) + ": " + bsi_last_error());
       return rc;
     }
-    if (adj_gather_blocks(geoms[i]) >= ((int64_t)1 << 31)) {  // a field far beyond device memory
+    if (adj_gather_blocks(make_adj_geom(geoms[i])) >= ((int64_t)1 << 31)) {  // a field far beyond device memory
       set_error("volume " + std::to_string(i) + ": too many control points");
       return BSI_ERR_UNSUPPORTED;
     }
@@ -588,7 +592,7 @@ int32_t bsi_batch_create(int32_t count, const int32_t* dims3xN, const int32_t* s
     d.first[kAdj1] = tot[kAdj1];
     d.first[kAdj2] = tot[kAdj2];
     tot[kAdj1] += (int64_t)d.a.x.nb * d.a.y.nb * d.a.z.nb;
-    tot[kAdj2] += adj_gather_blocks(g);
+    tot[kAdj2] += adj_gather_blocks(d.a);
   }
   int dev = 0;
   int32_t rc = current_device(&dev);

@@ -38,7 +38,7 @@ struct VolGeom {
 // meets one brick (the partial-window stride).
 struct AdjAxis {
   int32_t u, U, k, nb, w, cm;
-  uint32_t md;  // reciprocal of the spacing (adj_magic)
+  uint32_t md, mw;  // reciprocals of the spacing and of w (adj_magic; mw = 0: n w is too large for it)
 };
 
 // The adjoint's bricks (see adjoint_device.h).  A pure function of the
@@ -49,6 +49,8 @@ struct AdjGeom {
   int32_t cell;      // voxels in x of one wave's cell
   int32_t cw, ch;    // the largest control window of a cell (cw rounded up to a multiple of 4)
   int32_t slots;     // control planes of slabs held in LDS
+  int32_t lx;        // pass 2: 2^lx control points along x per workgroup; -1: a wave per point
+  uint32_t part_bytes;  // bytes of the partials; 0: more than pass 2's 32-bit offsets reach
 };
 
 // First voxel of brick b (b <= nb; brick nb begins at the axis end n).  For
@@ -58,7 +60,6 @@ __host__ __device__ __forceinline__ int adj_brick_begin(const AdjAxis& a, int n,
   const int v = b * a.w;
   return v < n ? v : n;
 }
-__host__ __device__ __forceinline__ int adj_brick_of_voxel(const AdjAxis& a, int v) { return v / a.w; }
 
 // Integer min / max callable from host code too (the host index checker runs
 // the kernels' address arithmetic on the CPU).

@@ -361,11 +361,10 @@ size_t fused_workspace_bytes(const AdjGeom& a) {
 // nblk sums the loss partials in a fixed order.
 constexpr int kTailThreads = kGatherThreads;
 
-__global__ __launch_bounds__(kTailThreads) void fused_tail_kernel(const float* __restrict__ part,
-                                                                   float* __restrict__ grad, float* __restrict__ grid,
-                                                                   float eta, int descend,
-                                                                   const float* __restrict__ lpart, int nlp,
-                                                                   float* __restrict__ loss, AdjGeom a, int nblk) {
+template <bool Small>
+__global__ __launch_bounds__(kTailThreads) __attribute__((amdgpu_waves_per_eu(8))) void fused_tail_kernel(
+    const float* __restrict__ part, float* __restrict__ grad, float* __restrict__ grid, float eta, int descend,
+    const float* __restrict__ lpart, int nlp, float* __restrict__ loss, AdjGeom a, int nblk) {
   if ((int)blockIdx.x == nblk) {
     __shared__ float red[kTailThreads];
     float acc = 0.f;
@@ -379,16 +378,13 @@ __global__ __launch_bounds__(kTailThreads) void fused_tail_kernel(const float* _
     if (threadIdx.x == 0) loss[0] = red[0];
     return;
   }
-  int cx, cy, cz;
-  if (!adj_gather_index(a.g, blockIdx.x, uniform(threadIdx.x / kWave), threadIdx.x & (kWave - 1), cx, cy, cz))
-    return;
-  const size_t i = ((size_t)cz * a.g.gy + cy) * a.g.gx + cx;
-  const F3 gv = adj_gather_point(part, a, cx, cy, cz);
-  stf3(grad + i * 3, gv);
-  if (descend) {  // the descent kernel's update, on the same values
-    float* p = grid + i * 3;
-    stf3(p, F3{fmaf(-eta, gv.x, p[0]), fmaf(-eta, gv.y, p[1]), fmaf(-eta, gv.z, p[2])});
-  }
+  adj_gather_block<Small>(part, a, xcd_remap(blockIdx.x, nblk), threadIdx.x, [&](size_t i, const F3& gv) {
+    stf3(grad + i * 3, gv);
+    if (descend) {  // the descent kernel's update, on the same values
+      float* p = grid + i * 3;
+      stf3(p, F3{fmaf(-eta, gv.x, p[0]), fmaf(-eta, gv.y, p[1]), fmaf(-eta, gv.z, p[2])});
+    }
+  });
 }
 
 hipError_t launch_ssd_fused(const float* grid, const float* moving, const float* fixed, float* grad, float* loss,
@@ -420,11 +416,12 @@ hipError_t launch_ssd_fused(const float* grid, const float* moving, const float*
 #undef BSI_FUSED_LAUNCH
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t nblk = adj_gather_blocks(a.g);
+  const int64_t nblk = adj_gather_blocks(a);
   if (nblk + 1 >= ((int64_t)1 << 31))
     return hipErrorInvalidConfiguration;  // a field far beyond device memory
-  hipLaunchKernelGGL(fused_tail_kernel, dim3((unsigned)(nblk + 1)), dim3(kTailThreads), 0, s, part, grad, descend_grid,
-                     eta, descend_grid != nullptr ? 1 : 0, lpart, (int)items, loss, a, (int)nblk);
+  const auto tail = a.part_bytes != 0 ? &fused_tail_kernel<true> : &fused_tail_kernel<false>;
+  hipLaunchKernelGGL(tail, dim3((unsigned)(nblk + 1)), dim3(kTailThreads), 0, s, part, grad, descend_grid, eta,
+                     descend_grid != nullptr ? 1 : 0, lpart, (int)items, loss, a, (int)nblk);
   return hipGetLastError();
 }
 

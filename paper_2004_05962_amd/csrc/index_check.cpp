@@ -140,21 +140,24 @@ bool check_adjoint(const AdjGeom& a, BrickCheck brick_check, Check& ck) {
         REQUIRE(meets == (b >= sp.lo && b <= sp.hi), "pass-2 span differs from the bricks meeting the support");
       }
     }
+  // pass 2's offsets: 32 bits with up to three bricks past their spans
+  static_assert(4 * (uint64_t)kAdjGatherSmall <= (uint64_t)1 << 32);
+  REQUIRE(a.part_bytes == (ws * 4 <= kAdjGatherSmall ? ws * 4 : 0), "pass-2 buffer over the partials");
+  REQUIRE(a.lx >= 0 || (a.part_bytes != 0 && (int64_t)g.gx * g.gy * g.gz <= 1 << 20), "points of the wave-per-point form");
   // pass 2's workgroups take every control point exactly once
   {
     std::vector<unsigned char> hit((size_t)g.gx * g.gy * g.gz, 0);
-    const int64_t nblk = adj_gather_blocks(g);
+    const int64_t nblk = adj_gather_blocks(a);
     REQUIRE(nblk < ((int64_t)1 << 31), "pass-2 grid above 2^31 workgroups");
     for (int64_t blk = 0; blk < nblk; ++blk)
-      for (int w = 0; w < kGatherWaves; ++w)
-        for (int l = 0; l < kWave; ++l) {
-          int cx, cy, cz;
-          if (!adj_gather_index(g, (int)blk, w, l, cx, cy, cz)) continue;
-          REQUIRE(0 <= cx && cx < g.gx && 0 <= cy && cy < g.gy && 0 <= cz && cz < g.gz, "pass-2 point off the grid");
-          unsigned char& h = hit[((size_t)cz * g.gy + cy) * g.gx + cx];
-          REQUIRE(h == 0, "pass-2 point taken twice");
-          h = 1;
-        }
+      for (int t = 0; t < kGatherThreads; t += a.lx < 0 ? kWave : 1) {
+        int cx, cy, cz;
+        if (!adj_gather_index(a, (int)blk, t, cx, cy, cz)) continue;
+        REQUIRE(0 <= cx && cx < g.gx && 0 <= cy && cy < g.gy && 0 <= cz && cz < g.gz, "pass-2 point off the grid");
+        unsigned char& h = hit[((size_t)cz * g.gy + cy) * g.gx + cx];
+        REQUIRE(h == 0, "pass-2 point taken twice");
+        h = 1;
+      }
     for (unsigned char h : hit) REQUIRE(h == 1, "pass-2 point never taken");
   }
   // pass 2: every brick a control point reads holds that point in its window
