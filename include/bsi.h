@@ -309,8 +309,8 @@ int32_t bsi_batch_tune(bsi_batch* plan, hipStream_t stream);
 /* Index of the schedule the plan uses, and the number of schedules. */
 int32_t bsi_batch_config(const bsi_batch* plan, int32_t* index, int32_t* count);
 
-/* The plan's schedule as text ("fwd_tile=4x1 fwd_items=2048 ..."), written
-   NUL-terminated into buf (host, len bytes; truncated to fit).
+/* The plan's schedule as text ("fwd_tile=4x1 fwd_items=2048 ..."; fwd_items=0:
+   forward items of about 15 planes), written NUL-terminated into buf (host, len bytes; truncated to fit).
    Errors: INVALID_ARG (null plan or buffer, len < 1). */
 int32_t bsi_batch_describe(const bsi_batch* plan, char* buf, int32_t len);
 

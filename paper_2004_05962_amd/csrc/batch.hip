@@ -61,7 +61,7 @@ constexpr int kNumFwdShapes = 3;
 static const char* const kFwdShapeName[kNumFwdShapes] = {"4x1", "2x2", "8x1"};
 static const int kFwdShapeWidth[kNumFwdShapes] = {64, 128, 64};
 static const int kFwdShapeRows[kNumFwdShapes] = {4, 2, 8};
-static const int kFwdItems[] = {512, 2048, 8192};  // forward items per volume (the z split aims at this)
+static const int kFwdItems[] = {512, 2048, 0};     // forward items per volume that the z split aims at; 0: chunks of 15 planes
 static const int kFwdPerCu[] = {0, 2, 4, 8};       // forward workgroups per CU (0: one per item)
 static const int kAdjPerCu[] = {0, 1, 2, 3};       // pass-1 workgroups per CU (0: one per brick)
 static const int kPtsPerCu[] = {0, 8};             // pass-2 workgroups per CU (0: one per block)
@@ -78,13 +78,14 @@ static_assert(kClassStreams + 1 >= 4, "the largest pass1_streams value");
 struct BatchConfig {
   int k[kNumKnobs];  // value index of each knob
 };
-// The starting point of the search: 8x1 forward, 2048 items per volume (short
-// workgroups in the order of the volumes: the forward 561 us against 672 with 512), one
-// workgroup per item in every pass, pass 1 in one launch for the spacings
+// The starting point of the search: 8x1 forward in chunks of 15 planes (short
+// workgroups in the order of the volumes, whatever their size: 32 volumes of 200 M
+// voxels 568 us, 613 with 2048 items per volume, 640 with 512; 4 volumes of 31 M
+// voxels 95, 99, 106), one workgroup per item in every pass, pass 1 in one launch for the spacings
 // 4..12 and per class for the rest over 4 streams, forward first with
 // ordinary stores (among the fastest graphs measured on the 32-volume
 // workload).
-static const BatchConfig kDefaultConfig = {{2, 1, 0, 0, 0, 2, 1, 0, 1}};
+static const BatchConfig kDefaultConfig = {{2, 2, 0, 0, 0, 2, 1, 0, 1}};
 
 int config_count() {
   int n = 1;
@@ -426,7 +427,9 @@ bool layout_forward(bsi_batch* p) {
   if (sh == p->layout_shape && it == p->layout_items) return false;
   int64_t tot = 0;
   for (VolDesc& d : p->host) {
-    d.f = make_fwd_launch(d.a.g, kFwdItems[it], kFwdShapeWidth[sh], kFwdShapeRows[sh]);
+    const int items = kFwdItems[it];
+    d.f = make_fwd_launch(d.a.g, items > 0 ? items : kFwdLeastItems, kFwdShapeWidth[sh], kFwdShapeRows[sh],
+                          items > 0 ? 0 : kFwdChunkBatch);
     d.first[kFwd] = tot;
     tot += (int64_t)d.f.nbx * d.f.nby * d.f.nbz;
   }

@@ -48,6 +48,8 @@ constexpr int kFwdTargetBlocks = BSI_FWD_BLOCKS; // z is split until this many w
 // of whole 512-voxel rows (512 x 512 x 256, spacing 5: 141.6 us with 20, 149 with 30, 178
 // with 10).
 constexpr int kFwdChunk = 30, kFwdChunkWide = 20;
+// The batched forward's (fwd_items = 0): planes per chunk, and the least items of a volume.
+constexpr int kFwdChunkBatch = 15, kFwdLeastItems = 64;
 // width x rows: the voxels and rows one workgroup covers in x and y; planes: chunks are
 // about this deep (0: as deep as the target leaves).
 FwdLaunch make_fwd_launch(const VolGeom& g, long target = kFwdTargetBlocks, int width = kWave, int rows = kFwdRows,

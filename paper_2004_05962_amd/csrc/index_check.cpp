@@ -250,20 +250,21 @@ bool check_forward_span(const VolGeom& g, Check& ck) {
 
 // The shape's instances for every smallest spacing that the geometry allows.
 template <int C, int R, int S, int V>
-bool check_forward_shape(const VolGeom& g, Check& ck, long target = kFwdTargetBlocks) {
+bool check_forward_shape(const VolGeom& g, Check& ck, long target = kFwdTargetBlocks,
+                         int planes = S > 1 ? kFwdChunkWide : kFwdChunk) {
   const int d = imin(g.dx, g.dy);
-  return check_forward_march<C, FwdTile<R, S, V>>(g, ck, target) &&
-         (d < 2 || check_forward_march<C, FwdTile<R, S, V, 2>>(g, ck, target)) &&
-         (d < 3 || check_forward_march<C, FwdTile<R, S, V, 3>>(g, ck, target)) &&
-         (d < 4 || check_forward_march<C, FwdTile<R, S, V, 4>>(g, ck, target)) &&
-         (d < 5 || check_forward_march<C, FwdTile<R, S, V, 5>>(g, ck, target));
+  return check_forward_march<C, FwdTile<R, S, V>>(g, ck, target, planes) &&
+         (d < 2 || check_forward_march<C, FwdTile<R, S, V, 2>>(g, ck, target, planes)) &&
+         (d < 3 || check_forward_march<C, FwdTile<R, S, V, 3>>(g, ck, target, planes)) &&
+         (d < 4 || check_forward_march<C, FwdTile<R, S, V, 4>>(g, ck, target, planes)) &&
+         (d < 5 || check_forward_march<C, FwdTile<R, S, V, 5>>(g, ck, target, planes));
 }
 
 // The batched forward's shapes and z-split targets (the schedule knobs).
 bool check_forward_batched(const VolGeom& g, Check& ck) {
-  for (long target : {512L, 2048L, 8192L})
-    if (!(check_forward_shape<3, 4, 1, 1>(g, ck, target) && check_forward_shape<3, 2, 2, 1>(g, ck, target) &&
-          check_forward_shape<3, 8, 1, 1>(g, ck, target)))
+  for (const auto& [target, planes] : {std::pair{512L, 0}, {2048L, 0}, {(long)kFwdLeastItems, kFwdChunkBatch}})
+    if (!(check_forward_shape<3, 4, 1, 1>(g, ck, target, planes) && check_forward_shape<3, 2, 2, 1>(g, ck, target, planes) &&
+          check_forward_shape<3, 8, 1, 1>(g, ck, target, planes)))
       return false;
   return true;
 }
