@@ -10,6 +10,7 @@ The library must be built in-tree (``paper_2004_05962_amd/libbsi.so``); there is
 no fallback: without it every call raises.
 """
 import ctypes
+import functools
 import os
 
 import torch
@@ -106,37 +107,63 @@ def _check(rc):
         raise BSIError(rc, msg.decode() if msg else "")
 
 
-def _triple(v, name):
-    t = tuple(int(a) for a in v)
+def _ints(v, name):
+    t = tuple(map(int, v))
     if len(t) != 3:
         raise ValueError(f"{name} must have three entries")
-    return _I32x3(*t)
+    return t
+
+
+def _triple(v, name):
+    return _I32x3(*_ints(v, name))
+
+
+# What a call needs of its geometry, a pure function of the integers: the arrays the
+# library reads and the shapes.  Kept for the last few hundred geometries, since
+# forming it took half of a small call's host time (64^3, spacing 5, on the thread
+# that autograd runs the backward on: forward and gradient 129 us, 69 with all of it
+# at hand).
+class _Geometry:
+    __slots__ = ("dims", "spacing", "grid", "field", "image")
+
+    def __init__(self, dims, spacing):
+        out = _I32x3()
+        self.dims, self.spacing = _I32x3(*dims), _I32x3(*spacing)
+        _check(lib().bsi_grid_dims(self.dims, self.spacing, out))
+        self.grid = (out[2], out[1], out[0], 3)
+        self.image = dims[::-1]
+        self.field = self.image + (3,)
+
+
+_geometry_of = functools.lru_cache(maxsize=512)(_Geometry)
+
+
+def _geometry(dims, spacing):
+    return _geometry_of(_ints(dims, "dims"), _ints(spacing, "spacing"))
 
 
 def _stream(stream):
     if stream is None:
+        if torch.cuda.is_initialized():  # as torch.cuda.current_stream(), without the Stream object
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
-    return _VP(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _ptr(t, name, shape=None):
     if t is None:
-        return _VP(0)
+        return None
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != torch.float32:
         raise TypeError(f"{name} must be float32, got {t.dtype}")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return _VP(t.data_ptr())
-
-
-def _raw(t):
-    return _VP(t.data_ptr()) if t is not None else _VP(0)
+    return t.data_ptr()
 
 
 # ------------------------------------------------------------------- geometry
@@ -151,14 +178,11 @@ def bsi_last_error():
 
 def bsi_grid_dims(dims, spacing):
     """(gx, gy, gz) = ceil(n/d) + 3 per axis."""
-    out = _I32x3()
-    _check(lib().bsi_grid_dims(_triple(dims, "dims"), _triple(spacing, "spacing"), out))
-    return tuple(out)
+    return _geometry(dims, spacing).grid[2::-1]
 
 
 def grid_shape(dims, spacing):
-    gx, gy, gz = bsi_grid_dims(dims, spacing)
-    return (gz, gy, gx, 3)
+    return _geometry(dims, spacing).grid
 
 
 def field_shape(dims):
@@ -169,25 +193,26 @@ def field_shape(dims):
 # ------------------------------------------------------------- forward/adjoint
 def bsi_forward(grid, dims, spacing, field, stream=None):
     """Eq. 1 into ``field`` (nz, ny, nx, 3) from ``grid`` (gz, gy, gx, 3)."""
-    g = _ptr(grid, "grid", grid_shape(dims, spacing))
-    f = _ptr(field, "field", field_shape(dims))
-    _check(lib().bsi_forward(g, _triple(dims, "dims"), _triple(spacing, "spacing"), f, _stream(stream)))
+    geo = _geometry(dims, spacing)
+    g = _ptr(grid, "grid", geo.grid)
+    f = _ptr(field, "field", geo.field)
+    _check(lib().bsi_forward(g, geo.dims, geo.spacing, f, _stream(stream)))
 
 
 def bsi_forward_lerp(grid, dims, spacing, field, stream=None):
     """Eq. 1 in the paper's lerp form (ablation; same result up to rounding, far more arithmetic)."""
-    g = _ptr(grid, "grid", grid_shape(dims, spacing))
-    f = _ptr(field, "field", field_shape(dims))
-    _check(lib().bsi_forward_lerp(g, _triple(dims, "dims"), _triple(spacing, "spacing"), f, _stream(stream)))
+    geo = _geometry(dims, spacing)
+    g = _ptr(grid, "grid", geo.grid)
+    f = _ptr(field, "field", geo.field)
+    _check(lib().bsi_forward_lerp(g, geo.dims, geo.spacing, f, _stream(stream)))
 
 
 def bsi_forward_scalar(grid, dims, spacing, image, stream=None):
     """Scalar Eq. 1 (B-spline upsampling): ``image`` (nz, ny, nx) from ``grid`` (gz, gy, gx)."""
-    gx, gy, gz = bsi_grid_dims(dims, spacing)
-    nx, ny, nz = (int(v) for v in dims)
-    g = _ptr(grid, "grid", (gz, gy, gx))
-    o = _ptr(image, "image", (nz, ny, nx))
-    _check(lib().bsi_forward_scalar(g, _triple(dims, "dims"), _triple(spacing, "spacing"), o, _stream(stream)))
+    geo = _geometry(dims, spacing)
+    g = _ptr(grid, "grid", geo.grid[:3])
+    o = _ptr(image, "image", geo.image)
+    _check(lib().bsi_forward_scalar(g, geo.dims, geo.spacing, o, _stream(stream)))
 
 
 def upsample(grid, spacing, dims=None, out=None, stream=None):
@@ -204,21 +229,26 @@ def upsample(grid, spacing, dims=None, out=None, stream=None):
     return out
 
 
-def bsi_adjoint_workspace_size(dims, spacing):
+@functools.lru_cache(maxsize=512)
+def _adjoint_bytes(dims, spacing):
     n = ctypes.c_size_t()
-    _check(lib().bsi_adjoint_workspace_size(_triple(dims, "dims"), _triple(spacing, "spacing"), ctypes.byref(n)))
+    _check(lib().bsi_adjoint_workspace_size(_I32x3(*dims), _I32x3(*spacing), ctypes.byref(n)))
     return int(n.value)
+
+
+def bsi_adjoint_workspace_size(dims, spacing):
+    return _adjoint_bytes(_ints(dims, "dims"), _ints(spacing, "spacing"))
 
 
 def bsi_adjoint(dfield, dims, spacing, grid_grad, workspace, stream=None):
     """Transpose of Eq. 1: ``grid_grad`` (overwritten) from ``dfield``.
 
     ``workspace`` is a device tensor of at least bsi_adjoint_workspace_size bytes."""
-    d = _ptr(dfield, "dfield", field_shape(dims))
-    g = _ptr(grid_grad, "grid_grad", grid_shape(dims, spacing))
+    geo = _geometry(dims, spacing)
+    d = _ptr(dfield, "dfield", geo.field)
+    g = _ptr(grid_grad, "grid_grad", geo.grid)
     w, nbytes = _workspace(workspace)
-    _check(lib().bsi_adjoint(d, _triple(dims, "dims"), _triple(spacing, "spacing"), g, w, nbytes,
-                             _stream(stream)))
+    _check(lib().bsi_adjoint(d, geo.dims, geo.spacing, g, w, nbytes, _stream(stream)))
 
 
 def bsi_adjoint_partials(dfield, dims, spacing, workspace, stream=None):
@@ -241,18 +271,19 @@ def bsi_adjoint_noalloc(dfield, dims, spacing, grid_grad, stream=None):
     """bsi_adjoint without a workspace and without allocating: the partials go to
     the library's fixed per-device scratch array (BSI_ADJOINT_NOALLOC_MAX_BYTES);
     calls that may overlap on one GPU race on it."""
-    d = _ptr(dfield, "dfield", field_shape(dims))
-    g = _ptr(grid_grad, "grid_grad", grid_shape(dims, spacing))
-    _check(lib().bsi_adjoint_noalloc(d, _triple(dims, "dims"), _triple(spacing, "spacing"), g, _stream(stream)))
+    geo = _geometry(dims, spacing)
+    d = _ptr(dfield, "dfield", geo.field)
+    g = _ptr(grid_grad, "grid_grad", geo.grid)
+    _check(lib().bsi_adjoint_noalloc(d, geo.dims, geo.spacing, g, _stream(stream)))
 
 
 BSI_ADJOINT_NOALLOC_MAX_BYTES = 64 << 20
 
 
 def _workspace(workspace):
-    if not isinstance(workspace, torch.Tensor) or workspace.device.type != "cuda" or not workspace.is_contiguous():
+    if not isinstance(workspace, torch.Tensor) or not workspace.is_cuda or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous device tensor")
-    return _raw(workspace), workspace.numel() * workspace.element_size()
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 # ------------------------------------------------- real spacing, origin offset
@@ -337,28 +368,27 @@ def bsi_ssd_fused_workspace_size(dims, spacing):
 
 def bsi_ssd_fused(grid, moving, fixed, dims, spacing, grid_grad, loss, workspace, stream=None):
     """Loss and control-grid gradient of the SSD step in one pass (field never stored)."""
-    nx, ny, nz = (int(v) for v in dims)
-    g = _ptr(grid, "grid", grid_shape(dims, spacing))
-    m = _ptr(moving, "moving", (nz, ny, nx))
-    x = _ptr(fixed, "fixed", (nz, ny, nx))
-    o = _ptr(grid_grad, "grid_grad", grid_shape(dims, spacing))
+    geo = _geometry(dims, spacing)
+    g = _ptr(grid, "grid", geo.grid)
+    m = _ptr(moving, "moving", geo.image)
+    x = _ptr(fixed, "fixed", geo.image)
+    o = _ptr(grid_grad, "grid_grad", geo.grid)
     l = _ptr(loss, "loss", (1,))
     w, nbytes = _workspace(workspace)
-    _check(lib().bsi_ssd_fused(g, m, x, _triple(dims, "dims"), _triple(spacing, "spacing"), o, l, w, nbytes,
-                               _stream(stream)))
+    _check(lib().bsi_ssd_fused(g, m, x, geo.dims, geo.spacing, o, l, w, nbytes, _stream(stream)))
 
 
 def bsi_ssd_fused_descent(grid, moving, fixed, dims, spacing, eta, grid_grad, loss, workspace, stream=None):
     """One fused registration iteration: loss and gradient at `grid`, then grid -= eta * grad in place."""
-    nx, ny, nz = (int(v) for v in dims)
-    g = _ptr(grid, "grid", grid_shape(dims, spacing))
-    m = _ptr(moving, "moving", (nz, ny, nx))
-    x = _ptr(fixed, "fixed", (nz, ny, nx))
-    o = _ptr(grid_grad, "grid_grad", grid_shape(dims, spacing))
+    geo = _geometry(dims, spacing)
+    g = _ptr(grid, "grid", geo.grid)
+    m = _ptr(moving, "moving", geo.image)
+    x = _ptr(fixed, "fixed", geo.image)
+    o = _ptr(grid_grad, "grid_grad", geo.grid)
     l = _ptr(loss, "loss", (1,))
     w, nbytes = _workspace(workspace)
-    _check(lib().bsi_ssd_fused_descent(g, m, x, _triple(dims, "dims"), _triple(spacing, "spacing"),
-                                       ctypes.c_float(float(eta)), o, l, w, nbytes, _stream(stream)))
+    _check(lib().bsi_ssd_fused_descent(g, m, x, geo.dims, geo.spacing, ctypes.c_float(float(eta)), o, l, w, nbytes,
+                                       _stream(stream)))
 
 
 def bsi_descent_step(grid, grad, eta, stream=None):
@@ -381,7 +411,7 @@ def _ptr_array(tensors, name, shapes):
         raise ValueError(f"{name} holds {len(tensors)} tensors; the plan has {len(shapes)} volumes")
     arr = (_VP * len(tensors))()
     for i, (t, shape) in enumerate(zip(tensors, shapes)):
-        arr[i] = _ptr(t, f"{name}[{i}]", shape).value
+        arr[i] = _ptr(t, f"{name}[{i}]", shape)
     return arr
 
 
