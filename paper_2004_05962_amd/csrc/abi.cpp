@@ -295,7 +295,7 @@ int32_t bsi_adjoint_general_workspace_size(const int32_t dims[3], const float sp
   VolGeom g;
   int32_t rc = make_gen_geom(dims, spacing, origin, &q, &g);
   if (rc) return rc;
-  *bytes = general_workspace_bytes(q);
+  *bytes = general_workspace_bytes(q, g);
   return BSI_OK;
 }
 
@@ -310,13 +310,13 @@ int32_t bsi_adjoint_general(const float* dfield, const int32_t dims[3], const fl
   if (!dfield) return null_arg("dfield");
   if (!grid_grad) return null_arg("grid_grad");
   if (!workspace) return null_arg("workspace");
-  const size_t need = general_workspace_bytes(q);
+  const size_t need = general_workspace_bytes(q, g);
   if (workspace_bytes < need) {
     set_error("workspace too small: need " + std::to_string(need) + " bytes");
     return BSI_ERR_INVALID_ARG;
   }
   if ((rc = device_only())) return rc;
-  hipError_t e = launch_adjoint_general(dfield, grid_grad, q, workspace, stream);
+  hipError_t e = launch_adjoint_general(dfield, grid_grad, q, g, workspace, stream);
   return e == hipSuccess ? BSI_OK : hip_fail(e, "launching the general adjoint kernels");
 }
 

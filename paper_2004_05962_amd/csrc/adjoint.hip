@@ -20,7 +20,7 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI
 template <bool Small>
 __global__ __launch_bounds__(kGatherThreads) __attribute__((amdgpu_waves_per_eu(8))) void adj_pass2_kernel(
     const float* __restrict__ part, float* __restrict__ grad, AdjGeom a) {
-  adj_gather_block<Small>(part, a, xcd_remap(blockIdx.x, gridDim.x), threadIdx.x,
+  adj_gather_block<Small>(part, a, AdjMap{a}, xcd_remap(blockIdx.x, gridDim.x), threadIdx.x,
                           [&](size_t i, const F3& v) { stf3(grad + i * 3, v); });
 }
 
@@ -49,7 +49,7 @@ static int adj_most_bricks(const AdjAxis& x, int d) { return imin(x.nb, (4 * d +
 // loads and the points are few, a wave each: 512 x 512 x 256, spacing 64 (847
 // points, 54 rounds) 4.2 us against 14.8, 150 x 130 x 100, spacing 20 (880, 8) 3.8
 // against 6.9, but 512 x 512 x 256, spacing 24 (8750, 8) 6.8 against 5.8.
-static int adj_gather_lx(const AdjGeom& a) {
+int adj_gather_lx(const AdjGeom& a) {
   const VolGeom& g = a.g;
   auto pairs = [](int n) { return (n + 1) / 2; };
   const int rounds = pairs(adj_most_bricks(a.x, g.dx)) * pairs(adj_most_bricks(a.y, g.dy)) *
@@ -59,6 +59,35 @@ static int adj_gather_lx(const AdjGeom& a) {
   for (int l = 5; l >= 4; --l)
     if (((g.gx + (1 << l) - 1) >> l << l) < ((g.gx + (1 << lx) - 1) >> lx << lx)) lx = l;
   return lx;
+}
+
+// Brick depths in z-tiles of dz voxels, by the rule stated with its constants
+// (adjoint_device.h).
+AdjDepth adj_depth(const AdjGeom& a, int tiles, double dz) {
+  AdjDepth d;
+  const int plane = kAdjWaves * adj_slab(a);  // slab floats of one control plane
+  const int fit3 = kAdjSlabFloats3 / plane - 3, fit2 = kAdjSlabFloats2 / plane - 3;
+  d.fit = fit3 >= kAdjMinStaged ? fit3 : fit2;
+  const bool staged = d.fit >= kAdjMinStaged;
+  d.most = imin(tiles, imax(1, (int)((staged ? kAdjDepthStaged : kAdjDepthTwo) / dz)));
+  if (staged) d.most = imin(d.most, d.fit);
+  // z-bricks: the fewest of those with the least modelled time (kAdjCuCost)
+  const long base = (long)a.x.nb * a.y.nb;
+  const int most = (tiles + d.most - 1) / d.most;
+  int nbz = most;
+  double best = 0.;
+  for (int n = most; n <= tiles && n <= 64 * most; ++n) {
+    const int k = (tiles + n - 1) / n;
+    const double per_cu = (double)(base * ((tiles + k - 1) / k)) / kAdjCus;
+    const double cost = (k * dz + kAdjBrickCost) * fmax(ceil(per_cu) * kAdjCuCost, per_cu);
+    if (n == most || cost < best) {
+      best = cost;
+      nbz = n;
+    }
+    if (per_cu >= 4) break;
+  }
+  d.best = (tiles + nbz - 1) / nbz;
+  return d;
 }
 
 // Bricks of pass 1: 2 x 2 cells in x and y by whole z-tiles; the depth by the
@@ -77,33 +106,13 @@ AdjGeom make_adj_geom(const VolGeom& g) {
   a.x = make_axis(g.nx, g.dx, 1, kAdjCellsX * a.cell);
   a.y = make_axis(g.ny, g.dy, 1, kAdjCellsY * kAdjCellY);
   const int tiles = (g.nz + g.dz - 1) / g.dz;
-  const int plane = kAdjWaves * adj_slab(a);  // slab floats of one control plane
-  const int fit3 = kAdjSlabFloats3 / plane - 3, fit2 = kAdjSlabFloats2 / plane - 3;
-  const int fit = fit3 >= kAdjMinStaged ? fit3 : fit2;  // deepest brick whose slabs hold all of its planes
-  const bool staged = fit >= kAdjMinStaged;
-  int kmax = imin(tiles, imax(1, (staged ? kAdjDepthStaged : kAdjDepthTwo) / g.dz));
-  if (staged) kmax = imin(kmax, fit);
-  // z-bricks: the fewest of those with the least modelled time (kAdjCuCost)
-  const long base = (long)a.x.nb * a.y.nb;
-  const int most = (tiles + kmax - 1) / kmax;
-  int nbz = most;
-  double best = 0.;
-  for (int n = most; n <= tiles && n <= 64 * most; ++n) {
-    const int k = (tiles + n - 1) / n;
-    const double per_cu = (double)(base * ((tiles + k - 1) / k)) / kAdjCus;
-    const double cost = (k * g.dz + kAdjBrickCost) * fmax(ceil(per_cu) * kAdjCuCost, per_cu);
-    if (n == most || cost < best) {
-      best = cost;
-      nbz = n;
-    }
-    if (per_cu >= 4) break;
-  }
+  const AdjDepth depth = adj_depth(a, tiles, g.dz);
   auto set_depth = [&](int k) {
     a.z = make_axis(g.nz, g.dz, g.dz, k);
-    a.slots = a.z.cm <= fit + 3 ? a.z.cm : 2;
+    a.slots = a.z.cm <= depth.fit + 3 ? a.z.cm : 2;
   };
-  set_depth((int)((tiles + nbz - 1) / nbz));
-  if (a.z.k < kmax && adj_workspace_bytes(a) > kAdjShallowBytes) set_depth(kmax);
+  set_depth(depth.best);
+  if (a.z.k < depth.most && adj_workspace_bytes(a) > kAdjShallowBytes) set_depth(depth.most);
   if (adj_limit_bytes(g) <= BSI_ADJOINT_NOALLOC_MAX_BYTES)
     for (int deeper : {kAdjDepthMost, g.nz}) {
       if (adj_workspace_bytes(a) <= kAdjScratchBytes) break;

@@ -148,18 +148,29 @@ struct AdjCell {
   int x0, nx, cx0, Cx;
   int y0, ny, cy0, Cy;
 };
-__host__ __device__ inline AdjCell adj_cell_geom(const AdjGeom& a, const AdjBrick& b, int w) {
+// The tile (first control index) of a voxel on the x and y axes; the real-spacing
+// grid reads its own from tables (GenTiles).
+struct AdjTiles {
+  const AdjGeom& a;
+  __host__ __device__ int x(int v) const { return adj_div(v, a.g.dx, a.x.md); }
+  __host__ __device__ int y(int v) const { return adj_div(v, a.g.dy, a.y.md); }
+};
+template <class Tiles>
+__host__ __device__ inline AdjCell adj_cell_of(const AdjGeom& a, const Tiles& t, const AdjBrick& b, int w) {
   AdjCell c;
   c.x0 = b.x0 + w % kAdjCellsX * a.cell;
   c.y0 = b.y0 + w / kAdjCellsX * kAdjCellY;
   c.nx = imax(0, imin(a.cell, b.xe - c.x0));
   c.ny = imax(0, imin(kAdjCellY, b.ye - c.y0));
-  c.cx0 = adj_div(c.x0, a.g.dx, a.x.md);
-  c.cy0 = adj_div(c.y0, a.g.dy, a.y.md);
   const bool any = c.nx > 0 && c.ny > 0;
-  c.Cx = any ? adj_div(c.x0 + c.nx - 1, a.g.dx, a.x.md) - c.cx0 + 4 : 0;
-  c.Cy = any ? adj_div(c.y0 + c.ny - 1, a.g.dy, a.y.md) - c.cy0 + 4 : 0;
+  c.cx0 = any ? t.x(c.x0) : b.cx0;
+  c.cy0 = any ? t.y(c.y0) : b.cy0;
+  c.Cx = any ? t.x(c.x0 + c.nx - 1) - c.cx0 + 4 : 0;
+  c.Cy = any ? t.y(c.y0 + c.ny - 1) - c.cy0 + 4 : 0;
   return c;
+}
+__host__ __device__ inline AdjCell adj_cell_geom(const AdjGeom& a, const AdjBrick& b, int w) {
+  return adj_cell_of(a, AdjTiles{a}, b, w);
 }
 
 // LDS slabs: wave w's plane in slot s begins at float (s * kAdjWaves + w) *
@@ -388,9 +399,10 @@ __device__ __forceinline__ void adj_cell_emit(const F3 (&f3)[kAdjSteps], const A
 // Sum the slabs of planes czl0 .. czl0 + np - 1 (slots slot0 ..) over the
 // brick's cells, in wave order, into the brick's partials.  Collective over
 // `threads` threads, after a barrier.
-__device__ __forceinline__ void adj_combine_slabs(const AdjGeom& a, const AdjBrick& b, const float* __restrict__ slabs,
-                                                  float* __restrict__ pbase, int czl0, int np, int slot0, int tid,
-                                                  int threads) {
+template <class Tiles>
+__device__ __forceinline__ void adj_combine_slabs(const AdjGeom& a, const Tiles& tiles, const AdjBrick& b,
+                                                  const float* __restrict__ slabs, float* __restrict__ pbase, int czl0,
+                                                  int np, int slot0, int tid, int threads) {
   // items: (plane, point), a wave's lanes consecutive; plane and row of an item
   // by reciprocal (at most 2^11 points, and 2^16 items: exact)
   const int slab = adj_slab(a), comp = a.ch * a.cw;
@@ -399,7 +411,7 @@ __device__ __forceinline__ void adj_combine_slabs(const AdjGeom& a, const AdjBri
   int fx[kAdjWaves], fy[kAdjWaves], nx[kAdjWaves], ny[kAdjWaves];
 #pragma unroll
   for (int w = 0; w < kAdjWaves; ++w) {
-    const AdjCell c = adj_cell_geom(a, b, w);
+    const AdjCell c = adj_cell_of(a, tiles, b, w);
     fx[w] = c.cx0 - b.cx0;
     fy[w] = c.cy0 - b.cy0;
     nx[w] = c.Cx;
@@ -521,16 +533,16 @@ __device__ __forceinline__ void adj_march(const char* base, size_t zs, uint32_t 
 }
 
 // Pass 1 for one brick.  Collective over the workgroup (kAdjThreads threads).
-// Stream: dfield is read with non-temporal loads.  Staged: adj_staged(a).
-template <bool Stream, bool Staged>
-__device__ __forceinline__ void adj_brick(const float* __restrict__ dfield, float* __restrict__ part,
-                                          const AdjGeom& a, const float* __restrict__ lut, int brick,
-                                          float* __restrict__ slabs, int tid) {
+// Stream: dfield is read with non-temporal loads.  Staged: adj_staged(a).  cz: the
+// brick's control planes; z: its march along z; weights(c): cell c's matrices.
+template <bool Stream, bool Staged, class Tiles, class Z, class Weights>
+__device__ __forceinline__ void adj_brick_of(const float* __restrict__ dfield, float* __restrict__ part,
+                                             const AdjGeom& a, const Tiles& tiles, const AdjBrick& b, int brick, int cz,
+                                             const Z& z, Weights&& weights, float* __restrict__ slabs, int tid) {
   const VolGeom& g = a.g;
-  const AdjBrick b = adj_brick_geom(a, brick);
   float* pbase = part + (size_t)brick * adj_brick_stride(a);
   const int lane = tid & (kWave - 1), wave = uniform(tid / kWave);
-  const AdjCell c = adj_cell_geom(a, b, wave);
+  const AdjCell c = adj_cell_of(a, tiles, b, wave);
   const bool any = c.nx > 0 && c.ny > 0;
   __syncthreads();  // a previous brick of this workgroup may still read the slabs
   // A cell past the volume has nothing to add; with two slots it marches all
@@ -544,21 +556,31 @@ __device__ __forceinline__ void adj_brick(const float* __restrict__ dfield, floa
     const size_t zs = (size_t)g.ny * g.nx * 12;
     const char* base = reinterpret_cast<const char*>(dfield) + (size_t)b.z0 * zs +
                        ((size_t)(any ? c.y0 : b.y0) * g.nx + (any ? c.x0 : b.x0)) * 12;
-    const auto setup = [&] { w = adj_cell_weights(a, c, lut, lane); };
-    adj_march<Stream>(base, zs, bytes, off, b.ze - b.z0, AdjZ(lut, g.dz), setup, [&](const F3(&f)[kAdjSteps], int czl) {
+    const auto setup = [&] { w = weights(c); };
+    adj_march<Stream>(base, zs, bytes, off, b.ze - b.z0, z, setup, [&](const F3(&f)[kAdjSteps], int czl) {
       const int slot = Staged ? czl : czl & 1;
       adj_cell_emit(f, w, slabs + adj_slab_at(a, slot, wave), a.cw, a.ch, lane);
       if constexpr (!Staged) {
         // the barrier of plane czl + 1 orders this sum before the slot's next store
         __syncthreads();
-        adj_combine_slabs(a, b, slabs, pbase, czl, 1, slot, tid, kAdjThreads);
+        adj_combine_slabs(a, tiles, b, slabs, pbase, czl, 1, slot, tid, kAdjThreads);
       }
     });
   }
   if constexpr (Staged) {
     __syncthreads();
-    adj_combine_slabs(a, b, slabs, pbase, 0, adj_brick_cz(a, b), 0, tid, kAdjThreads);
+    adj_combine_slabs(a, tiles, b, slabs, pbase, 0, cz, 0, tid, kAdjThreads);
   }
+}
+
+// The aligned grid's.
+template <bool Stream, bool Staged>
+__device__ __forceinline__ void adj_brick(const float* __restrict__ dfield, float* __restrict__ part,
+                                          const AdjGeom& a, const float* __restrict__ lut, int brick,
+                                          float* __restrict__ slabs, int tid) {
+  const AdjBrick b = adj_brick_geom(a, brick);
+  adj_brick_of<Stream, Staged>(dfield, part, a, AdjTiles{a}, b, brick, adj_brick_cz(a, b), AdjZ(lut, a.g.dz),
+                               [&](const AdjCell& c) { return adj_cell_weights(a, c, lut, tid & (kWave - 1)); }, slabs, tid);
 }
 
 // Pass 2: the fixed-order sum, per control point, of the partials of the bricks
@@ -592,6 +614,17 @@ __host__ __device__ inline size_t adj_part_addr(const AdjGeom& a, int bx, int by
   return adj_part_x(a, bx, cx) + adj_part_y(a, by, cy) + adj_part_z(a, bz, cz);
 }
 
+// The aligned grid's spans and terms; the real-spacing grid has its own (GenMap).
+struct AdjMap {
+  const AdjGeom& a;
+  __device__ AdjSpan span_x(int c) const { return adj_span(a.x, c, a.g.dx, a.g.nx); }
+  __device__ AdjSpan span_y(int c) const { return adj_span(a.y, c, a.g.dy, a.g.ny); }
+  __device__ AdjSpan span_z(int c) const { return adj_span(a.z, c, a.g.dz, a.g.nz); }
+  __device__ size_t part_x(int b, int c) const { return adj_part_x(a, b, c); }
+  __device__ size_t part_y(int b, int c) const { return adj_part_y(a, b, c); }
+  __device__ size_t part_z(int b, int c) const { return adj_part_z(a, b, c); }
+};
+
 // The partials of one point, of the bricks lo, lo + step, lo + 2 step .. of each span:
 // two by two by two, 8 loads in flight, summed pairwise.  Bound by the latency of
 // that one round, and at many points by the partials' bytes; so the instructions
@@ -601,9 +634,9 @@ __host__ __device__ inline size_t adj_part_addr(const AdjGeom& a, int bx, int by
 // and the largest offset stay below 2^32) and reads as zero without an access to
 // memory.  Otherwise 64-bit addresses, a branch per load, four of them in flight.
 constexpr uint32_t kAdjGatherSmall = 1u << 30;
-template <bool Small>
-__device__ __forceinline__ F3 adj_gather_point(const float* __restrict__ part, const AdjGeom& a, int cx, int cy, int cz,
-                                               AdjSpan sx, AdjSpan sy, AdjSpan sz, int step) {
+template <bool Small, class Map>
+__device__ __forceinline__ F3 adj_gather_point(const float* __restrict__ part, const AdjGeom& a, const Map& map, int cx,
+                                               int cy, int cz, AdjSpan sx, AdjSpan sy, AdjSpan sz, int step) {
   F3 s{0.f, 0.f, 0.f};
   if constexpr (Small) {
     const __amdgpu_buffer_rsrc_t rs =
@@ -615,9 +648,9 @@ __device__ __forceinline__ F3 adj_gather_point(const float* __restrict__ part, c
           F3 v[2][2][2];
 #pragma unroll
           for (int i = 0; i < 2; ++i) {
-            ox[i] = (uint32_t)adj_part_x(a, bx + i * step, cx) * 4;
-            oy[i] = (uint32_t)adj_part_y(a, by + i * step, cy) * 4;
-            oz[i] = (uint32_t)adj_part_z(a, bz + i * step, cz) * 4;
+            ox[i] = (uint32_t)map.part_x(bx + i * step, cx) * 4;
+            oy[i] = (uint32_t)map.part_y(by + i * step, cy) * 4;
+            oz[i] = (uint32_t)map.part_z(bz + i * step, cz) * 4;
           }
           if (bx + step > sx.hi) ox[1] = kAdjGatherSmall;
           if (by + step > sy.hi) oy[1] = kAdjGatherSmall;
@@ -644,7 +677,7 @@ __device__ __forceinline__ F3 adj_gather_point(const float* __restrict__ part, c
             for (int i = 0; i < 2; ++i) {
               const int x = bx + i * step, y = by + j * step;
               v[j][i] = F3{0.f, 0.f, 0.f};
-              if (x <= sx.hi && y <= sy.hi) v[j][i] = ldf3(part + adj_part_addr(a, x, y, bz, cx, cy, cz));
+              if (x <= sx.hi && y <= sy.hi) v[j][i] = ldf3(part + map.part_x(x, cx) + map.part_y(y, cy) + map.part_z(bz, cz));
             }
           s = s + ((v[0][0] + v[0][1]) + (v[1][0] + v[1][1]));
         }
@@ -686,21 +719,21 @@ __host__ __device__ inline bool adj_gather_index(const AdjGeom& a, int blk, int 
 }
 
 // Workgroup blk of pass 2, thread tid: put(i, v) for each control point i, by one thread.
-template <bool Small, class Put>
-__device__ __forceinline__ void adj_gather_block(const float* __restrict__ part, const AdjGeom& a, int blk, int tid,
-                                                 Put&& put) {
+template <bool Small, class Map, class Put>
+__device__ __forceinline__ void adj_gather_block(const float* __restrict__ part, const AdjGeom& a, const Map& map, int blk,
+                                                 int tid, Put&& put) {
   int cx, cy, cz;
   const VolGeom& g = a.g;
   const bool wave = a.lx < 0;  // uniform: a function of the geometry
   const int lane = tid % kWave;
   if (!adj_gather_index(a, blk, wave ? uniform(tid / kWave) * kWave : tid, cx, cy, cz)) return;
-  AdjSpan sx = adj_span(a.x, cx, g.dx, g.nx), sy = adj_span(a.y, cy, g.dy, g.ny), sz = adj_span(a.z, cz, g.dz, g.nz);
+  AdjSpan sx = map.span_x(cx), sy = map.span_y(cy), sz = map.span_z(cz);
   if (wave) {
     sx.lo += lane % kGatherLanes;
     sy.lo += lane / kGatherLanes % kGatherLanes;
     sz.lo += lane / (kGatherLanes * kGatherLanes);
   }
-  F3 s = adj_gather_point<Small>(part, a, cx, cy, cz, sx, sy, sz, wave ? kGatherLanes : 1);
+  F3 s = adj_gather_point<Small>(part, a, map, cx, cy, cz, sx, sy, sz, wave ? kGatherLanes : 1);
   if (wave) {
 #pragma unroll
     for (int h = 1; h < kWave; h *= 2) s = s + F3{__shfl_xor(s.x, h), __shfl_xor(s.y, h), __shfl_xor(s.z, h)};

@@ -204,8 +204,8 @@ __global__ __launch_bounds__(kPtThreads) __attribute__((amdgpu_waves_per_eu(8)))
     float* grad = as_global(d.grad);
     auto put = [&](size_t i, const F3& v) { stf3(grad + i * 3, v); };
     const int blk = (int)(item - d.first[kAdj2]);
-    if (a.part_bytes != 0) adj_gather_block<true>(as_global(d.part), a, blk, threadIdx.x, put);
-    else adj_gather_block<false>(as_global(d.part), a, blk, threadIdx.x, put);
+    if (a.part_bytes != 0) adj_gather_block<true>(as_global(d.part), a, AdjMap{a}, blk, threadIdx.x, put);
+    else adj_gather_block<false>(as_global(d.part), a, AdjMap{a}, blk, threadIdx.x, put);
   });
 }
 

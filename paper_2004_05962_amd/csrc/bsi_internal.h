@@ -28,6 +28,13 @@ int32_t lerp_lut_device_ptr(int dev, const float** out);
 int32_t make_geom(const int32_t dims[3], const int32_t spacing[3], VolGeom* g);
 int32_t check_control_plane(int32_t gx, int32_t gy);  // UNSUPPORTED at 2^31 floats or more
 AdjGeom make_adj_geom(const VolGeom& g);
+struct AdjDepth {
+  int fit;   // deepest brick, in z-tiles, whose slabs hold all of its planes
+  int most;  // depth bound
+  int best;  // depth of the least modelled time
+};
+AdjDepth adj_depth(const AdjGeom& a, int tiles, double dz);
+int adj_gather_lx(const AdjGeom& a);  // a.g's spacings at least the grid's
 size_t adj_workspace_bytes(const AdjGeom& a);
 // bsi_adjoint_noalloc: what its limit is compared with, and its scratch.  The
 // partials of a geometry within the limit take at most 1.11 times as much
@@ -96,8 +103,8 @@ int32_t make_gen_geom(const int32_t dims[3], const float spacing[3], const float
                       VolGeom* g);
 hipError_t launch_forward_general(const float* grid, float* field, const VolGeom& g, const GenGeom& q,
                                   hipStream_t s);
-size_t general_workspace_bytes(const GenGeom& q);
-hipError_t launch_adjoint_general(const float* dfield, float* grad, const GenGeom& q, void* workspace,
+size_t general_workspace_bytes(const GenGeom& q, const VolGeom& g);
+hipError_t launch_adjoint_general(const float* dfield, float* grad, const GenGeom& q, const VolGeom& g, void* workspace,
                                   hipStream_t s);
 hipError_t launch_descent(float* grid, const float* grad, float eta, int64_t count, hipStream_t s);
 

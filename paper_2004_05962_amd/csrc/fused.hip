@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
     }
     if constexpr (!Staged) {
       __syncthreads();
-      adj_combine_slabs(a, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, 1, slot, tid,
+      adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, 1, slot, tid,
                         kFusedThreads);
     }
     turn ^= 1;
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
       if constexpr (Staged) {
         // the next plane's barrier orders this sum before its store to the slabs
         __syncthreads();
-        adj_combine_slabs(a, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), 0, adj_brick_cz(a, b), 0,
+        adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), 0, adj_brick_cz(a, b), 0,
                           tid, kFusedThreads);
       }
       if (more) b = adj_brick_geom(a, ++bz * nxy + bxy);
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(kTailThreads) __attribute__((amdgpu_waves_per_eu(8)
     if (threadIdx.x == 0) loss[0] = red[0];
     return;
   }
-  adj_gather_block<Small>(part, a, xcd_remap(blockIdx.x, nblk), threadIdx.x, [&](size_t i, const F3& gv) {
+  adj_gather_block<Small>(part, a, AdjMap{a}, xcd_remap(blockIdx.x, nblk), threadIdx.x, [&](size_t i, const F3& gv) {
     stf3(grad + i * 3, gv);
     if (descend) {  // the descent kernel's update, on the same values
       float* p = grid + i * 3;

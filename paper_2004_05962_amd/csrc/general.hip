@@ -20,11 +20,8 @@
 //
 // Adjoint: the per-axis tables i(x), B(u(x)) and the first voxel of every
 // tile are computed once per call into the workspace; then the aligned
-// adjoint's two passes, z-first, with the tables in place of equal tiles
-// (gen_zf_pass1_kernel: bricks of 64 x 16 voxels by whole z-tiles, the
-// z-contraction in registers, each finished control plane contracted over x
-// and y in LDS; gen_zf_pass2_kernel: the fixed-order sum of brick partials per
-// control point).  Deterministic, no atomics.
+// adjoint's two passes (adjoint_device.h) over cells of up to 32 x 8 voxel columns,
+// with the tables in place of equal tiles.  Deterministic, no atomics.
 #include <cmath>
 
 #include "adjoint_device.h"
@@ -45,10 +42,6 @@ __device__ __forceinline__ int gen_weights(const GenAxis& a, int v, float (&w)[4
   w[2] = fmaf(3.f * u, fmaf(-u, u, u) + 1.f, 1.f) * sixth;
   w[3] = u2 * u * sixth;
   return i;
-}
-
-__device__ __forceinline__ F3 ldf3_nt(const float* p) {
-  return F3{__builtin_nontemporal_load(p), __builtin_nontemporal_load(p + 1), __builtin_nontemporal_load(p + 2)};
 }
 
 constexpr int kGenMaxZ = 256;  // voxel planes per workgroup (z table in LDS)
@@ -168,9 +161,7 @@ struct GenTables3 {
 // Thread k of an axis's workgroups writes entry k of its tables: tile[k] =
 // i(k) and w[k] = B(u(k)) for k < n, and first[k] = min{v : i(v) >= k} for
 // k <= g (first[g] = n), found by bisection on the exact i(v), so the three
-// tables need no order between them.  The z weights are stored in pass 1's
-// accumulator order: entry s of voxel k is the weight of control plane c with
-// c mod 4 = s, i.e. B_{(s - i(k)) mod 4}.
+// tables need no order between them.
 __global__ __launch_bounds__(256) void gen_tables3_kernel(GenTables3 p) {
   int blk = blockIdx.x, i = 0;
   while (i < 2 && blk >= p.nb[i]) blk -= p.nb[i++];
@@ -178,11 +169,9 @@ __global__ __launch_bounds__(256) void gen_tables3_kernel(GenTables3 p) {
   const int k = blk * 256 + threadIdx.x;
   if (k < a.n) {
     float b[4];
-    const int tk = gen_weights(a, k, b);
-    p.tile[i][k] = tk;
-    const int rot = i == 2 ? tk & 3 : 0;
+    p.tile[i][k] = gen_weights(a, k, b);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) p.w[i][4 * k + s] = b[(s - rot) & 3];
+    for (int s = 0; s < 4; ++s) p.w[i][4 * k + s] = b[s];
   }
   if (k <= a.g) {
     int lo = 0, hi = a.n;  // i(v) is nondecreasing in v
@@ -196,268 +185,71 @@ __global__ __launch_bounds__(256) void gen_tables3_kernel(GenTables3 p) {
 }
 
 // ---------------------------------------------------------------------------
-// The adjoint, z-first (as the aligned pass 1 in adjoint_device.h), with the
-// per-axis tables instead of tiles of equal length.  A brick is 64 x-voxels
-// (one per lane) by 16 rows (8 waves of 2 rows) by the voxels of kz whole
-// z-tiles, [first_z[b kz], first_z[(b+1) kz]).  Per voxel plane a lane adds
-// its 2 voxels into the 4 control planes they meet, with the plane's z
-// weights (scalar loads of the z table); slot k of the accumulators holds
-// control plane c with c mod 4 = k.  When the plane's z-tile ends,
-// control plane t is finished and is contracted in LDS: over x, output
-// column c of a row sums the brick's voxels v in [first_x[c-3], first_x[c+1])
-// (ascending) with weight B_{c - i(v)}(u(v)); then, after a workgroup barrier,
-// over y the same way, giving the brick's partial of that plane.  Pass 2
-// sums, per control point, the partials of the bricks meeting its support in
-// fixed order.  No atomics.
-// XTiles: every brick meets at most 16 x-tiles (window width cmx <= 19), so
-// the x-contraction runs on tile lanes.
-// Waves per SIMD pass 1 is compiled for (a register bound of 512 / this).
-#ifndef BSI_GZ_WPE
-#define BSI_GZ_WPE 6
-#endif
-template <bool XTiles>
-__global__ __launch_bounds__(kGzThreads) __attribute__((amdgpu_waves_per_eu(BSI_GZ_WPE))) void gen_zf_pass1_kernel(const float* __restrict__ dfield,
-                                                                   float* __restrict__ part, GenGeom q, GenAdj a,
-                                                                   GzTables T) {
-  extern __shared__ float gz_smem[];
-  const int nbricks = a.nbx * a.nby * a.nbz;
-  const int brick = xcd_remap(blockIdx.x, gridDim.x);
-  if (brick >= nbricks) return;  // uniform over the workgroup
-  const GzLayout L = gz_layout(a);
-  float* F = gz_smem + L.F;
-  float* wxT = gz_smem + L.wx;
-  int* fxT = reinterpret_cast<int*>(gz_smem + L.fx);
-  float* wyT = gz_smem + L.wy;
-  int* fyT = reinterpret_cast<int*>(gz_smem + L.fy);
-  const GzBrick b = gz_brick(q, a, T, brick);
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid / kWave);
-  const int nxb = b.xe - b.x0, nyb = b.ye - b.y0;
-  // the brick's x and y tables; fxT[j] = first_x[cx0 + j - 3] (clamped at 0),
-  // so output column cx0 + j takes the voxels [fxT[j], fxT[j + 4])
-  if (tid < nxb) {
-#pragma unroll
-    for (int l = 0; l < 4; ++l) wxT[4 * tid + l] = T.w[0][4 * (b.x0 + tid) + l];
-  }
-  if (tid < nyb) {
-#pragma unroll
-    for (int l = 0; l < 4; ++l) wyT[4 * tid + l] = T.w[1][4 * (b.y0 + tid) + l];
-  }
-  if (tid < b.Cx + 4) fxT[tid] = T.first[0][max(b.cx0 + tid - 3, 0)];
-  if (tid < b.Cy + 4) fyT[tid] = T.first[1][max(b.cy0 + tid - 3, 0)];
-  __syncthreads();
+// The adjoint: the aligned pass 1 and pass 2 (adjoint_device.h) with the tables.
+// What bounds them is the same.  512 x 512 x 256, spacing 5.3 x 4.7 x 5.1: pass 1 164 us,
+// 195 as moments per tile lane with two barriers per control plane; pass 2 12.1
+// against 16; 64^3: both and the tables 19.5 us against 58; 120 x 100 x 80, spacing
+// 1.5 x 1.2 x 1.1: 54 against 207.
 
-  const size_t plane = (size_t)q.x.n * q.y.n * 3;
-  uint32_t off[kGzRows];
-#pragma unroll
-  for (int r = 0; r < kGzRows; ++r)
-    off[r] = ((uint32_t)min(b.y0 + wave * kGzRows + r, b.ye - 1) * (uint32_t)q.x.n +
-              (uint32_t)min(b.x0 + lane, b.xe - 1)) * 3u;
-  float* pbase = part + (size_t)brick * a.cmz * a.cmy * a.cmx * 3;
-  float* P = a.stage_all ? gz_smem + L.P : pbase;
-
-  F3 acc[4][kGzRows];
-#pragma unroll
-  for (int k = 0; k < 4; ++k)
-#pragma unroll
-    for (int r = 0; r < kGzRows; ++r) acc[k][r] = F3{0.f, 0.f, 0.f};
-
-  // the x- and y-contractions of brick-relative control plane czl, whose
-  // rows the waves have put in F, into the partials
-  auto contract = [&](int czl, bool last) {
-    float* H = gz_smem + L.H + (czl & 1) * kGzBY * a.cmx * 3;
-    // x.  Tile lanes when the brick meets at most 16 x-tiles (as in the aligned
-    // pass 1): lane (rr, t) of this wave forms the 4 moments of tile cx0 + t
-    // of its row rr, M_l = sum over the tile's voxels (ascending) of
-    // B_l(u(v)) F[v], and DPP row shifts combine them into the window
-    // columns, H[j] = sum_l M_l(tile j - l).  Otherwise one lane per (row,
-    // column), summing the column's voxels tile by tile.
-    if constexpr (XTiles) {
-      const int rr = lane / kAdjTiles, tt = lane % kAdjTiles;
-      const int row = wave * kGzRows + rr;
-      const bool rowok = rr < kGzRows && row < nyb;
-      F3 M[4];
-#pragma unroll
-      for (int l = 0; l < 4; ++l) M[l] = F3{0.f, 0.f, 0.f};
-      if (rowok && tt < b.Cx - 3) {
-        const int va = max(fxT[tt + 3], b.x0) - b.x0, vb = min(fxT[tt + 4], b.xe) - b.x0;
-        const float* Fr = F + row * kGzBX * 3;
-#pragma unroll 2
-        for (int v = va; v < vb; ++v) adj_moment_step(wxT + 4 * v, ldf3(Fr + 3 * v), M);
-      }
-      F3 cm, cw;
-      adj_combine(M, cm, cw);  // every lane of the wave takes part
-      if (rowok) {
-        float* hrow = H + row * a.cmx * 3;
-        if (tt < b.Cx) stf3(hrow + tt * 3, cm);
-        if (tt < 3 && kAdjTiles + tt < b.Cx) stf3(hrow + (kAdjTiles + tt) * 3, cw);
-      }
-    } else {
-      for (int it = lane; it < kGzRows * b.Cx; it += kWave) {
-        const int r = it / b.Cx, j = it - r * b.Cx;
-        const int row = wave * kGzRows + r;
-        if (row < nyb) {
-          float sx = 0.f, sy = 0.f, sz = 0.f;
-          const float* Fr = F + row * kGzBX * 3;
-          // tiles c-3 .. c (weight index l = 3 .. 0): the voxels in ascending order
-#pragma unroll
-          for (int l = 3; l >= 0; --l) {
-            const int va = max(fxT[j + 3 - l], b.x0) - b.x0, vb = min(fxT[j + 4 - l], b.xe) - b.x0;
-#pragma unroll 2
-            for (int v = va; v < vb; ++v) {
-              const float wgt = wxT[4 * v + l];
-              sx = fmaf(wgt, Fr[3 * v], sx);
-              sy = fmaf(wgt, Fr[3 * v + 1], sy);
-              sz = fmaf(wgt, Fr[3 * v + 2], sz);
-            }
-          }
-          stf3(H + (row * a.cmx + j) * 3, F3{sx, sy, sz});
-        }
-      }
-    }
-    __syncthreads();
-    // y, on y-tile lanes (a brick of 16 rows meets at most 16 y-tiles): lane
-    // (c4, ty) of wave w takes window column 4 w + c4 (then + 32 ...) and
-    // y-tile cy0 + ty, forms N_m = sum over the tile's rows (ascending) of
-    // B_m(v(y)) H[y][column], and the shifts give window rows ty and
-    // (ty < 3) 16 + ty.
-    {
-      const int c4 = lane / kAdjTiles, ty = lane % kAdjTiles;
-      const int nty = b.Cy - 3;
-      for (int c0 = wave * 4; c0 < b.Cx; c0 += kGzWaves * 4) {  // uniform over the wave
-        const int j = c0 + c4;
-        F3 N[4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) N[m] = F3{0.f, 0.f, 0.f};
-        if (j < b.Cx && ty < nty) {
-          const int ya = max(fyT[ty + 3], b.y0) - b.y0, yb = min(fyT[ty + 4], b.ye) - b.y0;
-#pragma unroll 2
-          for (int y = ya; y < yb; ++y) adj_moment_step(wyT + 4 * y, ldf3(H + (y * a.cmx + j) * 3), N);
-        }
-        F3 gm, gw;
-        adj_combine(N, gm, gw);  // every lane of the wave takes part
-        if (j < b.Cx) {
-          if (ty < b.Cy) stf3(P + ((size_t)(czl * a.cmy + ty) * a.cmx + j) * 3, gm);
-          if (ty < 3 && kAdjTiles + ty < b.Cy) stf3(P + ((size_t)(czl * a.cmy + kAdjTiles + ty) * a.cmx + j) * 3, gw);
-        }
-      }
-    }
-    if (a.stage_all && last) {
-      __syncthreads();
-      const int n = (czl + 1) * a.cmy * a.cmx * 3;
-      for (int i = tid; i < n; i += kGzThreads) pbase[i] = P[i];
-    }
+// The cell's weight matrices from the tables (as adj_cell_weights).
+__device__ __forceinline__ AdjWeights gen_cell_weights(const AdjCell& c, const int* __restrict__ tx,
+                                                       const float* __restrict__ wx, const int* __restrict__ ty,
+                                                       const float* __restrict__ wy, int lane) {
+  const int m = lane % kAdjTile, q = lane / kAdjTile;
+  // weight of the cell's voxel v (of n, the first at v0) at control index c0 + m
+  auto weight = [&](const int* tile, const float* w, int v0, int n, int v, int c0) {
+    const int u = v0 + min(v, n - 1), l = c0 + m - tile[u];
+    const float b = w[4 * u + (l & 3)];
+    return v < n && (uint32_t)l < 4u ? (b == 0.f ? -0.f : b) : 0.f;
   };
-
-// Slot K (a constant) goes to this wave's rows of F and is cleared.
-#define BSI_GZ_PUT_SLOT(K)                                                                    \
-  _Pragma("unroll") for (int r = 0; r < kGzRows; ++r) {                                       \
-    stf3(F + ((wave * kGzRows + r) * kGzBX + lane) * 3, acc[K][r]);                           \
-    acc[K][r] = F3{0.f, 0.f, 0.f};                                                            \
-  }
-// Control plane CZL (brick-relative), held in slot PH (uniform): its rows go
-// to F by a scalar branch to that slot's own code, then the x- and
-// y-contractions into the partials.
-#define BSI_GZ_EMIT(CZL, PH, LAST)                                                              \
-  {                                                                                           \
-    wave_lds_sync(); /* this wave's x-contraction of the previous plane is done with F */      \
-    switch (PH) {                                                                             \
-      case 0: BSI_GZ_PUT_SLOT(0) break;                                                       \
-      case 1: BSI_GZ_PUT_SLOT(1) break;                                                       \
-      case 2: BSI_GZ_PUT_SLOT(2) break;                                                       \
-      default: BSI_GZ_PUT_SLOT(3) break;                                                      \
-    }                                                                                         \
-    wave_lds_sync();                                                                          \
-    contract((CZL), (LAST));                                                                  \
-  }
-
-// One voxel plane Z from register set D: the z-accumulation (slot k holds
-// control plane c with c mod 4 = k, and the table holds the plane's weights
-// in that order: one scalar load), the loads of the plane two ahead into the
-// same registers (when LOAD), then, when Z is the last plane of tile t
-// (tend = first_z[t+1]), the contraction of control plane t, in slot t mod 4;
-// s >= 1, so the next tile is t + 1.
-#define BSI_GZ_PLANE(D, Z, LOAD)                                                              \
-  {                                                                                           \
-    const float* ws = T.w[2] + 4 * (Z);                                                       \
-    _Pragma("unroll") for (int k = 0; k < 4; ++k)                                             \
-      _Pragma("unroll") for (int r = 0; r < kGzRows; ++r) {                                   \
-        acc[k][r].x = fmaf(ws[k], D[r].x, acc[k][r].x);                                       \
-        acc[k][r].y = fmaf(ws[k], D[r].y, acc[k][r].y);                                       \
-        acc[k][r].z = fmaf(ws[k], D[r].z, acc[k][r].z);                                       \
-      }                                                                                       \
-    if (LOAD) {                                                                               \
-      _Pragma("unroll") for (int r = 0; r < kGzRows; ++r) D[r] = ldf3_nt(ahead + off[r]); \
-    }                                                                                         \
-    ahead += plane;                                                                           \
-    if ((Z) + 1 == tend && (Z) + 1 < b.ze) {                                                  \
-      BSI_GZ_EMIT(t - b.cz0, t & 3, false)                                                    \
-      ++t;                                                                                    \
-      tend = T.first[2][t + 1];                                                               \
-    }                                                                                         \
-  }
-
-  // two register sets, each holding one plane's loads (as the aligned pass 1):
-  // in the main loop every load is unconditional, so waiting for one set
-  // leaves the other set's loads in flight
-  const float* base0 = dfield + (size_t)b.z0 * plane;
-  F3 d0[kGzRows], d1[kGzRows];
+  AdjWeights r;
 #pragma unroll
-  for (int r = 0; r < kGzRows; ++r) d0[r] = ldf3_nt(base0 + off[r]);
+  for (int g = 0; g < 2; ++g) {
 #pragma unroll
-  for (int r = 0; r < kGzRows; ++r) d1[r] = ldf3_nt(base0 + (b.ze - b.z0 > 1 ? plane : 0) + off[r]);
-  const float* ahead = base0 + 2 * plane;
-  int t = b.cz0;                    // the z-tile of the plane at hand (the brick starts on a tile)
-  int tend = T.first[2][t + 1];     // its end
-  int z = b.z0;
-  for (; z + 4 <= b.ze; z += 2) {
-    BSI_GZ_PLANE(d0, z, true)
-    BSI_GZ_PLANE(d1, z + 1, true)
+    for (int i = 0; i < 4; ++i) r.x[g][i] = weight(tx, wx, c.x0, c.nx, kAdjTile * g + 4 * q + i, c.cx0);
+    r.y[g] = weight(ty, wy, c.y0, c.ny, adj_step_row(g, q), c.cy0);
   }
-  for (; z < b.ze; z += 2) {
-    BSI_GZ_PLANE(d0, z, z + 2 < b.ze)
-    if (z + 1 < b.ze) BSI_GZ_PLANE(d1, z + 1, z + 3 < b.ze)
-  }
-#undef BSI_GZ_PLANE
-  // the brick's last four control planes, t .. t + 3, in ascending order
-#pragma unroll 1
-  for (int n = 0; n < 4; ++n) BSI_GZ_EMIT(t - b.cz0 + n, (t + n) & 3, n == 3)
-#undef BSI_GZ_EMIT
-#undef BSI_GZ_PUT_SLOT
+  return r;
 }
 
-// Pass 2: one thread per control point; a wave takes 64 points of one (cy, cz) row.
-__global__ __launch_bounds__(256) void gen_zf_pass2_kernel(const float* __restrict__ part, float* __restrict__ grad,
-                                                           GenGeom q, GenAdj a, GzTables T) {
-  const int nxb = (q.x.g + kWave - 1) / kWave, nyb = (q.y.g + 3) / 4;
-  int blk = blockIdx.x;
-  const int xb = blk % nxb;
-  blk /= nxb;
-  const int cy = (blk % nyb) * 4 + uniform(threadIdx.x / kWave);
-  const int cz = blk / nyb;
-  const int cx = xb * kWave + (threadIdx.x & (kWave - 1));
-  if (cy >= q.y.g || cx >= q.x.g) return;
-  // bricks meeting the support [first(c-3), first(c+1)) of each axis
-  const GzSpan spx = gz_span(T.first[0], cx, kGzBX), spy = gz_span(T.first[1], cy, kGzBY),
-               spz = gz_span_z(a, cz, q.z.g);
-  const int xa = spx.lo, xb2 = spx.hi, ya = spy.lo, yb2 = spy.hi, za = spz.lo, zb2 = spz.hi;
-  const size_t stride = (size_t)a.cmz * a.cmy * a.cmx * 3;
-  float sx = 0.f, sy = 0.f, sz = 0.f;
-  for (int bz = za; bz <= zb2; ++bz)
-    for (int by = ya; by <= yb2; ++by) {
-      const int cyl = cy - T.tile[1][by * kGzBY];
-      for (int bx = xa; bx <= xb2; ++bx) {
-        const int cxl = cx - T.tile[0][bx * kGzBX];
-        const size_t id = ((size_t)bz * a.nby + by) * a.nbx + bx;
-        const float* p = part + id * stride + ((size_t)((cz - bz * a.kz) * a.cmy + cyl) * a.cmx + cxl) * 3;
-        sx += p[0];
-        sy += p[1];
-        sz += p[2];
-      }
-    }
-  float* g = grad + (((size_t)cz * q.y.g + cy) * q.x.g + cx) * 3;
-  g[0] = sx;
-  g[1] = sy;
-  g[2] = sz;
+// A wave's march along z: the plane's weights, and the end of its tile; the next
+// tile's end is loaded a tile ahead.
+struct GenZ {
+  const float* w;
+  const int* first;
+  int z, t, end, next, last;
+  __device__ __forceinline__ GenZ(const float* w_, const int* first_, int z0, int t0, int last_)
+      : w(w_), first(first_), z(z0), t(t0), end(first_[t0 + 1]), next(first_[min(t0 + 2, last_)]), last(last_) {}
+  __device__ __forceinline__ const float* weights() const { return w + 4 * z; }
+  __device__ __forceinline__ bool step() {
+    if (++z != end) return false;
+    ++t;
+    end = next;
+    next = first[min(t + 2, last)];
+    return true;
+  }
+};
+
+template <bool Staged>
+__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI_ADJ_WPE))) void gen_pass1_kernel(
+    const float* __restrict__ dfield, float* __restrict__ part, AdjGeom a, const int* __restrict__ tx,
+    const int* __restrict__ ty, const int* __restrict__ fz, const float* __restrict__ wx, const float* __restrict__ wy,
+    const float* __restrict__ wz) {
+  extern __shared__ float gen_slabs[];
+  const int brick = xcd_remap(blockIdx.x, gridDim.x);
+  const GenTiles tiles{tx, ty};
+  const AdjBrick b = gen_brick(a, tiles, fz, brick);
+  adj_brick_of<true, Staged>(dfield, part, a, tiles, b, brick, gen_brick_cz(a, b), GenZ(wz, fz, b.z0, b.cz0, a.g.gz),
+                             [&](const AdjCell& c) { return gen_cell_weights(c, tx, wx, ty, wy, threadIdx.x % kWave); },
+                             gen_slabs, threadIdx.x);
+}
+
+template <bool Small>
+__global__ __launch_bounds__(kGatherThreads) __attribute__((amdgpu_waves_per_eu(8))) void gen_pass2_kernel(
+    const float* __restrict__ part, float* __restrict__ grad, AdjGeom a, const int* __restrict__ tx,
+    const int* __restrict__ ty, const int* __restrict__ fx, const int* __restrict__ fy) {
+  adj_gather_block<Small>(part, a, GenMap{a, tx, ty, fx, fy}, xcd_remap(blockIdx.x, gridDim.x), threadIdx.x,
+                          [&](size_t i, const F3& v) { stf3(grad + i * 3, v); });
 }
 
 constexpr size_t align256(size_t b) { return (b + 255) / 256 * 256; }
@@ -469,7 +261,7 @@ struct GenWork {
   float* part;    // brick partials of the z-first adjoint
 };
 
-size_t gen_layout(const GenGeom& q, void* base, GenWork* wk) {
+size_t gen_layout(const GenGeom& q, const AdjGeom& a, void* base, GenWork* wk) {
   char* p = static_cast<char*>(base);
   size_t off = 0;
   const GenAxis* ax[3] = {&q.x, &q.y, &q.z};
@@ -483,9 +275,8 @@ size_t gen_layout(const GenGeom& q, void* base, GenWork* wk) {
     if (wk) wk->first[i] = reinterpret_cast<int*>(p + off);
     off += align256((size_t)(ax[i]->g + 1) * sizeof(int));
   }
-  const GenAdj a = make_gen_adj(q);
   if (wk) wk->part = reinterpret_cast<float*>(p + off);
-  off += align256((size_t)a.nbx * a.nby * a.nbz * a.cmz * a.cmy * a.cmx * 3 * sizeof(float));
+  off += align256(adj_workspace_bytes(a));
   return off;
 }
 
@@ -558,12 +349,17 @@ hipError_t launch_forward_general(const float* grid, float* field, const VolGeom
   return hipGetLastError();
 }
 
-size_t general_workspace_bytes(const GenGeom& q) { return gen_layout(q, nullptr, nullptr); }
+size_t general_workspace_bytes(const GenGeom& q, const VolGeom& g) {
+  return gen_layout(q, make_gen_adj(q, g), nullptr, nullptr);
+}
 
-hipError_t launch_adjoint_general(const float* dfield, float* grad, const GenGeom& q, void* workspace,
+hipError_t launch_adjoint_general(const float* dfield, float* grad, const GenGeom& q, const VolGeom& g, void* workspace,
                                   hipStream_t s) {
+  const AdjGeom a = make_gen_adj(q, g);
+  const int64_t nbricks = (int64_t)a.x.nb * a.y.nb * a.z.nb, nblk = adj_gather_blocks(a);
+  if (nbricks > 0x7fffffffL || nblk > 0x7fffffffL) return hipErrorInvalidValue;
   GenWork wk;
-  gen_layout(q, workspace, &wk);
+  gen_layout(q, a, workspace, &wk);
   GenTables3 tp;
   const GenAxis* ax[3] = {&q.x, &q.y, &q.z};
   for (int i = 0; i < 3; ++i) {
@@ -575,27 +371,13 @@ hipError_t launch_adjoint_general(const float* dfield, float* grad, const GenGeo
   }
   hipLaunchKernelGGL(gen_tables3_kernel, dim3((unsigned)(tp.nb[0] + tp.nb[1] + tp.nb[2])), dim3(256), 0, s, tp);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  const GenAdj a = make_gen_adj(q);
-  GzTables T;
-  for (int i = 0; i < 3; ++i) {
-    T.tile[i] = wk.tile[i];
-    T.w[i] = wk.w[i];
-    T.first[i] = wk.first[i];
-  }
-  const long nbricks = (long)a.nbx * a.nby * a.nbz;
-  const int nxb = (q.x.g + kWave - 1) / kWave, nyb = (q.y.g + 3) / 4;
-  const long nblk = (long)nxb * nyb * q.z.g;
-  if (nbricks > 0x7fffffffL || nblk > 0x7fffffffL) return hipErrorInvalidValue;
-  const size_t lds = (size_t)gz_layout(a).total * sizeof(float);
-  if (a.cmx - 3 <= kAdjTiles)
-    hipLaunchKernelGGL(gen_zf_pass1_kernel<true>, dim3((unsigned)nbricks), dim3(kGzThreads), lds, s, dfield, wk.part, q,
-                       a, T);
-  else
-    hipLaunchKernelGGL(gen_zf_pass1_kernel<false>, dim3((unsigned)nbricks), dim3(kGzThreads), lds, s, dfield, wk.part,
-                       q, a, T);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(gen_zf_pass2_kernel, dim3((unsigned)nblk), dim3(256), 0, s, wk.part, grad, q, a, T);
+  const auto pass1 = adj_staged(a) ? &gen_pass1_kernel<true> : &gen_pass1_kernel<false>;
+  hipLaunchKernelGGL(pass1, dim3((unsigned)nbricks), dim3(kAdjThreads), adj_lds_bytes(a), s, dfield, wk.part, a,
+                     wk.tile[0], wk.tile[1], wk.first[2], wk.w[0], wk.w[1], wk.w[2]);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  const auto pass2 = a.part_bytes != 0 ? &gen_pass2_kernel<true> : &gen_pass2_kernel<false>;
+  hipLaunchKernelGGL(pass2, dim3((unsigned)nblk), dim3(kGatherThreads), 0, s, wk.part, grad, a, wk.tile[0], wk.tile[1],
+                     wk.first[0], wk.first[1]);
   return hipGetLastError();
 }
 

@@ -1,9 +1,11 @@
 // Real-spacing grid: the exact window-start decision shared by host and
-// device, and the geometry of the z-first adjoint's bricks (used by the
-// kernels in general.hip and by the host index checker).
+// device, and the geometry of the adjoint's bricks (used by the kernels in
+// general.hip and by the host index checker).
 #pragma once
 
-#include "bsi_device.h"
+#include <cmath>
+
+#include "adjoint_device.h"
 #include "bsi_internal.h"
 
 namespace bsi {
@@ -66,181 +68,108 @@ __host__ __device__ inline int gen_tile(const GenAxis& a, int v) {
 }
 
 
-constexpr int kAdjTiles = 16;  // tile lanes per row of lanes (DPP rows)
-
-// Value of lane i - N of this lane's row of 16 lanes, 0 for i < N (DPP
-// row_shr); row_shl: lane i + N, 0 for i + N >= 16.  Lanes past the row's
-// edge read the zero `old` operand.
-template <int N>
-__device__ __forceinline__ float row_shr(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x110 + N, 0xF, 0xF, true));
-}
-template <int N>
-__device__ __forceinline__ float row_shl(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x100 + N, 0xF, 0xF, true));
-}
-
-// Window column of tile lanes: lane t of a row of 16 holds the moments M_l of
-// tile t; this forms
-//   cm = S[t]      = sum_{l <= t} M_l(tile t - l)
-//   cw = S[16 + t] = sum_{l > t}  M_l(tile 16 + t - l)   (t < 3)
-// l ascending.  The shifts bring in zero for the terms a lane does not take
-// (row_shr by l for l > t, row_shl by 16 - l for l <= t), and adding zero is
-// exact, so no per-lane selects are needed.  Idle lanes hold M = 0, so columns
-// past the last tile come out right.  Every lane of the wave takes part (no
-// lane may be inactive).
-__device__ __forceinline__ void adj_combine(const F3 (&M)[4], F3& cm, F3& cw) {
-  cm = M[0];
-  cm.x += row_shr<1>(M[1].x);
-  cm.y += row_shr<1>(M[1].y);
-  cm.z += row_shr<1>(M[1].z);
-  cm.x += row_shr<2>(M[2].x);
-  cm.y += row_shr<2>(M[2].y);
-  cm.z += row_shr<2>(M[2].z);
-  cm.x += row_shr<3>(M[3].x);
-  cm.y += row_shr<3>(M[3].y);
-  cm.z += row_shr<3>(M[3].z);
-  cw.x = row_shl<15>(M[1].x);
-  cw.y = row_shl<15>(M[1].y);
-  cw.z = row_shl<15>(M[1].z);
-  cw.x += row_shl<14>(M[2].x);
-  cw.y += row_shl<14>(M[2].y);
-  cw.z += row_shl<14>(M[2].z);
-  cw.x += row_shl<13>(M[3].x);
-  cw.y += row_shl<13>(M[3].y);
-  cw.z += row_shl<13>(M[3].z);
-  // cm is formed here, not sunk into the callers' conditional stores (which
-  // keeps all nine shifted values live at once and spills)
-  asm volatile("" : "+v"(cm.x), "+v"(cm.y), "+v"(cm.z));
-}
-
-// Moments += w_l * v for l = 0..3.
-__device__ __forceinline__ void adj_moment_step(const float* __restrict__ w, const F3& v, F3 (&M)[4]) {
-#pragma unroll
-  for (int l = 0; l < 4; ++l) {
-    M[l].x = fmaf(w[l], v.x, M[l].x);
-    M[l].y = fmaf(w[l], v.y, M[l].y);
-    M[l].z = fmaf(w[l], v.z, M[l].z);
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Bricks of the z-first adjoint (general.hip): 64 x-voxels by 16 rows by the
-// voxels of kz whole z-tiles.
-constexpr int kGzBX = kWave;             // brick width (voxels)
-constexpr int kGzRows = 2;               // rows per lane
-constexpr int kGzWaves = 8;
-constexpr int kGzBY = kGzRows * kGzWaves;  // brick height (rows)
-constexpr int kGzThreads = kGzWaves * kWave;
-constexpr int kGzTargetZ = 48;           // about this many voxel planes per brick
-constexpr int kGzStage = 6144;           // floats of staged partials (24 KB)
-
-struct GenAdj {
-  int nbx, nby, nbz;  // bricks per axis
-  int kz;             // z-tiles per brick
-  int cmx, cmy, cmz;  // window extents (the largest over the bricks)
-  int stage_all;      // the whole window of partials fits the LDS stage
+// The adjoint over the aligned adjoint's cells and bricks (adjoint_device.h), with
+// per-axis tables in place of equal tiles.
+// i(v) of every voxel (tile), B_0 .. B_3 at u(v) (w), and min{v : i(v) >= k} (first).
+struct GenTiles {
+  const int *tx, *ty;
+  __host__ __device__ int x(int v) const { return tx[v]; }
+  __host__ __device__ int y(int v) const { return ty[v]; }
 };
 
-// LDS of one workgroup (floats): F, H[2], the brick's x and y weight rows and
-// first-voxel tables, the stage.
-struct GzLayout {
-  int F, H, wx, fx, wy, fy, P, total;
-};
-__host__ __device__ inline GzLayout gz_layout(const GenAdj& a) {
-  GzLayout L;
-  int o = 0;
-  L.F = o;
-  o += kGzBY * kGzBX * 3;
-  L.H = o;
-  o += 2 * kGzBY * a.cmx * 3;
-  L.wx = o;
-  o += kGzBX * 4;
-  L.fx = o;
-  o += a.cmx + 4;
-  L.wy = o;
-  o += kGzBY * 4;
-  L.fy = o;
-  o += a.cmy + 4;
-  L.P = o;
-  o += a.stage_all ? a.cmz * a.cmy * a.cmx * 3 : 0;
-  L.total = o;
-  return L;
-}
-
-struct GzTables {
-  const int* tile[3];
-  const float* w[3];
-  const int* first[3];
-};
-
-// Brick (bx, by, bz): its voxel range and the first control index of its window per axis.
-struct GzBrick {
-  int x0, xe, y0, ye, z0, ze;
-  int cx0, cy0, cz0;
-  int Cx, Cy;
-};
-
-__host__ __device__ inline GzBrick gz_brick(const GenGeom& q, const GenAdj& a, const GzTables& T, int id) {
-  GzBrick b;
-  const int bx = id % a.nbx;
-  const int r = id / a.nbx;
-  const int by = r % a.nby;
-  const int bz = r / a.nby;
-  b.x0 = bx * kGzBX;
-  b.xe = min(q.x.n, b.x0 + kGzBX);
-  b.y0 = by * kGzBY;
-  b.ye = min(q.y.n, b.y0 + kGzBY);
-  b.cz0 = bz * a.kz;
-  b.z0 = T.first[2][b.cz0];
-  b.ze = T.first[2][min(b.cz0 + a.kz, q.z.g - 3)];
-  b.cx0 = T.tile[0][b.x0];
-  b.Cx = T.tile[0][b.xe - 1] - b.cx0 + 4;
-  b.cy0 = T.tile[1][b.y0];
-  b.Cy = T.tile[1][b.ye - 1] - b.cy0 + 4;
+// Brick id: whole z-tiles [bz k, (bz + 1) k) of the g - 3 that hold voxels.
+__host__ __device__ inline AdjBrick gen_brick(const AdjGeom& a, const GenTiles& t, const int* first_z, int id) {
+  const VolGeom& g = a.g;
+  AdjBrick b;
+  const int bx = id % a.x.nb, r = id / a.x.nb, by = r % a.y.nb, bz = r / a.y.nb;
+  b.x0 = adj_brick_begin(a.x, g.nx, bx);
+  b.xe = adj_brick_begin(a.x, g.nx, bx + 1);
+  b.y0 = adj_brick_begin(a.y, g.ny, by);
+  b.ye = adj_brick_begin(a.y, g.ny, by + 1);
+  b.cz0 = bz * a.z.k;
+  b.z0 = first_z[b.cz0];
+  b.ze = first_z[imin(b.cz0 + a.z.k, g.gz - 3)];
+  b.cx0 = t.x(b.x0);
+  b.cy0 = t.y(b.y0);
+  b.Cx = t.x(b.xe - 1) - b.cx0 + 4;
+  b.Cy = t.y(b.ye - 1) - b.cy0 + 4;
   return b;
 }
+// Its control planes: every tile holds a voxel (s >= 1).
+__host__ __device__ inline int gen_brick_cz(const AdjGeom& a, const AdjBrick& b) {
+  return imin(a.z.k, a.g.gz - 3 - b.cz0) + 3;
+}
 
+// Largest control window of w consecutive voxels: their starts span at most
+// ceil((w - 1) / s) tiles (exact in FP64: s has 24 bits).
+inline int gen_window(const GenAxis& x, int w) { return imin((int)std::ceil((w - 1) / (double)x.s) + 4, x.g); }
 
-// Bricks of the z-first adjoint: about kGzTargetZ planes of whole z-tiles,
-// fewer (at least half as many) when that lets a brick's window of partials
-// fit the LDS stage.  A pure function of the geometry.
-inline GenAdj make_gen_adj(const GenGeom& q) {
-  GenAdj a;
-  a.nbx = (q.x.n + kGzBX - 1) / kGzBX;
-  a.nby = (q.y.n + kGzBY - 1) / kGzBY;
-  a.cmx = a.cmy = 0;
-  for (int bx = 0; bx < a.nbx; ++bx) {
-    const int x0 = bx * kGzBX, xe = imin(q.x.n, x0 + kGzBX);
-    a.cmx = imax(a.cmx, gen_tile(q.x, xe - 1) - gen_tile(q.x, x0) + 4);
+// Cells of up to 32 voxels in x, as many as a window of 16 control points takes (s
+// >= 2.59: 32), evenly wide where narrower.  A pure function of the geometry.
+inline AdjGeom make_gen_adj(const GenGeom& q, const VolGeom& vol) {
+  AdjGeom a;
+  a.g = vol;
+  a.g.dx = (int)std::ceil(q.x.s);  // bounds, for adj_gather_lx; the z axis counts tiles
+  a.g.dy = (int)std::ceil(q.y.s);
+  a.g.dz = 1;
+  a.cell = imin(kAdjCellX, (int)(12. * q.x.s) + 1);
+  if (a.cell < kAdjCellX) {
+    const int nb = (q.x.n + kAdjCellsX * a.cell - 1) / (kAdjCellsX * a.cell);
+    a.cell = (q.x.n + nb * kAdjCellsX - 1) / (nb * kAdjCellsX);
   }
-  for (int by = 0; by < a.nby; ++by) {
-    const int y0 = by * kGzBY, ye = imin(q.y.n, y0 + kGzBY);
-    a.cmy = imax(a.cmy, gen_tile(q.y, ye - 1) - gen_tile(q.y, y0) + 4);
-  }
+  a.cw = (gen_window(q.x, imin(a.cell, q.x.n)) + 3) / 4 * 4;
+  a.ch = gen_window(q.y, imin(kAdjCellY, q.y.n));
+  auto axis = [](int units, int u, int k, int cm) {
+    AdjAxis x;
+    x.u = u;
+    x.U = units;
+    x.k = imin(k, units);
+    x.nb = (units + x.k - 1) / x.k;
+    x.w = x.k * u;
+    x.md = 0;
+    x.mw = (int64_t)units * u * x.w < ((int64_t)1 << 32) ? adj_magic(x.w) : 0;
+    x.cm = cm;
+    return x;
+  };
+  a.x = axis(q.x.n, 1, kAdjCellsX * a.cell, gen_window(q.x, imin(kAdjCellsX * a.cell, q.x.n)));
+  a.y = axis(q.y.n, 1, kAdjCellsY * kAdjCellY, gen_window(q.y, imin(kAdjCellsY * kAdjCellY, q.y.n)));
   const int tiles = q.z.g - 3;  // z-tiles holding voxels
-  int kz = imax(1, (int)(kGzTargetZ / q.z.s));
-  kz = imin(kz, tiles);
-  const int kfit = kGzStage / (a.cmy * a.cmx * 3) - 3;
-  if (kfit < kz && 2 * kfit >= kz) kz = kfit;
-  a.kz = kz;
-  a.nbz = (tiles + kz - 1) / kz;
-  a.cmz = kz + 3;
-  a.stage_all = (long)a.cmz * a.cmy * a.cmx * 3 <= kGzStage;
+  const AdjDepth depth = adj_depth(a, tiles, q.z.s);
+  auto set_depth = [&](int k) {
+    a.z = axis(tiles, 1, k, imin(k, tiles) + 3);  // in tiles
+    a.slots = a.z.cm <= depth.fit + 3 ? a.z.cm : 2;
+  };
+  set_depth(depth.best);
+  if (a.z.k < depth.most && adj_workspace_bytes(a) > kAdjShallowBytes) set_depth(depth.most);
+  a.part_bytes = adj_workspace_bytes(a) <= kAdjGatherSmall ? (uint32_t)adj_workspace_bytes(a) : 0;
+  a.lx = adj_gather_lx(a);
   return a;
 }
 
-// Bricks whose voxels meet the support [first(c - 3), first(c + 1)) of
-// control index c along one axis, for bricks of `width` voxels (x, y).
-struct GzSpan {
-  int lo, hi;
+// Pass 2: the bricks whose voxels meet the support [first(c - 3), first(c + 1)) of
+// control index c, along z those of tiles c - 3 .. c that hold voxels.
+struct GenMap {
+  const AdjGeom& a;
+  const int *tx, *ty, *fx, *fy;
+  __host__ __device__ AdjSpan span(const AdjAxis& x, const int* first, int c) const {
+    return AdjSpan{adj_brick_of_voxel(x, first[c >= 3 ? c - 3 : 0]), adj_brick_of_voxel(x, first[c + 1] - 1)};
+  }
+  __host__ __device__ AdjSpan span_x(int c) const { return span(a.x, fx, c); }
+  __host__ __device__ AdjSpan span_y(int c) const { return span(a.y, fy, c); }
+  __host__ __device__ AdjSpan span_z(int c) const {
+    return AdjSpan{adj_brick_of_voxel(a.z, imax(0, c - 3)), adj_brick_of_voxel(a.z, imin(c, a.g.gz - 4))};
+  }
+  // (a brick past the axis, whose term is not used, reads the last voxel's tile)
+  __host__ __device__ size_t part_x(int b, int c) const {
+    return b * adj_brick_stride(a) + (c - tx[imin(b * a.x.w, a.g.nx - 1)]) * 3;
+  }
+  __host__ __device__ size_t part_y(int b, int c) const {
+    return b * (a.x.nb * adj_brick_stride(a)) + (c - ty[imin(b * a.y.w, a.g.ny - 1)]) * a.x.cm * 3;
+  }
+  __host__ __device__ size_t part_z(int b, int c) const {
+    return b * ((size_t)a.y.nb * a.x.nb * adj_brick_stride(a)) + (c - b * a.z.k) * (a.y.cm * a.x.cm * 3);
+  }
 };
-__host__ __device__ inline GzSpan gz_span(const int* first, int c, int width) {
-  return GzSpan{first[c >= 3 ? c - 3 : 0] / width, (first[c + 1] - 1) / width};
-}
-// Along z: bricks of kz tiles; tiles c - 3 .. c that hold voxels (g - 3 of them).
-__host__ __device__ inline GzSpan gz_span_z(const GenAdj& a, int c, int gz) {
-  return GzSpan{(c >= 3 ? c - 3 : 0) / a.kz, (c < gz - 4 ? c : gz - 4) / a.kz};
-}
 
 }  // namespace bsi

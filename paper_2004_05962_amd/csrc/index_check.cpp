@@ -33,19 +33,19 @@ struct Check {
     if (!(c)) return ck.fail(std::string(what) + " [" #c "]");                   \
   } while (0)
 
-// Loads and LDS indices of pass 1 (adj_brick) for one brick.
-bool check_adj_brick(const AdjGeom& a, const AdjBrick& b, Check& ck) {
+// Loads and LDS indices of pass 1 (adj_brick_of) for one brick of cz control planes.
+template <class Tiles>
+bool check_brick(const AdjGeom& a, const Tiles& tiles, const AdjBrick& b, int cz, Check& ck) {
   const VolGeom& g = a.g;
   const size_t plane = (size_t)g.nx * g.ny * 12;
   const size_t lds = adj_lds_bytes(a) / sizeof(float);
-  const int cz = adj_brick_cz(a, b);
-  REQUIRE(b.z0 == b.cz0 * g.dz, "z-bricks start on tile boundaries (the march starts at offset 0)");
+  REQUIRE(cz <= a.z.cm && b.Cx <= a.x.cm && b.Cy <= a.y.cm, "window within the partials' extents");
   REQUIRE(b.ye - b.y0 <= kAdjCellsY * kAdjCellY && b.xe - b.x0 <= kAdjCellsX * a.cell, "brick within its cells");
   REQUIRE(a.slots >= 2 && (!adj_staged(a) || cz <= a.slots), "slots for the brick's planes");
   REQUIRE(adj_lds_bytes(a) <= 80000, "LDS request of two workgroups per CU");
   std::vector<int> voxels((size_t)(b.xe - b.x0) * (b.ye - b.y0), 0), points((size_t)b.Cx * b.Cy, 0);
   for (int w = 0; w < kAdjWaves; ++w) {
-    const AdjCell c = adj_cell_geom(a, b, w);
+    const AdjCell c = adj_cell_of(a, tiles, b, w);
     const bool any = c.nx > 0 && c.ny > 0;
     if (adj_staged(a) && !any) continue;  // the wave only meets the barrier
     REQUIRE(c.Cx <= kAdjTile && c.Cx <= a.cw && c.Cy <= kAdjTile && c.Cy <= a.ch,
@@ -89,6 +89,37 @@ bool check_adj_brick(const AdjGeom& a, const AdjBrick& b, Check& ck) {
   for (int t = 0; t < 2; ++t)
     for (int k = 0; k < 4; ++k) rows |= 1 << adj_step_row(t, k);
   REQUIRE(rows == (1 << kAdjCellY) - 1, "product steps cover the cell's rows");
+  return true;
+}
+
+bool check_adj_brick(const AdjGeom& a, const AdjBrick& b, Check& ck) {
+  REQUIRE(b.z0 == b.cz0 * a.g.dz, "z-bricks start on tile boundaries (the march starts at offset 0)");
+  return check_brick(a, AdjTiles{a}, b, adj_brick_cz(a, b), ck);
+}
+
+// Pass 2's offsets in 32 bits with up to three bricks past their spans, and its
+// workgroups: every control point taken exactly once.
+bool check_gather(const AdjGeom& a, Check& ck) {
+  const VolGeom& g = a.g;
+  const size_t ws = adj_workspace_bytes(a) / sizeof(float);
+  static_assert(4 * (uint64_t)kAdjGatherSmall <= (uint64_t)1 << 32);
+  REQUIRE(a.part_bytes == (ws * 4 <= kAdjGatherSmall ? ws * 4 : 0), "pass-2 buffer over the partials");
+  REQUIRE(a.lx >= 0 || (a.part_bytes != 0 && (int64_t)g.gx * g.gy * g.gz <= 1 << 20), "points of the wave-per-point form");
+  {
+    std::vector<unsigned char> hit((size_t)g.gx * g.gy * g.gz, 0);
+    const int64_t nblk = adj_gather_blocks(a);
+    REQUIRE(nblk < ((int64_t)1 << 31), "pass-2 grid above 2^31 workgroups");
+    for (int64_t blk = 0; blk < nblk; ++blk)
+      for (int t = 0; t < kGatherThreads; t += a.lx < 0 ? kWave : 1) {
+        int cx, cy, cz;
+        if (!adj_gather_index(a, (int)blk, t, cx, cy, cz)) continue;
+        REQUIRE(0 <= cx && cx < g.gx && 0 <= cy && cy < g.gy && 0 <= cz && cz < g.gz, "pass-2 point off the grid");
+        unsigned char& h = hit[((size_t)cz * g.gy + cy) * g.gx + cx];
+        REQUIRE(h == 0, "pass-2 point taken twice");
+        h = 1;
+      }
+    for (unsigned char h : hit) REQUIRE(h == 1, "pass-2 point never taken");
+  }
   return true;
 }
 
@@ -140,26 +171,7 @@ bool check_adjoint(const AdjGeom& a, BrickCheck brick_check, Check& ck) {
         REQUIRE(meets == (b >= sp.lo && b <= sp.hi), "pass-2 span differs from the bricks meeting the support");
       }
     }
-  // pass 2's offsets: 32 bits with up to three bricks past their spans
-  static_assert(4 * (uint64_t)kAdjGatherSmall <= (uint64_t)1 << 32);
-  REQUIRE(a.part_bytes == (ws * 4 <= kAdjGatherSmall ? ws * 4 : 0), "pass-2 buffer over the partials");
-  REQUIRE(a.lx >= 0 || (a.part_bytes != 0 && (int64_t)g.gx * g.gy * g.gz <= 1 << 20), "points of the wave-per-point form");
-  // pass 2's workgroups take every control point exactly once
-  {
-    std::vector<unsigned char> hit((size_t)g.gx * g.gy * g.gz, 0);
-    const int64_t nblk = adj_gather_blocks(a);
-    REQUIRE(nblk < ((int64_t)1 << 31), "pass-2 grid above 2^31 workgroups");
-    for (int64_t blk = 0; blk < nblk; ++blk)
-      for (int t = 0; t < kGatherThreads; t += a.lx < 0 ? kWave : 1) {
-        int cx, cy, cz;
-        if (!adj_gather_index(a, (int)blk, t, cx, cy, cz)) continue;
-        REQUIRE(0 <= cx && cx < g.gx && 0 <= cy && cy < g.gy && 0 <= cz && cz < g.gz, "pass-2 point off the grid");
-        unsigned char& h = hit[((size_t)cz * g.gy + cy) * g.gx + cx];
-        REQUIRE(h == 0, "pass-2 point taken twice");
-        h = 1;
-      }
-    for (unsigned char h : hit) REQUIRE(h == 1, "pass-2 point never taken");
-  }
+  if (!check_gather(a, ck)) return false;
   // pass 2: every brick a control point reads holds that point in its window
   for (int cz = 0; cz < g.gz; ++cz)
     for (int cy = 0; cy < g.gy; ++cy)
@@ -275,10 +287,10 @@ bool check_forward(const VolGeom& g, Check& ck) {
          check_forward_span<3>(g, ck) && check_forward_span<1>(g, ck) && check_forward_batched(g, ck);
 }
 
-// The z-first adjoint of the real-spacing grid (general.hip): its bricks,
-// LDS request, table reads, partial offsets and pass-2 spans, with host
-// tables built by the same exact window-start function the device uses.
-bool check_general_adjoint(const GenGeom& q, Check& ck) {
+// The adjoint of the real-spacing grid (general.hip): its bricks, cells, LDS
+// request, partial offsets and pass-2 spans, with host tables built by the
+// same exact window-start function the device uses.
+bool check_general_adjoint(const GenGeom& q, const VolGeom& vol, Check& ck) {
   const GenAxis* ax[3] = {&q.x, &q.y, &q.z};
   std::vector<int> tile[3], first[3];
   for (int i = 0; i < 3; ++i) {
@@ -301,12 +313,6 @@ bool check_general_adjoint(const GenGeom& q, Check& ck) {
       first[i][(size_t)t] = lo;
     }
   }
-  GzTables T;
-  for (int i = 0; i < 3; ++i) {
-    T.tile[i] = tile[i].data();
-    T.w[i] = nullptr;
-    T.first[i] = first[i].data();
-  }
   // the forward's window of 64 voxels x 4 rows within its staging capacity
   {
     using T1 = FwdTile<kFwdRows, 1, 1>;
@@ -321,55 +327,54 @@ bool check_general_adjoint(const GenGeom& q, Check& ck) {
       REQUIRE(n <= (three ? T3::max_cy : T1::max_cy), "forward window rows");
     }
   }
-  const GenAdj a = make_gen_adj(q);
-  const GzLayout L = gz_layout(a);
-  REQUIRE((size_t)L.total * sizeof(float) <= 65536, "pass-1 LDS request within 64 KB");
-  REQUIRE(a.kz >= 1 && a.nbz * a.kz >= q.z.g - 3 && (a.nbz - 1) * a.kz < q.z.g - 3, "z-bricks cover the z-tiles");
-  const bool xtiles = a.cmx - 3 <= kAdjTiles;
-  const long nbricks = (long)a.nbx * a.nby * a.nbz;
+  const AdjGeom a = make_gen_adj(q, vol);
+  const GenTiles tiles{tile[0].data(), tile[1].data()};
+  const size_t ws = adj_workspace_bytes(a) / sizeof(float);
+  REQUIRE(a.z.nb * a.z.k >= q.z.g - 3 && (a.z.nb - 1) * a.z.k < q.z.g - 3, "z-bricks cover the z-tiles");
+  const long nbricks = (long)a.x.nb * a.y.nb * a.z.nb;
   REQUIRE(nbricks < (1L << 31), "pass-1 grid");
-  std::vector<int> last((size_t)a.nbz);
+  std::vector<int> Cx((size_t)a.x.nb), Cy((size_t)a.y.nb), Cz((size_t)a.z.nb);
+  long voxels = 0;
   for (long id = 0; id < nbricks; ++id) {
-    const GzBrick b = gz_brick(q, a, T, (int)id);
-    REQUIRE(b.x0 < b.xe && b.xe - b.x0 <= kGzBX && b.y0 < b.ye && b.ye - b.y0 <= kGzBY, "brick inside the volume");
-    REQUIRE(b.z0 < b.ze && b.ze <= q.z.n, "brick planes inside the volume");
-    REQUIRE(b.Cx <= a.cmx && b.Cy <= a.cmy, "window within the partials' extents");
-    REQUIRE(b.Cx + 4 <= kGzThreads && b.Cy + 4 <= kGzThreads, "table fill within the workgroup");
-    REQUIRE(b.cx0 + b.Cx <= q.x.g && b.cy0 + b.Cy <= q.y.g, "first-voxel reads within the tables");
-    REQUIRE(!xtiles || b.Cx - 3 <= kAdjTiles, "x-tiles within one row of tile lanes");
-    REQUIRE(b.Cy - 3 <= kAdjTiles, "y-tiles within one row of tile lanes");
-    const int tl = tile[2][(size_t)b.ze - 1];
-    REQUIRE(tl - b.cz0 >= 0 && tl - b.cz0 + 3 < a.cmz, "the brick's last control plane within its window");
-    if (a.stage_all) REQUIRE((tl - b.cz0 + 4) * a.cmy * a.cmx * 3 <= kGzStage, "staged partials within the stage");
-    last[(size_t)(id / ((long)a.nbx * a.nby))] = tl;
+    const AdjBrick b = gen_brick(a, tiles, first[2].data(), (int)id);
+    REQUIRE(b.x0 < b.xe && b.y0 < b.ye && b.z0 < b.ze && b.xe <= q.x.n && b.ye <= q.y.n && b.ze <= q.z.n,
+            "brick inside the volume");
+    REQUIRE(tile[2][(size_t)b.z0] == b.cz0 && (b.z0 == 0 || tile[2][(size_t)b.z0 - 1] < b.cz0),
+            "z-bricks start on tile boundaries");
+    REQUIRE(tile[2][(size_t)b.ze - 1] - b.cz0 + 4 == gen_brick_cz(a, b), "control planes of the brick");
+    if (!check_brick(a, tiles, b, gen_brick_cz(a, b), ck)) return false;
+    Cx[(size_t)(id % a.x.nb)] = b.Cx;
+    Cy[(size_t)(id / a.x.nb % a.y.nb)] = b.Cy;
+    Cz[(size_t)(id / a.x.nb / a.y.nb)] = gen_brick_cz(a, b);
+    voxels += (long)(b.xe - b.x0) * (b.ye - b.y0) * (b.ze - b.z0);
   }
-  // pass 2: every brick a control point reads holds it in its window
-  for (int c = 0; c < q.x.g; ++c) {
-    const GzSpan sp = gz_span(T.first[0], c, kGzBX);
-    REQUIRE(0 <= sp.lo && sp.lo <= sp.hi && sp.hi < a.nbx, "x span");
-    for (int bx = sp.lo; bx <= sp.hi; ++bx) {
-      const GzBrick b = gz_brick(q, a, T, bx);
-      REQUIRE(c - b.cx0 >= 0 && c - b.cx0 < b.Cx, "pass 2 reads an x column outside the brick's window");
+  REQUIRE(voxels == (long)q.x.n * q.y.n * q.z.n, "bricks tile the volume");
+  // the march along z: every step's tile end is read inside the table (GenZ)
+  REQUIRE((int)first[2].size() == q.z.g + 1, "first-voxel table");
+  if (!check_gather(a, ck)) return false;
+  // pass 2, per axis: a brick lies in c's span exactly when its voxels meet c's
+  // support, and then its window holds c
+  const GenMap map{a, tile[0].data(), tile[1].data(), first[0].data(), first[1].data()};
+  for (int i = 0; i < 3; ++i)
+    for (int c = 0; c < ax[i]->g; ++c) {
+      const AdjSpan sp = i == 0 ? map.span_x(c) : i == 1 ? map.span_y(c) : map.span_z(c);
+      const AdjAxis& X = i == 0 ? a.x : i == 1 ? a.y : a.z;
+      const int lo = first[i][(size_t)imax(0, c - 3)], hi = first[i][(size_t)c + 1];
+      REQUIRE(0 <= sp.lo && sp.lo <= sp.hi && sp.hi < X.nb, "pass-2 span");
+      for (int b = 0; b < X.nb; ++b) {
+        const int b0 = i == 2 ? first[2][(size_t)(b * X.k)] : b * X.w;
+        const int b1 = i == 2 ? first[2][(size_t)imin((b + 1) * X.k, q.z.g - 3)] : imin(ax[i]->n, (b + 1) * X.w);
+        REQUIRE((b0 < hi && lo < b1) == (b >= sp.lo && b <= sp.hi), "pass-2 span differs from the bricks meeting the support");
+        if (b < sp.lo || b > sp.hi) continue;
+        const int c0 = i == 2 ? b * X.k : tile[i][(size_t)b0];
+        const int window = i == 0 ? Cx[(size_t)b] : i == 1 ? Cy[(size_t)b] : Cz[(size_t)b];
+        REQUIRE(c - c0 >= 0 && c - c0 < window, "pass 2 reads a partial pass 1 did not write");
+      }
     }
-  }
-  for (int c = 0; c < q.y.g; ++c) {
-    const GzSpan sp = gz_span(T.first[1], c, kGzBY);
-    REQUIRE(0 <= sp.lo && sp.lo <= sp.hi && sp.hi < a.nby, "y span");
-    for (int by = sp.lo; by <= sp.hi; ++by) {
-      const GzBrick b = gz_brick(q, a, T, by * a.nbx);
-      REQUIRE(c - b.cy0 >= 0 && c - b.cy0 < b.Cy, "pass 2 reads a y row outside the brick's window");
-    }
-  }
-  for (int c = 0; c < q.z.g; ++c) {
-    const GzSpan sp = gz_span_z(a, c, q.z.g);
-    REQUIRE(0 <= sp.lo && sp.lo <= sp.hi && sp.hi < a.nbz, "z span");
-    for (int bz = sp.lo; bz <= sp.hi; ++bz) {
-      const int czl = c - bz * a.kz;
-      REQUIRE(czl >= 0 && czl <= last[(size_t)bz] - bz * a.kz + 3, "pass 2 reads a control plane the brick did not emit");
-    }
-  }
-  const long nblk = (long)((q.x.g + kWave - 1) / kWave) * ((q.y.g + 3) / 4) * q.z.g;
-  REQUIRE(nblk < (1L << 31), "pass-2 grid");
+  REQUIRE(map.part_x(a.x.nb - 1, tile[0][(size_t)((a.x.nb - 1) * a.x.w)] + a.x.cm - 1) +
+                  map.part_y(a.y.nb - 1, tile[1][(size_t)((a.y.nb - 1) * a.y.w)] + a.y.cm - 1) +
+                  map.part_z(a.z.nb - 1, (a.z.nb - 1) * a.z.k + a.z.cm - 1) + 3 <= ws,
+          "pass-2 load outside the workspace");
   return true;
 }
 
@@ -403,7 +408,7 @@ int bsi_check_general_indices(const int32_t dims[3], const float spacing[3], con
     return -1;
   }
   Check ck;
-  check_general_adjoint(q, ck);
+  check_general_adjoint(q, g, ck);
   std::snprintf(msg, msglen, "%s", ck.msg.c_str());
   return ck.ok ? 0 : 1;
 }
