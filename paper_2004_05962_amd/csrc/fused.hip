@@ -43,15 +43,16 @@ constexpr int kFusedThreads = kFusedWaves * kWave;
 // at once start 32 banks apart.
 constexpr int kFusedFRow = kWave * 3 + 32;
 
-// LDS (floats): F[2], the two-slot ring of staged control planes (the brick's
-// window, pitch x.cm points), the reduction, the slabs.
+// LDS (floats): F (two in turn, and with whole slabs two more for a brick's last
+// three planes), the two-slot ring of staged control planes (the brick's window,
+// pitch x.cm points), the reduction, the slabs.
 struct FusedLds {
   int F, ring, slot, red, slabs, total;
 };
 __host__ __device__ inline FusedLds fused_lds(const AdjGeom& a) {
   FusedLds l;
   l.F = 0;
-  l.ring = 2 * kFusedWaves * kFusedFRow;
+  l.ring = (adj_staged(a) ? 4 : 2) * kFusedWaves * kFusedFRow;
   l.slot = a.y.cm * a.x.cm * 3;
   l.red = l.ring + 2 * l.slot;
   l.slabs = (l.red + kFusedThreads + 3) / 4 * 4;  // 16-byte aligned
@@ -146,8 +147,8 @@ __device__ __forceinline__ F3 fused_contract(const float* __restrict__ slot, int
 }
 
 // Pairs: the sampler's x-neighbour loads (trilinear_load): 1 for nx >= 2, 0 for nx == 1.
-// L: staged floats per thread.
-template <int L, bool Staged, int Pairs>
+// L: staged floats per thread.  Small: the images are below 4 GiB (buffer loads).
+template <int L, bool Staged, int Pairs, bool Small>
 __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float* __restrict__ grid,
                                                                   const float* __restrict__ moving,
                                                                   const float* __restrict__ fixed,
@@ -185,25 +186,35 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   const int pitch = a.x.cm * 3;
   const int base = (ty - b.cy0) * pitch + (tx - b.cx0) * 3;
   const FusedStage<L> map = fused_stage_map<L>(a, b, tid);
-  // the cell whose planes this wave contracts (waves 0 .. kAdjWaves - 1)
-  const AdjCell cell = adj_cell_geom(a, b, imin(wave, kAdjWaves - 1));
-  const bool contracts = wave < kAdjWaves && cell.nx > 0 && cell.ny > 0;
+  // the cell whose planes this wave contracts: waves 0 .. kAdjWaves - 1 at the end of
+  // a z-tile, three times as many at the end of a brick
+  const AdjCell cell = adj_cell_geom(a, b, wave % kAdjWaves);
+  const bool any = cell.nx > 0 && cell.ny > 0;
   const AdjWeights cw = adj_cell_weights(a, cell, lut, lane);
 
-  // Q of the 4 control planes of the first z-tile, one plane staged at a time
+  // Q of the 4 control planes of the first z-tile: their loads together, through the
+  // two slots in pairs (one plane at a time waited for memory four times)
   int tz = b.cz0;  // z-bricks are whole tiles: b.z0 = tz * dz
   F3 Q[4];
   float st[L];
-#pragma unroll 1
-  for (int j = 0; j < 4; ++j) {
-    __syncthreads();  // the slot's previous plane has been contracted
-    fused_fetch<L>(grid, g, map, tz + j, st);
-    fused_stage<L>(ring + ((tz + j) & 1) * lds.slot, map, st);
+  {
+    float s1[L], s2[L], s3[L];
+    float *even = ring + (tz & 1) * lds.slot, *odd = ring + ((tz + 1) & 1) * lds.slot;
+    fused_fetch<L>(grid, g, map, tz, st);
+    fused_fetch<L>(grid, g, map, tz + 1, s1);
+    fused_fetch<L>(grid, g, map, tz + 2, s2);
+    fused_fetch<L>(grid, g, map, tz + 3, s3);
+    fused_stage<L>(even, map, st);
+    fused_stage<L>(odd, map, s1);
     __syncthreads();
-    const F3 q = fused_contract(ring + ((tz + j) & 1) * lds.slot, base, pitch, bx, by);
-#pragma unroll
-    for (int n = 0; n < 3; ++n) Q[n] = Q[n + 1];
-    Q[3] = q;
+    Q[0] = fused_contract(even, base, pitch, bx, by);
+    Q[1] = fused_contract(odd, base, pitch, bx, by);
+    __syncthreads();
+    fused_stage<L>(even, map, s2);
+    fused_stage<L>(odd, map, s3);
+    __syncthreads();
+    Q[2] = fused_contract(even, base, pitch, bx, by);
+    Q[3] = fused_contract(odd, base, pitch, bx, by);
   }
   // the next tile's new plane tz + 4 (when another tile follows inside the
   // workgroup's range, it is at most ceil(nz/dz) + 2 = gz - 1)
@@ -214,26 +225,30 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   for (int n = 0; n < 4; ++n) acc[n] = F3{0.f, 0.f, 0.f};
   float l2 = 0.f;
   int turn = 0;  // which F the next plane goes to
+  // This lane's value of a finished plane to F[n], and the contraction of F[n] by this
+  // wave's cell into the slabs, a barrier apart.
+  auto put = [&](int n, const F3& v) {
+    stf3(fused_smem + lds.F + (n * kFusedWaves + wave) * kFusedFRow + lane * 3, v);
+  };
+  auto contract = [&](int n, int czl) {
+    const float* F = fused_smem + lds.F + n * kFusedWaves * kFusedFRow;
+    F3 f[kAdjSteps];
+#pragma unroll
+    for (int s = 0; s < kAdjSteps; ++s)
+      f[s] = ldf3(F + (cell.y0 - b.y0 + adj_lane_row(lane, s)) * kFusedFRow + (cell.x0 - b.x0 + lane % kAdjCellX) * 3);
+    adj_cell_emit(f, cw, slabs + adj_slab_at(a, Staged ? czl : czl & 1, wave % kAdjWaves), a.cw, a.ch, lane);
+  };
   // The finished plane acc[0] to F, the barrier, its contraction into the
   // slabs; the accumulators move up.  A wave's store to F[turn] two planes on
   // follows a barrier that the contracting waves reach after their reads.
   auto emit = [&](int czl) {
-    float* F = fused_smem + lds.F + turn * kFusedWaves * kFusedFRow;
-    stf3(F + wave * kFusedFRow + lane * 3, acc[0]);
+    put(turn, acc[0]);
     __syncthreads();
-    const int slot = Staged ? czl : czl & 1;
-    if (contracts) {
-      F3 f[kAdjSteps];
-#pragma unroll
-      for (int s = 0; s < kAdjSteps; ++s)
-        f[s] = ldf3(F + (cell.y0 - b.y0 + adj_lane_row(lane, s)) * kFusedFRow +
-                    (cell.x0 - b.x0 + lane % kAdjCellX) * 3);
-      adj_cell_emit(f, cw, slabs + adj_slab_at(a, slot, wave), a.cw, a.ch, lane);
-    }
+    if (any && wave < kAdjWaves) contract(turn, czl);
     if constexpr (!Staged) {
       __syncthreads();
-      adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, 1, slot, tid,
-                        kFusedThreads);
+      adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, 1, czl & 1,
+                        tid, kFusedThreads);
     }
     turn ^= 1;
 #pragma unroll
@@ -257,17 +272,28 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   };
   const size_t izs = (size_t)g.ny * g.nx;
   const size_t fxy = (size_t)yc * g.nx + xc;  // the lane's (clamped) voxel column
+  const int sy = g.ny > 1 ? g.nx * 4 : 0, sz = g.nz > 1 ? (int)(izs * 4) : 0;
+  const int image_bytes = Small ? (int)(izs * g.nz * 4) : 0;
+  const __amdgpu_buffer_rsrc_t mrs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(moving), 0, image_bytes, kBufferFlags);
+  const __amdgpu_buffer_rsrc_t frs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(fixed), 0, image_bytes, kBufferFlags);
   auto stage_a = [&](int z, int oz) {
     Pending p;
     const float* wz = lut_row(lut, g.dz, oz);
 #pragma unroll
     for (int n = 0; n < 4; ++n) p.w[n] = wz[n];
-    p.fx = fixed[(size_t)z * izs + fxy];
+    if constexpr (Small)
+      p.fx = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(frs, (int)(fxy * 4), (int)(z * izs * 4), 0));
+    else
+      p.fx = fixed[(size_t)z * izs + fxy];
     // T as the forward kernel forms it
     const F3 t{fmaf(p.w[3], Q[3].x, fmaf(p.w[2], Q[2].x, fmaf(p.w[1], Q[1].x, p.w[0] * Q[0].x))),
                fmaf(p.w[3], Q[3].y, fmaf(p.w[2], Q[2].y, fmaf(p.w[1], Q[1].y, p.w[0] * Q[0].y))),
                fmaf(p.w[3], Q[3].z, fmaf(p.w[2], Q[2].z, fmaf(p.w[1], Q[1].z, p.w[0] * Q[0].z)))};
-    p.s = trilinear_load<Pairs>(moving, g.nx, g.ny, g.nz, (float)x + t.x, (float)y + t.y, (float)z + t.z);
+    const float px = (float)x + t.x, py = (float)y + t.y, pz = (float)z + t.z;
+    if constexpr (Small) p.s = trilinear_load_buffer<Pairs>(mrs, g.nx, g.ny, g.nz, sy, sz, px, py, pz);
+    else p.s = trilinear_load<Pairs>(moving, g.nx, g.ny, g.nz, px, py, pz);
     return p;
   };
   auto stage_b = [&](const Pending& p) {
@@ -321,9 +347,20 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
       Q[3] = fused_contract(ring + ((tz + 4) & 1) * lds.slot, base, pitch, bx, by);
     }
     if (z == b.ze) {  // the brick's last three control planes, then the next brick
+      if constexpr (!Staged) {
 #pragma unroll 1
-      for (int n = 1; n < 4; ++n) emit(tz - b.cz0 + n);
-      if constexpr (Staged) {
+        for (int n = 1; n < 4; ++n) emit(tz - b.cz0 + n);
+      } else {
+        // together: F[turn] and the two that no other plane uses, a plane per four waves
+        put(turn, acc[0]);
+        put(2, acc[1]);
+        put(3, acc[2]);
+        __syncthreads();
+        const int n = wave / kAdjWaves;
+        if (any && n < 3) contract(n == 0 ? turn : n + 1, tz - b.cz0 + 1 + n);
+        turn ^= 1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] = F3{0.f, 0.f, 0.f};
         // the next plane's barrier orders this sum before its store to the slabs
         __syncthreads();
         adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), 0, adj_brick_cz(a, b), 0,
@@ -398,9 +435,13 @@ hipError_t launch_ssd_fused(const float* grid, const float* moving, const float*
   const FusedLds lds = fused_lds(a);
   const dim3 gridd((unsigned)items), block(kFusedThreads);
   const size_t bytes = (size_t)lds.total * sizeof(float);
-#define BSI_FUSED_LAUNCH(L, STAGED, PAIRS)                                                                        \
-    hipLaunchKernelGGL((fused_pass1_kernel<L, STAGED, PAIRS>), gridd, block, bytes, s, grid, moving, fixed, part, \
-                       lpart, a, fs, lut)
+  // 32-bit byte offsets of buffer loads into the images
+  const bool small = (double)a.g.nx * a.g.ny * a.g.nz * 4 < 4294967296.0;
+#define BSI_FUSED_LAUNCH(L, STAGED, PAIRS)                                                                            \
+  do {                                                                                                               \
+    const auto k = small ? &fused_pass1_kernel<L, STAGED, PAIRS, true> : &fused_pass1_kernel<L, STAGED, PAIRS, false>; \
+    hipLaunchKernelGGL(k, gridd, block, bytes, s, grid, moving, fixed, part, lpart, a, fs, lut);                      \
+  } while (0)
   // a volume one voxel wide samples its x-neighbours one by one
   const bool staged = adj_staged(a), one = fused_loads(lds.slot) <= 1;
   if (a.g.nx < 2) {

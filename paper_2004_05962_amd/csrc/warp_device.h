@@ -19,14 +19,13 @@ struct Axis {
 
 __device__ __forceinline__ Axis sample_axis(float p, int n) {
   Axis a;
-  const float top = (float)(n - 1);
+  const float top = (float)(n - 1), last = (float)max(n - 2, 0);
   a.in = (p > 0.f && p < top) ? 1.f : 0.f;
-  const float pc = fminf(fmaxf(p, 0.f), top);  // NaN -> 0
-  int i = (int)floorf(pc);
-  i = min(i, n >= 2 ? n - 2 : 0);
-  a.i0 = i;
-  a.i1 = min(i + 1, n - 1);
-  a.f = n >= 2 ? pc - (float)i : 0.f;
+  const float pc = __builtin_amdgcn_fmed3f(p, 0.f, top);  // NaN -> 0
+  const float fl = fminf(floorf(pc), last);               // (n <= 2^20: exact)
+  a.i0 = (int)fl;
+  a.i1 = min(a.i0 + 1, n - 1);
+  a.f = pc - fl;
   return a;
 }
 
