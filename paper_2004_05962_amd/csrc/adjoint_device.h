@@ -14,7 +14,7 @@
 // matrix products on the matrix cores, straight from the accumulators, for each
 // half of 16 voxels:
 //   D[x][cy]  = sum_row  A[x][row] By[row][cy]      (2 steps of 4 rows)
-//   E[cx][cy] += sum_x   Bx[cx][x] D[x][cy]         (4 steps of 4 voxels)
+//   E[cx][cy] += sum_x   Bx[cx][x] D[x][cy]         (4 steps of 4 voxels, 4 sums)
 // (v_mfma_f32_16x16x4_f32, FP32 in and out: two row swaps between lanes turn
 // the accumulator registers into the first product's A operand, its result
 // registers are the second one's B operand, and the weight matrices of the
@@ -22,16 +22,19 @@
 // control points.  E goes to the wave's own slab in LDS; no wave waits for
 // another while it marches.  After the brick's last plane one barrier, and the
 // slabs of the brick's cells are summed in wave order into the brick's partials.
-// Where a brick's slabs would take more than kAdjSlabFloats, the slabs hold two
+// Where the slabs would leave a brick fewer than kAdjMinStaged tiles, they hold two
 // planes, and each plane is summed and stored when it is finished, after one
 // barrier per z-tile.
 //
 // What bounds it: reading dfield once (12 bytes per voxel).  The z-accumulation
 // is 12 FMAs per voxel (about 20 us of every SIMD at 512 x 512 x 256), the
-// contractions are 36 matrix instructions of 32 cycles per 256 columns and
-// z-tile (about 25 us at spacing 5), both under the 120 us that the read takes.
+// contractions are 20 matrix instructions of 32 cycles per 256 columns and
+// z-tile where a window has at most 5 rows, 28 up to 8 (about 20 us at spacing 5), both
+// under the 120 us that the read takes.  512 x 512 x 256, spacing 5: 148 us, with the
+// contractions as vector moments on tile lanes, two barriers a tile, 156; 267 x 169
+// x 237, spacing 16: 31 against 52.
 //
-// Pass 2 (one thread per control point) sums, in fixed brick order, the
+// Pass 2 (a lane or a wave per control point) sums, in a fixed order, the
 // partials of the bricks whose voxels meet the point's support.  No atomics
 // anywhere: the bits depend on the inputs only.
 #pragma once
@@ -633,6 +636,9 @@ struct AdjMap {
 // adds kAdjGatherSmall to the offset, which is then past the buffer (three of them
 // and the largest offset stay below 2^32) and reads as zero without an access to
 // memory.  Otherwise 64-bit addresses, a branch per load, four of them in flight.
+// Pass 2 at 512 x 512 x 256, spacing 5: 9.0 us (of which 6.5 for its bytes at a copy's rate),
+// 17.2 with divisions, clamped duplicate loads and 3 bricks on an axis in a loop;
+// 512 x 228 x 385, spacing 3: 13.9 against 32.4.
 constexpr uint32_t kAdjGatherSmall = 1u << 30;
 template <bool Small, class Map>
 __device__ __forceinline__ F3 adj_gather_point(const float* __restrict__ part, const AdjGeom& a, const Map& map, int cx,
