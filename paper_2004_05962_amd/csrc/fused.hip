@@ -154,7 +154,7 @@ __device__ __forceinline__ F3 fused_contract(const float* __restrict__ slot, int
 }
 
 // Pairs: the sampler's x-neighbour loads (trilinear_load): 1 for nx >= 2, 0 for nx == 1.
-// L: staged floats per thread.  Small: the images are below 4 GiB (buffer loads).
+// L: staged floats per thread.  Small: the images are below 4 GiB.
 template <int L, bool Staged, int Pairs, bool Small>
 __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float* __restrict__ grid,
                                                                   const float* __restrict__ moving,
@@ -279,27 +279,19 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   };
   const size_t izs = (size_t)g.ny * g.nx;
   const size_t fxy = (size_t)yc * g.nx + xc;  // the lane's (clamped) voxel column
-  const int sy = g.ny > 1 ? g.nx * 4 : 0, sz = g.nz > 1 ? (int)(izs * 4) : 0;
-  const int image_bytes = Small ? (int)(izs * g.nz * 4) : 0;
-  const __amdgpu_buffer_rsrc_t mrs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(moving), 0, image_bytes, kBufferFlags);
-  const __amdgpu_buffer_rsrc_t frs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(fixed), 0, image_bytes, kBufferFlags);
+  const uint32_t sy = g.ny > 1 ? (uint32_t)g.nx * 4u : 0u, sz = g.nz > 1 ? (uint32_t)izs * 4u : 0u;  // Small
   auto stage_a = [&](int z, int oz) {
     Pending p;
     const float* wz = lut_row(lut, g.dz, oz);
 #pragma unroll
     for (int n = 0; n < 4; ++n) p.w[n] = wz[n];
-    if constexpr (Small)
-      p.fx = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(frs, (int)(fxy * 4), (int)(z * izs * 4), 0));
-    else
-      p.fx = fixed[(size_t)z * izs + fxy];
+    p.fx = fixed[(size_t)z * izs + fxy];
     // T as the forward kernel forms it
     const F3 t{fmaf(p.w[3], Q[3].x, fmaf(p.w[2], Q[2].x, fmaf(p.w[1], Q[1].x, p.w[0] * Q[0].x))),
                fmaf(p.w[3], Q[3].y, fmaf(p.w[2], Q[2].y, fmaf(p.w[1], Q[1].y, p.w[0] * Q[0].y))),
                fmaf(p.w[3], Q[3].z, fmaf(p.w[2], Q[2].z, fmaf(p.w[1], Q[1].z, p.w[0] * Q[0].z)))};
     const float px = (float)x + t.x, py = (float)y + t.y, pz = (float)z + t.z;
-    if constexpr (Small) p.s = trilinear_load_buffer<Pairs>(mrs, g.nx, g.ny, g.nz, sy, sz, px, py, pz);
+    if constexpr (Small) p.s = trilinear_load_small<Pairs>(moving, g.nx, g.ny, g.nz, sy, sz, px, py, pz);
     else p.s = trilinear_load<Pairs>(moving, g.nx, g.ny, g.nz, px, py, pz);
     return p;
   };
@@ -442,7 +434,7 @@ hipError_t launch_ssd_fused(const float* grid, const float* moving, const float*
   const FusedLds lds = fused_lds(a);
   const dim3 gridd((unsigned)items), block(kFusedThreads);
   const size_t bytes = (size_t)lds.total * sizeof(float);
-  // 32-bit byte offsets of buffer loads into the images
+  // 32-bit byte offsets into the images
   const bool small = (double)a.g.nx * a.g.ny * a.g.nz * 4 < 4294967296.0;
 #define BSI_FUSED_LAUNCH(L, STAGED, PAIRS)                                                                            \
   do {                                                                                                               \

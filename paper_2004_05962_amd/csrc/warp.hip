@@ -27,13 +27,12 @@ __device__ __forceinline__ float col_block_sum(float v, float* red) {
 }
 
 // What one pass over the voxels does: Grad: the SSD residual, its gradient and the
-// loss partial; otherwise the warped image.  Small: the image is below 4 GiB
-// (buffer loads).  Bounds: reading the field and the images once and writing the
-// result once (20 bytes per voxel for the warp, 32 for the SSD); per voxel about 90
-// instructions and 4 gathers of 8 bytes.  One voxel per thread in workgroups of a
-// row's 256 voxels, with 64-bit addresses per corner, took 115 us for the warp at
-// 303 x 167 x 212 (half of the workgroups with one wave at work) and 87 for the SSD
-// at 294 x 130 x 208.
+// loss partial; otherwise the warped image.  Small: the image is below 4 GiB.
+// Bounds: reading the field and the images once and writing the result once (20
+// bytes per voxel for the warp, 32 for the SSD); per voxel about 80 instructions and
+// 4 gathers of 8 bytes.  Warp at 303 x 167 x 212 62 us, SSD at 294 x 130 x 208 57; one voxel
+// per thread in workgroups of a row's 256 voxels, with 64-bit addresses per corner,
+// took 115 (half of the workgroups with one wave at work) and 87.
 template <bool Grad, bool Small, int Pairs>
 __global__ __launch_bounds__(kColThreads) void sample_kernel(const float* __restrict__ field,
                                                               const float* __restrict__ image,
@@ -51,12 +50,10 @@ __global__ __launch_bounds__(kColThreads) void sample_kernel(const float* __rest
   const int y = (int)(p / (uint32_t)g.nx), x = (int)(p - (uint32_t)y * (uint32_t)g.nx);
   const int z0 = zb * L.zchunk, z1 = min(g.nz, z0 + L.zchunk);
   const float fx = (float)x, fy = (float)y;
-  const int sy = g.ny > 1 ? g.nx * 4 : 0, sz = g.nz > 1 ? (int)(plane * 4) : 0;
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(image), 0, Small ? (int)(plane * g.nz * 4) : 0, kBufferFlags);
+  const uint32_t sy = g.ny > 1 ? (uint32_t)g.nx * 4u : 0u, sz = g.nz > 1 ? (uint32_t)plane * 4u : 0u;
   auto load = [&](const F3& d, int z) {
     const float px = fx + d.x, py = fy + d.y, pz = (float)z + d.z;
-    if constexpr (Small) return trilinear_load_buffer<Pairs>(rs, g.nx, g.ny, g.nz, sy, sz, px, py, pz);
+    if constexpr (Small) return trilinear_load_small<Pairs>(image, g.nx, g.ny, g.nz, sy, sz, px, py, pz);
     else return trilinear_load<Pairs>(image, g.nx, g.ny, g.nz, px, py, pz);
   };
   float l2 = 0.f;

@@ -95,29 +95,31 @@ __device__ __forceinline__ Sample trilinear_finish(const SampleIn& c) {
   return s;
 }
 
-// trilinear_load through a buffer resource over an image below 4 GiB: one 32-bit
-// lane offset, and the cell's other rows at the uniform distances sy and sz (bytes
-// to the next row and plane; 0 along an axis of one voxel, whose corners coincide).
-// The same operations on the same values as trilinear_load.  Pairs as there.
+// trilinear_load for an image below 4 GiB: one 32-bit lane offset, and the cell's
+// other rows from base addresses at the uniform distances sy and sz (bytes to the
+// next row and plane; 0 along an axis of one voxel, whose corners coincide).  Global
+// loads: through a buffer resource the same gathers, which seldom start on 8 bytes,
+// took longer (warp of 303 x 167 x 212 72 us against 62; fused step of 256 x 256 x 160 at
+// rough displacements 72 against 67).  The same operations on the same values as
+// trilinear_load.  Pairs as there.
 template <int Pairs>
-__device__ __forceinline__ SampleIn trilinear_load_buffer(__amdgpu_buffer_rsrc_t img, int nx, int ny, int nz, int sy,
-                                                          int sz, float px, float py, float pz) {
+__device__ __forceinline__ SampleIn trilinear_load_small(const float* __restrict__ img, int nx, int ny, int nz,
+                                                         uint32_t sy, uint32_t sz, float px, float py, float pz) {
   const Axis ax = sample_axis(px, nx), ay = sample_axis(py, ny), az = sample_axis(pz, nz);
-  const int o = (int)((((uint32_t)az.i0 * (uint32_t)ny + (uint32_t)ay.i0) * (uint32_t)nx + (uint32_t)ax.i0) * 4u);
+  const uint32_t o = (((uint32_t)az.i0 * (uint32_t)ny + (uint32_t)ay.i0) * (uint32_t)nx + (uint32_t)ax.i0) * 4u;
+  const char* p00 = reinterpret_cast<const char*>(img);
+  const char *p01 = p00 + sy, *p10 = p00 + sz, *p11 = p10 + sy;
   SampleIn s;
   if constexpr (Pairs == 1) {
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 q00 = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(img, o, 0, 0));
-    const f2 q01 = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(img, o, sy, 0));
-    const f2 q10 = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(img, o, sz, 0));
-    const f2 q11 = __builtin_bit_cast(f2, __builtin_amdgcn_raw_buffer_load_b64(img, o, sy + sz, 0));
+    const F2 q00 = *reinterpret_cast<const F2*>(p00 + o), q01 = *reinterpret_cast<const F2*>(p01 + o);
+    const F2 q10 = *reinterpret_cast<const F2*>(p10 + o), q11 = *reinterpret_cast<const F2*>(p11 + o);
     s.c000 = q00.x, s.c001 = q00.y, s.c010 = q01.x, s.c011 = q01.y;
     s.c100 = q10.x, s.c101 = q10.y, s.c110 = q11.x, s.c111 = q11.y;
   } else {
-    s.c000 = s.c001 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(img, o, 0, 0));
-    s.c010 = s.c011 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(img, o, sy, 0));
-    s.c100 = s.c101 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(img, o, sz, 0));
-    s.c110 = s.c111 = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(img, o, sy + sz, 0));
+    s.c000 = s.c001 = *reinterpret_cast<const float*>(p00 + o);
+    s.c010 = s.c011 = *reinterpret_cast<const float*>(p01 + o);
+    s.c100 = s.c101 = *reinterpret_cast<const float*>(p10 + o);
+    s.c110 = s.c111 = *reinterpret_cast<const float*>(p11 + o);
   }
   s.fx = ax.f, s.fy = ay.f, s.fz = az.f;
   s.inx = ax.in, s.iny = ay.in, s.inz = az.in;
