@@ -314,16 +314,16 @@ __device__ __forceinline__ adj_f4 adj_cell_sparse(const float (&f)[2][2], const 
 // Components [C0, C0 + N) of a finished plane, together in one set of products:
 // component C0 + c takes rows c S .. of the first product's result, so that the
 // second product's 16 columns hold N windows of at most S rows.
-template <int C0, int N, int S, int A = 4>
+template <int C0, int N, int S, int A = 4, int G = 2>
 __device__ __forceinline__ void adj_contract(const float (&f)[3][2][2], const AdjWeights& w, adj_f4& E) {
   static_assert(N * S <= kAdjTile || N == 1, "the windows fit a tile");
   adj_f4 D[2];
 #pragma unroll
-  for (int g = 0; g < 2; ++g) D[g] = adj_f4{0.f, 0.f, 0.f, 0.f};
+  for (int g = 0; g < G; ++g) D[g] = adj_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
+    for (int g = 0; g < G; ++g) {
       D[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[C0][g][t], w.y[t], D[g], 0, 0, 0);
       if constexpr (N > 1)
         D[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[C0 + 1][g][t], adj_row_ror<S % 16>(w.y[t]), D[g], 0, 0, 0);
@@ -337,7 +337,7 @@ __device__ __forceinline__ void adj_contract(const float (&f)[3][2][2], const Ad
 #pragma unroll
   for (int i = 0; i < A; ++i) X[i] = adj_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int g = 0; g < 2; ++g)
+  for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int i = 0; i < 4; ++i) X[i % A] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x[g][i], D[g][i], X[i % A], 0, 0, 0);
   E = X[0] + X[1];
@@ -385,12 +385,23 @@ __device__ __forceinline__ void adj_cell_emit(const F3 (&f3)[kAdjSteps], const A
     probe = E[0] + E2[0];
   } else {
     adj_f4 E, E1, E2;
-    adj_contract<0, 1, 16, 2>(f, w, E);
-    store(E, m, 0);
-    adj_contract<1, 1, 16, 2>(f, w, E1);
-    store(E1, m, 1);
-    adj_contract<2, 1, 16, 2>(f, w, E2);
-    store(E2, m, 2);
+    // a cell of at most 16 voxels has no second half: 18 products in place of 36
+    // (300 x 256 x 200, spacing 1: 242 us against 289)
+    if (!__any((w.x[1][0] != 0.f) | (w.x[1][1] != 0.f) | (w.x[1][2] != 0.f) | (w.x[1][3] != 0.f))) {
+      adj_contract<0, 1, 16, 2, 1>(f, w, E);
+      store(E, m, 0);
+      adj_contract<1, 1, 16, 2, 1>(f, w, E1);
+      store(E1, m, 1);
+      adj_contract<2, 1, 16, 2, 1>(f, w, E2);
+      store(E2, m, 2);
+    } else {
+      adj_contract<0, 1, 16, 2>(f, w, E);
+      store(E, m, 0);
+      adj_contract<1, 1, 16, 2>(f, w, E1);
+      store(E1, m, 1);
+      adj_contract<2, 1, 16, 2>(f, w, E2);
+      store(E2, m, 2);
+    }
     probe = E[0] + E1[0] + E2[0];
   }
   if (__builtin_expect(__any(!(fabsf(probe) < __builtin_inff())), 0)) {
