@@ -22,8 +22,8 @@
 // Each workgroup sums its voxels' squared residuals in a fixed order into one
 // loss partial; pass 2 is the adjoint's fixed-order gather, and the
 // loss is the fixed-order sum of the partials.  No atomics.
-#include "adjoint_device.h"
 #include "bsi_internal.h"
+#include "fused_device.h"
 #include "warp_device.h"
 
 namespace bsi {
@@ -44,52 +44,6 @@ namespace {
 // depth, 64-bit addresses per corner and moments on tile lanes), 22 at 64 x 64 x 40
 // (62).  Starting the next tile's gathers before the border, its control plane a
 // tile earlier, took more registers than 128: 68 us.
-constexpr int kFusedWaves = kAdjCellsY * kAdjCellY;
-constexpr int kFusedThreads = kFusedWaves * kWave;
-// Floats per row of F: 64 voxels, padded so that the 2 rows a cell's lanes read
-// at once start 32 banks apart.
-constexpr int kFusedFRow = kWave * 3 + 32;
-
-// LDS (floats): F (two in turn, and with whole slabs two more for a brick's last
-// three planes), the two-slot ring of staged control planes (the brick's window,
-// pitch x.cm points), the reduction, the slabs.
-struct FusedLds {
-  int F, ring, slot, red, slabs, total;
-};
-__host__ __device__ inline FusedLds fused_lds(const AdjGeom& a) {
-  FusedLds l;
-  l.F = 0;
-  l.ring = (adj_staged(a) ? 4 : 2) * kFusedWaves * kFusedFRow;
-  l.slot = a.y.cm * a.x.cm * 3;
-  l.red = l.ring + 2 * l.slot;
-  l.slabs = (l.red + kFusedThreads + 3) / 4 * 4;  // 16-byte aligned
-  l.total = l.slabs + a.slots * kAdjWaves * adj_slab(a);
-  return l;
-}
-// Staged floats per thread: one plane's window is at most 825 floats at
-// spacings dx >= 3, dy >= 2, and at most 2640 at spacing 1.
-__host__ __device__ constexpr int fused_loads(int slot) { return (slot + kFusedThreads - 1) / kFusedThreads; }
-constexpr int kFusedMaxLoads = 3;
-
-// A workgroup takes `deep` consecutive z-bricks of one (x, y) brick column: it
-// marches on through their borders with the planes it has contracted, and
-// only the adjoint's partials are cut there.  So the depth of a workgroup is
-// chosen for this kernel, which runs one workgroup per CU and pays for the
-// first 4 control planes, and not by the adjoint's bricks: as deep as leaves
-// kFusedTargetWg workgroups.
-constexpr int kFusedTargetWg = 256;
-struct FusedSplit {
-  int deep, nz;  // z-bricks per workgroup, workgroups along z
-};
-__host__ __device__ inline FusedSplit fused_split(const AdjGeom& a) {
-  const long base = (long)a.x.nb * a.y.nb;
-  long nz = (kFusedTargetWg + base - 1) / base;
-  nz = nz < a.z.nb ? nz : a.z.nb;
-  FusedSplit f;
-  f.deep = (int)((a.z.nb + nz - 1) / nz);
-  f.nz = (a.z.nb + f.deep - 1) / f.deep;
-  return f;
-}
 
 // Loads of control plane cz's window into registers (thread tid takes floats
 // e = tid + k kFusedThreads of the Cy x Cx x 3 window), and their store into a
@@ -199,39 +153,26 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   const bool any = cell.nx > 0 && cell.ny > 0;
   const AdjWeights cw = adj_cell_weights(a, cell, lut, lane);
 
-  // Q of the 4 control planes of the first z-tile: their loads together, through the
-  // two slots in pairs (one plane at a time waited for memory four times)
-  int tz = b.cz0;  // z-bricks are whole tiles: b.z0 = tz * dz
+  // Q: the 4 contracted control planes of the z-tile
   F3 Q[4];
-  float st[L];
-  {
-    float s1[L], s2[L], s3[L];
-    float *even = ring + (tz & 1) * lds.slot, *odd = ring + ((tz + 1) & 1) * lds.slot;
-    fused_fetch<L>(grid, g, map, tz, st);
-    fused_fetch<L>(grid, g, map, tz + 1, s1);
-    fused_fetch<L>(grid, g, map, tz + 2, s2);
-    fused_fetch<L>(grid, g, map, tz + 3, s3);
-    fused_stage<L>(even, map, st);
-    fused_stage<L>(odd, map, s1);
-    __syncthreads();
-    Q[0] = fused_contract(even, base, pitch, bx, by);
-    Q[1] = fused_contract(odd, base, pitch, bx, by);
-    __syncthreads();
-    fused_stage<L>(even, map, s2);
-    fused_stage<L>(odd, map, s3);
-    __syncthreads();
-    Q[2] = fused_contract(even, base, pitch, bx, by);
-    Q[3] = fused_contract(odd, base, pitch, bx, by);
-  }
-  // the next tile's new plane tz + 4 (when another tile follows inside the
-  // workgroup's range, it is at most ceil(nz/dz) + 2 = gz - 1)
-  if ((tz + 1) * g.dz < zend) fused_fetch<L>(grid, g, map, tz + 4, st);
+  float st[L], s1[L], s2[L], s3[L];
+  auto slot = [&](int cz) { return ring + (cz & 1) * lds.slot; };
+  const auto ring_ops = fused_ring(
+      [&](int cz) {
+        fused_fetch<L>(grid, g, map, cz, st);
+        fused_fetch<L>(grid, g, map, cz + 1, s1);
+        fused_fetch<L>(grid, g, map, cz + 2, s2);
+        fused_fetch<L>(grid, g, map, cz + 3, s3);
+      },
+      [&](int k, int cz) { fused_stage<L>(slot(cz), map, k == 0 ? st : k == 1 ? s1 : k == 2 ? s2 : s3); },
+      [&](int cz) { fused_fetch<L>(grid, g, map, cz, st); },
+      [&](int n, int cz) { Q[n] = fused_contract(slot(cz), base, pitch, bx, by); }, [] { __syncthreads(); });
+  fused_start(g, b.cz0, zend, ring_ops);
 
   F3 acc[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n) acc[n] = F3{0.f, 0.f, 0.f};
   float l2 = 0.f;
-  int turn = 0;  // which F the next plane goes to
   // This lane's value of a finished plane to F[n], and the contraction of F[n] by this
   // wave's cell into the slabs, a barrier apart.
   auto put = [&](int n, const F3& v) {
@@ -245,24 +186,6 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
       f[s] = ldf3(F + (cell.y0 - b.y0 + adj_lane_row(lane, s)) * kFusedFRow + (cell.x0 - b.x0 + lane % kAdjCellX) * 3);
     adj_cell_emit(f, cw, slabs + adj_slab_at(a, Staged ? czl : czl & 1, wave % kAdjWaves), a.cw, a.ch, lane);
   };
-  // The finished plane acc[0] to F, the barrier, its contraction into the
-  // slabs; the accumulators move up.  A wave's store to F[turn] two planes on
-  // follows a barrier that the contracting waves reach after their reads.
-  auto emit = [&](int czl) {
-    put(turn, acc[0]);
-    __syncthreads();
-    if (any && wave < kAdjWaves) contract(turn, czl);
-    if constexpr (!Staged) {
-      __syncthreads();
-      adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, 1, czl & 1,
-                        tid, kFusedThreads);
-    }
-    turn ^= 1;
-#pragma unroll
-    for (int n = 0; n < 3; ++n) acc[n] = acc[n + 1];
-    acc[3] = F3{0.f, 0.f, 0.f};
-  };
-
   // Per voxel plane, in two stages: (a) T from the 4 contracted planes, the
   // sample's cell and the loads of its corners and of `fixed`; (b) the
   // residual, the gradient and the z-accumulation.  Within a z-tile, (a) of
@@ -314,8 +237,8 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
     }
   };
 
-  for (int z = b.z0; z < zend;) {  // one z-tile (the volume's last may be partial)
-    const int np = imin(g.dz, zend - z);
+  // the np voxel planes from z of one z-tile
+  auto planes = [&](int z, int np) {
     // two register sets, used in turn (a copy from one to the other would
     // wait for the loads it copies)
     Pending p0 = stage_a(z, 0);
@@ -333,45 +256,28 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
     } else {
       stage_b(p0);
     }
-    z += np;
-    // plane tz + 4 goes to the slot of plane tz + 2, contracted before the
-    // previous tile's barrier; the emission's barrier orders the store
-    // before the contraction below
-    const bool more = z < zend;
-    if (more) fused_stage<L>(ring + ((tz + 4) & 1) * lds.slot, map, st);
-    emit(tz - b.cz0);
-    if (more) {
+  };
+
+  const auto march_ops = fused_march(
+      [&] {
 #pragma unroll
-      for (int n = 0; n < 3; ++n) Q[n] = Q[n + 1];
-      Q[3] = fused_contract(ring + ((tz + 4) & 1) * lds.slot, base, pitch, bx, by);
-    }
-    if (z == b.ze) {  // the brick's last three control planes, then the next brick
-      if constexpr (!Staged) {
-#pragma unroll 1
-        for (int n = 1; n < 4; ++n) emit(tz - b.cz0 + n);
-      } else {
-        // together: F[turn] and the two that no other plane uses, a plane per four waves
-        put(turn, acc[0]);
-        put(2, acc[1]);
-        put(3, acc[2]);
-        __syncthreads();
-        const int n = wave / kAdjWaves;
-        if (any && n < 3) contract(n == 0 ? turn : n + 1, tz - b.cz0 + 1 + n);
-        turn ^= 1;
+        for (int n = 0; n < 3; ++n) Q[n] = Q[n + 1];
+      },
+      planes,
+      [&](int n, int k) { put(n, acc[k]); },
+      [&](int n, int czl, int np) {
+        const int k = wave / kAdjWaves;
+        if (any && k < np) contract(k == 0 ? n : k + 1, czl + k);
+      },
+      [&](int n) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] = F3{0.f, 0.f, 0.f};
-        // the next plane's barrier orders this sum before its store to the slabs
-        __syncthreads();
-        adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), 0, adj_brick_cz(a, b), 0,
-                          tid, kFusedThreads);
-      }
-      if (more) b = adj_brick_geom(a, ++bz * nxy + bxy);
-    }
-    if (more) {
-      ++tz;
-      if ((tz + 1) * g.dz < zend) fused_fetch<L>(grid, g, map, tz + 4, st);
-    }
-  }
+        for (int k = 0; k < 4; ++k) acc[k] = k + n < 4 ? acc[k + n] : F3{0.f, 0.f, 0.f};
+      },
+      [&](int czl, int np) {
+        adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, np,
+                          Staged ? czl : czl & 1, tid, kFusedThreads);
+      });
+  fused_walk<Staged>(a, bxy, zend, b, bz, ring_ops, march_ops);
 
   // the workgroup's loss partial: fixed-order tree
   red[tid] = l2;

@@ -1,0 +1,177 @@
+// The fused SSD step's use of LDS, shared by its kernel (fused.hip) and the host
+// checker: sizes, layout, and the order of a workgroup's stores, reads and barriers.
+#pragma once
+
+#include "adjoint_device.h"
+
+namespace bsi {
+
+constexpr int kFusedWaves = kAdjCellsY * kAdjCellY;
+constexpr int kFusedThreads = kFusedWaves * kWave;
+// Floats per row of F: 64 voxels, padded so that the 2 rows a cell's lanes read
+// at once start 32 banks apart.
+constexpr int kFusedFRow = kWave * 3 + 32;
+
+// LDS (floats): F (two in turn, and with whole slabs two more for a brick's last
+// three planes), the two-slot ring of staged control planes (the brick's window,
+// pitch x.cm points), the reduction, the slabs.
+struct FusedLds {
+  int F, ring, slot, red, slabs, total;
+};
+__host__ __device__ inline FusedLds fused_lds(const AdjGeom& a) {
+  FusedLds l;
+  l.F = 0;
+  l.ring = (adj_staged(a) ? 4 : 2) * kFusedWaves * kFusedFRow;
+  l.slot = a.y.cm * a.x.cm * 3;
+  l.red = l.ring + 2 * l.slot;
+  l.slabs = (l.red + kFusedThreads + 3) / 4 * 4;  // 16-byte aligned
+  l.total = l.slabs + a.slots * kAdjWaves * adj_slab(a);
+  return l;
+}
+// Staged floats per thread: one plane's window is at most 825 floats at
+// spacings dx >= 3, dy >= 2, and at most 2640 at spacing 1.
+__host__ __device__ constexpr int fused_loads(int slot) { return (slot + kFusedThreads - 1) / kFusedThreads; }
+constexpr int kFusedMaxLoads = 3;
+
+// A workgroup takes `deep` consecutive z-bricks of one (x, y) brick column: it
+// marches on through their borders with the planes it has contracted, and
+// only the adjoint's partials are cut there.  So the depth of a workgroup is
+// chosen for this kernel, which runs one workgroup per CU and pays for the
+// first 4 control planes, and not by the adjoint's bricks: as deep as leaves
+// kFusedTargetWg workgroups.
+constexpr int kFusedTargetWg = 256;
+struct FusedSplit {
+  int deep, nz;  // z-bricks per workgroup, workgroups along z
+};
+__host__ __device__ inline FusedSplit fused_split(const AdjGeom& a) {
+  const long base = (long)a.x.nb * a.y.nb;
+  long nz = (kFusedTargetWg + base - 1) / base;
+  nz = nz < a.z.nb ? nz : a.z.nb;
+  FusedSplit f;
+  f.deep = (int)((a.z.nb + nz - 1) / nz);
+  f.nz = (a.z.nb + f.deep - 1) / f.deep;
+  return f;
+}
+
+// What a workgroup does, as the steps that fused_start and fused_walk put in order; every
+// thread takes each of them.  Planes cz are the grid's, czl = cz - b.cz0 the brick's.
+template <class Load4, class Fill, class Load, class Take, class Barrier>
+struct FusedRing {
+  Load4 load4;      // (cz): load control planes cz .. cz + 3 into four register sets
+  Fill fill;        // (k, cz): set k, plane cz, to ring slot cz & 1
+  Load load;        // (cz): load plane cz into set 0
+  Take take;        // (n, cz): Q[n] from the slot of plane cz
+  Barrier barrier;
+};
+template <class Shift, class Planes, class Put, class Cells, class Move, class Sum>
+struct FusedMarch {
+  Shift shift;      // Q[n] = Q[n + 1]
+  Planes planes;    // (z, np): the voxel planes [z, z + np) of one z-tile, with Q
+  Put put;          // (n, k): accumulator k to F[n]
+  Cells cells;      // (n, czl, np): four waves each contract F[n], F[2], F[3] into the slabs of planes czl .. czl + np - 1
+  Move move;        // (n): the accumulators move down by n, zeros above
+  Sum sum;          // (czl, np): slabs of planes czl .. czl + np - 1 into brick bz's partials
+};
+template <class... T>
+__host__ __device__ __forceinline__ FusedRing<T...> fused_ring(T... t) {
+  return FusedRing<T...>{t...};
+}
+template <class... T>
+__host__ __device__ __forceinline__ FusedMarch<T...> fused_march(T... t) {
+  return FusedMarch<T...>{t...};
+}
+
+// Q of the 4 control planes of the first z-tile, and the load of the next one.  Two
+// accesses of one LDS region by different waves, one of them a store, lie on two sides
+// of a barrier, here and in fused_walk:
+// - ring slot cz & 1: filled with plane cz, read by take(cz), then filled with plane
+//   cz + 2.  At a z-tile's border plane tz + 4 replaces tz + 2, which was taken
+//   before the previous border's barrier, at the first border before the barrier
+//   that ends the start (left out where no border follows); take(tz + 4) follows the
+//   emission's barrier.
+// - F[0], F[1] in turn: a store to F[turn] two planes on follows a barrier that the
+//   contracting waves reach after their reads.  F[2], F[3]: once a brick.
+// - slabs: with whole slabs a barrier on either side of the brick's sum (the next
+//   plane's barrier is the later one); with two planes' slabs the barrier of plane
+//   czl + 1 lies between the sum of czl and the store of czl + 2.
+template <class Ring>
+__host__ __device__ __forceinline__ void fused_start(const VolGeom& g, int tz, int zend, const Ring& op) {
+  // the four loads together, through the two slots in pairs (one plane at a time waited
+  // for memory four times)
+  op.load4(tz);
+  op.fill(0, tz);
+  op.fill(1, tz + 1);
+  op.barrier();
+  op.take(0, tz);
+  op.take(1, tz + 1);
+  op.barrier();
+  op.fill(2, tz + 2);
+  op.fill(3, tz + 3);
+  op.barrier();
+  op.take(2, tz + 2);
+  op.take(3, tz + 3);
+  // the next tile's new plane tz + 4 (when another tile follows inside the
+  // workgroup's range, it is at most ceil(nz/dz) + 2 = gz - 1)
+  if ((tz + 1) * g.dz < zend) {
+    op.barrier();  // the slot of plane tz + 2 is free for it
+    op.load(tz + 4);
+  }
+}
+
+// The z-bricks from b (number bz) on of brick column bxy, up to plane zend.
+template <bool Staged, class Ring, class March>
+__host__ __device__ __forceinline__ void fused_walk(const AdjGeom& a, int bxy, int zend, AdjBrick& b, int& bz,
+                                                    const Ring& r, const March& op) {
+  const VolGeom& g = a.g;
+  int tz = b.cz0;  // z-bricks are whole tiles: b.z0 = tz * dz
+  int turn = 0;  // which F the next plane goes to
+  // The finished plane, accumulator 0: to F, and by the cells' waves into the slabs
+  auto emit = [&](int czl) {
+    op.put(turn, 0);
+    r.barrier();
+    op.cells(turn, czl, 1);
+    if constexpr (!Staged) {
+      r.barrier();
+      op.sum(czl, 1);
+    }
+    turn ^= 1;
+    op.move(1);
+  };
+  for (int z = b.z0; z < zend;) {  // one z-tile (the volume's last may be partial)
+    const int np = imin(g.dz, zend - z);
+    op.planes(z, np);
+    z += np;
+    const bool more = z < zend;
+    if (more) r.fill(0, tz + 4);
+    emit(tz - b.cz0);
+    if (more) {
+      op.shift();
+      r.take(3, tz + 4);
+    }
+    if (z == b.ze) {  // the brick's last three control planes, then the next brick
+      const int czl = tz - b.cz0 + 1;
+      if constexpr (!Staged) {
+#pragma unroll 1
+        for (int n = 0; n < 3; ++n) emit(czl + n);
+      } else {
+        // together: F[turn] and the two that no other plane uses, a plane per four waves
+        op.put(turn, 0);
+        op.put(2, 1);
+        op.put(3, 2);
+        r.barrier();
+        op.cells(turn, czl, 3);
+        turn ^= 1;
+        op.move(4);
+        r.barrier();
+        op.sum(0, adj_brick_cz(a, b));
+      }
+      if (more) b = adj_brick_geom(a, ++bz * (a.x.nb * a.y.nb) + bxy);
+    }
+    if (more) {
+      ++tz;
+      if ((tz + 1) * g.dz < zend) r.load(tz + 4);
+    }
+  }
+}
+
+}  // namespace bsi

@@ -12,6 +12,7 @@
 
 #include "adjoint_device.h"
 #include "bsi_internal.h"
+#include "fused_device.h"
 #include "general_device.h"
 #include "warp_device.h"
 
@@ -378,6 +379,112 @@ bool check_general_adjoint(const GenGeom& q, const VolGeom& vol, Check& ck) {
   return true;
 }
 
+// One LDS region of the fused step: what it holds, and the barrier interval of its
+// last store and read.  A store and another access of one region lie in different
+// intervals; a read finds the plane it is meant for.
+struct LdsRegion {
+  int holds = -1, stored = -1, read = -1;
+  bool store(int what, int now) {
+    const bool ok = stored < now && read < now;
+    holds = what;
+    stored = now;
+    return ok;
+  }
+  bool load(int what, int now) {
+    read = now;
+    return holds == what && stored < now;
+  }
+};
+
+// The order of the fused step's LDS accesses (fused_start, fused_walk) for one workgroup.
+template <bool Staged>
+bool check_fused_walk(const AdjGeom& a, int bxy, int bz0, int bz1, Check& ck) {
+  const VolGeom& g = a.g;
+  const int nxy = a.x.nb * a.y.nb, zend = adj_brick_begin(a.z, g.nz, bz1);
+  AdjBrick b = adj_brick_geom(a, bz0 * nxy + bxy);
+  int bz = bz0, now = 0, z = b.z0;
+  LdsRegion ring[2], F[4];
+  std::vector<LdsRegion> slab((size_t)a.slots);
+  int in[4] = {-1, -1, -1, -1};     // control planes in the register sets
+  int Q[4] = {-1, -1, -1, -1};      // and in Q
+  int acc = b.cz0, full = 0;        // control plane of accumulator 0, accumulators that hold something
+  int summed = 0;                   // planes of brick bz in its partials
+  bool ok = true;
+  auto must = [&](bool c, const char* what) {
+    if (ok && !c) {
+      ck.fail(std::string("fused step, brick ") + std::to_string(bz) + ", plane " + std::to_string(z) + ": " + what);
+      ok = false;
+    }
+  };
+  auto slot_of = [&](int czl) { return (size_t)(Staged ? czl : czl & 1); };
+  auto planes = [&](int z0, int np) {
+    must(z0 == z && np >= 1 && z0 / g.dz == (z0 + np - 1) / g.dz && z0 % g.dz == 0, "planes of one z-tile");
+    for (int n = 0; n < 4; ++n) must(Q[n] == z0 / g.dz + n, "Q of the tile's planes");
+    if (z0 == b.z0) {
+      must(full == 0, "empty accumulators at a brick's start");
+      acc = b.cz0;
+    }
+    must(acc == z0 / g.dz, "accumulators of the tile's planes");
+    full = 4;
+    z = z0 + np;
+  };
+  const auto ring_ops = fused_ring(
+      [&](int cz) {
+        for (int k = 0; k < 4; ++k) in[k] = cz + k;
+        must(cz >= 0 && cz + 3 < g.gz, "load inside the grid");
+      },
+      [&](int k, int cz) {
+        must(in[k] == cz, "the loaded plane is stored");
+        must(ring[cz & 1].store(cz, now), "ring slot stored while other waves may still read it");
+      },
+      [&](int cz) {
+        in[0] = cz;
+        must(cz >= 0 && cz < g.gz, "load inside the grid");
+      },
+      [&](int n, int cz) {
+        must(ring[cz & 1].load(cz, now), "ring slot read before a barrier follows its store");
+        Q[n] = cz;
+      },
+      [&] { ++now; });
+  const auto march_ops = fused_march(
+      [&] {
+        for (int n = 0; n < 3; ++n) Q[n] = Q[n + 1];
+      },
+      planes, [&](int n, int k) { must(F[n].store(acc + k, now), "F stored while other waves may still read it"); },
+      [&](int n, int czl, int np) {
+        for (int k = 0; k < np; ++k) {
+          must(F[k == 0 ? n : k + 1].load(b.cz0 + czl + k, now), "F read before a barrier follows its store");
+          must(slab[slot_of(czl + k)].store(czl + k, now), "slab stored while other waves may still read it");
+        }
+      },
+      [&](int n) {
+        acc += n;
+        full = imax(0, full - n);
+      },
+      [&](int czl, int np) {
+        must(czl == summed, "planes summed in order");
+        for (int k = 0; k < np; ++k)
+          must(slab[slot_of(czl + k)].load(czl + k, now), "slab read before a barrier follows its store");
+        summed += np;
+        if (summed == adj_brick_cz(a, b)) summed = 0;  // the brick is complete
+      });
+  fused_start(g, b.cz0, zend, ring_ops);
+  fused_walk<Staged>(a, bxy, zend, b, bz, ring_ops, march_ops);
+  must(z == zend && bz == bz1 - 1 && summed == 0 && full == 0, "every plane and brick");
+  return ok;
+}
+
+bool check_fused(const AdjGeom& a, Check& ck) {
+  const FusedSplit fs = fused_split(a);
+  REQUIRE(fs.deep >= 1 && fs.nz * fs.deep >= a.z.nb && (fs.nz - 1) * fs.deep < a.z.nb, "workgroups cover the z-bricks");
+  for (int i = 0; i < fs.nz; ++i) {  // a column's bricks have the same planes in every column
+    const int bz0 = i * fs.deep, bz1 = imin(bz0 + fs.deep, a.z.nb);
+    if (!(adj_staged(a) ? check_fused_walk<true>(a, 0, bz0, bz1, ck) : check_fused_walk<false>(a, 0, bz0, bz1, ck)))
+      return false;
+  }
+  return true;
+}
+
 }  // namespace
 }  // namespace bsi
 
@@ -441,6 +548,24 @@ int bsi_check_batch_items(char* msg, int msglen) {
       if (grid <= total && !run(total, grid, true)) break;
     if (!ck.ok) break;
   }
+  std::snprintf(msg, msglen, "%s", ck.msg.c_str());
+  return ck.ok ? 0 : 1;
+}
+
+// 0: the fused SSD step's LDS accesses are ordered by its barriers; 1: a violation
+// (message in msg); -1: invalid geometry.  info: z-bricks per workgroup, and
+// whether the slabs hold every plane of a brick.
+int bsi_check_fused(const int32_t dims[3], const int32_t spacing[3], int32_t info[2], char* msg, int msglen) {
+  VolGeom g;
+  if (make_geom(dims, spacing, &g)) {
+    std::snprintf(msg, msglen, "invalid geometry");
+    return -1;
+  }
+  Check ck;
+  const AdjGeom a = make_adj_geom(g);
+  info[0] = fused_split(a).deep;
+  info[1] = adj_staged(a);
+  check_fused(a, ck);
   std::snprintf(msg, msglen, "%s", ck.msg.c_str());
   return ck.ok ? 0 : 1;
 }
