@@ -172,7 +172,9 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   F3 acc[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n) acc[n] = F3{0.f, 0.f, 0.f};
-  float l2 = 0.f;
+  // squared residuals of the z-brick, and of the bricks before it: no chain of sums grows
+  // with the volume (2 x 4096 x 2000, equal residuals: relative error 2.5e-5 in one chain)
+  float l2 = 0.f, loss = 0.f;
   // This lane's value of a finished plane to F[n], and the contraction of F[n] by this
   // wave's cell into the slabs, a barrier apart.
   auto put = [&](int n, const F3& v) {
@@ -276,11 +278,15 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
       [&](int czl, int np) {
         adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, np,
                           Staged ? czl : czl & 1, tid, kFusedThreads);
+      },
+      [&] {
+        loss += l2;
+        l2 = 0.f;
       });
   fused_walk<Staged>(a, bxy, zend, b, bz, ring_ops, march_ops);
 
   // the workgroup's loss partial: fixed-order tree
-  red[tid] = l2;
+  red[tid] = loss;
   __syncthreads();
   for (int h = kFusedThreads / 2; h > 0; h >>= 1) {
     if (tid < h) red[tid] += red[tid + h];

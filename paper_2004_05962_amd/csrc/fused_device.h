@@ -63,7 +63,7 @@ struct FusedRing {
   Take take;        // (n, cz): Q[n] from the slot of plane cz
   Barrier barrier;
 };
-template <class Shift, class Planes, class Put, class Cells, class Move, class Sum>
+template <class Shift, class Planes, class Put, class Cells, class Move, class Sum, class Close>
 struct FusedMarch {
   Shift shift;      // Q[n] = Q[n + 1]
   Planes planes;    // (z, np): the voxel planes [z, z + np) of one z-tile, with Q
@@ -71,6 +71,7 @@ struct FusedMarch {
   Cells cells;      // (n, czl, np): four waves each contract F[n], F[2], F[3] into the slabs of planes czl .. czl + np - 1
   Move move;        // (n): the accumulators move down by n, zeros above
   Sum sum;          // (czl, np): slabs of planes czl .. czl + np - 1 into brick bz's partials
+  Close close;      // after a brick's last plane: its loss joins the workgroup's
 };
 template <class... T>
 __host__ __device__ __forceinline__ FusedRing<T...> fused_ring(T... t) {
@@ -165,6 +166,7 @@ __host__ __device__ __forceinline__ void fused_walk(const AdjGeom& a, int bxy, i
         r.barrier();
         op.sum(0, adj_brick_cz(a, b));
       }
+      op.close();
       if (more) b = adj_brick_geom(a, ++bz * (a.x.nb * a.y.nb) + bxy);
     }
     if (more) {

@@ -408,7 +408,7 @@ bool check_fused_walk(const AdjGeom& a, int bxy, int bz0, int bz1, Check& ck) {
   int in[4] = {-1, -1, -1, -1};     // control planes in the register sets
   int Q[4] = {-1, -1, -1, -1};      // and in Q
   int acc = b.cz0, full = 0;        // control plane of accumulator 0, accumulators that hold something
-  int summed = 0;                   // planes of brick bz in its partials
+  int summed = 0, closed = 0;       // planes of brick bz in its partials, bricks in the loss
   bool ok = true;
   auto must = [&](bool c, const char* what) {
     if (ok && !c) {
@@ -467,10 +467,14 @@ bool check_fused_walk(const AdjGeom& a, int bxy, int bz0, int bz1, Check& ck) {
           must(slab[slot_of(czl + k)].load(czl + k, now), "slab read before a barrier follows its store");
         summed += np;
         if (summed == adj_brick_cz(a, b)) summed = 0;  // the brick is complete
+      },
+      [&] {
+        must(summed == 0 && z == b.ze, "the brick's loss after its last plane");
+        ++closed;
       });
   fused_start(g, b.cz0, zend, ring_ops);
   fused_walk<Staged>(a, bxy, zend, b, bz, ring_ops, march_ops);
-  must(z == zend && bz == bz1 - 1 && summed == 0 && full == 0, "every plane and brick");
+  must(z == zend && bz == bz1 - 1 && summed == 0 && full == 0 && closed == bz1 - bz0, "every plane and brick");
   return ok;
 }
 
