@@ -184,8 +184,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
     const float* F = fused_smem + lds.F + n * kFusedWaves * kFusedFRow;
     F3 f[kAdjSteps];
 #pragma unroll
-    for (int s = 0; s < kAdjSteps; ++s)
-      f[s] = ldf3(F + (cell.y0 - b.y0 + adj_lane_row(lane, s)) * kFusedFRow + (cell.x0 - b.x0 + lane % kAdjCellX) * 3);
+    for (int s = 0; s < kAdjSteps; ++s) f[s] = ldf3(F + fused_f_at(b, cell, lane, s));
     adj_cell_emit(f, cw, slabs + adj_slab_at(a, Staged ? czl : czl & 1, wave % kAdjWaves), a.cw, a.ch, lane);
   };
   // Per voxel plane, in two stages: (a) T from the 4 contracted planes, the

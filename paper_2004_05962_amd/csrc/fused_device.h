@@ -28,6 +28,13 @@ __host__ __device__ inline FusedLds fused_lds(const AdjGeom& a) {
   l.total = l.slabs + a.slots * kAdjWaves * adj_slab(a);
   return l;
 }
+// Offset in F of this lane's voxel of row 2 s + h of a cell, its column clamped into the
+// cell as the adjoint's loads are (adj_cell_offsets): an infinity in a neighbour's
+// column must not decide how this cell is summed.  (Rows past the cell lie past the
+// brick, and hold zeros.)
+__host__ __device__ inline int fused_f_at(const AdjBrick& b, const AdjCell& c, int lane, int s) {
+  return (c.y0 - b.y0 + adj_lane_row(lane, s)) * kFusedFRow + (c.x0 - b.x0 + imin(lane % kAdjCellX, c.nx - 1)) * 3;
+}
 // Staged floats per thread: one plane's window is at most 825 floats at
 // spacings dx >= 3, dy >= 2, and at most 2640 at spacing 1.
 __host__ __device__ constexpr int fused_loads(int slot) { return (slot + kFusedThreads - 1) / kFusedThreads; }

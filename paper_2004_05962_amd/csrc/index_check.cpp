@@ -478,7 +478,26 @@ bool check_fused_walk(const AdjGeom& a, int bxy, int bz0, int bz1, Check& ck) {
   return ok;
 }
 
+// The voxels of F that each cell of a brick contracts: in F, and of the cell's own columns.
+bool check_fused_cells(const AdjGeom& a, const AdjBrick& b, Check& ck) {
+  for (int w = 0; w < kAdjWaves; ++w) {
+    const AdjCell c = adj_cell_geom(a, b, w);
+    if (c.nx <= 0 || c.ny <= 0) continue;  // the wave contracts nothing
+    for (int lane = 0; lane < kWave; ++lane)
+      for (int s = 0; s < kAdjSteps; ++s) {
+        const int e = fused_f_at(b, c, lane, s), row = e / kFusedFRow, x = b.x0 + e % kFusedFRow / 3;
+        REQUIRE(e >= 0 && row < kFusedWaves && e % kFusedFRow + 3 <= kWave * 3, "fused contraction outside F");
+        REQUIRE(x >= c.x0 && x < c.x0 + c.nx, "fused contraction of another cell's column");
+        REQUIRE(adj_lane_row(lane, s) < c.ny ? b.y0 + row == c.y0 + adj_lane_row(lane, s) : b.y0 + row >= b.ye,
+                "fused contraction of another cell's row");
+      }
+  }
+  return true;
+}
+
 bool check_fused(const AdjGeom& a, Check& ck) {
+  for (int i = 0; i < a.x.nb * a.y.nb; ++i)
+    if (!check_fused_cells(a, adj_brick_geom(a, i), ck)) return false;
   const FusedSplit fs = fused_split(a);
   REQUIRE(fs.deep >= 1 && fs.nz * fs.deep >= a.z.nb && (fs.nz - 1) * fs.deep < a.z.nb, "workgroups cover the z-bricks");
   for (int i = 0; i < fs.nz; ++i) {  // a column's bricks have the same planes in every column
@@ -556,7 +575,7 @@ int bsi_check_batch_items(char* msg, int msglen) {
   return ck.ok ? 0 : 1;
 }
 
-// 0: the fused SSD step's LDS accesses are ordered by its barriers; 1: a violation
+// 0: the fused SSD step's LDS accesses are in bounds and ordered by its barriers; 1: a violation
 // (message in msg); -1: invalid geometry.  info: z-bricks per workgroup, and
 // whether the slabs hold every plane of a brick.
 int bsi_check_fused(const int32_t dims[3], const int32_t spacing[3], int32_t info[2], char* msg, int msglen) {
