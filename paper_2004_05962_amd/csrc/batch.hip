@@ -553,8 +553,10 @@ std::string plan_key(const bsi_batch* p) {
     mix(d.a.g.dx); mix(d.a.g.dy); mix(d.a.g.dz);
   }
   char buf[64];
-  // "k3": the knob tables of this version (an index means another schedule under other tables)
-  std::snprintf(buf, sizeof(buf), "k3-gfx950-cu%d-%016llx", p->cus, (unsigned long long)h);
+  // "k4": the knob tables of this version.  An index means another schedule under other tables
+  // (under k3 the third fwd_items was 8192 items, not chunks of 15 planes), so this
+  // changes with every change of a table, and with kernels that rank the schedules anew.
+  std::snprintf(buf, sizeof(buf), "k4-gfx950-cu%d-%016llx", p->cus, (unsigned long long)h);
   return buf;
 }
 
