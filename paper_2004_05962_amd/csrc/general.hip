@@ -192,22 +192,22 @@ __global__ __launch_bounds__(256) void gen_tables3_kernel(GenTables3 p) {
 // 1.5 x 1.2 x 1.1: 54 against 207.
 
 // The cell's weight matrices from the tables (as adj_cell_weights).
-__device__ __forceinline__ AdjWeights gen_cell_weights(const AdjCell& c, const int* __restrict__ tx,
+__device__ __forceinline__ AdjWeights gen_cell_weights(const VolGeom& g, const AdjCell& c, const int* __restrict__ tx,
                                                        const float* __restrict__ wx, const int* __restrict__ ty,
                                                        const float* __restrict__ wy, int lane) {
   const int m = lane % kAdjTile, q = lane / kAdjTile;
   // weight of the cell's voxel v (of n, the first at v0) at control index c0 + m
-  auto weight = [&](const int* tile, const float* w, int v0, int n, int v, int c0) {
-    const int u = v0 + min(v, n - 1), l = c0 + m - tile[u];
+  auto weight = [&](const int* tile, const float* w, int v0, int n, int v, int c0, int size) {
+    const int u = gen_weight_voxel(v0, n, v, size), l = c0 + m - tile[u];
     const float b = w[4 * u + (l & 3)];
     return v < n && (uint32_t)l < 4u ? (b == 0.f ? -0.f : b) : 0.f;
   };
   AdjWeights r;
 #pragma unroll
-  for (int g = 0; g < 2; ++g) {
+  for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) r.x[g][i] = weight(tx, wx, c.x0, c.nx, kAdjTile * g + 4 * q + i, c.cx0);
-    r.y[g] = weight(ty, wy, c.y0, c.ny, adj_step_row(g, q), c.cy0);
+    for (int i = 0; i < 4; ++i) r.x[h][i] = weight(tx, wx, c.x0, c.nx, kAdjTile * h + 4 * q + i, c.cx0, g.nx);
+    r.y[h] = weight(ty, wy, c.y0, c.ny, adj_step_row(h, q), c.cy0, g.ny);
   }
   return r;
 }
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI
   const GenTiles tiles{tx, ty};
   const AdjBrick b = gen_brick(a, tiles, fz, brick);
   adj_brick_of<true, Staged>(dfield, part, a, tiles, b, brick, gen_brick_cz(a, b), GenZ(wz, fz, b.z0, b.cz0, a.g.gz),
-                             [&](const AdjCell& c) { return gen_cell_weights(c, tx, wx, ty, wy, threadIdx.x % kWave); },
+                             [&](const AdjCell& c) { return gen_cell_weights(a.g, c, tx, wx, ty, wy, threadIdx.x % kWave); },
                              gen_slabs, threadIdx.x);
 }
 

@@ -147,6 +147,12 @@ inline AdjGeom make_gen_adj(const GenGeom& q, const VolGeom& vol) {
   return a;
 }
 
+// The voxel whose table entries lane (q, m) reads for voxel v of a cell's n from v0 on an
+// axis of `size` voxels; a cell past the volume (n = 0) reads the last one's.
+__host__ __device__ inline int gen_weight_voxel(int v0, int n, int v, int size) {
+  return imin(v0 + imax(0, imin(v, n - 1)), size - 1);
+}
+
 // Pass 2: the bricks whose voxels meet the support [first(c - 3), first(c + 1)) of
 // control index c, along z those of tiles c - 3 .. c that hold voxels.
 struct GenMap {

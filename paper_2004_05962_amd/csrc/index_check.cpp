@@ -344,6 +344,16 @@ bool check_general_adjoint(const GenGeom& q, const VolGeom& vol, Check& ck) {
             "z-bricks start on tile boundaries");
     REQUIRE(tile[2][(size_t)b.ze - 1] - b.cz0 + 4 == gen_brick_cz(a, b), "control planes of the brick");
     if (!check_brick(a, tiles, b, gen_brick_cz(a, b), ck)) return false;
+    for (int w = 0; w < kAdjWaves; ++w) {
+      const AdjCell c = adj_cell_of(a, tiles, b, w);
+      if (adj_staged(a) && (c.nx <= 0 || c.ny <= 0)) continue;  // the wave reads no weights
+      for (int v = 0; v < kAdjCellX; ++v) {
+        const int ux = gen_weight_voxel(c.x0, c.nx, v, q.x.n), uy = gen_weight_voxel(c.y0, c.ny, v % kAdjCellY, q.y.n);
+        REQUIRE(0 <= ux && ux < q.x.n && 0 <= uy && uy < q.y.n, "cell weights read outside the axis's tables");
+        REQUIRE(v >= c.nx || ux == c.x0 + v, "cell weights of the lane's voxel");
+        REQUIRE(v >= c.ny || v >= kAdjCellY || uy == c.y0 + v, "cell weights of the lane's row");
+      }
+    }
     Cx[(size_t)(id % a.x.nb)] = b.Cx;
     Cy[(size_t)(id / a.x.nb % a.y.nb)] = b.Cy;
     Cz[(size_t)(id / a.x.nb / a.y.nb)] = gen_brick_cz(a, b);
