@@ -163,7 +163,7 @@ hipError_t launch_adjoint_partials(const float* dfield, const AdjGeom& a, const 
 
 hipError_t launch_adjoint_reduce(const float* part, float* grad, const AdjGeom& a, hipStream_t s) {
   const int64_t nblk = adj_gather_blocks(a);
-  if (nblk >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;  // a field far beyond device memory
+  if (nblk > kMaxLaunchThreads / kGatherThreads) return hipErrorInvalidConfiguration;  // 2^32 control points
   if (a.part_bytes != 0)
     hipLaunchKernelGGL(adj_pass2_kernel<true>, dim3((unsigned)nblk), dim3(kGatherThreads), 0, s, part, grad, a);
   else

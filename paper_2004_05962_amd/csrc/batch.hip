@@ -275,18 +275,10 @@ void drop_graph(bsi_batch* p) {
   p->graph = nullptr;
 }
 
-// Workgroups of a pass: one per item, or a persistent grid of per_cu per CU.
-// A pass of 2^31 items or more always runs persistent (on the largest grid).
-int64_t pass_grid(const bsi_batch* p, int64_t total, int per_cu) {
-  int64_t grid = per_cu == 0 ? total : std::min<int64_t>(total, (int64_t)per_cu * p->cus);
-  return std::min<int64_t>(grid, 0x7fffffff);
-}
-bool pass_persistent(int64_t total, int per_cu) { return per_cu > 0 || total > 0x7fffffff; }
-
 template <class T>
 void launch_fwd_sized(const bsi_batch* p, int64_t total, int per_cu, bool nt, hipStream_t s) {
-  const dim3 gd((unsigned)pass_grid(p, total, per_cu)), bd(T::threads);
-  const bool pers = pass_persistent(total, per_cu);
+  const auto [blocks, pers] = pass_grid(total, per_cu, p->cus, T::threads);
+  const dim3 gd((unsigned)blocks), bd(T::threads);
   if (!pers && !nt)
     hipLaunchKernelGGL((batch_fwd_kernel<T, false, false>), gd, bd, 0, s, p->d_desc, p->count, total, p->lut);
   else if (!pers)
@@ -320,8 +312,9 @@ hipError_t launch_pass(bsi_batch* p, int pass, hipStream_t s) {
     return hipErrorInvalidValue;  // pass 1 is launched per class (launch_adj1_class)
   } else {
     const int per_cu = kPtsPerCu[p->cfg.k[kKPtsPerCu]];
-    const dim3 gd((unsigned)pass_grid(p, total, per_cu)), bd(kPtThreads);
-    if (!pass_persistent(total, per_cu))
+    const auto [blocks, pers] = pass_grid(total, per_cu, p->cus, kPtThreads);
+    const dim3 gd((unsigned)blocks), bd(kPtThreads);
+    if (!pers)
       hipLaunchKernelGGL(batch_adj2_kernel<false>, gd, bd, 0, s, p->d_desc, p->count, total);
     else
       hipLaunchKernelGGL(batch_adj2_kernel<true>, gd, bd, 0, s, p->d_desc, p->count, total);
@@ -336,8 +329,9 @@ void launch_adj1(const bsi_batch* p, int first, int n, int64_t ct, hipStream_t s
   size_t lds = 0;
   for (int i = first; i < first + n; ++i) lds = std::max(lds, adj_lds_bytes(p->cls_host[(size_t)i].a));
   const VolDesc* v = p->d_cls + first;
-  const dim3 gd((unsigned)pass_grid(p, ct, per_cu)), bd(kAdjThreads);
-  if (!pass_persistent(ct, per_cu))
+  const auto [blocks, pers] = pass_grid(ct, per_cu, p->cus, kAdjThreads);
+  const dim3 gd((unsigned)blocks), bd(kAdjThreads);
+  if (!pers)
     hipLaunchKernelGGL((batch_adj1_kernel<AllTiles, false>), gd, bd, lds, s, v, n, ct, p->lut);
   else
     hipLaunchKernelGGL((batch_adj1_kernel<AllTiles, true>), gd, bd, lds, s, v, n, ct, p->lut);

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 #include "bsi.h"
@@ -42,6 +43,10 @@ size_t adj_workspace_bytes(const AdjGeom& a);
 size_t adj_limit_bytes(const VolGeom& g);
 constexpr size_t kAdjScratchBytes = BSI_ADJOINT_NOALLOC_MAX_BYTES / 8 * 9;
 
+// Threads of one launch: a dispatch counts them in 32 bits, and a larger grid is cut
+// without an error.
+constexpr int64_t kMaxLaunchThreads = ((int64_t)1 << 32) - 1;
+
 // Forward launch shape (workgroups of kFwdRows waves; z split into chunks).
 struct FwdLaunch {
   int nbx, nby, nbz, zchunk;
@@ -61,6 +66,18 @@ constexpr int kFwdChunkBatch = 15, kFwdLeastItems = 64;
 // about this deep (0: as deep as the target leaves).
 FwdLaunch make_fwd_launch(const VolGeom& g, long target = kFwdTargetBlocks, int width = kWave, int rows = kFwdRows,
                           int planes = 0);
+// Workgroups of a pass of the batch over `total` items: one per item (per_cu = 0) or
+// per_cu per CU, and whether they take more than one item each, which a pass above
+// kMaxLaunchThreads always does.
+struct PassGrid {
+  int64_t blocks;
+  bool persistent;
+};
+inline PassGrid pass_grid(int64_t total, int per_cu, int cus, int threads) {
+  const int64_t most = kMaxLaunchThreads / threads;
+  const int64_t grid = per_cu == 0 ? total : std::min<int64_t>(total, (int64_t)per_cu * cus);
+  return PassGrid{std::min<int64_t>(grid, most), per_cu > 0 || total > most};
+}
 // Rows per span of the span forward (fwd_span), 0 when a span of one row does not fit.
 int span_rows(const VolGeom& g, int C);
 
@@ -101,6 +118,7 @@ struct GenGeom {
 };
 int32_t make_gen_geom(const int32_t dims[3], const float spacing[3], const float origin[3], GenGeom* q,
                       VolGeom* g);
+FwdLaunch make_gen_fwd_launch(const VolGeom& g, const GenGeom& q);
 hipError_t launch_forward_general(const float* grid, float* field, const VolGeom& g, const GenGeom& q,
                                   hipStream_t s);
 size_t general_workspace_bytes(const GenGeom& q, const VolGeom& g);

@@ -95,7 +95,9 @@ FwdLaunch make_fwd_launch(const VolGeom& g, long target, int width, int rows, in
   int chunks = (int)((target + base - 1) / base);
   if (planes > 0) {
     const int deep = std::max(2, (planes + g.dz - 1) / g.dz);
-    chunks = std::max(chunks, (tiles_z + deep - 1) / deep);
+    // (narrow volumes of very many rows: as many chunks as a launch's threads allow)
+    const long most = std::max(1L, (long)(kMaxLaunchThreads / ((int64_t)width * rows * base)));
+    chunks = std::max(chunks, (int)std::min<long>(most, (tiles_z + deep - 1) / deep));
   }
   if (chunks > tiles_z) chunks = tiles_z;
   if (chunks < 1) chunks = 1;

@@ -368,8 +368,7 @@ hipError_t launch_ssd_fused(const float* grid, const float* moving, const float*
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t nblk = adj_gather_blocks(a);
-  if (nblk + 1 >= ((int64_t)1 << 31))
-    return hipErrorInvalidConfiguration;  // a field far beyond device memory
+  if (nblk + 1 > kMaxLaunchThreads / kTailThreads) return hipErrorInvalidConfiguration;  // 2^32 control points
   const auto tail = a.part_bytes != 0 ? &fused_tail_kernel<true> : &fused_tail_kernel<false>;
   hipLaunchKernelGGL(tail, dim3((unsigned)(nblk + 1)), dim3(kTailThreads), 0, s, part, grad, descend_grid, eta,
                      descend_grid != nullptr ? 1 : 0, lpart, (int)items, loss, a, (int)nblk);

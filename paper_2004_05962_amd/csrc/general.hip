@@ -325,8 +325,7 @@ int32_t make_gen_geom(const int32_t dims[3], const float spacing[3], const float
   return check_control_plane(g->gx, g->gy);
 }
 
-hipError_t launch_forward_general(const float* grid, float* field, const VolGeom& g, const GenGeom& q,
-                                  hipStream_t s) {
+FwdLaunch make_gen_fwd_launch(const VolGeom& g, const GenGeom& q) {
   const int nbx = (g.nx + kWave - 1) / kWave, nby = (g.ny + kFwdRows - 1) / kFwdRows;
   const long base = (long)nbx * nby;
   int chunks = (int)((kFwdTargetBlocks + base - 1) / base);
@@ -336,13 +335,20 @@ hipError_t launch_forward_general(const float* grid, float* field, const VolGeom
   // 128 that the target leaves; 512 x 300 x 200, spacing 4: 76 and 82; 511 x 512 x 256
   // at 5.3 x 4.7 x 5: 172 and 200; 512 x 512 x 256, spacing 3: 163 with 48, 177 with 25)
   const int planes = q.z.s < 4.f ? 48 : 25;
-  chunks = std::max(chunks, (g.nz + planes - 1) / planes);
+  // (narrow volumes of very many rows: as many chunks as a launch's threads allow)
+  const long most = std::max(1L, (long)(kMaxLaunchThreads / ((int64_t)kFwdThreads * base)));
+  chunks = std::max(chunks, (int)std::min<long>(most, (g.nz + planes - 1) / planes));
   chunks = std::max(1, std::min(chunks, g.nz));
   const int zchunk = (g.nz + chunks - 1) / chunks;
-  const int nbz = (g.nz + zchunk - 1) / zchunk;
+  return FwdLaunch{nbx, nby, (g.nz + zchunk - 1) / zchunk, zchunk};
+}
+
+hipError_t launch_forward_general(const float* grid, float* field, const VolGeom& g, const GenGeom& q,
+                                  hipStream_t s) {
+  const auto [nbx, nby, nbz, zchunk] = make_gen_fwd_launch(g, q);
   // rows on 64-byte boundaries: non-temporal stores; otherwise edge stores
   const bool aligned = (g.nx * 12) % 64 == 0 && reinterpret_cast<uintptr_t>(field) % 64 == 0;
-  const dim3 gd((unsigned)(base * nbz)), bd(kFwdThreads);
+  const dim3 gd((unsigned)((long)nbx * nby * nbz)), bd(kFwdThreads);
   using T1 = FwdTile<kFwdRows, 1, 1>;
   using T3 = FwdTile<kFwdRows, 1, 1, 3>;
   if (q.x.s >= 3.f && q.y.s >= 3.f) {
@@ -363,7 +369,7 @@ hipError_t launch_adjoint_general(const float* dfield, float* grad, const GenGeo
                                   hipStream_t s) {
   const AdjGeom a = make_gen_adj(q, g);
   const int64_t nbricks = (int64_t)a.x.nb * a.y.nb * a.z.nb, nblk = adj_gather_blocks(a);
-  if (nbricks > 0x7fffffffL || nblk > 0x7fffffffL) return hipErrorInvalidValue;
+  if (nbricks > kMaxLaunchThreads / kAdjThreads || nblk > kMaxLaunchThreads / kGatherThreads) return hipErrorInvalidValue;
   GenWork wk;
   gen_layout(q, a, workspace, &wk);
   GenTables3 tp;

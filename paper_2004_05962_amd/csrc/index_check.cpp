@@ -603,4 +603,31 @@ int bsi_check_fused(const int32_t dims[3], const int32_t spacing[3], int32_t inf
   return ck.ok ? 0 : 1;
 }
 
+// The largest thread counts of the forward launches of one volume, and of a batch that
+// holds it alone (every shape and z split): aligned (spacing), scalar, real spacing
+// (the same spacing, origin 0), batched.
+int bsi_check_launch_threads(const int32_t dims[3], const int32_t spacing[3], int64_t out[4]) {
+  VolGeom g, gg;
+  GenGeom q;
+  const float s[3] = {(float)spacing[0], (float)spacing[1], (float)spacing[2]}, o[3] = {0.f, 0.f, 0.f};
+  if (make_geom(dims, spacing, &g) || make_gen_geom(dims, s, o, &q, &gg)) return -1;
+  auto threads = [](const FwdLaunch& L, int64_t t) { return (int64_t)L.nbx * L.nby * L.nbz * t; };
+  auto shape = [&](auto tile, int planes) {
+    using T = decltype(tile);
+    return threads(make_fwd_launch(g, kFwdTargetBlocks, T::width, T::rows, planes), T::threads);
+  };
+  out[0] = std::max(shape(FwdTileDefault{}, kFwdChunk), shape(FwdTile<2, 8, 1>{}, kFwdChunkWide));
+  out[1] = std::max(shape(FwdTile<kFwdRows, 1, 4>{}, kFwdChunk), shape(FwdTileDefault{}, kFwdChunk));
+  out[2] = threads(make_gen_fwd_launch(gg, q), kFwdThreads);
+  out[3] = 0;
+  for (const auto& [target, planes] : {std::pair{512L, 0}, {2048L, 0}, {(long)kFwdLeastItems, kFwdChunkBatch}})
+    for (const auto& [width, rows] : {std::pair{64, 4}, {128, 2}, {64, 8}}) {
+      const int64_t items = threads(make_fwd_launch(g, target, width, rows, planes), 1);
+      const PassGrid p = pass_grid(items, 0, 256, width * rows);
+      if (!p.persistent && p.blocks != items) return 1;
+      out[3] = std::max(out[3], p.blocks * width * rows);
+    }
+  return 0;
+}
+
 }  // extern "C"
