@@ -45,30 +45,7 @@ namespace {
 // (62).  Starting the next tile's gathers before the border, its control plane a
 // tile earlier, took more registers than 128: 68 us.
 
-// Loads of control plane cz's window into registers (thread tid takes floats
-// e = tid + k kFusedThreads of the Cy x Cx x 3 window), and their store into a
-// slot with row pitch x.cm points.
-template <int L>
-struct FusedStage {
-  int src[L];  // float offset within a control plane, -1 outside the window
-  int dst[L];
-};
-
-template <int L>
-__device__ __forceinline__ FusedStage<L> fused_stage_map(const AdjGeom& a, const AdjBrick& b, int tid) {
-  FusedStage<L> m;
-  const int wrow = b.Cx * 3;
-#pragma unroll
-  for (int k = 0; k < L; ++k) {
-    const int e = tid + k * kFusedThreads;
-    const int cyl = e / wrow, i = e - cyl * wrow;
-    const bool in = cyl < b.Cy;
-    m.src[k] = in ? ((b.cy0 + cyl) * a.g.gx + b.cx0) * 3 + i : -1;
-    m.dst[k] = cyl * a.x.cm * 3 + i;
-  }
-  return m;
-}
-
+// Loads of control plane cz's window into registers, and their store into a slot.
 template <int L>
 __device__ __forceinline__ void fused_fetch(const float* __restrict__ grid, const VolGeom& g, const FusedStage<L>& m,
                                             int cz, float (&r)[L]) {

@@ -35,10 +35,35 @@ __host__ __device__ inline FusedLds fused_lds(const AdjGeom& a) {
 __host__ __device__ inline int fused_f_at(const AdjBrick& b, const AdjCell& c, int lane, int s) {
   return (c.y0 - b.y0 + adj_lane_row(lane, s)) * kFusedFRow + (c.x0 - b.x0 + imin(lane % kAdjCellX, c.nx - 1)) * 3;
 }
-// Staged floats per thread: one plane's window is at most 825 floats at
-// spacings dx >= 3, dy >= 2, and at most 2640 at spacing 1.
+// Staged floats per thread.  One plane's window is at most 1653 floats (29 x 19 points, at
+// spacing 1), and at most 1024 from spacings 3 x 2 on.  One load more, which no
+// window needs, cost the two-plane kernels 12 to 24 bytes of scratch per lane.
 __host__ __device__ constexpr int fused_loads(int slot) { return (slot + kFusedThreads - 1) / kFusedThreads; }
-constexpr int kFusedMaxLoads = 3;
+constexpr int kFusedMaxLoads = 2;
+static_assert(fused_loads((kAdjCellsX * adj_cell(1) + 3) * (kAdjCellsY * kAdjCellY + 3) * 3) == kFusedMaxLoads);
+
+// Staging map: thread tid takes floats e = tid + k kFusedThreads of the Cy x Cx x 3
+// window of a control plane, into a slot with row pitch x.cm points.
+template <int L>
+struct FusedStage {
+  int src[L];  // float offset within a control plane, -1 outside the window
+  int dst[L];
+};
+
+template <int L>
+__host__ __device__ inline FusedStage<L> fused_stage_map(const AdjGeom& a, const AdjBrick& b, int tid) {
+  FusedStage<L> m;
+  const int wrow = b.Cx * 3;
+#pragma unroll
+  for (int k = 0; k < L; ++k) {
+    const int e = tid + k * kFusedThreads;
+    const int cyl = e / wrow, i = e - cyl * wrow;
+    const bool in = cyl < b.Cy;
+    m.src[k] = in ? ((b.cy0 + cyl) * a.g.gx + b.cx0) * 3 + i : -1;
+    m.dst[k] = cyl * a.x.cm * 3 + i;
+  }
+  return m;
+}
 
 // A workgroup takes `deep` consecutive z-bricks of one (x, y) brick column: it
 // marches on through their borders with the planes it has contracted, and

@@ -505,9 +505,42 @@ bool check_fused_cells(const AdjGeom& a, const AdjBrick& b, Check& ck) {
   return true;
 }
 
+// The staging of a brick's control planes: every float of the window by one thread, from
+// inside the grid's plane to its place in the slot.
+template <int L>
+bool check_fused_stage(const AdjGeom& a, const AdjBrick& b, const FusedLds& lds, Check& ck) {
+  std::vector<int> hit((size_t)lds.slot, 0);
+  for (int tid = 0; tid < kFusedThreads; ++tid) {
+    const FusedStage<L> m = fused_stage_map<L>(a, b, tid);
+    for (int k = 0; k < L; ++k) {
+      if (m.src[k] < 0) continue;
+      REQUIRE(m.src[k] < (int64_t)a.g.gx * a.g.gy * 3, "staging load outside the control plane");
+      REQUIRE(m.dst[k] >= 0 && m.dst[k] < lds.slot, "staging store outside the slot");
+      const int row = m.dst[k] / (a.x.cm * 3), i = m.dst[k] % (a.x.cm * 3);
+      REQUIRE(m.src[k] == ((b.cy0 + row) * a.g.gx + b.cx0) * 3 + i, "staged float of the window");
+      ++hit[(size_t)m.dst[k]];
+    }
+  }
+  for (int y = 0; y < b.Cy; ++y)
+    for (int i = 0; i < b.Cx * 3; ++i)
+      REQUIRE(hit[(size_t)(y * a.x.cm * 3 + i)] == 1, "every float of the window is staged once");
+  return true;
+}
+
 bool check_fused(const AdjGeom& a, Check& ck) {
-  for (int i = 0; i < a.x.nb * a.y.nb; ++i)
-    if (!check_fused_cells(a, adj_brick_geom(a, i), ck)) return false;
+  const FusedLds lds = fused_lds(a);
+  REQUIRE(lds.total * (int64_t)sizeof(float) <= 160 * 1024, "LDS request of a workgroup");
+  REQUIRE(lds.ring >= lds.F + (adj_staged(a) ? 4 : 2) * kFusedWaves * kFusedFRow && lds.red >= lds.ring + 2 * lds.slot &&
+              lds.slabs >= lds.red + kFusedThreads && lds.slabs % 4 == 0 &&
+              lds.total >= lds.slabs + adj_slab_at(a, a.slots - 1, kAdjWaves - 1) + adj_slab(a),
+          "LDS regions apart");
+  REQUIRE(fused_loads(lds.slot) <= kFusedMaxLoads, "staged loads per thread");
+  for (int i = 0; i < a.x.nb * a.y.nb; ++i) {
+    const AdjBrick b = adj_brick_geom(a, i);
+    if (!check_fused_cells(a, b, ck)) return false;
+    if (!(fused_loads(lds.slot) <= 1 ? check_fused_stage<1>(a, b, lds, ck) : check_fused_stage<kFusedMaxLoads>(a, b, lds, ck)))
+      return false;
+  }
   const FusedSplit fs = fused_split(a);
   REQUIRE(fs.deep >= 1 && fs.nz * fs.deep >= a.z.nb && (fs.nz - 1) * fs.deep < a.z.nb, "workgroups cover the z-bricks");
   for (int i = 0; i < fs.nz; ++i) {  // a column's bricks have the same planes in every column
