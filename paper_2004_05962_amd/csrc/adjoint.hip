@@ -7,14 +7,14 @@
 
 namespace bsi {
 
-template <bool Staged>
-__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI_ADJ_WPE))) void adj_pass1_kernel(
+template <bool Staged, bool Narrow>
+__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(adj_wpe(Narrow)))) void adj_pass1_kernel(
     const float* __restrict__ dfield, float* __restrict__ part, AdjGeom a, const float* __restrict__ lut) {
   extern __shared__ float adj_slabs[];
   const int nbricks = a.x.nb * a.y.nb * a.z.nb;
   const int brick = xcd_remap(blockIdx.x, gridDim.x);
   if (brick >= nbricks) return;  // uniform over the workgroup
-  adj_brick<true, Staged>(dfield, part, a, lut, brick, adj_slabs, threadIdx.x);
+  adj_brick<true, Staged, Narrow>(dfield, part, a, lut, brick, adj_slabs, threadIdx.x);
 }
 
 template <bool Small>
@@ -67,12 +67,15 @@ AdjDepth adj_depth(const AdjGeom& a, int tiles, double dz) {
   AdjDepth d;
   const int plane = kAdjWaves * adj_slab(a);  // slab floats of one control plane
   const int fit3 = kAdjSlabFloats3 / plane - 3, fit2 = kAdjSlabFloats2 / plane - 3;
-  d.fit = fit3 >= kAdjMinStaged ? fit3 : fit2;
-  const bool staged = d.fit >= kAdjMinStaged;
+  // (fewer planes than that with the slabs of three workgroups per CU: of two)
+  auto deep = [&](int fit) { return fit * dz >= kAdjMinStagedDeep; };
+  d.fit = fit3 >= kAdjMinStaged && deep(fit3) ? fit3 : fit2;
+  const long base = (long)a.x.nb * a.y.nb;
+  const bool many = base * (tiles * dz / kAdjDepthTwo) >= 4 * kAdjCus;
+  const bool staged = d.fit >= kAdjMinStaged && (deep(d.fit) || !many);
   d.most = imin(tiles, imax(1, (int)((staged ? kAdjDepthStaged : kAdjDepthTwo) / dz)));
   if (staged) d.most = imin(d.most, d.fit);
   // z-bricks: the fewest of those with the least modelled time (kAdjCuCost)
-  const long base = (long)a.x.nb * a.y.nb;
   const int most = (tiles + d.most - 1) / d.most;
   int nbz = most;
   double best = 0.;
@@ -154,10 +157,9 @@ hipError_t launch_adjoint_partials(const float* dfield, const AdjGeom& a, const 
                                   hipStream_t s) {
   const long nbricks = (long)a.x.nb * a.y.nb * a.z.nb;
   const dim3 grid((unsigned)nbricks), block(kAdjThreads);
-  if (adj_staged(a))
-    hipLaunchKernelGGL(adj_pass1_kernel<true>, grid, block, adj_lds_bytes(a), s, dfield, part, a, lut);
-  else
-    hipLaunchKernelGGL(adj_pass1_kernel<false>, grid, block, adj_lds_bytes(a), s, dfield, part, a, lut);
+  const auto kernel = adj_narrow(a) ? (adj_staged(a) ? &adj_pass1_kernel<true, true> : &adj_pass1_kernel<false, true>)
+                                    : (adj_staged(a) ? &adj_pass1_kernel<true, false> : &adj_pass1_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, grid, block, adj_lds_bytes(a), s, dfield, part, a, lut);
   return hipGetLastError();
 }
 

@@ -49,12 +49,23 @@ namespace bsi {
 #ifndef BSI_ADJ_WPE
 #define BSI_ADJ_WPE 3
 #endif
+// Narrow cells (adj_narrow) hold half of that: 6 (300 x 256 x 200, spacing 1: 212 us, 230 at 4
+// and 5; what spills at 6 lies in adj_cell_sparse).
+constexpr int kAdjWpeNarrow = 6;
+__host__ __device__ constexpr int adj_wpe(bool narrow) { return narrow ? kAdjWpeNarrow : BSI_ADJ_WPE; }
 constexpr int kAdjCellsX = 2, kAdjCellsY = 2;      // cells of a brick, one per wave
 constexpr int kAdjWaves = kAdjCellsX * kAdjCellsY;
 constexpr int kAdjThreads = kAdjWaves * kWave;
 constexpr int kAdjTile = 16;                       // points per axis of a matrix tile
 constexpr int kAdjCellX = 32, kAdjCellY = 8;       // voxel columns of a cell
-constexpr int kAdjSteps = 4;                       // a lane's voxels: rows 2 s + h
+// A lane's voxels.  Cells of up to 32 columns: row s is 2 s + h, h = lane / 32.  Narrow: cells
+// of up to 16 (spacing 1, adj_narrow), 16 lanes a row: row s is adj_step_row(s, lane / 16),
+// which is the first product's operand as it stands, half the accumulators and loads, and no
+// second half of products.  Pass 1 of 300 x 256 x 200 at spacing 1: 212 us, with 32 lanes a
+// row, 13 of them at work, 272; of 118 x 357 x 486 286 and 353 (then 183 and 254 by
+// adj_combine_slabs).
+template <bool Narrow>
+constexpr int kAdjSteps = Narrow ? 2 : 4;
 // The brick depth rule (make_adj_geom), measured on pass 1 alone:
 // - the number of z-bricks: a CU reads at most about 28 bytes per ns, whatever
 //   it holds (a plane of a brick in 0.44 us), and all CUs together 22 each (0.54), so
@@ -68,12 +79,17 @@ constexpr int kAdjSteps = 4;                       // a lane's voxels: rows 2 s 
 // - LDS of those slabs: three workgroups per CU, or, for the wide windows of
 //   spacings 2 and 3, two (512 x 228 x 385, spacing 3: 129 us; with two-plane
 //   slabs 138 to 147, as before them 145 to 152).
-// - depth with two-plane slabs (spacing 1, or 1 along z): 30 voxels (200^3,
-//   spacing 1: 144 us against 218 at 48; 174 before).
+// - depth with two-plane slabs (spacing 1, or 1 along z): 20 voxels (both passes at
+//   spacing 1: 300 x 256 x 200 279 us, 285 at 30, 280 at 16; 512 x 512 x 100 440, 462 and 464;
+//   128^3 67, 74 and 60; 200^3 141, 135 and 138).
+// - whole slabs of fewer than kAdjMinStagedDeep planes (spacings 4 to 7 x 1 x 1), whose
+//   partials are 4/3 of their voxels' points, only where bricks of that depth would not
+//   fill the CUs four times: 300 x 260 x 400 at 4 x 1 x 1 256 us with them, 224 without; 200^3
+//   at 6 x 1 x 1 86 and 89.
 constexpr int kAdjCus = 256;
 constexpr double kAdjCuCost = 0.9, kAdjBrickCost = 4;
-constexpr int kAdjDepthStaged = 96, kAdjDepthTwo = 30, kAdjDepthMost = 48;
-constexpr int kAdjMinStaged = 8;                                     // tiles a brick with whole slabs holds at least
+constexpr int kAdjDepthStaged = 96, kAdjDepthTwo = 20, kAdjDepthMost = 48;
+constexpr int kAdjMinStaged = 8, kAdjMinStagedDeep = 10;             // tiles and planes, of a brick with whole slabs
 constexpr int kAdjSlabFloats3 = 13312, kAdjSlabFloats2 = 20000;      // slabs of 3 and of 2 workgroups per CU
 // Shallower bricks than the depth bounds are used up to this workspace size,
 // and deeper ones, of kAdjDepthMost planes or all of them, where only those fit
@@ -185,22 +201,34 @@ __host__ __device__ inline int adj_slab_at(const AdjGeom& a, int slot, int w) { 
 __host__ __device__ inline int adj_slab_point(const AdjGeom& a, int c, int cyl, int cxl) {
   return (c * a.ch + cyl) * a.cw + cxl;
 }
+// Cells of one matrix tile's width (kAdjSteps).
+__host__ __device__ inline bool adj_narrow(const AdjGeom& a) { return a.cell <= kAdjTile; }
 // Slots: every plane of the brick, or two in turn.
 __host__ __device__ inline bool adj_staged(const AdjGeom& a) { return a.slots >= a.z.cm; }
 __host__ __device__ inline size_t adj_lds_bytes(const AdjGeom& a) {
   return (size_t)a.slots * kAdjWaves * adj_slab(a) * sizeof(float);
 }
 
-// This lane's voxels within the plane: byte offset, from the cell's first voxel,
-// of voxel v of row 2 s + h, clamped into the cell so that every lane loads from
+// The row that lanes 16 k .. 16 k + 15 hold in step t of the first product,
+// after the row swaps of adj_cell_emit.
+__host__ __device__ constexpr int adj_step_row(int t, int k) { return 4 * t + 2 * (k & 1) + (k >> 1); }
+// This lane's voxels within the plane: their column in the cell and rows, and their byte
+// offsets from the cell's first voxel, clamped into the cell so that every lane loads from
 // a valid address without a branch (a clamped voxel's weights are zero).  8 rows
 // of at most 2^20 voxels: below 2^32 bytes.
-__host__ __device__ inline int adj_lane_row(int lane, int s) { return 2 * s + lane / kAdjCellX; }
-__host__ __device__ inline void adj_cell_offsets(int nx, int cnx, int cny, int lane, uint32_t (&off)[kAdjSteps]) {
-  const int v = imin(lane % kAdjCellX, cnx - 1);
+template <bool Narrow>
+__host__ __device__ constexpr int adj_lane_col(int lane) { return lane % (Narrow ? kAdjTile : kAdjCellX); }
+template <bool Narrow>
+__host__ __device__ constexpr int adj_lane_row(int lane, int s) {
+  return Narrow ? adj_step_row(s, lane / kAdjTile) : 2 * s + lane / kAdjCellX;
+}
+template <bool Narrow>
+__host__ __device__ inline void adj_cell_offsets(int nx, int cnx, int cny, int lane,
+                                                 uint32_t (&off)[kAdjSteps<Narrow>]) {
+  const int v = imin(adj_lane_col<Narrow>(lane), cnx - 1);
 #pragma unroll
-  for (int s = 0; s < kAdjSteps; ++s)
-    off[s] = ((uint32_t)imin(adj_lane_row(lane, s), cny - 1) * (uint32_t)nx + (uint32_t)v) * 12u;
+  for (int s = 0; s < kAdjSteps<Narrow>; ++s)
+    off[s] = ((uint32_t)imin(adj_lane_row<Narrow>(lane, s), cny - 1) * (uint32_t)nx + (uint32_t)v) * 12u;
 }
 
 // Load of three floats through a buffer resource (uniform base, 32-bit lane offset:
@@ -229,9 +257,6 @@ __host__ __device__ inline uint32_t adj_cell_bytes(int nx, int cnx, int cny) {
 struct AdjWeights {
   float x[2][4], y[2];
 };
-// The row that lanes 16 k .. 16 k + 15 hold in step t of the first product,
-// after the row swaps of adj_cell_emit.
-__host__ __device__ constexpr int adj_step_row(int t, int k) { return 4 * t + 2 * (k & 1) + (k >> 1); }
 // Weight of voxel o0 + v (o0: the offset in its tile of the cell's first voxel, `in`: v lies in the cell)
 // at the cell's control index c; rows: the weight rows of this spacing.  Every
 // lane loads, from a row and entry within the table.
@@ -283,8 +308,9 @@ __device__ __forceinline__ float adj_row_ror(float v) {
 
 // E of a plane that holds an infinity or a NaN, whose product with a zero
 // weight would reach the whole window: the same sums over each point's own
-// support only.  f[g][t]: the first product's operands of half g.
+// support only.  f[g][t]: the first product's operands of half g, of G halves.
 // Lane (q, m) forms columns 4 q + j, row m.
+template <int G>
 __device__ __forceinline__ adj_f4 adj_cell_sparse(const float (&f)[2][2], const AdjWeights& w, int lane) {
   const int m = lane % kAdjTile, q = lane / kAdjTile;
   adj_f4 e{0.f, 0.f, 0.f, 0.f};
@@ -294,7 +320,7 @@ __device__ __forceinline__ adj_f4 adj_cell_sparse(const float (&f)[2][2], const 
     for (int k = 0; k < 4; ++k) {  // the row that lanes 16 k .. hold in step t
       const float wy = __shfl(w.y[t], kAdjTile * k + m);
 #pragma unroll
-      for (int g = 0; g < 2; ++g)
+      for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll 1
@@ -344,23 +370,29 @@ __device__ __forceinline__ void adj_contract(const float (&f)[3][2][2], const Ad
   if constexpr (A == 4) E += X[2] + X[3];
 }
 
-// Contract a finished plane of a cell (f3[s]: this lane's voxel of row
-// 2 s + h) and store its window to `dst`, the wave's slab slot: all of a slab's
+// Contract a finished plane of a cell (f3[s]: this lane's voxel of its row s) and store its window to `dst`, the wave's slab slot: all of a slab's
 // rows and columns (those past the cell's window are zeros).  cw, ch: of the
 // geometry; ch decides how many components share the products (a uniform
 // branch, the same bits: the other components only add zeros).  28 matrix
 // instructions for windows of up to 8 rows, 20 for up to 5 (spacings 4 and 6 and
-// up) and 36 for more (spacing 1).  Every lane of the wave takes part.
-__device__ __forceinline__ void adj_cell_emit(const F3 (&f3)[kAdjSteps], const AdjWeights& w, float* __restrict__ dst,
-                                              int cw, int ch, int lane) {
+// up) and 36 for more; narrow cells have no second half: 18 for more than 8 rows (spacing 1).
+// Every lane of the wave takes part.
+template <bool Narrow>
+__device__ __forceinline__ void adj_cell_emit(const F3 (&f3)[kAdjSteps<Narrow>], const AdjWeights& w,
+                                              float* __restrict__ dst, int cw, int ch, int lane) {
+  constexpr int G = Narrow ? 1 : 2;
   const int m = lane % kAdjTile, q = lane / kAdjTile;
   float f[3][2][2];  // [component][half][step]
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    f[0][0][t] = f3[2 * t].x, f[1][0][t] = f3[2 * t].y, f[2][0][t] = f3[2 * t].z;
-    f[0][1][t] = f3[2 * t + 1].x, f[1][1][t] = f3[2 * t + 1].y, f[2][1][t] = f3[2 * t + 1].z;
+    if constexpr (Narrow) {
+      f[0][0][t] = f3[t].x, f[1][0][t] = f3[t].y, f[2][0][t] = f3[t].z;
+    } else {
+      f[0][0][t] = f3[2 * t].x, f[1][0][t] = f3[2 * t].y, f[2][0][t] = f3[2 * t].z;
+      f[0][1][t] = f3[2 * t + 1].x, f[1][1][t] = f3[2 * t + 1].y, f[2][1][t] = f3[2 * t + 1].z;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) adj_swap_rows(f[c][0][t], f[c][1][t]);
+      for (int c = 0; c < 3; ++c) adj_swap_rows(f[c][0][t], f[c][1][t]);
+    }
   }
   // an infinity or NaN anywhere in the plane makes every entry of its E
   // non-finite (0 * inf = NaN), so any one entry per set of products tells
@@ -372,77 +404,80 @@ __device__ __forceinline__ void adj_cell_emit(const F3 (&f3)[kAdjSteps], const A
   };
   if (ch <= 5) {
     adj_f4 E;
-    adj_contract<0, 3, 5>(f, w, E);
+    adj_contract<0, 3, 5, 4, G>(f, w, E);
     const int c = (m >= 5) + (m >= 10) + (m >= 15);
     store(E, m - 5 * c, c);
     probe = E[0];
   } else if (ch <= 8) {
     adj_f4 E, E2;
-    adj_contract<0, 2, 8>(f, w, E);
-    adj_contract<2, 1, 16>(f, w, E2);
+    adj_contract<0, 2, 8, 4, G>(f, w, E);
+    adj_contract<2, 1, 16, 4, G>(f, w, E2);
     store(E, m & 7, m >> 3);
     store(E2, m, 2);
     probe = E[0] + E2[0];
   } else {
     adj_f4 E, E1, E2;
-    // a cell of at most 16 voxels has no second half: 18 products in place of 36
-    // (300 x 256 x 200, spacing 1: 242 us against 289)
-    if (!__any((w.x[1][0] != 0.f) | (w.x[1][1] != 0.f) | (w.x[1][2] != 0.f) | (w.x[1][3] != 0.f))) {
-      adj_contract<0, 1, 16, 2, 1>(f, w, E);
-      store(E, m, 0);
-      adj_contract<1, 1, 16, 2, 1>(f, w, E1);
-      store(E1, m, 1);
-      adj_contract<2, 1, 16, 2, 1>(f, w, E2);
-      store(E2, m, 2);
-    } else {
-      adj_contract<0, 1, 16, 2>(f, w, E);
-      store(E, m, 0);
-      adj_contract<1, 1, 16, 2>(f, w, E1);
-      store(E1, m, 1);
-      adj_contract<2, 1, 16, 2>(f, w, E2);
-      store(E2, m, 2);
-    }
+    adj_contract<0, 1, 16, 2, G>(f, w, E);
+    store(E, m, 0);
+    adj_contract<1, 1, 16, 2, G>(f, w, E1);
+    store(E1, m, 1);
+    adj_contract<2, 1, 16, 2, G>(f, w, E2);
+    store(E2, m, 2);
     probe = E[0] + E1[0] + E2[0];
   }
   if (__builtin_expect(__any(!(fabsf(probe) < __builtin_inff())), 0)) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) store(adj_cell_sparse(f[c], w, lane), m, c);
+    for (int c = 0; c < 3; ++c) store(adj_cell_sparse<G>(f[c], w, lane), m, c);
   }
+}
+
+// The cells' windows within their brick's (first point, and extent), and the reciprocals of
+// the brick's points per plane and per row.
+struct AdjWindows {
+  int fx[kAdjWaves], fy[kAdjWaves], nx[kAdjWaves], ny[kAdjWaves];
+  uint32_t mp, mc;
+};
+template <class Tiles>
+__host__ __device__ inline AdjWindows adj_windows(const AdjGeom& a, const Tiles& tiles, const AdjBrick& b) {
+  AdjWindows v;
+  v.mp = adj_magic(b.Cy * b.Cx);
+  v.mc = adj_magic(b.Cx);
+#pragma unroll
+  for (int w = 0; w < kAdjWaves; ++w) {
+    const AdjCell c = adj_cell_of(a, tiles, b, w);
+    v.fx[w] = c.cx0 - b.cx0;
+    v.fy[w] = c.cy0 - b.cy0;
+    v.nx[w] = c.Cx;
+    v.ny[w] = c.Cy;
+  }
+  return v;
 }
 
 // Sum the slabs of planes czl0 .. czl0 + np - 1 (slots slot0 ..) over the
 // brick's cells, in wave order, into the brick's partials.  Collective over
-// `threads` threads, after a barrier.
-template <class Tiles>
-__device__ __forceinline__ void adj_combine_slabs(const AdjGeom& a, const Tiles& tiles, const AdjBrick& b,
+// `threads` threads, after a barrier.  Without branches: a point outside a cell's window
+// reads the slab's first and leaves it, and the windows are the caller's: with two-plane slabs
+// this runs at every plane (a branch per cell took 300 instructions per point, the
+// windows 181 per wave; pass 1 of 300 x 256 x 200 at spacing 1: 183 us against 212).
+__device__ __forceinline__ void adj_combine_slabs(const AdjGeom& a, const AdjWindows& win, const AdjBrick& b,
                                                   const float* __restrict__ slabs, float* __restrict__ pbase, int czl0,
                                                   int np, int slot0, int tid, int threads) {
   // items: (plane, point), a wave's lanes consecutive; plane and row of an item
   // by reciprocal (at most 2^11 points, and 2^16 items: exact)
   const int slab = adj_slab(a), comp = a.ch * a.cw;
   const int points = b.Cy * b.Cx, n = np * points;
-  const uint32_t mp = adj_magic(points), mc = adj_magic(b.Cx);
-  int fx[kAdjWaves], fy[kAdjWaves], nx[kAdjWaves], ny[kAdjWaves];
-#pragma unroll
-  for (int w = 0; w < kAdjWaves; ++w) {
-    const AdjCell c = adj_cell_of(a, tiles, b, w);
-    fx[w] = c.cx0 - b.cx0;
-    fy[w] = c.cy0 - b.cy0;
-    nx[w] = c.Cx;
-    ny[w] = c.Cy;
-  }
   for (int i = tid; i < n; i += threads) {
-    const int p = adj_div(i, points, mp), j = i - p * points;
-    const int cyl = adj_div(j, b.Cx, mc), cxl = j - cyl * b.Cx;
+    const int p = np == 1 ? 0 : adj_div(i, points, win.mp), j = i - p * points;
+    const int cyl = adj_div(j, b.Cx, win.mc), cxl = j - cyl * b.Cx;
     const float* slot = slabs + (slot0 + p) * kAdjWaves * slab;
     F3 h[2]{};  // per cell row
 #pragma unroll
     for (int w = 0; w < kAdjWaves; ++w) {
-      const int y = cyl - fy[w], x = cxl - fx[w];
-      if ((uint32_t)y < (uint32_t)ny[w] && (uint32_t)x < (uint32_t)nx[w]) {
-        const float* v = slot + w * slab + y * a.cw + x;
-        h[w / kAdjCellsX] = h[w / kAdjCellsX] + F3{v[0], v[comp], v[2 * comp]};
-      }
+      const int y = cyl - win.fy[w], x = cxl - win.fx[w];
+      const bool in = ((uint32_t)y < (uint32_t)win.ny[w]) & ((uint32_t)x < (uint32_t)win.nx[w]);
+      const float* v = slot + w * slab + (in ? y * a.cw + x : 0);
+      const F3 e{v[0], v[comp], v[2 * comp]};
+      h[w / kAdjCellsX] = h[w / kAdjCellsX] + F3{in ? e.x : 0.f, in ? e.y : 0.f, in ? e.z : 0.f};
     }
     const F3 s = h[0] + h[1];
     stf3(pbase + adj_part_offset(a, czl0 + p, cyl, cxl), s);
@@ -481,32 +516,32 @@ __device__ __forceinline__ void adj_shift(float& a0, float& a1, float& a2, float
 // them and its loads are unconditional (past the end, from the last plane
 // again), so each set keeps fixed registers, and waiting for one set's loads
 // leaves the other set's in flight.
-template <bool Stream, class Z, class Setup, class Emit>
-__device__ __forceinline__ void adj_march(const char* base, size_t zs, uint32_t bytes, const uint32_t (&off)[kAdjSteps],
+template <bool Stream, int S, class Z, class Setup, class Emit>
+__device__ __forceinline__ void adj_march(const char* base, size_t zs, uint32_t bytes, const uint32_t (&off)[S],
                                           int np, Z zp, Setup&& setup, Emit&& emit) {
-  F3 acc[4][kAdjSteps];
+  F3 acc[4][S];
 #pragma unroll
   for (int n = 0; n < 4; ++n)
 #pragma unroll
-    for (int s = 0; s < kAdjSteps; ++s) acc[n][s] = F3{0.f, 0.f, 0.f};
+    for (int s = 0; s < S; ++s) acc[n][s] = F3{0.f, 0.f, 0.f};
   const char* ahead = base;  // the plane to be loaded next, at most the last
   int left = np - 1;         // planes after it
   int czl = 0;
-  auto load = [&](F3(&d)[kAdjSteps]) {
+  auto load = [&](F3(&d)[S]) {
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(ahead), 0, (int)bytes, kBufferFlags);
 #pragma unroll
-    for (int s = 0; s < kAdjSteps; ++s) d[s] = adj_load3<Stream>(rs, off[s]);
+    for (int s = 0; s < S; ++s) d[s] = adj_load3<Stream>(rs, off[s]);
     ahead += left > 0 ? zs : 0;
     --left;
   };
-  auto add = [&](const F3(&d)[kAdjSteps]) {
+  auto add = [&](const F3(&d)[S]) {
     const float* ws = zp.weights();  // uniform: one scalar load
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
       const float w = ws[n];
 #pragma unroll
-      for (int s = 0; s < kAdjSteps; ++s) {
+      for (int s = 0; s < S; ++s) {
         acc[n][s].x = fmaf(w, d[s].x, acc[n][s].x);
         acc[n][s].y = fmaf(w, d[s].y, acc[n][s].y);
         acc[n][s].z = fmaf(w, d[s].z, acc[n][s].z);
@@ -516,14 +551,14 @@ __device__ __forceinline__ void adj_march(const char* base, size_t zs, uint32_t 
   auto finish = [&]() {
     emit(acc[0], czl++);
 #pragma unroll
-    for (int s = 0; s < kAdjSteps; ++s) {
+    for (int s = 0; s < S; ++s) {
       adj_shift(acc[0][s].x, acc[1][s].x, acc[2][s].x, acc[3][s].x);
       adj_shift(acc[0][s].y, acc[1][s].y, acc[2][s].y, acc[3][s].y);
       adj_shift(acc[0][s].z, acc[1][s].z, acc[2][s].z, acc[3][s].z);
     }
     asm volatile("s_nop 4");  // the moves above are done before a lane swap may read their results
   };
-  F3 d0[kAdjSteps], d1[kAdjSteps];
+  F3 d0[S], d1[S];
   load(d0);
   __builtin_amdgcn_sched_barrier(0);  // d0's loads are issued first: waiting for them leaves d1's in flight
   load(d1);
@@ -547,9 +582,10 @@ __device__ __forceinline__ void adj_march(const char* base, size_t zs, uint32_t 
 }
 
 // Pass 1 for one brick.  Collective over the workgroup (kAdjThreads threads).
-// Stream: dfield is read with non-temporal loads.  Staged: adj_staged(a).  cz: the
-// brick's control planes; z: its march along z; weights(c): cell c's matrices.
-template <bool Stream, bool Staged, class Tiles, class Z, class Weights>
+// Stream: dfield is read with non-temporal loads.  Staged: adj_staged(a), Narrow:
+// adj_narrow(a).  cz: the brick's control planes; z: its march along z; weights(c): cell c's
+// matrices.
+template <bool Stream, bool Staged, bool Narrow, class Tiles, class Z, class Weights>
 __device__ __forceinline__ void adj_brick_of(const float* __restrict__ dfield, float* __restrict__ part,
                                              const AdjGeom& a, const Tiles& tiles, const AdjBrick& b, int brick, int cz,
                                              const Z& z, Weights&& weights, float* __restrict__ slabs, int tid) {
@@ -564,36 +600,40 @@ __device__ __forceinline__ void adj_brick_of(const float* __restrict__ dfield, f
   if (!Staged || any) {
     AdjWeights w;
     const int cnx = any ? c.nx : 1, cny = any ? c.ny : 1;
-    uint32_t off[kAdjSteps];
-    adj_cell_offsets(g.nx, cnx, cny, lane, off);
+    uint32_t off[kAdjSteps<Narrow>];
+    adj_cell_offsets<Narrow>(g.nx, cnx, cny, lane, off);
     const uint32_t bytes = adj_cell_bytes(g.nx, cnx, cny);
     const size_t zs = (size_t)g.ny * g.nx * 12;
     const char* base = reinterpret_cast<const char*>(dfield) + (size_t)b.z0 * zs +
                        ((size_t)(any ? c.y0 : b.y0) * g.nx + (any ? c.x0 : b.x0)) * 12;
-    const auto setup = [&] { w = weights(c); };
-    adj_march<Stream>(base, zs, bytes, off, b.ze - b.z0, z, setup, [&](const F3(&f)[kAdjSteps], int czl) {
+    AdjWindows win;
+    const auto setup = [&] {
+      w = weights(c);
+      if constexpr (!Staged) win = adj_windows(a, tiles, b);
+    };
+    adj_march<Stream>(base, zs, bytes, off, b.ze - b.z0, z, setup, [&](const F3(&f)[kAdjSteps<Narrow>], int czl) {
       const int slot = Staged ? czl : czl & 1;
-      adj_cell_emit(f, w, slabs + adj_slab_at(a, slot, wave), a.cw, a.ch, lane);
+      adj_cell_emit<Narrow>(f, w, slabs + adj_slab_at(a, slot, wave), a.cw, a.ch, lane);
       if constexpr (!Staged) {
         // the barrier of plane czl + 1 orders this sum before the slot's next store
         __syncthreads();
-        adj_combine_slabs(a, tiles, b, slabs, pbase, czl, 1, slot, tid, kAdjThreads);
+        adj_combine_slabs(a, win, b, slabs, pbase, czl, 1, slot, tid, kAdjThreads);
       }
     });
   }
   if constexpr (Staged) {
     __syncthreads();
-    adj_combine_slabs(a, tiles, b, slabs, pbase, 0, cz, 0, tid, kAdjThreads);
+    adj_combine_slabs(a, adj_windows(a, tiles, b), b, slabs, pbase, 0, cz, 0, tid, kAdjThreads);
   }
 }
 
 // The aligned grid's.
-template <bool Stream, bool Staged>
+template <bool Stream, bool Staged, bool Narrow>
 __device__ __forceinline__ void adj_brick(const float* __restrict__ dfield, float* __restrict__ part,
                                           const AdjGeom& a, const float* __restrict__ lut, int brick,
                                           float* __restrict__ slabs, int tid) {
   const AdjBrick b = adj_brick_geom(a, brick);
-  adj_brick_of<Stream, Staged>(dfield, part, a, AdjTiles{a}, b, brick, adj_brick_cz(a, b), AdjZ(lut, a.g.dz),
+  adj_brick_of<Stream, Staged, Narrow>(dfield, part, a, AdjTiles{a}, b, brick, adj_brick_cz(a, b), AdjZ(lut, a.g.dz),
                                [&](const AdjCell& c) { return adj_cell_weights(a, c, lut, tid & (kWave - 1)); }, slabs, tid);
 }
 

@@ -25,6 +25,7 @@
 #include <unistd.h>
 #include <sstream>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "adjoint_device.h"
@@ -187,10 +188,18 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI
     // ordinary loads: with the forward running beside pass 1 in the graph,
     // streaming loads measured 2-5% slower here
     const int brick = (int)(item - d.first[kPass]);
-    if (adj_staged(a))  // uniform: a function of the geometry
-      adj_brick<false, true>(as_global(d.dfield), as_global(d.part), a, lut, brick, batch_slabs, threadIdx.x);
-    else
-      adj_brick<false, false>(as_global(d.dfield), as_global(d.part), a, lut, brick, batch_slabs, threadIdx.x);
+    const auto run = [&](auto staged, auto narrow) {
+      adj_brick<false, decltype(staged)::value, decltype(narrow)::value>(as_global(d.dfield), as_global(d.part), a, lut,
+                                                                         brick, batch_slabs, threadIdx.x);
+    };
+    // uniform branches: functions of the geometry
+    if (!AllTiles && adj_narrow(a)) {
+      if (adj_staged(a)) run(std::true_type{}, std::true_type{});
+      else run(std::false_type{}, std::true_type{});
+    } else {
+      if (adj_staged(a)) run(std::true_type{}, std::false_type{});
+      else run(std::false_type{}, std::false_type{});
+    }
   });
 }
 

@@ -159,10 +159,10 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   };
   auto contract = [&](int n, int czl) {
     const float* F = fused_smem + lds.F + n * kFusedWaves * kFusedFRow;
-    F3 f[kAdjSteps];
+    F3 f[kAdjSteps<false>];
 #pragma unroll
-    for (int s = 0; s < kAdjSteps; ++s) f[s] = ldf3(F + fused_f_at(b, cell, lane, s));
-    adj_cell_emit(f, cw, slabs + adj_slab_at(a, Staged ? czl : czl & 1, wave % kAdjWaves), a.cw, a.ch, lane);
+    for (int s = 0; s < kAdjSteps<false>; ++s) f[s] = ldf3(F + fused_f_at(b, cell, lane, s));
+    adj_cell_emit<false>(f, cw, slabs + adj_slab_at(a, Staged ? czl : czl & 1, wave % kAdjWaves), a.cw, a.ch, lane);
   };
   // Per voxel plane, in two stages: (a) T from the 4 contracted planes, the
   // sample's cell and the loads of its corners and of `fixed`; (b) the
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
         for (int k = 0; k < 4; ++k) acc[k] = k + n < 4 ? acc[k + n] : F3{0.f, 0.f, 0.f};
       },
       [&](int czl, int np) {
-        adj_combine_slabs(a, AdjTiles{a}, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, np,
+        adj_combine_slabs(a, adj_windows(a, AdjTiles{a}, b), b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, np,
                           Staged ? czl : czl & 1, tid, kFusedThreads);
       },
       [&] {

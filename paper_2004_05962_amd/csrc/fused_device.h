@@ -33,7 +33,7 @@ __host__ __device__ inline FusedLds fused_lds(const AdjGeom& a) {
 // column must not decide how this cell is summed.  (Rows past the cell lie past the
 // brick, and hold zeros.)
 __host__ __device__ inline int fused_f_at(const AdjBrick& b, const AdjCell& c, int lane, int s) {
-  return (c.y0 - b.y0 + adj_lane_row(lane, s)) * kFusedFRow + (c.x0 - b.x0 + imin(lane % kAdjCellX, c.nx - 1)) * 3;
+  return (c.y0 - b.y0 + adj_lane_row<false>(lane, s)) * kFusedFRow + (c.x0 - b.x0 + imin(lane % kAdjCellX, c.nx - 1)) * 3;
 }
 // Staged floats per thread.  One plane's window is at most 1653 floats (29 x 19 points, at
 // spacing 1), and at most 1024 from spacings 3 x 2 on.  One load more, which no

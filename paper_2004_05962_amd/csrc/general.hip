@@ -230,8 +230,8 @@ struct GenZ {
   }
 };
 
-template <bool Staged>
-__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI_ADJ_WPE))) void gen_pass1_kernel(
+template <bool Staged, bool Narrow>
+__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(adj_wpe(Narrow)))) void gen_pass1_kernel(
     const float* __restrict__ dfield, float* __restrict__ part, AdjGeom a, const int* __restrict__ tx,
     const int* __restrict__ ty, const int* __restrict__ fz, const float* __restrict__ wx, const float* __restrict__ wy,
     const float* __restrict__ wz) {
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(BSI
   const int brick = xcd_remap(blockIdx.x, gridDim.x);
   const GenTiles tiles{tx, ty};
   const AdjBrick b = gen_brick(a, tiles, fz, brick);
-  adj_brick_of<true, Staged>(dfield, part, a, tiles, b, brick, gen_brick_cz(a, b), GenZ(wz, fz, b.z0, b.cz0, a.g.gz),
+  adj_brick_of<true, Staged, Narrow>(dfield, part, a, tiles, b, brick, gen_brick_cz(a, b), GenZ(wz, fz, b.z0, b.cz0, a.g.gz),
                              [&](const AdjCell& c) { return gen_cell_weights(a.g, c, tx, wx, ty, wy, threadIdx.x % kWave); },
                              gen_slabs, threadIdx.x);
 }
@@ -383,7 +383,8 @@ hipError_t launch_adjoint_general(const float* dfield, float* grad, const GenGeo
   }
   hipLaunchKernelGGL(gen_tables3_kernel, dim3((unsigned)(tp.nb[0] + tp.nb[1] + tp.nb[2])), dim3(256), 0, s, tp);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  const auto pass1 = adj_staged(a) ? &gen_pass1_kernel<true> : &gen_pass1_kernel<false>;
+  const auto pass1 = adj_narrow(a) ? (adj_staged(a) ? &gen_pass1_kernel<true, true> : &gen_pass1_kernel<false, true>)
+                                   : (adj_staged(a) ? &gen_pass1_kernel<true, false> : &gen_pass1_kernel<false, false>);
   hipLaunchKernelGGL(pass1, dim3((unsigned)nbricks), dim3(kAdjThreads), adj_lds_bytes(a), s, dfield, wk.part, a,
                      wk.tile[0], wk.tile[1], wk.first[2], wk.w[0], wk.w[1], wk.w[2]);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;

@@ -35,8 +35,8 @@ struct Check {
   } while (0)
 
 // Loads and LDS indices of pass 1 (adj_brick_of) for one brick of cz control planes.
-template <class Tiles>
-bool check_brick(const AdjGeom& a, const Tiles& tiles, const AdjBrick& b, int cz, Check& ck) {
+template <bool Narrow, class Tiles>
+bool check_brick_lanes(const AdjGeom& a, const Tiles& tiles, const AdjBrick& b, int cz, Check& ck) {
   const VolGeom& g = a.g;
   const size_t plane = (size_t)g.nx * g.ny * 12;
   const size_t lds = adj_lds_bytes(a) / sizeof(float);
@@ -68,16 +68,17 @@ bool check_brick(const AdjGeom& a, const Tiles& tiles, const AdjBrick& b, int cz
     const int cnx = any ? c.nx : 1, cny = any ? c.ny : 1;
     const size_t base = ((size_t)(any ? c.y0 : b.y0) * g.nx + (any ? c.x0 : b.x0)) * 12;
     for (int lane = 0; lane < kWave; ++lane) {
-      uint32_t off[kAdjSteps];
-      adj_cell_offsets(g.nx, cnx, cny, lane, off);
-      for (int s = 0; s < kAdjSteps; ++s) {
+      uint32_t off[kAdjSteps<Narrow>];
+      adj_cell_offsets<Narrow>(g.nx, cnx, cny, lane, off);
+      for (int s = 0; s < kAdjSteps<Narrow>; ++s) {
         REQUIRE(base + off[s] + 12 <= plane, "pass-1 load outside its voxel plane");
         REQUIRE(off[s] + 12 <= adj_cell_bytes(g.nx, cnx, cny), "pass-1 load outside its buffer");
         const size_t v = (base + off[s]) / 12;
         const int x = (int)(v % g.nx), y = (int)(v / g.nx);
         REQUIRE(x >= b.x0 && x < b.xe && y >= b.y0 && y < b.ye, "pass-1 load outside its brick");
-        if (any && lane % kAdjCellX < c.nx && adj_lane_row(lane, s) < c.ny) {
-          REQUIRE(x == c.x0 + lane % kAdjCellX && y == c.y0 + adj_lane_row(lane, s), "pass-1 lane's voxel");
+        const int col = adj_lane_col<Narrow>(lane), row = adj_lane_row<Narrow>(lane, s);
+        if (any && col < c.nx && row < c.ny) {
+          REQUIRE(x == c.x0 + col && y == c.y0 + row, "pass-1 lane's voxel");
           ++voxels[(size_t)(y - b.y0) * (b.xe - b.x0) + x - b.x0];
         }
       }
@@ -91,6 +92,11 @@ bool check_brick(const AdjGeom& a, const Tiles& tiles, const AdjBrick& b, int cz
     for (int k = 0; k < 4; ++k) rows |= 1 << adj_step_row(t, k);
   REQUIRE(rows == (1 << kAdjCellY) - 1, "product steps cover the cell's rows");
   return true;
+}
+
+template <class Tiles>
+bool check_brick(const AdjGeom& a, const Tiles& tiles, const AdjBrick& b, int cz, Check& ck) {
+  return adj_narrow(a) ? check_brick_lanes<true>(a, tiles, b, cz, ck) : check_brick_lanes<false>(a, tiles, b, cz, ck);
 }
 
 bool check_adj_brick(const AdjGeom& a, const AdjBrick& b, Check& ck) {
@@ -494,11 +500,11 @@ bool check_fused_cells(const AdjGeom& a, const AdjBrick& b, Check& ck) {
     const AdjCell c = adj_cell_geom(a, b, w);
     if (c.nx <= 0 || c.ny <= 0) continue;  // the wave contracts nothing
     for (int lane = 0; lane < kWave; ++lane)
-      for (int s = 0; s < kAdjSteps; ++s) {
+      for (int s = 0; s < kAdjSteps<false>; ++s) {
         const int e = fused_f_at(b, c, lane, s), row = e / kFusedFRow, x = b.x0 + e % kFusedFRow / 3;
         REQUIRE(e >= 0 && row < kFusedWaves && e % kFusedFRow + 3 <= kWave * 3, "fused contraction outside F");
         REQUIRE(x >= c.x0 && x < c.x0 + c.nx, "fused contraction of another cell's column");
-        REQUIRE(adj_lane_row(lane, s) < c.ny ? b.y0 + row == c.y0 + adj_lane_row(lane, s) : b.y0 + row >= b.ye,
+        REQUIRE(adj_lane_row<false>(lane, s) < c.ny ? b.y0 + row == c.y0 + adj_lane_row<false>(lane, s) : b.y0 + row >= b.ye,
                 "fused contraction of another cell's row");
       }
   }

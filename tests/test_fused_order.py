@@ -23,7 +23,7 @@ CASES = [
     ((1024, 260, 210), (5, 5, 5), 4, 1),   # every z-brick in one workgroup
     ((300, 260, 40), (5, 5, 1), 2, 1),        # a z-tile per plane
     ((64, 64, 200), (1, 1, 1), 1, 0),
-    ((300, 256, 200), (1, 1, 1), 4, 0),       # two-plane slabs, several z-bricks
+    ((300, 256, 200), (1, 1, 1), 5, 0),       # two-plane slabs, several z-bricks
     ((40, 70, 21), (12, 35, 7), None, 1),
     ((5, 5, 1), (1, 1, 1), 1, 1),             # one plane
     ((1, 40, 50), (3, 3, 3), None, 1),
