@@ -68,20 +68,31 @@ __host__ __device__ inline FusedStage<L> fused_stage_map(const AdjGeom& a, const
 // A workgroup takes `deep` consecutive z-bricks of one (x, y) brick column: it
 // marches on through their borders with the planes it has contracted, and
 // only the adjoint's partials are cut there.  So the depth of a workgroup is
-// chosen for this kernel, which runs one workgroup per CU and pays for the
-// first 4 control planes, and not by the adjoint's bricks: as deep as leaves
-// kFusedTargetWg workgroups.
-constexpr int kFusedTargetWg = 256;
+// chosen for this kernel, which runs one workgroup per CU: its CUs take the workgroups in
+// rounds, and a round costs a workgroup's planes and its start and end, about
+// kFusedRoundCost planes.  Of the depths with the fewest planes for each number of
+// rounds, the cheapest is taken.  512 x 400 x 220, spacing 6 (200 brick columns of 5 bricks):
+// 277 us as 200 workgroups in one round, 273 as 1000 in 4, 354 as 400 in 2; 152 x 343 x 409,
+// spacing 3: 194 us as 462, 311 as 264, which are 2 rounds as well.  Measured with every depth
+// of 17 sizes: costs of 8 to 10 choose the fastest or one within 2%.
+constexpr int kFusedRoundCost = 9, kFusedRounds = 16;
 struct FusedSplit {
   int deep, nz;  // z-bricks per workgroup, workgroups along z
 };
 __host__ __device__ inline FusedSplit fused_split(const AdjGeom& a) {
-  const long base = (long)a.x.nb * a.y.nb;
-  long nz = (kFusedTargetWg + base - 1) / base;
-  nz = nz < a.z.nb ? nz : a.z.nb;
-  FusedSplit f;
-  f.deep = (int)((a.z.nb + nz - 1) / nz);
-  f.nz = (a.z.nb + f.deep - 1) / f.deep;
+  const int64_t base = (int64_t)a.x.nb * a.y.nb, first = (base + kAdjCus - 1) / kAdjCus;
+  FusedSplit f{a.z.nb, 1};
+  int64_t best = -1;
+  for (int64_t r = first; r < first + kFusedRounds; ++r) {
+    const int64_t most = r * kAdjCus / base;  // workgroups along z in r rounds, at least 1
+    const int deep = (int)((a.z.nb + most - 1) / most), nz = (a.z.nb + deep - 1) / deep;
+    const int64_t rounds = (base * nz + kAdjCus - 1) / kAdjCus;
+    const int64_t cost = rounds * (imin(deep * a.z.w, a.g.nz) + kFusedRoundCost);
+    if (best < 0 || cost < best) {
+      best = cost;
+      f = FusedSplit{deep, nz};
+    }
+  }
   return f;
 }
 

@@ -642,6 +642,21 @@ int bsi_check_fused(const int32_t dims[3], const int32_t spacing[3], int32_t inf
   return ck.ok ? 0 : 1;
 }
 
+// How the fused SSD step splits a volume: brick columns, z-bricks, planes per z-brick,
+// z-bricks per workgroup, workgroups along z.
+int bsi_check_fused_split(const int32_t dims[3], const int32_t spacing[3], int32_t out[5]) {
+  VolGeom g;
+  if (make_geom(dims, spacing, &g)) return -1;
+  const AdjGeom a = make_adj_geom(g);
+  const FusedSplit f = fused_split(a);
+  out[0] = a.x.nb * a.y.nb;
+  out[1] = a.z.nb;
+  out[2] = a.z.w;
+  out[3] = f.deep;
+  out[4] = f.nz;
+  return 0;
+}
+
 // The largest thread counts of the forward launches of one volume, and of a batch that
 // holds it alone (every shape and z split): aligned (spacing), scalar, real spacing
 // (the same spacing, origin 0), batched.

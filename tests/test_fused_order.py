@@ -19,11 +19,13 @@ LIB = os.path.join(ROOT, "paper_2004_05962_amd", "libbsi_check.so")
 CASES = [
     ((64, 64, 40), (5, 5, 5), 1, 1),
     ((256, 256, 160), (5, 5, 5), 1, 1),
-    ((512, 300, 199), (5, 5, 5), 3, 1),       # several z-bricks per workgroup, a partial last tile
-    ((1024, 260, 210), (5, 5, 5), 4, 1),   # every z-brick in one workgroup
+    ((512, 300, 199), (5, 5, 5), 1, 1),       # a partial last tile
+    ((512, 510, 199), (5, 5, 5), 4, 1),       # every z-brick in one workgroup
+    ((1024, 260, 210), (5, 5, 5), 1, 1),
+    ((200, 220, 240), (2, 3, 1), 8, 1),       # several z-bricks per workgroup
     ((300, 260, 40), (5, 5, 1), 2, 1),        # a z-tile per plane
     ((64, 64, 200), (1, 1, 1), 1, 0),
-    ((300, 256, 200), (1, 1, 1), 5, 0),       # two-plane slabs, several z-bricks
+    ((300, 256, 200), (1, 1, 1), 2, 0),       # two-plane slabs, several z-bricks
     ((40, 70, 21), (12, 35, 7), None, 1),
     ((5, 5, 1), (1, 1, 1), 1, 1),             # one plane
     ((1, 40, 50), (3, 3, 3), None, 1),

@@ -18,6 +18,8 @@ CASES = [
     ((256, 256, 160), (5, 5, 5)),
     ((512, 300, 199), (5, 5, 5)),
     ((1024, 260, 210), (5, 5, 5)),
+    ((512, 510, 199), (5, 5, 5)),
+    ((200, 220, 240), (2, 3, 1)),
     ((300, 260, 40), (5, 5, 1)),
     ((64, 64, 200), (1, 1, 1)),
     ((300, 256, 200), (1, 1, 1)),
