@@ -31,7 +31,8 @@ namespace bsi {
 namespace {
 
 // The fused pass uses the adjoint's bricks with one voxel column per lane: 16
-// waves of one row each, lane = x, so each lane keeps the forward's 4 contracted
+// waves of one row each, lane = x (fewer for bricks of x spacings 1 and 2, FusedShape), so each
+// lane keeps the forward's 4 contracted
 // planes and the adjoint's 4 accumulators of a single column.  When a z-tile
 // ends, the rows of the finished control plane meet in LDS (F, two in turn, one
 // barrier per tile), and the first kAdjWaves waves contract one cell each with
@@ -86,15 +87,19 @@ __device__ __forceinline__ F3 fused_contract(const float* __restrict__ slot, int
 
 // Pairs: the sampler's x-neighbour loads (trilinear_load): 1 for nx >= 2, 0 for nx == 1.
 // L: staged floats per thread.  Small: the images are below 4 GiB.
-template <int L, bool Staged, int Pairs, bool Small>
-__global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float* __restrict__ grid,
+// Cols: fused_cols(a).
+template <int L, bool Staged, int Pairs, bool Small, int Cols>
+__global__ __launch_bounds__(FusedShape<Cols>::threads) __attribute__((amdgpu_waves_per_eu(Cols == 48 ? 3 : 4))) void fused_pass1_kernel(const float* __restrict__ grid,
                                                                   const float* __restrict__ moving,
                                                                   const float* __restrict__ fixed,
                                                                   float* __restrict__ part,
                                                                   float* __restrict__ lpart, AdjGeom a, FusedSplit fs,
                                                                   const float* __restrict__ lut) {
+  using Shape = FusedShape<Cols>;
+  static_assert(!(Shape::narrow && Staged));
+  constexpr int kThreads = Shape::threads;
   extern __shared__ float fused_smem[];
-  const FusedLds lds = fused_lds(a);
+  const FusedLds lds = fused_lds<Cols>(a);
   float* ring = fused_smem + lds.ring;
   float* red = fused_smem + lds.red;
   float* slabs = fused_smem + lds.slabs;
@@ -110,7 +115,8 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   const int lane = tid & (kWave - 1), wave = uniform(tid / kWave);
 
   // this lane's voxel column (x, y): forward weights and window base
-  const int x = b.x0 + lane, y = b.y0 + wave;
+  const int row = Cols == kWave ? wave : tid / Cols, col = Cols == kWave ? lane : tid - row * Cols;
+  const int x = b.x0 + col, y = b.y0 + row;
   const int xc = imin(x, b.xe - 1), yc = imin(y, b.ye - 1);
   const bool act = x < b.xe && y < b.ye;
   const int tx = xc / g.dx, ty = yc / g.dy;
@@ -123,7 +129,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   }
   const int pitch = a.x.cm * 3;
   const int base = (ty - b.cy0) * pitch + (tx - b.cx0) * 3;
-  const FusedStage<L> map = fused_stage_map<L>(a, b, tid);
+  const FusedStage<L> map = fused_stage_map<L, kThreads>(a, b, tid);
   // the cell whose planes this wave contracts: waves 0 .. kAdjWaves - 1 at the end of
   // a z-tile, three times as many at the end of a brick
   const AdjCell cell = adj_cell_geom(a, b, wave % kAdjWaves);
@@ -155,14 +161,14 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   // This lane's value of a finished plane to F[n], and the contraction of F[n] by this
   // wave's cell into the slabs, a barrier apart.
   auto put = [&](int n, const F3& v) {
-    stf3(fused_smem + lds.F + (n * kFusedWaves + wave) * kFusedFRow + lane * 3, v);
+    stf3(fused_smem + lds.F + (n * kFusedRows + row) * Shape::f_row + col * 3, v);
   };
   auto contract = [&](int n, int czl) {
-    const float* F = fused_smem + lds.F + n * kFusedWaves * kFusedFRow;
-    F3 f[kAdjSteps<false>];
+    const float* F = fused_smem + lds.F + n * kFusedRows * Shape::f_row;
+    F3 f[kAdjSteps<Shape::narrow>];
 #pragma unroll
-    for (int s = 0; s < kAdjSteps<false>; ++s) f[s] = ldf3(F + fused_f_at(b, cell, lane, s));
-    adj_cell_emit<false>(f, cw, slabs + adj_slab_at(a, Staged ? czl : czl & 1, wave % kAdjWaves), a.cw, a.ch, lane);
+    for (int s = 0; s < kAdjSteps<Shape::narrow>; ++s) f[s] = ldf3(F + fused_f_at<Cols>(b, cell, lane, s));
+    adj_cell_emit<Shape::narrow>(f, cw, slabs + adj_slab_at(a, Staged ? czl : czl & 1, wave % kAdjWaves), a.cw, a.ch, lane);
   };
   // Per voxel plane, in two stages: (a) T from the 4 contracted planes, the
   // sample's cell and the loads of its corners and of `fixed`; (b) the
@@ -236,6 +242,10 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
     }
   };
 
+  // (with two-plane slabs the sum runs at every plane: 300 x 256 x 200 at spacing 1 took 633 us
+  // with the windows formed there, 506 so)
+  AdjWindows win;
+  if constexpr (!Staged) win = adj_windows(a, AdjTiles{a}, b);
   const auto march_ops = fused_march(
       [&] {
 #pragma unroll
@@ -252,8 +262,8 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
         for (int k = 0; k < 4; ++k) acc[k] = k + n < 4 ? acc[k + n] : F3{0.f, 0.f, 0.f};
       },
       [&](int czl, int np) {
-        adj_combine_slabs(a, adj_windows(a, AdjTiles{a}, b), b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, np,
-                          Staged ? czl : czl & 1, tid, kFusedThreads);
+        adj_combine_slabs(a, Staged ? adj_windows(a, AdjTiles{a}, b) : win, b, slabs, part + (size_t)(bz * nxy + bxy) * adj_brick_stride(a), czl, np,
+                          Staged ? czl : czl & 1, tid, kThreads);
       },
       [&] {
         loss += l2;
@@ -264,8 +274,8 @@ __global__ __launch_bounds__(kFusedThreads) void fused_pass1_kernel(const float*
   // the workgroup's loss partial: fixed-order tree
   red[tid] = loss;
   __syncthreads();
-  for (int h = kFusedThreads / 2; h > 0; h >>= 1) {
-    if (tid < h) red[tid] += red[tid + h];
+  for (int h = 512; h > 0; h >>= 1) {  // at most 1024 threads
+    if (tid < h && tid + h < kThreads) red[tid] += red[tid + h];
     __syncthreads();
   }
   if (tid == 0) lpart[item] = red[0];
@@ -312,34 +322,43 @@ __global__ __launch_bounds__(kTailThreads) __attribute__((amdgpu_waves_per_eu(8)
 }
 
 hipError_t launch_ssd_fused(const float* grid, const float* moving, const float* fixed, float* grad, float* loss,
-                            const AdjGeom& a, const float* lut, void* workspace, hipStream_t s, float* descend_grid,
+                            const AdjGeom& adj, const float* lut, void* workspace, hipStream_t s, float* descend_grid,
                             float eta) {
+  const AdjGeom a = fused_geom(adj);
   float* part = static_cast<float*>(workspace);
   float* lpart = reinterpret_cast<float*>(static_cast<char*>(workspace) +
                                           (adj_workspace_bytes(a) + 255) / 256 * 256);
   const FusedSplit fs = fused_split(a);
   const long items = (long)a.x.nb * a.y.nb * fs.nz;
-  const FusedLds lds = fused_lds(a);
-  const dim3 gridd((unsigned)items), block(kFusedThreads);
+  const int cols = fused_cols(a);
+  const FusedLds lds = cols == 32 ? fused_lds<32>(a) : cols == 48 ? fused_lds<48>(a) : fused_lds<64>(a);
+  const dim3 gridd((unsigned)items), block((unsigned)(kFusedRows * cols));
   const size_t bytes = (size_t)lds.total * sizeof(float);
   // 32-bit byte offsets into the images
   const bool small = (double)a.g.nx * a.g.ny * a.g.nz * 4 < 4294967296.0;
-#define BSI_FUSED_LAUNCH(L, STAGED, PAIRS)                                                                            \
+#define BSI_FUSED_LAUNCH(L, STAGED, PAIRS, COLS)                                                                    \
   do {                                                                                                               \
-    const auto k = small ? &fused_pass1_kernel<L, STAGED, PAIRS, true> : &fused_pass1_kernel<L, STAGED, PAIRS, false>; \
+    const auto k = small ? &fused_pass1_kernel<L, STAGED, PAIRS, true, COLS>                                        \
+                         : &fused_pass1_kernel<L, STAGED, PAIRS, false, COLS>;                                      \
     hipLaunchKernelGGL(k, gridd, block, bytes, s, grid, moving, fixed, part, lpart, a, fs, lut);                      \
   } while (0)
   // a volume one voxel wide samples its x-neighbours one by one
-  const bool staged = adj_staged(a), one = fused_loads(lds.slot) <= 1;
-  if (a.g.nx < 2) {
-    if (staged) BSI_FUSED_LAUNCH(kFusedMaxLoads, true, 0);
-    else BSI_FUSED_LAUNCH(kFusedMaxLoads, false, 0);
+  const bool staged = adj_staged(a), one = fused_loads<64>(lds.slot) <= 1;
+  constexpr int kMost = FusedShape<64>::max_loads;
+  if (cols == 32) {
+    BSI_FUSED_LAUNCH(FusedShape<32>::max_loads, false, 1, 32);
+  } else if (cols == 48) {
+    if (staged) BSI_FUSED_LAUNCH(FusedShape<48>::max_loads, true, 1, 48);
+    else BSI_FUSED_LAUNCH(FusedShape<48>::max_loads, false, 1, 48);
+  } else if (a.g.nx < 2) {
+    if (staged) BSI_FUSED_LAUNCH(kMost, true, 0, 64);
+    else BSI_FUSED_LAUNCH(kMost, false, 0, 64);
   } else if (one) {
-    if (staged) BSI_FUSED_LAUNCH(1, true, 1);
-    else BSI_FUSED_LAUNCH(1, false, 1);
+    if (staged) BSI_FUSED_LAUNCH(1, true, 1, 64);
+    else BSI_FUSED_LAUNCH(1, false, 1, 64);
   } else {
-    if (staged) BSI_FUSED_LAUNCH(kFusedMaxLoads, true, 1);
-    else BSI_FUSED_LAUNCH(kFusedMaxLoads, false, 1);
+    if (staged) BSI_FUSED_LAUNCH(kMost, true, 1, 64);
+    else BSI_FUSED_LAUNCH(kMost, false, 1, 64);
   }
 #undef BSI_FUSED_LAUNCH
   hipError_t e = hipGetLastError();

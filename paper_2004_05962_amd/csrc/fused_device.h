@@ -6,11 +6,32 @@
 
 namespace bsi {
 
-constexpr int kFusedWaves = kAdjCellsY * kAdjCellY;
-constexpr int kFusedThreads = kFusedWaves * kWave;
-// Floats per row of F: 64 voxels, padded so that the 2 rows a cell's lanes read
-// at once start 32 banks apart.
-constexpr int kFusedFRow = kWave * 3 + 32;
+// A workgroup's threads: a voxel column each, 16 rows of a brick.  Cols: the columns that a row
+// of threads holds (fused_cols): 64, a wave per row; 48 for the bricks of x spacing 2, 12 waves;
+// 32 for narrow cells (spacing 1), 8 waves, and two workgroups per CU.  300 x 256 x 200 at
+// spacing 1: 506 us, with a wave per row of 26 columns 1036; 300 x 300 x 200 at spacing 2, rows of
+// 44: 275 and 283.
+constexpr int kFusedRows = kAdjCellsY * kAdjCellY;
+template <int Cols>
+struct FusedShape {
+  static constexpr int threads = kFusedRows * Cols, waves = threads / kWave;
+  static constexpr bool narrow = Cols <= 2 * kAdjTile;
+  // Floats per row of F: the columns, padded so that the 2 rows (narrow: 4) a cell's lanes
+  // read at once start 32 banks apart (48: the 16 lanes' floats).
+  static constexpr int f_row = Cols * 3 + (Cols == 64 ? 32 : 16);
+  static constexpr int max_loads = Cols == 64 ? 2 : Cols == 48 ? 3 : 4;  // staged floats per thread
+  static constexpr int per_cu = narrow ? 2 : 1;                          // workgroups
+};
+static_assert(FusedShape<64>::f_row % 64 == 32 && FusedShape<48>::f_row % 64 == 32 && FusedShape<32>::f_row % 64 == 48);
+__host__ __device__ inline int fused_cols(const AdjGeom& a) {
+  return a.g.nx < 2 || a.cell > adj_cell(2) ? 64 : adj_narrow(a) ? 32 : 48;
+}
+// The adjoint's bricks, so its partials and bits; narrow ones always with two-plane slabs, which
+// leave room for the second workgroup.
+__host__ __device__ inline AdjGeom fused_geom(AdjGeom a) {
+  if (fused_cols(a) == 32) a.slots = 2;
+  return a;
+}
 
 // LDS (floats): F (two in turn, and with whole slabs two more for a brick's last
 // three planes), the two-slot ring of staged control planes (the brick's window,
@@ -18,31 +39,41 @@ constexpr int kFusedFRow = kWave * 3 + 32;
 struct FusedLds {
   int F, ring, slot, red, slabs, total;
 };
+template <int Cols>
 __host__ __device__ inline FusedLds fused_lds(const AdjGeom& a) {
+  using S = FusedShape<Cols>;
   FusedLds l;
   l.F = 0;
-  l.ring = (adj_staged(a) ? 4 : 2) * kFusedWaves * kFusedFRow;
+  l.ring = (adj_staged(a) ? 4 : 2) * kFusedRows * S::f_row;
   l.slot = a.y.cm * a.x.cm * 3;
   l.red = l.ring + 2 * l.slot;
-  l.slabs = (l.red + kFusedThreads + 3) / 4 * 4;  // 16-byte aligned
+  l.slabs = (l.red + S::threads + 3) / 4 * 4;  // 16-byte aligned
   l.total = l.slabs + a.slots * kAdjWaves * adj_slab(a);
   return l;
 }
-// Offset in F of this lane's voxel of row 2 s + h of a cell, its column clamped into the
+// Offset in F of this lane's voxel of its row s of a cell, its column clamped into the
 // cell as the adjoint's loads are (adj_cell_offsets): an infinity in a neighbour's
 // column must not decide how this cell is summed.  (Rows past the cell lie past the
 // brick, and hold zeros.)
+template <int Cols>
 __host__ __device__ inline int fused_f_at(const AdjBrick& b, const AdjCell& c, int lane, int s) {
-  return (c.y0 - b.y0 + adj_lane_row<false>(lane, s)) * kFusedFRow + (c.x0 - b.x0 + imin(lane % kAdjCellX, c.nx - 1)) * 3;
+  using S = FusedShape<Cols>;
+  return (c.y0 - b.y0 + adj_lane_row<S::narrow>(lane, s)) * S::f_row +
+         (c.x0 - b.x0 + imin(adj_lane_col<S::narrow>(lane), c.nx - 1)) * 3;
 }
 // Staged floats per thread.  One plane's window is at most 1653 floats (29 x 19 points, at
 // spacing 1), and at most 1024 from spacings 3 x 2 on.  One load more, which no
 // window needs, cost the two-plane kernels 12 to 24 bytes of scratch per lane.
-__host__ __device__ constexpr int fused_loads(int slot) { return (slot + kFusedThreads - 1) / kFusedThreads; }
-constexpr int kFusedMaxLoads = 2;
-static_assert(fused_loads((kAdjCellsX * adj_cell(1) + 3) * (kAdjCellsY * kAdjCellY + 3) * 3) == kFusedMaxLoads);
+template <int Cols>
+__host__ __device__ constexpr int fused_loads(int slot) {
+  return (slot + FusedShape<Cols>::threads - 1) / FusedShape<Cols>::threads;
+}
+constexpr int kFusedMaxWindow = (kAdjCellsX * adj_cell(1) + 3) * (kFusedRows + 3) * 3;
+static_assert(fused_loads<64>(kFusedMaxWindow) == FusedShape<64>::max_loads &&
+              fused_loads<48>(kFusedMaxWindow) == FusedShape<48>::max_loads &&
+              fused_loads<32>(kFusedMaxWindow) == FusedShape<32>::max_loads);
 
-// Staging map: thread tid takes floats e = tid + k kFusedThreads of the Cy x Cx x 3
+// Staging map: thread tid takes floats e = tid + k threads of the Cy x Cx x 3
 // window of a control plane, into a slot with row pitch x.cm points.
 template <int L>
 struct FusedStage {
@@ -50,13 +81,13 @@ struct FusedStage {
   int dst[L];
 };
 
-template <int L>
+template <int L, int Threads>
 __host__ __device__ inline FusedStage<L> fused_stage_map(const AdjGeom& a, const AdjBrick& b, int tid) {
   FusedStage<L> m;
   const int wrow = b.Cx * 3;
 #pragma unroll
   for (int k = 0; k < L; ++k) {
-    const int e = tid + k * kFusedThreads;
+    const int e = tid + k * Threads;
     const int cyl = e / wrow, i = e - cyl * wrow;
     const bool in = cyl < b.Cy;
     m.src[k] = in ? ((b.cy0 + cyl) * a.g.gx + b.cx0) * 3 + i : -1;
@@ -68,8 +99,8 @@ __host__ __device__ inline FusedStage<L> fused_stage_map(const AdjGeom& a, const
 // A workgroup takes `deep` consecutive z-bricks of one (x, y) brick column: it
 // marches on through their borders with the planes it has contracted, and
 // only the adjoint's partials are cut there.  So the depth of a workgroup is
-// chosen for this kernel, which runs one workgroup per CU: its CUs take the workgroups in
-// rounds, and a round costs a workgroup's planes and its start and end, about
+// chosen for this kernel, which runs one workgroup per CU (two of 32 columns): the CUs take the
+// workgroups in rounds, and a round costs a workgroup's planes and its start and end, about
 // kFusedRoundCost planes.  Of the depths with the fewest planes for each number of
 // rounds, the cheapest is taken.  512 x 400 x 220, spacing 6 (200 brick columns of 5 bricks):
 // 277 us as 200 workgroups in one round, 273 as 1000 in 4, 354 as 400 in 2; 152 x 343 x 409,
@@ -80,13 +111,14 @@ struct FusedSplit {
   int deep, nz;  // z-bricks per workgroup, workgroups along z
 };
 __host__ __device__ inline FusedSplit fused_split(const AdjGeom& a) {
-  const int64_t base = (int64_t)a.x.nb * a.y.nb, first = (base + kAdjCus - 1) / kAdjCus;
+  const int64_t round = kAdjCus * (fused_cols(a) == 32 ? FusedShape<32>::per_cu : 1);
+  const int64_t base = (int64_t)a.x.nb * a.y.nb, first = (base + round - 1) / round;
   FusedSplit f{a.z.nb, 1};
   int64_t best = -1;
   for (int64_t r = first; r < first + kFusedRounds; ++r) {
-    const int64_t most = r * kAdjCus / base;  // workgroups along z in r rounds, at least 1
+    const int64_t most = r * round / base;  // workgroups along z in r rounds, at least 1
     const int deep = (int)((a.z.nb + most - 1) / most), nz = (a.z.nb + deep - 1) / deep;
-    const int64_t rounds = (base * nz + kAdjCus - 1) / kAdjCus;
+    const int64_t rounds = (base * nz + round - 1) / round;
     const int64_t cost = rounds * (imin(deep * a.z.w, a.g.nz) + kFusedRoundCost);
     if (best < 0 || cost < best) {
       best = cost;
@@ -111,7 +143,7 @@ struct FusedMarch {
   Shift shift;      // Q[n] = Q[n + 1]
   Planes planes;    // (z, np): the voxel planes [z, z + np) of one z-tile, with Q
   Put put;          // (n, k): accumulator k to F[n]
-  Cells cells;      // (n, czl, np): four waves each contract F[n], F[2], F[3] into the slabs of planes czl .. czl + np - 1
+  Cells cells;      // (n, czl, np): four waves each contract F[n], F[2], F[3] (np of them) into the slabs of planes czl .. czl + np - 1
   Move move;        // (n): the accumulators move down by n, zeros above
   Sum sum;          // (czl, np): slabs of planes czl .. czl + np - 1 into brick bz's partials
   Close close;      // after a brick's last plane: its loss joins the workgroup's

@@ -495,16 +495,19 @@ bool check_fused_walk(const AdjGeom& a, int bxy, int bz0, int bz1, Check& ck) {
 }
 
 // The voxels of F that each cell of a brick contracts: in F, and of the cell's own columns.
+template <int Cols>
 bool check_fused_cells(const AdjGeom& a, const AdjBrick& b, Check& ck) {
+  constexpr int kFRow = FusedShape<Cols>::f_row;
+  REQUIRE(b.xe - b.x0 <= Cols && b.ye - b.y0 <= kFusedRows, "a lane per column of the brick");
   for (int w = 0; w < kAdjWaves; ++w) {
     const AdjCell c = adj_cell_geom(a, b, w);
     if (c.nx <= 0 || c.ny <= 0) continue;  // the wave contracts nothing
     for (int lane = 0; lane < kWave; ++lane)
-      for (int s = 0; s < kAdjSteps<false>; ++s) {
-        const int e = fused_f_at(b, c, lane, s), row = e / kFusedFRow, x = b.x0 + e % kFusedFRow / 3;
-        REQUIRE(e >= 0 && row < kFusedWaves && e % kFusedFRow + 3 <= kWave * 3, "fused contraction outside F");
+      for (int s = 0; s < kAdjSteps<FusedShape<Cols>::narrow>; ++s) {
+        const int e = fused_f_at<Cols>(b, c, lane, s), row = e / kFRow, x = b.x0 + e % kFRow / 3;
+        REQUIRE(e >= 0 && row < kFusedRows && e % kFRow + 3 <= Cols * 3, "fused contraction outside F");
         REQUIRE(x >= c.x0 && x < c.x0 + c.nx, "fused contraction of another cell's column");
-        REQUIRE(adj_lane_row<false>(lane, s) < c.ny ? b.y0 + row == c.y0 + adj_lane_row<false>(lane, s) : b.y0 + row >= b.ye,
+        REQUIRE(adj_lane_row<FusedShape<Cols>::narrow>(lane, s) < c.ny ? b.y0 + row == c.y0 + adj_lane_row<FusedShape<Cols>::narrow>(lane, s) : b.y0 + row >= b.ye,
                 "fused contraction of another cell's row");
       }
   }
@@ -513,11 +516,11 @@ bool check_fused_cells(const AdjGeom& a, const AdjBrick& b, Check& ck) {
 
 // The staging of a brick's control planes: every float of the window by one thread, from
 // inside the grid's plane to its place in the slot.
-template <int L>
+template <int L, int Threads>
 bool check_fused_stage(const AdjGeom& a, const AdjBrick& b, const FusedLds& lds, Check& ck) {
   std::vector<int> hit((size_t)lds.slot, 0);
-  for (int tid = 0; tid < kFusedThreads; ++tid) {
-    const FusedStage<L> m = fused_stage_map<L>(a, b, tid);
+  for (int tid = 0; tid < Threads; ++tid) {
+    const FusedStage<L> m = fused_stage_map<L, Threads>(a, b, tid);
     for (int k = 0; k < L; ++k) {
       if (m.src[k] < 0) continue;
       REQUIRE(m.src[k] < (int64_t)a.g.gx * a.g.gy * 3, "staging load outside the control plane");
@@ -533,20 +536,30 @@ bool check_fused_stage(const AdjGeom& a, const AdjBrick& b, const FusedLds& lds,
   return true;
 }
 
-bool check_fused(const AdjGeom& a, Check& ck) {
-  const FusedLds lds = fused_lds(a);
-  REQUIRE(lds.total * (int64_t)sizeof(float) <= 160 * 1024, "LDS request of a workgroup");
-  REQUIRE(lds.ring >= lds.F + (adj_staged(a) ? 4 : 2) * kFusedWaves * kFusedFRow && lds.red >= lds.ring + 2 * lds.slot &&
-              lds.slabs >= lds.red + kFusedThreads && lds.slabs % 4 == 0 &&
+template <int Cols>
+bool check_fused_lds(const AdjGeom& a, Check& ck) {
+  using S = FusedShape<Cols>;
+  const FusedLds lds = fused_lds<Cols>(a);
+  REQUIRE(lds.total * (int64_t)sizeof(float) <= 160 * 1024 / S::per_cu, "LDS request of the workgroups of a CU");
+  REQUIRE(lds.ring >= lds.F + (adj_staged(a) ? 4 : 2) * kFusedRows * S::f_row && lds.red >= lds.ring + 2 * lds.slot &&
+              lds.slabs >= lds.red + S::threads && lds.slabs % 4 == 0 &&
               lds.total >= lds.slabs + adj_slab_at(a, a.slots - 1, kAdjWaves - 1) + adj_slab(a),
           "LDS regions apart");
-  REQUIRE(fused_loads(lds.slot) <= kFusedMaxLoads, "staged loads per thread");
+  REQUIRE(fused_loads<Cols>(lds.slot) <= S::max_loads, "staged loads per thread");
   for (int i = 0; i < a.x.nb * a.y.nb; ++i) {
     const AdjBrick b = adj_brick_geom(a, i);
-    if (!check_fused_cells(a, b, ck)) return false;
-    if (!(fused_loads(lds.slot) <= 1 ? check_fused_stage<1>(a, b, lds, ck) : check_fused_stage<kFusedMaxLoads>(a, b, lds, ck)))
+    if (!check_fused_cells<Cols>(a, b, ck)) return false;
+    if (!(Cols == 64 && fused_loads<Cols>(lds.slot) <= 1 ? check_fused_stage<1, S::threads>(a, b, lds, ck)
+                                                        : check_fused_stage<S::max_loads, S::threads>(a, b, lds, ck)))
       return false;
   }
+  return true;
+}
+
+bool check_fused(const AdjGeom& a, Check& ck) {
+  const int cols = fused_cols(a);
+  if (!(cols == 32 ? check_fused_lds<32>(a, ck) : cols == 48 ? check_fused_lds<48>(a, ck) : check_fused_lds<64>(a, ck)))
+    return false;
   const FusedSplit fs = fused_split(a);
   REQUIRE(fs.deep >= 1 && fs.nz * fs.deep >= a.z.nb && (fs.nz - 1) * fs.deep < a.z.nb, "workgroups cover the z-bricks");
   for (int i = 0; i < fs.nz; ++i) {  // a column's bricks have the same planes in every column
@@ -634,7 +647,7 @@ int bsi_check_fused(const int32_t dims[3], const int32_t spacing[3], int32_t inf
     return -1;
   }
   Check ck;
-  const AdjGeom a = make_adj_geom(g);
+  const AdjGeom a = fused_geom(make_adj_geom(g));
   info[0] = fused_split(a).deep;
   info[1] = adj_staged(a);
   check_fused(a, ck);
@@ -643,17 +656,18 @@ int bsi_check_fused(const int32_t dims[3], const int32_t spacing[3], int32_t inf
 }
 
 // How the fused SSD step splits a volume: brick columns, z-bricks, planes per z-brick,
-// z-bricks per workgroup, workgroups along z.
-int bsi_check_fused_split(const int32_t dims[3], const int32_t spacing[3], int32_t out[5]) {
+// z-bricks per workgroup, workgroups along z, workgroups of a round.
+int bsi_check_fused_split(const int32_t dims[3], const int32_t spacing[3], int32_t out[6]) {
   VolGeom g;
   if (make_geom(dims, spacing, &g)) return -1;
-  const AdjGeom a = make_adj_geom(g);
+  const AdjGeom a = fused_geom(make_adj_geom(g));
   const FusedSplit f = fused_split(a);
   out[0] = a.x.nb * a.y.nb;
   out[1] = a.z.nb;
   out[2] = a.z.w;
   out[3] = f.deep;
   out[4] = f.nz;
+  out[5] = kAdjCus * (fused_cols(a) == 32 ? FusedShape<32>::per_cu : 1);
   return 0;
 }
 

@@ -27,9 +27,10 @@ CASES = [
     ((64, 64, 200), (1, 1, 1), 1, 0),
     ((300, 256, 200), (1, 1, 1), 2, 0),       # two-plane slabs, several z-bricks
     ((40, 70, 21), (12, 35, 7), None, 1),
-    ((5, 5, 1), (1, 1, 1), 1, 1),             # one plane
+    ((5, 5, 1), (1, 1, 1), 1, 0),             # one plane
     ((1, 40, 50), (3, 3, 3), None, 1),
     ((70, 33, 129), (2, 3, 64), None, 1),
+    ((30, 33, 129), (2, 3, 64), None, 0),     # narrow bricks: two-plane slabs
 ]
 
 

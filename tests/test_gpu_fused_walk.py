@@ -26,6 +26,9 @@ CASES = [
     ((1, 40, 50), (3, 3, 3)),
     ((100, 50, 90), (2, 2, 2)),
     ((130, 33, 129), (2, 3, 64)),
+    ((97, 40, 41), (2, 1, 3)),
+    ((59, 35, 23), (1, 4, 5)),
+    ((31, 20, 40), (2, 2, 1)),
 ]
 
 
