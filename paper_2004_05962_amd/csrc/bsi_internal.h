@@ -118,7 +118,7 @@ struct GenGeom {
 };
 int32_t make_gen_geom(const int32_t dims[3], const float spacing[3], const float origin[3], GenGeom* q,
                       VolGeom* g);
-FwdLaunch make_gen_fwd_launch(const VolGeom& g, const GenGeom& q);
+FwdLaunch make_gen_fwd_launch(const VolGeom& g, const GenGeom& q, bool aligned);  // aligned: rows on 64-byte boundaries
 hipError_t launch_forward_general(const float* grid, float* field, const VolGeom& g, const GenGeom& q,
                                   hipStream_t s);
 size_t general_workspace_bytes(const GenGeom& q, const VolGeom& g);

@@ -44,8 +44,6 @@ __device__ __forceinline__ int gen_weights(const GenAxis& a, int v, float (&w)[4
   return i;
 }
 
-constexpr int kGenMaxZ = 256;  // voxel planes per workgroup (z table in LDS)
-
 template <class T>
 struct GenFwdSmem {
   FwdSmem<3, T> f;
@@ -325,16 +323,18 @@ int32_t make_gen_geom(const int32_t dims[3], const float spacing[3], const float
   return check_control_plane(g->gx, g->gy);
 }
 
-FwdLaunch make_gen_fwd_launch(const VolGeom& g, const GenGeom& q) {
+FwdLaunch make_gen_fwd_launch(const VolGeom& g, const GenGeom& q, bool aligned) {
   const int nbx = (g.nx + kWave - 1) / kWave, nby = (g.ny + kFwdRows - 1) / kFwdRows;
   const long base = (long)nbx * nby;
   int chunks = (int)((kFwdTargetBlocks + base - 1) / base);
   chunks = std::max(chunks, (g.nz + kGenMaxZ - 1) / kGenMaxZ);  // the z table holds kGenMaxZ planes
   // chunks of about 25 planes, 48 where a tile holds fewer than 4, as in the aligned
   // forward (512 x 512 x 256, spacing 5.3 x 4.7 x 5.1: 153 us with 25, 167 with the
-  // 128 that the target leaves; 512 x 300 x 200, spacing 4: 76 and 82; 511 x 512 x 256
-  // at 5.3 x 4.7 x 5: 172 and 200; 512 x 512 x 256, spacing 3: 163 with 48, 177 with 25)
-  const int planes = q.z.s < 4.f ? 48 : 25;
+  // 128 that the target leaves; 512 x 300 x 200, spacing 4: 76 and 82; 512 x 512 x 256,
+  // spacing 3: 163 with 48, 177 with 25).  Rows off 64-byte boundaries: 50 planes, and at
+  // least 4 tiles (510 x 512 x 256, spacing 5.3 x 4.7 x 5.1: 150 us with 50, 165 with 25; spacing
+  // 10.5 on every axis 131 and 143; 301 x 300 x 300, 1.5 x 1.5 x 12.5: 64 and 70).
+  const int planes = q.z.s < 4.f ? 48 : aligned ? 25 : std::max(50, (int)(4.f * q.z.s));
   // (narrow volumes of very many rows: as many chunks as a launch's threads allow)
   const long most = std::max(1L, (long)(kMaxLaunchThreads / ((int64_t)kFwdThreads * base)));
   chunks = std::max(chunks, (int)std::min<long>(most, (g.nz + planes - 1) / planes));
@@ -345,9 +345,9 @@ FwdLaunch make_gen_fwd_launch(const VolGeom& g, const GenGeom& q) {
 
 hipError_t launch_forward_general(const float* grid, float* field, const VolGeom& g, const GenGeom& q,
                                   hipStream_t s) {
-  const auto [nbx, nby, nbz, zchunk] = make_gen_fwd_launch(g, q);
   // rows on 64-byte boundaries: non-temporal stores; otherwise edge stores
   const bool aligned = (g.nx * 12) % 64 == 0 && reinterpret_cast<uintptr_t>(field) % 64 == 0;
+  const auto [nbx, nby, nbz, zchunk] = make_gen_fwd_launch(g, q, aligned);
   const dim3 gd((unsigned)((long)nbx * nby * nbz)), bd(kFwdThreads);
   using T1 = FwdTile<kFwdRows, 1, 1>;
   using T3 = FwdTile<kFwdRows, 1, 1, 3>;

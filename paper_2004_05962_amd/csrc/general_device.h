@@ -68,6 +68,8 @@ __host__ __device__ inline int gen_tile(const GenAxis& a, int v) {
 }
 
 
+constexpr int kGenMaxZ = 256;  // the forward's voxel planes per workgroup (z table in LDS)
+
 // ---------------------------------------------------------------------------
 // The adjoint over the aligned adjoint's cells and bricks (adjoint_device.h), with
 // per-axis tables in place of equal tiles.

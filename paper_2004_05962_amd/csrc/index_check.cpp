@@ -686,7 +686,12 @@ int bsi_check_launch_threads(const int32_t dims[3], const int32_t spacing[3], in
   };
   out[0] = std::max(shape(FwdTileDefault{}, kFwdChunk), shape(FwdTile<2, 8, 1>{}, kFwdChunkWide));
   out[1] = std::max(shape(FwdTile<kFwdRows, 1, 4>{}, kFwdChunk), shape(FwdTileDefault{}, kFwdChunk));
-  out[2] = threads(make_gen_fwd_launch(gg, q), kFwdThreads);
+  out[2] = 0;
+  for (bool aligned : {false, true}) {
+    const FwdLaunch f = make_gen_fwd_launch(gg, q, aligned);
+    if (f.zchunk > kGenMaxZ || f.zchunk < 1 || (int64_t)f.nbz * f.zchunk < gg.nz) return 1;
+    out[2] = std::max(out[2], threads(f, kFwdThreads));
+  }
   out[3] = 0;
   for (const auto& [target, planes] : {std::pair{512L, 0}, {2048L, 0}, {(long)kFwdLeastItems, kFwdChunkBatch}})
     for (const auto& [width, rows] : {std::pair{64, 4}, {128, 2}, {64, 8}}) {
