@@ -331,10 +331,14 @@ FwdLaunch make_gen_fwd_launch(const VolGeom& g, const GenGeom& q, bool aligned) 
   // chunks of about 25 planes, 48 where a tile holds fewer than 4, as in the aligned
   // forward (512 x 512 x 256, spacing 5.3 x 4.7 x 5.1: 153 us with 25, 167 with the
   // 128 that the target leaves; 512 x 300 x 200, spacing 4: 76 and 82; 512 x 512 x 256,
-  // spacing 3: 163 with 48, 177 with 25).  Rows off 64-byte boundaries: 50 planes, and at
+  // spacing 3: 163 with 48, 177 with 25; fewer than 3: 72, spacing 2: 192 us against 201).
+  // Rows off 64-byte boundaries: 50 planes, and at
   // least 4 tiles (510 x 512 x 256, spacing 5.3 x 4.7 x 5.1: 150 us with 50, 165 with 25; spacing
   // 10.5 on every axis 131 and 143; 301 x 300 x 300, 1.5 x 1.5 x 12.5: 64 and 70).
-  const int planes = q.z.s < 4.f ? 48 : aligned ? 25 : std::max(50, (int)(4.f * q.z.s));
+  const int planes = q.z.s < 3.f && aligned ? 72
+                     : q.z.s < 4.f          ? 48
+                     : aligned              ? 25
+                                            : std::max(50, (int)(4.f * q.z.s));
   // (narrow volumes of very many rows: as many chunks as a launch's threads allow)
   const long most = std::max(1L, (long)(kMaxLaunchThreads / ((int64_t)kFwdThreads * base)));
   chunks = std::max(chunks, (int)std::min<long>(most, (g.nz + planes - 1) / planes));

@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     ((70, 130, 101), (13.46, 1.59, 10.34), (-3.0, -0.5, -2.0)),
     ((33, 260, 151), (2.0, 5.1, 12.5), (0.0, -5.0, -12.0)),
     ((31, 40, 103), (4.5, 4.5, 3.9), (-4.0, 0.0, -1.0)),
+    ((80, 40, 149), (2.5, 1.5, 2.2), (-1.0, 0.0, -2.0)),
 ])
 def test_general_forward_chunks(dims, spacing, origin):
     say("general forward chunks", dims, spacing, origin)
