@@ -98,7 +98,8 @@ int32_t bsi_forward_lerp(const float* grid, const int32_t dims[3], const int32_t
 int32_t bsi_forward_scalar(const float* grid, const int32_t dims[3], const int32_t spacing[3],
                            float* image, hipStream_t stream);
 
-/* Scratch size in bytes that bsi_adjoint needs for this geometry (host-only). */
+/* Scratch size in bytes for bsi_adjoint with this geometry (host-only); also what to
+   compare with BSI_ADJOINT_NOALLOC_MAX_BYTES (bsi_adjoint_noalloc). */
 int32_t bsi_adjoint_workspace_size(const int32_t dims[3], const int32_t spacing[3],
                                    size_t* bytes);
 
@@ -149,7 +150,8 @@ int32_t bsi_adjoint_reduce(const void* workspace, size_t workspace_bytes,
    Arguments, layouts and ownership as in bsi_adjoint; grid_grad OVERWRITTEN.
    Errors: INVALID_ARG, UNSUPPORTED (also when this geometry's partials in
    bricks of 64 x 16 voxel columns by about 48 planes exceed
-   BSI_ADJOINT_NOALLOC_MAX_BYTES), NO_DEVICE, HIP. */
+   BSI_ADJOINT_NOALLOC_MAX_BYTES; a geometry whose bsi_adjoint_workspace_size()
+   does not exceed it is always taken), NO_DEVICE, HIP. */
 #define BSI_ADJOINT_NOALLOC_MAX_BYTES ((size_t)64 << 20) /* 64 MiB per device */
 int32_t bsi_adjoint_noalloc(const float* dfield, const int32_t dims[3], const int32_t spacing[3],
                             float* grid_grad, hipStream_t stream);

@@ -198,7 +198,10 @@ int32_t bsi_adjoint_workspace_size(const int32_t dims[3], const int32_t spacing[
   VolGeom g;
   int32_t rc = make_geom(dims, spacing, &g);
   if (rc) return rc;
-  *bytes = adj_workspace_bytes(make_adj_geom(g));
+  // At least the size that bsi_adjoint_noalloc's limit is stated for: a caller that compares
+  // this one with the limit is not refused.  (The adjoint itself asks for what it needs.)
+  const size_t need = adj_workspace_bytes(make_adj_geom(g)), limit = adj_limit_bytes(g);
+  *bytes = need > limit ? need : limit;
   return BSI_OK;
 }
 
