@@ -59,7 +59,7 @@ constexpr int kAdjThreads = kAdjWaves * kWave;
 constexpr int kAdjTile = 16;                       // points per axis of a matrix tile
 constexpr int kAdjCellX = 32, kAdjCellY = 8;       // voxel columns of a cell
 // A lane's voxels.  Cells of up to 32 columns: row s is 2 s + h, h = lane / 32.  Narrow: cells
-// of up to 16 (spacing 1, adj_narrow), 16 lanes a row: row s is adj_step_row(s, lane / 16),
+// of up to 16 (spacings 1 and 2, adj_narrow), 16 lanes a row: row s is adj_step_row(s, lane / 16),
 // which is the first product's operand as it stands, half the accumulators and loads, and no
 // second half of products.  Pass 1 of 300 x 256 x 200 at spacing 1: 212 us, with 32 lanes a
 // row, 13 of them at work, 272; of 118 x 357 x 486 286 and 353 (then 183 and 254 by
@@ -97,10 +97,11 @@ constexpr int kAdjSlabFloats3 = 13312, kAdjSlabFloats2 = 20000;      // slabs of
 constexpr size_t kAdjShallowBytes = (size_t)32 << 20;
 
 // Voxels of a cell along x at spacing d: the most, up to 32, whose window is at
-// most 16 control points ((31 + 2) / 3 + 4 = 15 at spacing 3; 24 / 2 + 3 = 15 at
-// spacing 2, where cells start on even voxels; w + 3 at spacing 1).  Along y a
+// most 16 control points ((31 + 2) / 3 + 4 = 15 at spacing 3; w + 3 at spacing 1), but 16 at
+// spacing 2, where 24 would fit: 16 lanes a row all at work, 24 of 32 otherwise
+// (300 x 300 x 200: the adjoint 95 us against 112, the fused step 207 against 265).  Along y a
 // cell of 8 rows meets at most 11.
-__host__ __device__ constexpr int adj_cell(int d) { return d == 1 ? 13 : d == 2 ? 24 : kAdjCellX; }
+__host__ __device__ constexpr int adj_cell(int d) { return d == 1 ? 13 : d == 2 ? 16 : kAdjCellX; }
 
 __host__ __device__ constexpr int adj_gcd(int a, int b) { return b == 0 ? a : adj_gcd(b, a % b); }
 // Largest control window of runs of w voxels that start at multiples of w, at

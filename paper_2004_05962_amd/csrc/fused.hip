@@ -89,7 +89,7 @@ __device__ __forceinline__ F3 fused_contract(const float* __restrict__ slot, int
 // L: staged floats per thread.  Small: the images are below 4 GiB.
 // Cols: fused_cols(a).
 template <int L, bool Staged, int Pairs, bool Small, int Cols>
-__global__ __launch_bounds__(FusedShape<Cols>::threads) __attribute__((amdgpu_waves_per_eu(Cols == 48 ? 3 : 4))) void fused_pass1_kernel(const float* __restrict__ grid,
+__global__ __launch_bounds__(FusedShape<Cols>::threads) __attribute__((amdgpu_waves_per_eu(4))) void fused_pass1_kernel(const float* __restrict__ grid,
                                                                   const float* __restrict__ moving,
                                                                   const float* __restrict__ fixed,
                                                                   float* __restrict__ part,
@@ -331,7 +331,7 @@ hipError_t launch_ssd_fused(const float* grid, const float* moving, const float*
   const FusedSplit fs = fused_split(a);
   const long items = (long)a.x.nb * a.y.nb * fs.nz;
   const int cols = fused_cols(a);
-  const FusedLds lds = cols == 32 ? fused_lds<32>(a) : cols == 48 ? fused_lds<48>(a) : fused_lds<64>(a);
+  const FusedLds lds = cols == 32 ? fused_lds<32>(a) : fused_lds<64>(a);
   const dim3 gridd((unsigned)items), block((unsigned)(kFusedRows * cols));
   const size_t bytes = (size_t)lds.total * sizeof(float);
   // 32-bit byte offsets into the images
@@ -346,10 +346,8 @@ hipError_t launch_ssd_fused(const float* grid, const float* moving, const float*
   const bool staged = adj_staged(a), one = fused_loads<64>(lds.slot) <= 1;
   constexpr int kMost = FusedShape<64>::max_loads;
   if (cols == 32) {
-    BSI_FUSED_LAUNCH(FusedShape<32>::max_loads, false, 1, 32);
-  } else if (cols == 48) {
-    if (staged) BSI_FUSED_LAUNCH(FusedShape<48>::max_loads, true, 1, 48);
-    else BSI_FUSED_LAUNCH(FusedShape<48>::max_loads, false, 1, 48);
+    if (fused_loads<32>(lds.slot) <= 2) BSI_FUSED_LAUNCH(2, false, 1, 32);
+    else BSI_FUSED_LAUNCH(FusedShape<32>::max_loads, false, 1, 32);
   } else if (a.g.nx < 2) {
     if (staged) BSI_FUSED_LAUNCH(kMost, true, 0, 64);
     else BSI_FUSED_LAUNCH(kMost, false, 0, 64);

@@ -7,10 +7,9 @@
 namespace bsi {
 
 // A workgroup's threads: a voxel column each, 16 rows of a brick.  Cols: the columns that a row
-// of threads holds (fused_cols): 64, a wave per row; 48 for the bricks of x spacing 2, 12 waves;
-// 32 for narrow cells (spacing 1), 8 waves, and two workgroups per CU.  300 x 256 x 200 at
-// spacing 1: 506 us, with a wave per row of 26 columns 1036; 300 x 300 x 200 at spacing 2, rows of
-// 44: 275 and 283.
+// of threads holds (fused_cols): 64, a wave per row, or 32 for narrow cells (spacings 1 and 2),
+// 8 waves, and two workgroups per CU.  300 x 256 x 200 at spacing 1: 506 us, with a wave per
+// row of 26 columns 1036; 300 x 300 x 200 at spacing 2 207, rows of 44 283 (48 threads a row 275).
 constexpr int kFusedRows = kAdjCellsY * kAdjCellY;
 template <int Cols>
 struct FusedShape {
@@ -19,13 +18,11 @@ struct FusedShape {
   // Floats per row of F: the columns, padded so that the 2 rows (narrow: 4) a cell's lanes
   // read at once start 32 banks apart (48: the 16 lanes' floats).
   static constexpr int f_row = Cols * 3 + (Cols == 64 ? 32 : 16);
-  static constexpr int max_loads = Cols == 64 ? 2 : Cols == 48 ? 3 : 4;  // staged floats per thread
-  static constexpr int per_cu = narrow ? 2 : 1;                          // workgroups
+  static constexpr int max_loads = Cols == 64 ? 2 : 4;  // staged floats per thread
+  static constexpr int per_cu = narrow ? 2 : 1;         // workgroups
 };
-static_assert(FusedShape<64>::f_row % 64 == 32 && FusedShape<48>::f_row % 64 == 32 && FusedShape<32>::f_row % 64 == 48);
-__host__ __device__ inline int fused_cols(const AdjGeom& a) {
-  return a.g.nx < 2 || a.cell > adj_cell(2) ? 64 : adj_narrow(a) ? 32 : 48;
-}
+static_assert(FusedShape<64>::f_row % 64 == 32 && FusedShape<32>::f_row % 64 == 48);
+__host__ __device__ inline int fused_cols(const AdjGeom& a) { return a.g.nx >= 2 && adj_narrow(a) ? 32 : 64; }
 // The adjoint's bricks, so its partials and bits; narrow ones always with two-plane slabs, which
 // leave room for the second workgroup.
 __host__ __device__ inline AdjGeom fused_geom(AdjGeom a) {
@@ -70,7 +67,6 @@ __host__ __device__ constexpr int fused_loads(int slot) {
 }
 constexpr int kFusedMaxWindow = (kAdjCellsX * adj_cell(1) + 3) * (kFusedRows + 3) * 3;
 static_assert(fused_loads<64>(kFusedMaxWindow) == FusedShape<64>::max_loads &&
-              fused_loads<48>(kFusedMaxWindow) == FusedShape<48>::max_loads &&
               fused_loads<32>(kFusedMaxWindow) == FusedShape<32>::max_loads);
 
 // Staging map: thread tid takes floats e = tid + k threads of the Cy x Cx x 3

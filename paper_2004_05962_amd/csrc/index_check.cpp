@@ -549,17 +549,16 @@ bool check_fused_lds(const AdjGeom& a, Check& ck) {
   for (int i = 0; i < a.x.nb * a.y.nb; ++i) {
     const AdjBrick b = adj_brick_geom(a, i);
     if (!check_fused_cells<Cols>(a, b, ck)) return false;
-    if (!(Cols == 64 && fused_loads<Cols>(lds.slot) <= 1 ? check_fused_stage<1, S::threads>(a, b, lds, ck)
-                                                        : check_fused_stage<S::max_loads, S::threads>(a, b, lds, ck)))
+    constexpr int kFew = S::max_loads / 2;
+    if (!(fused_loads<Cols>(lds.slot) <= kFew ? check_fused_stage<kFew, S::threads>(a, b, lds, ck)
+                                              : check_fused_stage<S::max_loads, S::threads>(a, b, lds, ck)))
       return false;
   }
   return true;
 }
 
 bool check_fused(const AdjGeom& a, Check& ck) {
-  const int cols = fused_cols(a);
-  if (!(cols == 32 ? check_fused_lds<32>(a, ck) : cols == 48 ? check_fused_lds<48>(a, ck) : check_fused_lds<64>(a, ck)))
-    return false;
+  if (!(fused_cols(a) == 32 ? check_fused_lds<32>(a, ck) : check_fused_lds<64>(a, ck))) return false;
   const FusedSplit fs = fused_split(a);
   REQUIRE(fs.deep >= 1 && fs.nz * fs.deep >= a.z.nb && (fs.nz - 1) * fs.deep < a.z.nb, "workgroups cover the z-bricks");
   for (int i = 0; i < fs.nz; ++i) {  // a column's bricks have the same planes in every column

@@ -22,14 +22,14 @@ CASES = [
     ((512, 300, 199), (5, 5, 5), 1, 1),       # a partial last tile
     ((512, 510, 199), (5, 5, 5), 4, 1),       # every z-brick in one workgroup
     ((1024, 260, 210), (5, 5, 5), 1, 1),
-    ((200, 220, 240), (2, 3, 1), 8, 1),       # several z-bricks per workgroup
+    ((200, 220, 240), (2, 3, 1), 5, 0),       # several z-bricks per workgroup
     ((300, 260, 40), (5, 5, 1), 2, 1),        # a z-tile per plane
     ((64, 64, 200), (1, 1, 1), 1, 0),
     ((300, 256, 200), (1, 1, 1), 2, 0),       # two-plane slabs, several z-bricks
     ((40, 70, 21), (12, 35, 7), None, 1),
     ((5, 5, 1), (1, 1, 1), 1, 0),             # one plane
     ((1, 40, 50), (3, 3, 3), None, 1),
-    ((70, 33, 129), (2, 3, 64), None, 1),
+    ((70, 33, 129), (2, 3, 64), None, 0),
     ((30, 33, 129), (2, 3, 64), None, 0),     # narrow bricks: two-plane slabs
 ]
 
