@@ -139,9 +139,8 @@ __device__ __forceinline__ int find_volume(const VolDesc* __restrict__ v, int co
 
 // body(item) for each item of this workgroup (batch_items): a loop over a
 // persistent grid; otherwise one test and one call, so that no loop state stays
-// live across the body (pass 1's body needs every scalar register it can get:
-// with a loop around it, its scalar registers spill to vector registers and
-// those to scratch).
+// live across the body (pass 1 of the spacings 4..12: 16 scalar registers spilled
+// with a loop around it, 1 without; with all its forms 8 more bytes of scratch).
 template <bool Persistent, bool Runs, class Body>
 __device__ __forceinline__ void batch_for_items(int64_t total, Body&& body) {
   const ItemRange r = batch_items(blockIdx.x, gridDim.x, total, Persistent, Runs);

@@ -118,17 +118,6 @@ __host__ __device__ inline ItemRange batch_items(int block, int grid, int64_t to
   return ItemRange{runs ? xcd_runs(block, grid) : xcd_remap(block, grid), persistent ? (int64_t)grid : total};
 }
 
-// Order this wave's LDS writes before its following LDS reads (and vice versa):
-// lanes exchange data through the wave's own region, no workgroup barrier.
-// The fences name the LDS ("local") address space only: a fence without an
-// address space would also order global memory, i.e. wait for the wave's
-// outstanding prefetch loads.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
 __device__ __forceinline__ F3 operator+(F3 a, F3 b) { return F3{a.x + b.x, a.y + b.y, a.z + b.z}; }
 __device__ __forceinline__ F3 ldf3(const float* p) { return *reinterpret_cast<const F3*>(p); }
 __device__ __forceinline__ void stf3(float* p, F3 v) { *reinterpret_cast<F3*>(p) = v; }

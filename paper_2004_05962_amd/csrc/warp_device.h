@@ -49,9 +49,9 @@ struct SampleIn {
   float inx, iny, inz;                                   // 1 strictly inside, else 0
 };
 
-// Pairs: 1 when the caller guarantees nx >= 2 (x-neighbours as one 8-byte
-// load, no branch), 0 when nx == 1, -1 to test nx here.
-template <int Pairs = -1>
+// Pairs: 1 when the caller guarantees nx >= 2 (x-neighbours as one 8-byte load), 0 when
+// nx == 1.
+template <int Pairs>
 __device__ __forceinline__ SampleIn trilinear_load(const float* __restrict__ img, int nx, int ny, int nz, float px,
                                                    float py, float pz) {
   const Axis ax = sample_axis(px, nx), ay = sample_axis(py, ny), az = sample_axis(pz, nz);
@@ -61,7 +61,7 @@ __device__ __forceinline__ SampleIn trilinear_load(const float* __restrict__ img
   const float* p10 = img + az.i1 * sz + ay.i0 * sy;
   const float* p11 = img + az.i1 * sz + ay.i1 * sy;
   SampleIn s;
-  if (Pairs == 1 || (Pairs == -1 && nx >= 2)) {
+  if constexpr (Pairs == 1) {
     // i1 = i0 + 1: each pair of x-neighbours is one 8-byte load
     const F2 q00 = ldf2(p00 + ax.i0), q01 = ldf2(p01 + ax.i0);
     const F2 q10 = ldf2(p10 + ax.i0), q11 = ldf2(p11 + ax.i0);
