@@ -141,7 +141,7 @@ int32_t bsi_adjoint_reduce(const void* workspace, size_t workspace_bytes,
    any allocation.  For callers that cannot allocate device memory: code
    under HIP graph capture, tight serving loops, harnesses that forbid
    hipMalloc.  Same kernels and same bits as bsi_adjoint.
-   The partials live in a static device array of 9/8 BSI_ADJOINT_NOALLOC_MAX_BYTES
+   The partials live in a static device array of 5/4 BSI_ADJOINT_NOALLOC_MAX_BYTES
    that each GPU the library runs on holds until the process ends; all calls on
    one GPU share it, so calls that may overlap on one GPU (other streams or
    host threads) race, and the caller must order them.  The first call on a

@@ -117,9 +117,9 @@ AdjGeom make_adj_geom(const VolGeom& g) {
   set_depth(depth.best);
   if (a.z.k < depth.most && adj_workspace_bytes(a) > kAdjShallowBytes) set_depth(depth.most);
   if (adj_limit_bytes(g) <= BSI_ADJOINT_NOALLOC_MAX_BYTES)
-    for (int deeper : {kAdjDepthMost, g.nz}) {
-      if (adj_workspace_bytes(a) <= kAdjScratchBytes) break;
-      set_depth(imin(tiles, imax(1, deeper / g.dz)));
+    for (int deeper : {imax(1, kAdjDepthMost / g.dz), tiles}) {
+      if (adj_workspace_bytes(a) <= BSI_ADJOINT_NOALLOC_MAX_BYTES / 8 * 9) break;
+      set_depth(imin(tiles, deeper));
     }
   a.part_bytes = adj_workspace_bytes(a) <= kAdjGatherSmall ? (uint32_t)adj_workspace_bytes(a) : 0;
   a.lx = adj_gather_lx(a);

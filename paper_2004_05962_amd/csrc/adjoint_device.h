@@ -92,8 +92,8 @@ constexpr int kAdjDepthStaged = 96, kAdjDepthTwo = 20, kAdjDepthMost = 48;
 constexpr int kAdjMinStaged = 8, kAdjMinStagedDeep = 10;             // tiles and planes, of a brick with whole slabs
 constexpr int kAdjSlabFloats3 = 13312, kAdjSlabFloats2 = 20000;      // slabs of 3 and of 2 workgroups per CU
 // Shallower bricks than the depth bounds are used up to this workspace size,
-// and deeper ones, of kAdjDepthMost planes or all of them, where only those fit
-// the fixed scratch of bsi_adjoint_noalloc and its limit takes the geometry.
+// and deeper ones, of kAdjDepthMost planes or all of them, where the partials of a
+// geometry that bsi_adjoint_noalloc takes would be above 9/8 of its limit.
 constexpr size_t kAdjShallowBytes = (size_t)32 << 20;
 
 // Voxels of a cell along x at spacing d: the most, up to 32, whose window is at

@@ -37,11 +37,13 @@ struct AdjDepth {
 AdjDepth adj_depth(const AdjGeom& a, int tiles, double dz);
 int adj_gather_lx(const AdjGeom& a);  // a.g's spacings at least the grid's
 size_t adj_workspace_bytes(const AdjGeom& a);
-// bsi_adjoint_noalloc: what its limit is compared with, and its scratch.  The
-// partials of a geometry within the limit take at most 1.11 times as much
-// (spacing 1, a width a little above a multiple of 26 voxels).
+// bsi_adjoint_noalloc: what its limit is compared with, and its scratch.  With one brick
+// along z, which make_adj_geom falls back to, the partials of a geometry within the limit
+// take at most 26 / 21 of it: along x the most is 2 windows of 13 points at 33 voxels and
+// spacing 2, where the limit's one window has 21 (23 x 3 against 58 at 55 and spacing 1;
+// from spacing 3 on at most as much), along y and z at most as much.
 size_t adj_limit_bytes(const VolGeom& g);
-constexpr size_t kAdjScratchBytes = BSI_ADJOINT_NOALLOC_MAX_BYTES / 8 * 9;
+constexpr size_t kAdjScratchBytes = BSI_ADJOINT_NOALLOC_MAX_BYTES / 4 * 5;
 
 // Threads of one launch: a dispatch counts them in 32 bits, and a larger grid is cut
 // without an error.

@@ -65,3 +65,27 @@ def test_narrow_cells_real_spacing(dims, spacing, origin):
     bsi.bsi_adjoint_general(dev(dfield), dims, spacing, origin, grad, ws)
     ref = ogen.adjoint(dfield, dims, spacing, origin)
     assert max_abs(host(grad), ref) <= 1e-5 * float(np.abs(ref).max())
+
+
+@pytest.mark.parametrize("dims,spacing", [((34, 6200, 33), (2, 1, 1)), ((55, 7000, 32), (1, 10, 1)),
+                                          ((991, 885, 107), (1, 20, 12))])
+def test_noalloc_with_the_largest_partials(dims, spacing):
+    """Partials of up to 1.24 times the limit's size, in the fixed scratch: the bits of
+    bsi_adjoint, whose workspace is followed by a guard."""
+    say("adjoint noalloc, largest partials", dims, spacing)
+    dfield = torch.randn(bsi.field_shape(dims), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    nbytes = bsi.bsi_adjoint_workspace_size(dims, spacing)
+    ws = torch.full((nbytes + 1024,), 0xFF, dtype=torch.uint8, device="cuda")
+    expect = torch.empty(bsi.grid_shape(dims, spacing), device="cuda")
+    bsi.bsi_adjoint(dfield, dims, spacing, expect, ws[:nbytes])
+    got = torch.full_like(expect, float("nan"))
+    bsi.bsi_adjoint_noalloc(dfield, dims, spacing, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, expect)
+    assert bool((ws[nbytes:] == 0xFF).all())
+    # the transpose identity <A g, d> = <g, A^T d>, in FP64 sums of FP32 values
+    grid = torch.randn(expect.shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(4))
+    field = bsi.forward(grid, dims, spacing).double()
+    a, b = float((field * dfield).sum()), float((grid.double() * got).sum())
+    scale = float(field.square().sum().sqrt() * dfield.double().square().sum().sqrt())
+    assert abs(a - b) <= 1e-6 * scale
