@@ -1,8 +1,8 @@
 // Adjoint of Eq. 1 (its transpose), as a deterministic two-pass gather.
 //
 // Pass 1, z-first.  A brick is 2 x 2 cells in x and y by a run of whole
-// z-tiles; a cell is 32 x 8 voxel columns (narrower in x at spacings 1 and 2,
-// adj_cell) and belongs to one wave.  Lane (h, v) = (lane / 32, lane % 32) of
+// z-tiles; a cell is 32 x 8 voxel columns (13 or 16 x 8 at x spacings 1 and 2, adj_cell,
+// with other lanes, kAdjSteps) and belongs to one wave.  Lane (h, v) = (lane / 32, lane % 32) of
 // the wave owns voxel v of the cell's rows h, 2 + h, 4 + h, 6 + h and marches z:
 // per voxel plane it loads its 4 voxels (a load instruction reads 2 row segments
 // of 384 bytes, three whole 128-byte lines each when rows are aligned; 16 x 16
@@ -77,8 +77,8 @@ constexpr int kAdjSteps = Narrow ? 2 : 4;
 // - depth bound where a brick's slabs hold all of its planes: 96 voxels
 //   (spacing 8 at 511 x 509 x 250: 140 us against 148 at 48).
 // - LDS of those slabs: three workgroups per CU, or, for the wide windows of
-//   spacings 2 and 3, two (512 x 228 x 385, spacing 3: 129 us; with two-plane
-//   slabs 138 to 147, as before them 145 to 152).
+//   spacing 3, two (512 x 228 x 385, spacing 3: 129 us; with two-plane
+//   slabs 138 to 147, before the cells 145 to 152).
 // - depth with two-plane slabs (spacing 1, or 1 along z): 20 voxels (both passes at
 //   spacing 1: 300 x 256 x 200 279 us, 285 at 30, 280 at 16; 512 x 512 x 100 440, 462 and 464;
 //   128^3 67, 74 and 60; 200^3 141, 135 and 138).

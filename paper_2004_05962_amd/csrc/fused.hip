@@ -31,8 +31,8 @@ namespace bsi {
 namespace {
 
 // The fused pass uses the adjoint's bricks with one voxel column per lane: 16
-// waves of one row each, lane = x (fewer for bricks of x spacings 1 and 2, FusedShape), so each
-// lane keeps the forward's 4 contracted
+// waves of one row each, lane = x (8 waves for bricks of x spacings 1 and 2,
+// FusedShape), so each lane keeps the forward's 4 contracted
 // planes and the adjoint's 4 accumulators of a single column.  When a z-tile
 // ends, the rows of the finished control plane meet in LDS (F, two in turn, one
 // barrier per tile), and the first kAdjWaves waves contract one cell each with
@@ -41,10 +41,10 @@ namespace {
 // Bounds: per voxel about 105 vector instructions and 4 gathers of 8 bytes, and at
 // each tile's border a barrier, the contraction and the first gathers of the next
 // tile, which nothing hides: 1.4 us per plane of a workgroup at 256 x 256 x 160,
-// spacing 5, half of it instructions.  63 us there (83 with the adjoint's brick
-// depth, 64-bit addresses per corner and moments on tile lanes), 22 at 64 x 64 x 40
-// (62).  Starting the next tile's gathers before the border, its control plane a
-// tile earlier, took more registers than 128: 68 us.
+// spacing 5, half of it instructions.  61 to 70 us there, by how rough the
+// displacements are (73 to 84 with the adjoint's brick depth, 64-bit addresses per
+// corner and moments on tile lanes), 22 at 64 x 64 x 40 (62).  Starting the next tile's gathers before the border, its control plane a
+// tile earlier, took more registers than 128: 68 us against 63.
 
 // Loads of control plane cz's window into registers, and their store into a slot.
 template <int L>
