@@ -1,4 +1,4 @@
-// The fused SSD step's use of LDS, shared by its kernel (fused.hip) and the host
+// The fused SSD step's use of LDS, shared by its kernel (fused.hip) and the host index
 // checker: sizes, layout, and the order of a workgroup's stores, reads and barriers.
 #pragma once
 

@@ -131,7 +131,7 @@ hipError_t launch_sample(const float* field, const float* image, const float* fi
                          float* partials, long* blocks, hipStream_t s) {
   const ColLaunch L = make_col_launch(g);
   *blocks = (long)L.npb * L.nzb;
-  if (*blocks > 0x7fffffffL) return hipErrorInvalidConfiguration;  // a field far beyond device memory
+  if (*blocks > kMaxLaunchThreads / kColThreads) return hipErrorInvalidConfiguration;  // a field beyond device memory
   const bool small = (double)g.nx * g.ny * g.nz * 4 < 4294967296.0;
   const dim3 grid((unsigned)*blocks), block(kColThreads);
 #define BSI_SAMPLE(SMALL, PAIRS) \
